@@ -5,16 +5,29 @@
 //   out [T][N] = X [T][K] . W [N][K]^T      bf16 operands, fp32 sums
 //
 // T <= 192 rows meet N weight rows: every weight is needed once, so the launch is bound by reading W
-// from HBM, and behind that by what a compute unit can take in from L2, because every workgroup
-// needs X for all of its K range.  A workgroup owns all 192 rows of a block of 64, 128 or 160
-// output features (the wider the block, the fewer times X passes through a compute unit) and a
-// contiguous share of K (split-K where N alone gives too few blocks for 256 compute units).
-// 64 input features at a time, a tile of 192 rows of X and the block's rows of W goes from global
-// memory straight into LDS, whole 128-byte lines per 8 lanes, into a ring of 3 or 4 buffers, one
-// barrier per tile.  The 16-byte pieces of a row are stored permuted (piece ^ ((row >> 1) & 7))
-// so that the fragment reads of v_mfma_f32_16x16x32_bf16 (16 rows x one piece) hit all banks.
-// Of the 8 wavefronts, w multiplies the 16-row sub-tiles w&3, +4, +8 with all feature sub-tiles
-// for half w>>2 of each tile's input features; the halves are added through LDS at the end.
+// from HBM or by what a compute unit can have under way, because every workgroup needs X for all of its K
+// range.  A workgroup owns all rows of a block of 64, 112, 128 or 160 output features (the wider the
+// block, the fewer times X passes through a compute unit) and a contiguous share of K (split-K where
+// N alone gives too few blocks for 256 compute units).  Rows are taken as 64, 128 or 192 (RS = 1, 2, 3).
+// 64 input features at a time, a tile of X and the block's rows of W go from global memory straight
+// into LDS, whole 128-byte lines per 8 lanes, each into a ring of its own (3 or 4 tiles of X, up to 6
+// of W: what 160 KB hold), one barrier per tile.  The 16-byte pieces of a row are stored permuted
+// (piece ^ ((row >> 1) & 7)) so that the fragment reads of v_mfma_f32_16x16x32_bf16 (16 rows x one
+// piece) hit all banks.
+//
+// Eight wavefronts, two per SIMD: four multiply (wavefront w the 16-row sub-tiles w, w + 4, w + 8 with
+// all feature sub-tiles), two fetch W and two fetch X.  With fetching in the wavefronts that
+// multiply, its instructions (address, M0, load: ~5 slots each, 11 per tile) sat between the matrix
+// instructions of the only wavefront of a SIMD; and with all eight doing everything in step, as
+// before, reading fragments and multiplying took turns.  The fragments of half a tile are
+// requested while the other half is multiplied.
+//
+// What bounds it now (measured with parts left out): at 50 rows the weights' way from HBM: gate/up of
+// the 7B layer (272 MB) 43.0 us = 6.3 TB/s, 51.5 us before; down 27.7 (33.1), Q/K/V and output projection
+// 11.6 each (16.0).  At 170 rows what a compute unit can have under way: a request holds a line of the
+// 32 KB vector cache until its data is back, hits queue behind misses, and so W and X together come in at
+// ~45 KB/us per compute unit however many tiles are asked for ahead: 60 us for gate/up (62.3 before;
+// 39 us without loads, 46 us without X's), down 41.3 (46.4), the other two 18.2 (19.4).
 //
 // What happens to the sums (fp32) is the caller's choice:
 //   store      out = bf16(sum)
@@ -28,6 +41,8 @@
 // finished: the same sums in the same order.  Without split-K the multiplying kernel does it itself.
 #include <hip/hip_runtime.h>
 
+#include <type_traits>
+
 #include "vs_internal.h"
 #include "vs_prefill_map.h"
 
@@ -39,8 +54,7 @@ typedef __bf16 bf16x4 __attribute__((ext_vector_type(4)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef __attribute__((address_space(3))) void* lds_ptr;
 
-constexpr int kRows = 192;      // rows of X a tile holds; rows from T on repeat row T-1
-constexpr int kThreads = 512;
+constexpr int kThreads = 512, kWaves = 8;
 
 struct LinParams {
     const __bf16* x;    // [T][ldx]
@@ -151,14 +165,24 @@ __device__ __forceinline__ void write_tile(const LinParams& p, const float* tile
     }
 }
 
-template <int NSUB, int RING>
+template <int RS, int NSUB>
+struct LinTile {
+    static constexpr int kRows = 64 * RS;            // rows of X a tile has room for (T <= kRows)
+    static constexpr int kTileN = 16 * NSUB;
+    static constexpr int kXBytes = kRows * 128, kWBytes = kTileN * 128;
+    static constexpr int kXRing = RS == 3 ? 3 : 4;   // tiles of X in LDS; the rest of the 160 KB holds tiles of W
+    static constexpr int kWFit = (163840 - kXRing * kXBytes) / kWBytes;
+    static constexpr int kWRing = kWFit < 6 ? kWFit : 6;
+    static constexpr int kLds = kXRing * kXBytes + kWRing * kWBytes;
+    static_assert((kXRing - 1) * 4 * RS <= 63 && (kWRing - 1) * NSUB <= 63, "loads under way are counted to 63");
+};
+
+template <int RS, int NSUB>
 __global__ __launch_bounds__(kThreads) void linear_kernel(LinParams p) {
-    constexpr int kTileN = 16 * NSUB;
-    constexpr int kTileBytes = (kRows + kTileN) * 128;
-    constexpr int kGroups = (kRows + kTileN) / 8;   // load instructions (8 rows each) per tile
-    constexpr int kMaxMine = (kGroups + 7) / 8;     // ... of one wavefront, at most
-    constexpr int kAccs = 3 * NSUB;
-    extern __shared__ __attribute__((aligned(1024))) char ring[];  // RING tiles: 192 rows of X, then the rows of W
+    using Tile = LinTile<RS, NSUB>;
+    constexpr int kRows = Tile::kRows, kTileN = Tile::kTileN, kXRing = Tile::kXRing, kWRing = Tile::kWRing;
+    constexpr int kAccs = RS * NSUB;
+    extern __shared__ __attribute__((aligned(1024))) char ring[];  // kXRing tiles of X, then kWRing tiles of W
 
     const int tid = threadIdx.x, lane = tid & 63;
     const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -173,119 +197,146 @@ __global__ __launch_bounds__(kThreads) void linear_kernel(LinParams p) {
         asm volatile("s_getreg_b32 %0, hwreg(HW_REG_XCC_ID)" : "=s"(xcc));
         if ((xcc & 15u) != (unsigned)((p.xcc_of_residue >> (4 * at.xcd)) & 15u) && threadIdx.x == 0)
             __hip_atomic_store(p.misplaced, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);  // (see vs_workspace_init)
-        blk = at.unit;
-        share = at.split;
+        blk = __builtin_amdgcn_readfirstlane(at.unit);  // (worked out in floats, and so in vector registers)
+        share = __builtin_amdgcn_readfirstlane(at.split);
     }
     const int n0 = blk * kTileN;
     const int n_tiles_all = p.K / 64;
     const int t_begin = share * p.tiles_per_split;
-    const int n_tiles = max(0, min(p.tiles_per_split, n_tiles_all - t_begin));
+    const int n_tiles = min(p.tiles_per_split, n_tiles_all - t_begin);  // at least 1 (the plan has no empty shares)
 
-    // ---- global -> LDS.  A load instruction of a wavefront fills 8 rows: lane l -> row l >> 3, 16-byte
-    // slot l & 7, which holds piece (l & 7) ^ ((row >> 1) & 7) of the row.  Wavefront w issues row
-    // groups w, w + 8, .. of the tile: 24 groups of X rows, then 2 NSUB of W rows. ----
-    const int my_groups = (kGroups - w + 7) / 8;
-    const char* src[kMaxMine];
+    if (w >= 4) {
+        // ---- global -> LDS, by wavefronts of their own: two for W, two for X.  A load instruction
+        // fills 8 rows: lane l -> row l >> 3, 16-byte slot l & 7, which holds piece
+        // (l & 7) ^ ((row >> 1) & 7) of the row.  Each of the two takes every other group of 8 rows.  (Written as
+        // assembly: for the builtin form of these loads the compiler waits for all of them before
+        // any LDS read.  M0 is the LDS address of the 1 KB; a write of M0 is kept one instruction
+        // away from its use.  Every byte of W is needed once, by one workgroup, so it is asked for
+        // as non-temporal and leaves the L2 to X.) ----
+        auto run = [&](auto n_loads, auto n_ring, const char* src, unsigned lds, int bytes, auto offset_of, auto is_w) {
+            constexpr int kLoads = decltype(n_loads)::value, kRing = decltype(n_ring)::value;
+            const int half = w & 1;
+            unsigned off[kLoads];
 #pragma unroll
-    for (int u = 0; u < kMaxMine; ++u) {
-        const int grp = min(w + 8 * u, kGroups - 1), r = grp * 8 + (lane >> 3);  // row within the tile (X rows, then W rows)
-        const int piece = (lane & 7) ^ ((r >> 1) & 7);
-        const __bf16* row = r < kRows ? p.x + (int64_t)min(r, p.T - 1) * p.ldx
-                                      : p.w + (int64_t)min(n0 + r - kRows, p.N - 1) * p.K;
-        src[u] = reinterpret_cast<const char*>(row) + piece * 16 + (int64_t)t_begin * 128;
-    }
-    // (written as assembly: for the builtin form of these loads the compiler waits for all of them
-    // before any LDS read, whichever buffer it is from.  M0 is the LDS address of the wavefront's
-    // 1 KB; a write of M0 is kept one instruction away from its use.  Every wavefront issues
-    // kMaxMine loads per tile, the ones beyond its share repeating its last group into the same
-    // place, so that the counts the waits below assume are the same for all.)
-    const unsigned ring_lds = (unsigned)(size_t)(lds_ptr)ring;
-    auto issue = [&](int t) {  // tile t of this share (clamped: past the end the last tile is fetched again)
-        const int64_t off = (int64_t)min(t, n_tiles - 1) * 128;
-        const unsigned base = ring_lds + (unsigned)(t % RING) * kTileBytes;
+            for (int u = 0; u < kLoads; ++u) {
+                const int r = (half + 2 * u) * 8 + (lane >> 3);
+                off[u] = offset_of(r) + (unsigned)(((lane & 7) ^ ((r >> 1) & 7)) << 4);
+            }
+            auto issue = [&](int t, int slot) {
+                if (t >= n_tiles) return;
+                const char* const at = src + (int64_t)t * 128;
+                const unsigned dst = lds + (unsigned)slot * bytes + (unsigned)half * 1024;
 #pragma unroll
-        for (int u = 0; u < kMaxMine; ++u) {
-            const int grp = min(w + 8 * u, w + 8 * (my_groups - 1));
-            const unsigned dst = base + (unsigned)grp * 1024;
-            const char* const from = src[min(u, my_groups - 1)] + off;
-            // groups from 24 on (u >= 3 for every wavefront) are rows of W: each byte of W is needed
-            // once by one workgroup, so it is asked for as non-temporal and leaves the L2 to X
-            if (u >= kRows / 64)
-                asm volatile("s_mov_b32 m0, %[dst]\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %[a], off nt"
-                             :
-                             : [dst] "s"(dst), [a] "v"(from)
-                             : "memory");
-            else
-                asm volatile("s_mov_b32 m0, %[dst]\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %[a], off"
-                             :
-                             : [dst] "s"(dst), [a] "v"(from)
-                             : "memory");
+                for (int u = 0; u < kLoads; ++u) {
+                    if (decltype(is_w)::value)
+                        asm volatile("s_mov_b32 m0, %[dst]\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %[o], %[b] nt"
+                                     :
+                                     : [dst] "s"(dst + 2048 * u), [o] "v"(off[u]), [b] "s"(at)
+                                     : "memory");
+                    else
+                        asm volatile("s_mov_b32 m0, %[dst]\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %[o], %[b]"
+                                     :
+                                     : [dst] "s"(dst + 2048 * u), [o] "v"(off[u]), [b] "s"(at)
+                                     : "memory");
+                }
+            };
+#pragma unroll
+            for (int t = 0; t < kRing; ++t) issue(t, t);
+            int slot = kRing - 1;
+            for (int t = 0;; ++t) {
+                // this wavefront's part of tile t has landed when no more than the tiles behind it are under way
+                const int behind = min(t == 0 ? kRing - 1 : kRing - 2, n_tiles - 1 - t);
+#pragma unroll
+                for (int k = 0; k < kRing; ++k)
+                    if (behind == k) asm volatile("s_waitcnt vmcnt(%0)" : : "n"(k * kLoads) : "memory");
+                __builtin_amdgcn_s_barrier();  // tile t is complete, and tile t-1 is in the registers of those who multiply
+                if (t == n_tiles) break;
+                slot = slot + 1 == kRing ? 0 : slot + 1;
+                if (t > 0) issue(t - 1 + kRing, slot);
+                else slot = kRing - 1;
+            }
+        };
+        using std::integral_constant;
+        const unsigned lds0 = (unsigned)(size_t)(lds_ptr)ring;
+        if (w < 6)
+            run(integral_constant<int, NSUB>{}, integral_constant<int, kWRing>{},
+                reinterpret_cast<const char*>(p.w) + (int64_t)n0 * p.K * 2 + (int64_t)t_begin * 128,
+                lds0 + kXRing * Tile::kXBytes, Tile::kWBytes,
+                [&](int r) { return (unsigned)min(r, p.N - 1 - n0) * (unsigned)p.K * 2u; }, std::true_type{});
+        else {
+            // (only the 16-row groups that exist: what lies in LDS behind them ends up in rows nobody writes)
+            auto run_x = [&](auto n_loads) {
+                run(n_loads, integral_constant<int, kXRing>{}, reinterpret_cast<const char*>(p.x) + (int64_t)t_begin * 128,
+                    lds0, Tile::kXBytes, [&](int r) { return (unsigned)min(r, p.T - 1) * (unsigned)p.ldx * 2u; }, std::false_type{});
+            };
+            switch ((p.T + 15) / 16 - 4 * (RS - 1)) {
+                case 1: run_x(integral_constant<int, 4 * RS - 3>{}); break;
+                case 2: run_x(integral_constant<int, 4 * RS - 2>{}); break;
+                case 3: run_x(integral_constant<int, 4 * RS - 1>{}); break;
+                default: run_x(integral_constant<int, 4 * RS>{}); break;
+            }
         }
-    };
+    }
 
     f32x4 acc[kAccs];
 #pragma unroll
     for (int a = 0; a < kAccs; ++a) acc[a] = f32x4{0.f, 0.f, 0.f, 0.f};
 
-    // fragment reads: lane (i16, kq): piece kh*4 + kq of row r.  This wavefront: row sub-tiles mg,
-    // mg+4, mg+8 x all feature sub-tiles, for half kh of every tile's 64 input features
-    const int mg = w & 3, kh = w >> 2;
-    int a_off[3], b_off[NSUB];
+    // ---- The four wavefronts that multiply.  Fragment reads: lane (i16, kq): piece h*4 + kq of row r for half
+    // h of the tile's 64 input features.  Wavefront w: row sub-tiles w, w + 4, .. x all feature sub-tiles. ----
+    if (w < 4) {
+        const int rd = i16 * 128 + ((kq ^ ((i16 >> 1) & 7)) << 4);  // ((row >> 1) & 7 is the same in every 16-row sub-tile)
+        const char* const x_rd = ring + w * 2048 + rd;
+        const char* const w_rd = ring + kXRing * Tile::kXBytes + rd;
+        bf16x8 af[2][RS], bfr[2][NSUB];
+        int x_slot = 0, w_slot = 0;
+        auto read_one = [&](int h, int j) {  // fragment j of half h of the tile in the current slots: X first
+            if (j < RS)
+                af[h][j] = *reinterpret_cast<const bf16x8*>(ring + ((x_rd - ring + x_slot * Tile::kXBytes) ^ (h * 64)) + j * 8192);
+            else
+                bfr[h][j - RS] = *reinterpret_cast<const bf16x8*>(ring + ((w_rd - ring + w_slot * Tile::kWBytes) ^ (h * 64)) + (j - RS) * 2048);
+        };
+        // Multiplies half h; the fragments of the next half are requested on the way, two behind each
+        // feature sub-tile.  (The matrix instructions are written as assembly because the builtin's sums
+        // wander through copies; the wait between the last of them and the first ordinary use of a sum is
+        // then this code's business.)
+        auto multiply_half = [&](int h) {
 #pragma unroll
-    for (int i = 0; i < 3; ++i) {
-        const int r = (mg + 4 * i) * 16 + i16;
-        a_off[i] = r * 128 + (((kh * 4 + kq) ^ ((r >> 1) & 7)) << 4);
+            for (int ni = 0; ni < NSUB; ++ni) {
+#pragma unroll
+                for (int i = 0; i < RS; ++i)
+                    asm volatile("v_mfma_f32_16x16x32_bf16 %0, %1, %2, %0" : "+a"(acc[i * NSUB + ni]) : "v"(af[h][i]), "v"(bfr[h][ni]));
+#pragma unroll
+                for (int j = 2 * ni; j < 2 * ni + 2; ++j)
+                    if (j < RS + NSUB) read_one(1 - h, j);
+                __builtin_amdgcn_sched_barrier(0);
+            }
+        };
+        __builtin_amdgcn_s_barrier();  // tile 0 is complete
+        asm volatile("" : : : "memory");
+#pragma unroll
+        for (int j = 0; j < RS + NSUB; ++j) read_one(0, j);
+        __builtin_amdgcn_sched_barrier(0);
+        int t = 0;
+        do {
+            // half 1 of tile t is read while half 0 is multiplied, half 0 of tile t+1 while half 1 is
+            multiply_half(0);
+            asm volatile("s_waitcnt lgkmcnt(0)" : : : "memory");  // all of tile t is in registers
+            __builtin_amdgcn_s_barrier();  // so for everybody: the buffers of tile t are free; and tile t+1 is complete
+            asm volatile("" : : : "memory");
+            x_slot = x_slot + 1 == kXRing ? 0 : x_slot + 1;
+            w_slot = w_slot + 1 == kWRing ? 0 : w_slot + 1;
+            multiply_half(1);  // (behind the last tile it reads whatever is there, and nobody multiplies that)
+        } while (++t < n_tiles);
+        asm volatile("s_nop 7\n\ts_nop 7" : : : "memory");
+        __builtin_amdgcn_sched_barrier(0);
     }
-#pragma unroll
-    for (int ni = 0; ni < NSUB; ++ni) {
-        const int r = kRows + ni * 16 + i16;
-        b_off[ni] = r * 128 + (((kh * 4 + kq) ^ ((r >> 1) & 7)) << 4);
-    }
-
-    if (n_tiles > 0) {
-#pragma unroll
-        for (int t = 0; t < RING - 1; ++t) issue(t);
-        for (int t = 0; t < n_tiles; ++t) {
-            VS_WAIT_VM((RING - 2) * kMaxMine);  // this wavefront's part of tile t has landed
-            __syncthreads();                     // everybody's has, and tile t-1 has been read by all
-            issue(t + RING - 1);                 // into the buffer of tile t-1
-            const char* buf = ring + (t % RING) * kTileBytes;
-            // all fragments of the tile are requested before the first matrix instruction (the
-            // wavefronts of a workgroup move in step, tile by tile: left to the compiler, which asks
-            // for a fragment just before its use, every one of them waits out an LDS round trip)
-            bf16x8 af[3], bfr[NSUB];
-#pragma unroll
-            for (int i = 0; i < 3; ++i) af[i] = *reinterpret_cast<const bf16x8*>(buf + a_off[i]);
-#pragma unroll
-            for (int ni = 0; ni < NSUB; ++ni) bfr[ni] = *reinterpret_cast<const bf16x8*>(buf + b_off[ni]);
-            __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-            for (int ni = 0; ni < NSUB; ++ni)
-#pragma unroll
-                for (int i = 0; i < 3; ++i)
-                    acc[i * NSUB + ni] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(af[i], bfr[ni], acc[i * NSUB + ni], 0, 0, 0);
-        }
-        VS_WAIT_VM(0);  // the spare loads behind the last tile must not land in LDS after the workgroup has gone
-    }
-
-    // ---- the two halves of the input features are added (the ring is free now) ----
-    __syncthreads();
-    float* const xch = reinterpret_cast<float*>(ring) + ((size_t)mg * kAccs * 64 + lane) * 4;
-    if (kh == 1) {
-#pragma unroll
-        for (int a = 0; a < kAccs; ++a) *reinterpret_cast<f32x4*>(xch + a * 256) = acc[a];
-    }
-    __syncthreads();
-    if (kh == 0) {
-#pragma unroll
-        for (int a = 0; a < kAccs; ++a) acc[a] += *reinterpret_cast<const f32x4*>(xch + a * 256);
-    }
-    // lane (i16, kq) of accumulator (i, ni): rows (mg + 4 i)*16 + 4 kq + 0..3, feature n0 + 16 ni + i16
+    __syncthreads();  // (the ring is free)
+    // lane (i16, kq) of accumulator (i, ni): rows (w + 4 i)*16 + 4 kq + 0..3, feature n0 + 16 ni + i16
     if (p.ws) {
-        if (kh != 0 && !p.arrivals) return;
-        if (kh == 0) {
-            // this share's sums, in register order: [split][block][mg][accumulator][lane] x 4 floats
-            f32x4* dst = reinterpret_cast<f32x4*>(p.ws) + ((((int64_t)share * p.n_blocks + blk) * 4 + mg) * kAccs) * 64 + lane;
+        if (w < 4) {
+            // this share's sums, in register order: [split][block][wavefront][accumulator][lane] x 4 floats
+            f32x4* dst = reinterpret_cast<f32x4*>(p.ws) + ((((int64_t)share * p.n_blocks + blk) * 4 + w) * kAccs) * 64 + lane;
             if (p.arrivals) {  // (written through while the kernel runs, not left for the write-back at its end)
 #pragma unroll
                 for (int a = 0; a < kAccs; ++a) __builtin_nontemporal_store(acc[a], &dst[a * 64]);
@@ -308,7 +359,7 @@ __global__ __launch_bounds__(kThreads) void linear_kernel(LinParams p) {
         // linear_reduce_kernel does, and the rows leave through LDS as below.  A workgroup that has looked max_looks
         // times in vain reports through the host word of the placement guard and returns. ----
         __builtin_amdgcn_s_waitcnt(0x0F70);  // vmcnt(0)
-        __syncthreads();                     // (also: the exchange area has been read)
+        __syncthreads();
         unsigned* const box = reinterpret_cast<unsigned*>(ring);
         unsigned* const counter = p.arrivals + (int64_t)blk * (kCounterStrideBytes / 4);
         if (tid == 0) *box = __builtin_amdgcn_atomic_inc32(counter, (unsigned)(p.ksplit - 1), __ATOMIC_RELAXED, "workgroup");
@@ -329,19 +380,19 @@ __global__ __launch_bounds__(kThreads) void linear_kernel(LinParams p) {
             if (!box[1]) return;
         }
         // this workgroup's sub-tiles: rs = share, share + ksplit, .. below 12 and below T rows
-        const int n_rs = min(kRows / 16, (p.T + 15) >> 4);
+        const int n_rs = (p.T + 15) >> 4;
         const int n_mine = share < n_rs ? (n_rs - share + p.ksplit - 1) / p.ksplit : 0;
         float* const mine = reinterpret_cast<float*>(ring + 1024);  // [n_mine * 16][kTileN + 4]
         const int64_t step = (int64_t)p.n_blocks * 4 * kAccs * 64;    // f32x4 between shares
         const int items = n_mine * NSUB;                              // (sub-tile, feature sub-tile) pairs
         // two items per wavefront and pass, all their shares requested before any is used: with the
         // plans in use one pass, so one round trip to L2
-        for (int it0 = w; it0 < items; it0 += 16) {
+        for (int it0 = w; it0 < items; it0 += 2 * kWaves) {
             const f32x4* src[2];
             int k_of[2], ni_of[2];
 #pragma unroll
             for (int b2 = 0; b2 < 2; ++b2) {
-                const int it = min(it0 + 8 * b2, items - 1);
+                const int it = min(it0 + kWaves * b2, items - 1);
                 k_of[b2] = it / NSUB;
                 ni_of[b2] = it - k_of[b2] * NSUB;
                 const int rs = share + k_of[b2] * p.ksplit, mg_r = rs & 3, i_r = rs >> 2;  // accumulator row i_r of row group mg_r
@@ -362,7 +413,7 @@ __global__ __launch_bounds__(kThreads) void linear_kernel(LinParams p) {
             }
 #pragma unroll
             for (int b2 = 0; b2 < 2; ++b2)
-                if (it0 + 8 * b2 < items) put_acc<kTileN>(mine, sum[b2], 16 * k_of[b2], 16 * ni_of[b2], lane);
+                if (it0 + kWaves * b2 < items) put_acc<kTileN>(mine, sum[b2], 16 * k_of[b2], 16 * ni_of[b2], lane);
         }
         __syncthreads();
         const int ks = p.ksplit;
@@ -370,25 +421,24 @@ __global__ __launch_bounds__(kThreads) void linear_kernel(LinParams p) {
                            [share, ks](int r) { return (share + (r >> 4) * ks) * 16 + (r & 15); });
         return;
     }
-    __syncthreads();  // the exchange area has been read: the tile of sums may overwrite it
-    float* const tile = reinterpret_cast<float*>(ring);  // [192][kTileN + 4]
-    if (kh == 0) {
+    float* const tile = reinterpret_cast<float*>(ring);  // [kRows][kTileN + 4]
+    if (w < 4) {
 #pragma unroll
-        for (int i = 0; i < 3; ++i)
+        for (int i = 0; i < RS; ++i)
 #pragma unroll
-            for (int ni = 0; ni < NSUB; ++ni) put_acc<kTileN>(tile, acc[i * NSUB + ni], (mg + 4 * i) * 16, 16 * ni, lane);
+            for (int ni = 0; ni < NSUB; ++ni) put_acc<kTileN>(tile, acc[i * NSUB + ni], (w + 4 * i) * 16, 16 * ni, lane);
     }
     __syncthreads();
     write_tile<kTileN>(p, tile, kRows, n0, tid, kThreads, [](int r) { return r; });
 }
 
 // Adds the split-K shares in index order and finishes the sums.  Grid (blocks, 4 row groups): a
-// workgroup owns the 48 rows of sub-tiles mg, mg + 4, mg + 8 of a block; a wavefront takes
+// workgroup owns the rows of sub-tiles mg, mg + 4, .. of a block; a wavefront takes
 // accumulators wave, wave + 4, .. (all shares of one are requested at once).
-template <int NSUB>
+template <int RS, int NSUB>
 __global__ __launch_bounds__(256) void linear_reduce_kernel(LinParams p, int n_blocks) {
-    constexpr int kAccs = 3 * NSUB, kTileN = 16 * NSUB;
-    __shared__ __attribute__((aligned(16))) float tile[48 * (kTileN + 4)];
+    constexpr int kAccs = RS * NSUB, kTileN = 16 * NSUB;
+    __shared__ __attribute__((aligned(16))) float tile[16 * RS * (kTileN + 4)];
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int blk = blockIdx.x, mg = blockIdx.y;
     for (int a = wave; a < kAccs; a += 4) {
@@ -408,7 +458,7 @@ __global__ __launch_bounds__(256) void linear_reduce_kernel(LinParams p, int n_b
     }
     __syncthreads();
     // local row r = 16 i + j is row (mg + 4 i) * 16 + j of the output
-    write_tile<kTileN>(p, tile, 48, blk * kTileN, threadIdx.x, 256, [mg](int r) { return (mg + 4 * (r >> 4)) * 16 + (r & 15); });
+    write_tile<kTileN>(p, tile, 16 * RS, blk * kTileN, threadIdx.x, 256, [mg](int r) { return (mg + 4 * (r >> 4)) * 16 + (r & 15); });
 }
 
 // RMS norm of T rows of d numbers: out = x * gamma / sqrt(mean(x^2) + eps), fp32 arithmetic, one
@@ -455,8 +505,10 @@ constexpr int kPlanXcds = 8, kPlanCusPerXcd = 32;
 // Block width and split of K: estimated time = rounds through the chip x (tiles of a workgroup x
 // bytes a tile brings into its compute unit) at ~60 GB/s per compute unit, plus, with split-K,
 // the trip of the shares through memory and their addition.
+inline int row_subs(int T) { return (T + 63) / 64; }  // 16-row sub-tiles of X a wavefront owns
+
 LinPlan make_lin_plan(int T, int N, int K) {
-    (void)T;
+    const int kRows = 64 * row_subs(T);
     const int ktiles = K / 64;
     LinPlan best{4, 1, (N + 63) / 64, ktiles};
     double best_cost = 1e30;
@@ -467,6 +519,7 @@ LinPlan make_lin_plan(int T, int N, int K) {
                            ((blocks + kPlanXcds - 1) / kPlanXcds) * ks > kPlanCusPerXcd))
                 break;
             const int tps = (ktiles + ks - 1) / ks;
+            if ((ks - 1) * tps >= ktiles) continue;  // (the last share would be empty)
             const int rounds = (blocks * ks + 255) / 256;
             double cost = rounds * (2.0 + tps * (kRows + 16.0 * nsub) * 128.0 / 60e3);  // us
             if (ks > 1) cost += 3.0 + (double)ks * kRows * (double)(blocks * 16 * nsub) * 4.0 * 2.0 / 4e6;
@@ -479,25 +532,36 @@ LinPlan make_lin_plan(int T, int N, int K) {
     return best;
 }
 
-template <int NSUB, int RING>
+template <int RS, int NSUB>
 hipError_t launch_lin(const LinParams& p, const LinPlan& pl, int dev, hipStream_t st) {
     static bool attr_set_on[16] = {};  // dynamic LDS above 64 KB has to be allowed once per kernel and device
-    constexpr int kLds = RING * (kRows + 16 * NSUB) * 128;
+    constexpr int kLds = LinTile<RS, NSUB>::kLds;
+    const auto kernel = &linear_kernel<RS, NSUB>;
     if (!attr_set_on[dev]) {
-        hipError_t err = hipFuncSetAttribute(reinterpret_cast<const void*>(&linear_kernel<NSUB, RING>),
+        hipError_t err = hipFuncSetAttribute(reinterpret_cast<const void*>(kernel),
                                              hipFuncAttributeMaxDynamicSharedMemorySize, kLds);
         if (err != hipSuccess) return err;
         attr_set_on[dev] = true;
     }
     if (p.arrivals) {  // 1-D grid, the shares of a block on one XCD; they are added inside the launch
-        linear_kernel<NSUB, RING><<<prefill_grid_ids(pl.n_blocks, pl.ksplit, p.xcd_shift), kThreads, kLds, st>>>(p);
+        kernel<<<prefill_grid_ids(pl.n_blocks, pl.ksplit, p.xcd_shift), kThreads, kLds, st>>>(p);
         return hipGetLastError();
     }
-    linear_kernel<NSUB, RING><<<dim3(pl.n_blocks, pl.ksplit), kThreads, kLds, st>>>(p);
+    kernel<<<dim3(pl.n_blocks, pl.ksplit), kThreads, kLds, st>>>(p);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess || pl.ksplit == 1) return e;
-    linear_reduce_kernel<NSUB><<<dim3(pl.n_blocks, 4), 256, 0, st>>>(p, pl.n_blocks);
+    linear_reduce_kernel<RS, NSUB><<<dim3(pl.n_blocks, 4), 256, 0, st>>>(p, pl.n_blocks);
     return hipGetLastError();
+}
+
+template <int RS>
+hipError_t launch_lin_rows(const LinParams& p, const LinPlan& pl, int dev, hipStream_t st) {
+    switch (pl.nsub) {
+        case 4: return launch_lin<RS, 4>(p, pl, dev, st);
+        case 7: return launch_lin<RS, 7>(p, pl, dev, st);
+        case 8: return launch_lin<RS, 8>(p, pl, dev, st);
+        default: return launch_lin<RS, 10>(p, pl, dev, st);
+    }
 }
 
 }  // namespace
@@ -505,7 +569,7 @@ hipError_t launch_lin(const LinParams& p, const LinPlan& pl, int dev, hipStream_
 size_t linear_workspace_bytes(int32_t n_rows, int32_t K, int32_t N) {
     const LinPlan pl = make_lin_plan(n_rows, N, K);
     if (pl.ksplit == 1) return 0;
-    return (size_t)pl.ksplit * pl.n_blocks * 4 * (3 * pl.nsub) * 64 * sizeof(f32x4);
+    return (size_t)pl.ksplit * pl.n_blocks * 4 * (row_subs(n_rows) * pl.nsub) * 64 * sizeof(f32x4);
 }
 
 hipError_t launch_linear(const void* x, int32_t ldx, const void* w, int32_t n_rows, int32_t K, int32_t N, int32_t mode,
@@ -547,12 +611,8 @@ hipError_t launch_linear(const void* x, int32_t ldx, const void* w, int32_t n_ro
         p.units_per_xcd = prefill_units_per_xcd(pl.n_blocks, where.xcd_shift);
         p.max_looks = where.max_looks;
     }
-    switch (pl.nsub) {
-        case 4: return launch_lin<4, 4>(p, pl, dev, st);
-        case 7: return launch_lin<7, 4>(p, pl, dev, st);
-        case 8: return launch_lin<8, 3>(p, pl, dev, st);
-        default: return launch_lin<10, 3>(p, pl, dev, st);
-    }
+    return n_rows <= 64 ? launch_lin_rows<1>(p, pl, dev, st)
+                        : n_rows <= 128 ? launch_lin_rows<2>(p, pl, dev, st) : launch_lin_rows<3>(p, pl, dev, st);
 }
 
 hipError_t launch_rmsnorm(const void* x, const void* gamma, int32_t n_rows, int32_t d, float eps, void* out,

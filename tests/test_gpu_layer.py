@@ -125,6 +125,23 @@ def test_linear_against_the_oracle(T, K, N, mode):
     _check_stage(_f64(out), ref, slack, f"linear mode {mode} T={T} K={K} N={N} split-K ws {0 if ws is None else ws.numel()}")
 
 
+@pytest.mark.parametrize("T,K,N", [
+    # rows at the edges of the 16-row groups and of the 64-row classes; K of one tile, of as many as the rings
+    # of X (3, 4) and W (4, 5, 6) hold, and one more; N at the edges of blocks and sub-tiles
+    (16, 64, 160), (17, 192, 158), (48, 256, 162), (49, 320, 64), (64, 384, 66), (65, 448, 320), (80, 256, 48), (113, 320, 160),
+    (128, 384, 2), (129, 192, 160), (144, 256, 318), (145, 320, 16), (160, 384, 64), (161, 448, 160), (176, 256, 34), (177, 192, 96),
+])
+def test_linear_row_groups_and_rings(T, K, N):
+    x, w = draw(1100 + T, (T, K), 1.0, "bf16"), draw(2100 + N, (N, K), K ** -0.5, "bf16")
+    canvas = torch.full((T + 16, N), float("nan"), dtype=BF, device=DEV)
+    out = canvas[8:T + 8]
+    vs.linear(_dev(x), _dev(w), out, workspace=_linear_ws(T, K, N))
+    torch.cuda.synchronize()
+    assert torch.isnan(canvas[:8]).all() and torch.isnan(canvas[T + 8:]).all(), "wrote outside its rows"
+    ref, slack = _ref_linear(x, w, vs.LINEAR_STORE, None)
+    _check_stage(_f64(out), ref, slack, f"linear T={T} K={K} N={N}")
+
+
 def test_linear_is_deterministic_and_leaves_inputs_alone():
     T, K, N = 170, 3584, 3584
     x, w = _dev(draw(11, (T, K), 1.0, "bf16")), _dev(draw(12, (N, K), K ** -0.5, "bf16"))
