@@ -46,6 +46,10 @@ hipError_t launch_prefill_mfma(const vs_shape& s, const void* kc, const void* vc
                                const void* q, const void* kf, const void* vf, int32_t n_tokens,
                                void* out, void* k_append_dst, void* v_append_dst, void* counters,
                                void* workspace, hipStream_t st, int32_t n_frames = 1, bool append_all = false);
+// the same for a single run over few keys, with nothing split and no workspace
+hipError_t launch_prefill_short(const vs_shape& s, const void* kc, const void* vc, int32_t len, const void* q,
+                                const void* kf, const void* vf, int32_t n_tokens, void* out, void* k_append_dst,
+                                void* v_append_dst, hipStream_t st, bool append_all);
 size_t prefill_frames_workspace_bytes(const vs_shape& s, int32_t n_frames, int32_t n_tokens, int32_t nsplit);
 int prefill_frames_splits(const vs_shape& s, int32_t n_frames, int32_t n_tokens, int32_t len);
 

@@ -1089,6 +1089,20 @@ __global__ void xcd_probe_kernel(unsigned* out) {
     if (threadIdx.x == 0) out[blockIdx.x] = x & 15u;
 }
 
+// Short key sequences go to the kernel that splits nothing (vs_prefill_short.hip).  Its time is ~5.2 us + ~1.05 us per
+// round of 4 x 32 keys, this kernel's 8.2 us and up with little dependence on the keys: 170 tokens over 16 / 264 /
+// 430 rows 8.3 / 9.1 / 10.4 us there, 11.4 / 12.0 / 12.6 here with the best plan, over 800 rows 13.8 and
+// 13.3; with few units (10 tokens: 4) this kernel starts lower, and the line lies at 4 rounds (430 rows: 9.2 and 9.9
+// us; 800 rows: 12.6 and 10.5).  It needs one compute unit per 32 packed rows and KV head.
+bool prefers_short_kernel(const vs_shape& s, int n_tokens, int len) {
+    if (g_tune_prefill_splits || g_tune_prefill_kv_groups) return false;  // (a plan of this kernel has been asked for)
+    const int64_t M = (int64_t)n_tokens * (s.n_q_heads / s.n_kv_heads);
+    const int64_t workgroups = (M + 31) / 32 * s.n_kv_heads, units = (M + BM - 1) / BM * s.n_kv_heads;
+    if (workgroups > 256) return false;
+    const int rounds = ((len + n_tokens + 31) / 32 + 3) / 4;
+    return rounds <= 4 + (units < 39 ? (int)units / 13 : 3);
+}
+
 Plan make_plan(const vs_shape& s, int n_tokens, int len, int n_frames) {
     const int G = s.n_q_heads / s.n_kv_heads;
     const int M = n_tokens * G;
@@ -1245,6 +1259,8 @@ hipError_t launch_prefill_mfma(const vs_shape& s, const void* kc, const void* vc
                                const void* q, const void* kf, const void* vf, int32_t n_tokens,
                                void* out, void* k_append_dst, void* v_append_dst, void* counters,
                                void* workspace, hipStream_t st, int32_t n_frames, bool append_all) {
+    if (n_frames == 1 && prefers_short_kernel(s, n_tokens, len))
+        return launch_prefill_short(s, kc, vc, len, q, kf, vf, n_tokens, out, k_append_dst, v_append_dst, st, append_all);
     const Plan pl = make_plan(s, n_tokens, len, n_frames);
     PrefillParams p;
     p.kc = (const __bf16*)kc;

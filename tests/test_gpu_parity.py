@@ -990,6 +990,24 @@ def test_prefill_random_shapes_sweep():
             assert row == L and cache.len == L + 1 and same_bits(cache.k[L], kf[T - 1]) and same_bits(cache.v[L], vf[T - 1])
 
 
+@pytest.mark.parametrize("gain", [1, 12])
+@pytest.mark.parametrize("hq,hkv,L,T", [
+    # key counts at the edges of blocks of 32 and of rounds of four blocks, blocks that straddle cache and frame,
+    # packed rows at the edges of groups of 32, no cache, one token, every row count up to the last round taken
+    (28, 4, 0, 1), (28, 4, 0, 32), (28, 4, 1, 31), (28, 4, 31, 1), (28, 4, 32, 33), (28, 4, 33, 95), (8, 1, 95, 4), (8, 8, 96, 32),
+    (16, 2, 127, 33), (12, 6, 128, 128), (24, 8, 200, 170), (28, 4, 264, 170), (28, 4, 342, 170), (28, 4, 511, 2), (28, 4, 700, 192),
+])
+def test_prefill_short_key_sequences(hq, hkv, L, T, gain):
+    s = AttnShape(hq, hkv, 128, "bf16")
+    hk, hv = cache_rows(1400 + L, s, L, 0.5)
+    q, kf, vf = frame_inputs(1400 + L, s, T, 0.5, q_gain=gain)
+    out, cache, row = run_prefill(s, hk, hv, L, q, kf, vf, fused=True)
+    ref = oracle_prefill_rows(s, q, hk, hv, L, kf, vf)
+    bound = oracle_prefill_rows(s, q, hk, hv.abs(), L, kf, vf.abs())
+    check_close(out, ref, "bf16", f"short keys Hq/Hkv {hq}/{hkv} L={L} T={T} gain={gain}", abs_v_out=bound)
+    assert row == L and cache.len == L + 1 and same_bits(cache.k[L], kf[T - 1]) and same_bits(cache.v[L], vf[T - 1])
+
+
 def test_runs_of_frames_random_shapes_sweep():
     rng = np.random.default_rng(77)
     for case in range(24):
