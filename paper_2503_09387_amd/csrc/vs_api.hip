@@ -370,13 +370,8 @@ size_t vs_frames_workspace_bytes(const vs_shape* shape, int32_t n_frames, int32_
     if (n_frames < 1 || n_frames > 64 || n_tokens < 1 || (int64_t)n_frames * n_tokens > kMaxTokens ||
         max_cache_rows < 0)
         return 0;
-    // the plan's number of splits grows with the rows: size for the longest cache
-    int ns = prefill_frames_splits(*shape, n_frames, n_tokens, max_cache_rows);
-    // (short caches run one key group per workgroup and may take a split or two more)
-    for (int tiles = 1; tiles <= 7; ++tiles) {
-        const int len = tiles * 64 - n_tokens - (n_frames - 1);
-        if (len >= 0 && len <= max_cache_rows) ns = std::max(ns, prefill_frames_splits(*shape, n_frames, n_tokens, len));
-    }
+    const int ns = std::max(prefill_frames_max_splits(*shape, n_frames, n_tokens, max_cache_rows),
+                            prefill_frames_splits(*shape, n_frames, n_tokens, max_cache_rows));  // (the latter: a tuning override)
     size_t need = prefill_frames_workspace_bytes(*shape, n_frames, n_tokens, ns);
     if (n_frames == 1) need = std::max(need, prefill_mfma_workspace_bytes(*shape, n_tokens));
     return control_block_bytes(*shape) + round256(need);

@@ -52,6 +52,7 @@ hipError_t launch_prefill_short(const vs_shape& s, const void* kc, const void* v
                                 void* v_append_dst, hipStream_t st, bool append_all);
 size_t prefill_frames_workspace_bytes(const vs_shape& s, int32_t n_frames, int32_t n_tokens, int32_t nsplit);
 int prefill_frames_splits(const vs_shape& s, int32_t n_frames, int32_t n_tokens, int32_t len);
+int prefill_frames_max_splits(const vs_shape& s, int32_t n_frames, int32_t n_tokens, int32_t max_len);
 
 // bf16 split-row decode over ragged streams; appends (k_new, v_new) on the side when given.
 // `counters` points at the front of an initialised workspace's control block: reserved for the decode

@@ -222,6 +222,12 @@ __device__ __forceinline__ void merge_splits_chunked(int nsplit, MlOf ml_of, VOf
     }
 }
 
+// pieces per wavefront in the merge shared by a unit's workgroups: the fewest that cover the 32 pieces with the
+// unit's 2 n_kg nsplit wavefronts
+__host__ __device__ __forceinline__ int merge_pieces_per_wave(int n_kg, int nsplit) {
+    return n_kg == 2 ? (nsplit >= 8 ? 1 : nsplit >= 4 ? 2 : 4) : (nsplit >= 16 ? 1 : nsplit >= 8 ? 2 : nsplit >= 4 ? 4 : 8);
+}
+
 template <int NKG>
 __global__ __launch_bounds__(kGroupThreads * NKG) __attribute__((amdgpu_waves_per_eu(1, 1)))
 void prefill_mfma_kernel(PrefillParams p) {
@@ -834,8 +840,7 @@ void prefill_mfma_kernel(PrefillParams p) {
                 __syncthreads();
                 if (!*seen_box) return;
             }
-            // pieces per wavefront: the fewest that cover the 32 pieces with the unit's 2 NKG nsplit wavefronts
-            const int ppw = NKG == 2 ? (nsplit >= 8 ? 1 : nsplit >= 4 ? 2 : 4) : (nsplit >= 16 ? 1 : nsplit >= 8 ? 2 : nsplit >= 4 ? 4 : 8);
+            const int ppw = merge_pieces_per_wave(NKG, nsplit);
             const int first = (w * nsplit + split) * ppw;            // of the unit's 4 x 8 pieces: dealt to the workgroups in turn
             if (first >= 32) return;
             const int rg = first >> 3, piece0 = first & 7;
@@ -1089,6 +1094,41 @@ __global__ void xcd_probe_kernel(unsigned* out) {
     if (threadIdx.x == 0) out[blockIdx.x] = x & 15u;
 }
 
+// The chip the plans are made for: workgroup ids are dealt to 8 XCDs of 32 compute units in turn, and a
+// compute unit holds one workgroup of two key groups (128 KB of LDS) or two of one.
+constexpr int kPlanXcds = 8, kPlanCusPerXcd = 32;
+
+// How the keys of a launch of at most 128 units are shared out: nsplit workgroups of kvg key groups
+// per unit.  All splits of a unit run on one XCD, and units are dealt to XCDs evenly, so a launch goes
+// through the chip in one round iff units_per_xcd * nsplit workgroups fit an XCD (counting the chip as one pool
+// of 256 instead put 12 units with 20 splits, 40 workgroups, on each of six XCDs: a question of 37
+// tokens over 4552 rows took 29.4 us, 17.1 with 13 splits).  Among those plans the cheapest by a model in
+// us, fitted to 3400 measured (shape, tokens, rows, plan) combinations: a step of the pipeline (one tile per
+// key group), the second key group, the merge, and what a wavefront loads for it.  Its choice is 1.5 % from
+// the best measured plan on average, 8 % at worst.
+struct SplitPlan {
+    int kvg, nsplit;
+};
+SplitPlan make_split_plan(int units, int max_tiles) {
+    const int per_xcd = (units + kPlanXcds - 1) / kPlanXcds;
+    SplitPlan best{1, 1};
+    float best_cost = 0.f;
+    for (int kvg = 1; kvg <= 2; ++kvg) {
+        if (g_tune_prefill_kv_groups && kvg != g_tune_prefill_kv_groups) continue;
+        for (int ns = 1; ns <= kMaxPrefillSplits; ++ns) {
+            if (ns > 1 && (per_xcd * ns > kPlanCusPerXcd * (kvg == 1 ? 2 : 1) || ns * kvg > max_tiles + kvg - 1)) break;
+            const int steps = (max_tiles + ns * kvg - 1) / (ns * kvg);
+            float cost = steps * (kvg == 1 ? 1.5f : 1.4f) + (kvg == 2 ? 0.7f : 0.f);
+            if (ns > 1) cost += 0.8f + 0.06f * (float)(ns * merge_pieces_per_wave(kvg, ns)) + (ns > 8 ? 0.3f : 0.f);
+            if (best_cost == 0.f || cost < best_cost) {
+                best_cost = cost;
+                best = SplitPlan{kvg, ns};
+            }
+        }
+    }
+    return best;
+}
+
 // Short key sequences go to the kernel that splits nothing (vs_prefill_short.hip).  Its time is ~5.2 us + ~1.05 us per
 // round of 4 x 32 keys, this kernel's 8.2 us and up with little dependence on the keys: 170 tokens over 16 / 264 /
 // 430 rows 8.3 / 9.1 / 10.4 us there, 11.4 / 12.0 / 12.6 here with the best plan, over 800 rows 13.8 and
@@ -1098,7 +1138,7 @@ bool prefers_short_kernel(const vs_shape& s, int n_tokens, int len) {
     if (g_tune_prefill_splits || g_tune_prefill_kv_groups) return false;  // (a plan of this kernel has been asked for)
     const int64_t M = (int64_t)n_tokens * (s.n_q_heads / s.n_kv_heads);
     const int64_t workgroups = (M + 31) / 32 * s.n_kv_heads, units = (M + BM - 1) / BM * s.n_kv_heads;
-    if (workgroups > 256) return false;
+    if (workgroups > kPlanXcds * kPlanCusPerXcd) return false;
     const int rounds = ((len + n_tokens + 31) / 32 + 3) / 4;
     return rounds <= 4 + (units < 39 ? (int)units / 13 : 3);
 }
@@ -1115,13 +1155,12 @@ Plan make_plan(const vs_shape& s, int n_tokens, int len, int n_frames) {
     pl.kvg = g_tune_prefill_kv_groups ? g_tune_prefill_kv_groups : (max_tiles >= 8 ? 2 : 1);
     int ns = (pl.kvg == 1 ? 512 : 256) / units;  // fill the chip in a single round
     if (ns > max_tiles / pl.kvg) ns = max_tiles / pl.kvg;
-    if (ns > kMaxPrefillSplits) ns = kMaxPrefillSplits;
     if (ns < 1) ns = 1;
-    // keep nsplit*Hkv a multiple of 8 when splitting, so K/V sharers land on one XCD
-    int gcd8 = 8, h = s.n_kv_heads;
-    while (h % gcd8 != 0) gcd8 >>= 1;
-    const int step = 8 / gcd8;
-    if (ns >= step) ns -= ns % step;
+    if (units <= 128) {
+        const SplitPlan sp = make_split_plan(units, max_tiles);
+        pl.kvg = sp.kvg;
+        ns = sp.nsplit;
+    }
     // More units than half the chip has compute units (runs of frames, long runs of tokens): the
     // workgroups go through the chip in several rounds, and more, shorter ones may end sooner
     // than few long ones with a thin last round.  Estimated time of a launch in units of one
@@ -1253,6 +1292,20 @@ size_t prefill_frames_workspace_bytes(const vs_shape& s, int32_t n_frames, int32
 
 int prefill_frames_splits(const vs_shape& s, int32_t n_frames, int32_t n_tokens, int32_t len) {
     return make_plan(s, n_tokens, len, n_frames).nsplit;
+}
+
+// The most splits the plan takes for any number of retained rows up to max_len.
+int prefill_frames_max_splits(const vs_shape& s, int32_t n_frames, int32_t n_tokens, int32_t max_len) {
+    const int M = n_tokens * (s.n_q_heads / s.n_kv_heads);
+    const int units = (M + BM - 1) / BM * s.n_kv_heads * n_frames;
+    const int max_tiles = (max_len + n_frames - 1 + n_tokens + BN - 1) / BN;
+    int ns = 8;
+    if (units <= 128) {
+        const int per_xcd = (units + kPlanXcds - 1) / kPlanXcds;
+        ns = 2 * kPlanCusPerXcd / per_xcd;
+        if (ns > kMaxPrefillSplits) ns = kMaxPrefillSplits;
+    }
+    return ns < max_tiles ? ns : max_tiles;
 }
 
 hipError_t launch_prefill_mfma(const vs_shape& s, const void* kc, const void* vc, int32_t len,

@@ -990,6 +990,22 @@ def test_prefill_random_shapes_sweep():
             assert row == L and cache.len == L + 1 and same_bits(cache.k[L], kf[T - 1]) and same_bits(cache.v[L], vf[T - 1])
 
 
+@pytest.mark.parametrize("hq,hkv,L,T", [
+    # units (KV heads x row tiles) that do not divide evenly over the XCDs, with keys enough to be split up to
+    # what an XCD holds; one key group and two; more than 8 splits and fewer
+    (28, 4, 4552, 37), (28, 4, 3000, 19), (28, 4, 1600, 37), (28, 4, 1200, 128), (12, 6, 1600, 170), (16, 2, 2500, 9),
+    (24, 8, 1600, 100), (28, 4, 1100, 192), (28, 4, 1500, 330),
+])
+def test_prefill_plans_over_units_and_keys(hq, hkv, L, T):
+    s = AttnShape(hq, hkv, 128, "bf16")
+    hk, hv = cache_rows(1300 + T, s, L, 0.5)
+    q, kf, vf = frame_inputs(1300 + T, s, T, 0.5, q_gain=3)
+    out, cache, row = run_prefill(s, hk, hv, L, q, kf, vf, fused=True)
+    ref = oracle_prefill_rows(s, q, hk, hv, L, kf, vf)
+    check_close(out, ref, "bf16", f"plan Hq/Hkv {hq}/{hkv} L={L} T={T}")
+    assert row == L and cache.len == L + 1 and same_bits(cache.k[L], kf[T - 1]) and same_bits(cache.v[L], vf[T - 1])
+
+
 @pytest.mark.parametrize("gain", [1, 12])
 @pytest.mark.parametrize("hq,hkv,L,T", [
     # key counts at the edges of blocks of 32 and of rounds of four blocks, blocks that straddle cache and frame,
