@@ -3,18 +3,22 @@
 // Section 3.2: it is the frame's last row).  One launch; X = [E ; mean(E)] is never written out,
 // the outputs land in the layouts the frame prefill reads.
 //
-// N + 1 <= 192 rows meet n_out = (Hq + 2 Hkv) D weight rows of d numbers each; the weights (33 MB
-// at the 7B shape) are what the launch has to pull in from HBM, once.  A workgroup owns 32 output
-// features and all of the d input features, so nothing has to be added up across workgroups; what
-// bounds it is the 64 bytes per clock a compute unit takes in, because every workgroup reads all of
-// E (from L2).  64 input features at a time, a tile of 192 rows of E and 32 rows of W (28 KB) goes
-// from global memory straight into LDS, whole 128-byte lines per 8 lanes, into a ring of five
-// buffers: four tiles are on their way while one is multiplied, with one barrier per tile.  The
-// 16-byte pieces of a row are stored permuted (piece ^ ((row >> 1) & 7)) so that the fragment
-// reads of v_mfma_f32_16x16x32_bf16 (16 rows x one piece) hit all banks.  Of the 8 wavefronts, w
-// multiplies the 16-row sub-tiles w&3, +4, +8 with both 16-feature sub-tiles for half w>>2 of each
-// tile's input features: two wavefronts per SIMD, each part of a tile read from LDS by one of
-// them only; the halves are added through LDS at the end.
+// N + 1 <= 192 rows meet n_out = (Hq + 2 Hkv) D weight rows of d numbers each.  A workgroup owns 32
+// output features and all of the d input features, so nothing has to be added up across workgroups (there
+// is no workspace to do it in).  64 input features at a time, a tile of the rows of E and 32 rows of W
+// goes from global memory straight into LDS, whole 128-byte lines per 8 lanes, into a ring of tiles, the
+// 16-byte pieces of a row stored permuted (piece ^ ((row >> 1) & 7)) so that the fragment reads of
+// v_mfma_f32_16x16x32_bf16 (16 rows x one piece) hit all banks.  Four wavefronts multiply (wavefront w
+// the 16-row sub-tiles w, w + 4, w + 8 with both 16-feature sub-tiles), four fetch; one barrier per tile.
+//
+// Every workgroup takes in all of E (1.2 MB with the weights' 0.2 at the 7B shape) through its compute
+// unit, and that is what the launch is bound by: a request holds one of the 256 lines of the vector
+// cache until its data is back and data comes back in order, so behind weights on their way from HBM the
+// rows of E, which wait in L2, come in no faster than those: 28.9 us (51 GB/s per compute unit).  But 144
+// workgroups leave 112 compute units idle: they run ahead as helpers and ask for the weight and embedding
+// rows of the workgroups of their XCD, so that these find both in L2: 17.3 us (30.9 without helpers, 23.6 with
+// helpers for the weights alone, the same with 4 .. 16 loads of a helper's wavefront under way, 22.6 with 2).
+// When done the helpers sum up the carrier embedding.
 //
 // The carrier's row is not multiplied at all: the projection is linear, so its Q/K/V are the means
 // over the token rows of the fp32 sums the workgroup holds anyway (the mean enters unrounded).
@@ -23,6 +27,8 @@
 // the groups in order, one division, one rounding), so it is the same bits as vs_carrier_mean_pool.
 #include <hip/hip_runtime.h>
 
+#include <type_traits>
+
 #include "vs_internal.h"
 
 namespace vs {
@@ -30,14 +36,13 @@ namespace {
 
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
-typedef __attribute__((address_space(1))) const void* global_cptr;
+typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
 typedef __attribute__((address_space(3))) void* lds_ptr;
 
 constexpr int kTileN = 32;       // output features per workgroup (2 sub-tiles of 16)
-// rows of E a tile holds: ROWS = 176 (up to 175 tokens) or 192; rows from N on repeat row N-1
 constexpr int kThreads = 512;
-// RING tile buffers of (ROWS + 32) * 128 bytes: 6 x 26 KB or 5 x 28 KB
-constexpr int kAccs = 3 * 2;
+constexpr int kXcds = 8, kCus = 256;  // the chip the helpers are counted for: ids are dealt to the XCDs in turn
+constexpr int kHelperDepth = 4;       // loads of a helper's wavefront under way: 8 x 4 KB fill the vector cache
 
 struct QkvParams {
     const __bf16* e;   // [N][d]
@@ -47,6 +52,7 @@ struct QkvParams {
     __bf16* v;         // [N + 1][nk]
     __bf16* c_out;     // [d] or null
     int N, d, n_out, nq, nk;
+    int n_blocks;      // workgroups that multiply; ids from n_blocks on are helpers
 };
 
 __device__ __forceinline__ __bf16* dest(const QkvParams& p, int m, int n) {
@@ -56,14 +62,39 @@ __device__ __forceinline__ __bf16* dest(const QkvParams& p, int m, int n) {
     return p.v + (int64_t)m * p.nk + (n - p.nk);
 }
 
-// s_waitcnt vmcnt(n) only (gfx9 encoding: vmcnt in bits 3:0 and 15:14; expcnt, lgkmcnt left at "no wait")
-#define VS_WAIT_VM(n) __builtin_amdgcn_s_waitcnt(((n) & 15) | (((n) >> 4) << 14) | 0x0F70)
+// The carrier embedding: share `part` of `parts` of the columns, by all threads of a workgroup.
+__device__ __forceinline__ void pool_share(const QkvParams& p, int part, int parts, float (*poolsum)[32], int tid) {
+    const int c_begin = (int)((int64_t)p.d * part / parts), c_end = (int)((int64_t)p.d * (part + 1) / parts);
+    for (int c0 = c_begin; c0 < c_end; c0 += 32) {  // 32 columns x 16 row groups at a time
+        const int col = c0 + (tid & 31), rg = tid >> 5;
+        float sum = 0.f;
+        if (col < c_end)
+            for (int r = rg; r < p.N; r += 16) sum += (float)p.e[(int64_t)r * p.d + col];
+        poolsum[rg][tid & 31] = sum;
+        __syncthreads();
+        if (tid < 32 && col < c_end) {
+            float tot = poolsum[0][tid];
+#pragma unroll
+            for (int g = 1; g < 16; ++g) tot += poolsum[g][tid];
+            p.c_out[col] = (__bf16)(tot / (float)p.N);
+        }
+        __syncthreads();
+    }
+}
 
-template <int kRows, int kRing>
+template <int RS>
+struct QkvTile {
+    static constexpr int kRows = 64 * RS;  // rows of E a tile has room for
+    static constexpr int kBytes = (kRows + kTileN) * 128;
+    static constexpr int kRing = RS == 3 ? 5 : 6;
+    static constexpr int kLds = kRing * kBytes;
+};
+
+template <int RS>
 __global__ __launch_bounds__(kThreads) void frame_qkv_kernel(QkvParams p) {
-    constexpr int kTileBytes = (kRows + kTileN) * 128;
-    constexpr int kGroups = (kRows + kTileN) / 8;  // load instructions (8 rows each) per tile; a wavefront issues 4 or 3
-    extern __shared__ __attribute__((aligned(1024))) char ring[];  // kRing tiles: 192 rows of E, then 32 rows of W
+    using Tile = QkvTile<RS>;
+    constexpr int kRows = Tile::kRows, kTileBytes = Tile::kBytes, kRing = Tile::kRing;
+    extern __shared__ __attribute__((aligned(1024))) char ring[];  // kRing tiles: kRows rows of E, then 32 rows of W
     __shared__ float colsum[4][kTileN];
     __shared__ float poolsum[16][32];
 
@@ -71,168 +102,201 @@ __global__ __launch_bounds__(kThreads) void frame_qkv_kernel(QkvParams p) {
     const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int i16 = lane & 15, kq = lane >> 4;
     const int N = p.N, d = p.d;
-    const int n0 = blockIdx.x * kTileN;
     const int n_tiles = d / 64;
 
-    // ---- global -> LDS.  A load instruction of a wavefront fills 8 rows: lane l -> row l >> 3, 16-byte
-    // slot l & 7, which holds piece (l & 7) ^ ((row >> 1) & 7) of the row.  Wavefront w issues row
-    // groups w, w + 8, .. of the tile: 24 groups of E rows, then 4 of W rows. ----
-    const int my_groups = w + 24 < kGroups ? 4 : 3;
-    const char* src[4];
+    if ((int)blockIdx.x >= p.n_blocks) {
+        // ---- a helper: the rows that the workgroups of this XCD (ids of the same residue) will ask for, tile by
+        // tile, 8 rows (1 KB) per load, the wavefronts of the XCD's helpers taking turns ----
+        const int x = blockIdx.x % kXcds;
+        const int first = p.n_blocks + ((x - p.n_blocks) & (kXcds - 1));  // the XCD's first helper
+        const int n_waves = (((int)gridDim.x - first + kXcds - 1) / kXcds) * 8;
+        const int e_groups = (N + 7) / 8, w_groups = ((p.n_blocks - x + kXcds - 1) / kXcds) * (kTileN / 8);
+        const int per_tile = e_groups + w_groups;
+        int t = 0, u = (((int)blockIdx.x - first) / kXcds) * 8 + w;
+        while (t < n_tiles) {
+            u32x4 v[kHelperDepth];
 #pragma unroll
-    for (int u = 0; u < 4; ++u) {
-        const int grp = min(w + 8 * u, kGroups - 1), r = grp * 8 + (lane >> 3);  // row within the tile (E rows, then W rows)
-        const int piece = (lane & 7) ^ ((r >> 1) & 7);
-        const __bf16* row = r < kRows ? p.e + (int64_t)min(r, N - 1) * d
-                                      : p.w + (int64_t)min(n0 + r - kRows, p.n_out - 1) * d;
-        src[u] = reinterpret_cast<const char*>(row) + piece * 16;
-    }
-    // (written as assembly: for the builtin form of these loads the compiler waits for all of them
-    // before any LDS read, whichever buffer it is from.  M0 is the LDS address of the wavefront's
-    // 1 KB; a write of M0 is kept one instruction away from its use.)
-    const unsigned ring_lds = (unsigned)(size_t)(lds_ptr)ring;
-    auto issue = [&](int t) {  // tile t (clamped: past the end the last tile is fetched again, so that
-                               // the number of loads in flight stays what the waits below assume)
-        const int64_t off = (int64_t)min(t, n_tiles - 1) * 128;
-        const unsigned dst = ring_lds + (unsigned)(t % kRing) * kTileBytes + (unsigned)w * 1024;
-        // the groups of W rows (those from kRows / 8 on) are asked for as non-temporal: every byte of W
-        // is needed once, by one workgroup
-        asm volatile(
-            "s_mov_b32 m0, %[dst]\n\ts_nop 0\n\t"
-            "global_load_lds_dwordx4 %[a0], off\n\ts_add_u32 m0, m0, 0x2000\n\ts_nop 0\n\t"
-            "global_load_lds_dwordx4 %[a1], off"
-            :
-            : [dst] "s"(dst), [a0] "v"(src[0] + off), [a1] "v"(src[1] + off)
-            : "memory");
-        if (w + 16 >= kRows / 8)
-            asm volatile("s_mov_b32 m0, %[dst]\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %[a2], off nt"
-                         :
-                         : [dst] "s"(dst + 2 * 0x2000), [a2] "v"(src[2] + off)
-                         : "memory");
-        else
-            asm volatile("s_mov_b32 m0, %[dst]\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %[a2], off"
-                         :
-                         : [dst] "s"(dst + 2 * 0x2000), [a2] "v"(src[2] + off)
-                         : "memory");
-        if (my_groups == 4)
-            asm volatile("s_mov_b32 m0, %[dst]\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %[a3], off nt"
-                         :
-                         : [dst] "s"(dst + 3 * 0x2000), [a3] "v"(src[3] + off)
-                         : "memory");
-    };
-
-    f32x4 acc[kAccs];
+            for (int k = 0; k < kHelperDepth; ++k) {
+                while (u >= per_tile) {
+                    u -= per_tile;
+                    ++t;
+                }
+                const int r = lane >> 3;  // row of the group
+                const __bf16* row;
+                if (u < e_groups) {
+                    row = p.e + (int64_t)min(u * 8 + r, N - 1) * d;
+                } else {
+                    const int g = u - e_groups, blk = x + kXcds * (g >> 2);
+                    row = p.w + (int64_t)min(blk * kTileN + (g & 3) * 8 + r, p.n_out - 1) * d;
+                }
+                v[k] = *reinterpret_cast<const u32x4*>(row + (int64_t)min(t, n_tiles - 1) * 64 + (lane & 7) * 8);
+                u += n_waves;
+            }
 #pragma unroll
-    for (int a = 0; a < kAccs; ++a) acc[a] = f32x4{0.f, 0.f, 0.f, 0.f};
-
-    // fragment reads: lane (i16, kq), step st of the tile: piece st*4 + kq of row r
-    // this wavefront: row sub-tiles mg, mg+4, mg+8 x both feature sub-tiles, for half kh of every tile's
-    // 64 input features (so that the wavefronts read different parts of a tile, not the same twice)
-    const int mg = w & 3, kh = w >> 2;
-    int a_row[3], b_row[2];
-#pragma unroll
-    for (int i = 0; i < 3; ++i) a_row[i] = (mg + 4 * i) * 16 + i16;
-#pragma unroll
-    for (int ni = 0; ni < 2; ++ni) b_row[ni] = kRows + ni * 16 + i16;
-
-#pragma unroll
-    for (int t = 0; t < kRing - 1; ++t) issue(t);
-    for (int t = 0; t < n_tiles; ++t) {
-        if (my_groups == 4) VS_WAIT_VM((kRing - 2) * 4);  // this wavefront's part of tile t has landed
-        else VS_WAIT_VM((kRing - 2) * 3);
-        __syncthreads();                           // everybody's has, and tile t-1 has been read by all
-        issue(t + kRing - 1);                      // into the buffer of tile t-1
-        const char* buf = ring + (t % kRing) * kTileBytes;
-        {
-            bf16x8 af[3], bfr[2];
-#pragma unroll
-            for (int i = 0; i < 3; ++i)
-                af[i] = *reinterpret_cast<const bf16x8*>(buf + a_row[i] * 128 + (((kh * 4 + kq) ^ ((a_row[i] >> 1) & 7)) << 4));
-#pragma unroll
-            for (int ni = 0; ni < 2; ++ni)
-                bfr[ni] = *reinterpret_cast<const bf16x8*>(buf + b_row[ni] * 128 + (((kh * 4 + kq) ^ ((b_row[ni] >> 1) & 7)) << 4));
-#pragma unroll
-            for (int i = 0; i < 3; ++i)
-#pragma unroll
-                for (int ni = 0; ni < 2; ++ni)
-                    acc[i * 2 + ni] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(af[i], bfr[ni], acc[i * 2 + ni], 0, 0, 0);
+            for (int k = 0; k < kHelperDepth; ++k) asm volatile("" : : "v"(v[k]));  // (nothing is done with them)
         }
+        if (p.c_out) pool_share(p, blockIdx.x - p.n_blocks, gridDim.x - p.n_blocks, poolsum, tid);
+        return;
     }
-    VS_WAIT_VM(0);  // the spare loads behind the last tile must not land in LDS after the workgroup has gone
 
-    // ---- the two halves of the input features are added (the ring is free now) ----
-    __syncthreads();
-    float* const xch = reinterpret_cast<float*>(ring) + ((size_t)mg * kAccs * 64 + lane) * 4;
-    if (kh == 1) {
+    const int n0 = blockIdx.x * kTileN;
+    if (w >= 4) {
+        // ---- global -> LDS.  A load instruction fills 8 rows: lane l -> row l >> 3, 16-byte slot l & 7,
+        // which holds piece (l & 7) ^ ((row >> 1) & 7) of the row.  The four wavefronts take every
+        // fourth group of 8 rows: those of E that exist, then the four of W.  (Written as assembly: for the builtin
+        // form of these loads the compiler waits for all of them before any LDS read.  M0 is the LDS
+        // address of the 1 KB; a write of M0 is kept one instruction away from its use.) ----
+        const int e_groups = (N + 15) / 16 * 2, mine = (e_groups + kTileN / 8 - (w - 4) + 3) / 4;
+        auto run = [&](auto n_loads) {
+            constexpr int kLoads = decltype(n_loads)::value;
+            unsigned off[kLoads], dst[kLoads];
+            const char* base[kLoads];
 #pragma unroll
-        for (int a = 0; a < kAccs; ++a) *reinterpret_cast<f32x4*>(xch + a * 256) = acc[a];
-    }
-    __syncthreads();
-    if (kh == 0) {
+            for (int u = 0; u < kLoads; ++u) {
+                const int grp = w - 4 + 4 * u, r8 = lane >> 3;
+                const bool is_w = grp >= e_groups;
+                const int r = (is_w ? grp - e_groups : grp) * 8 + r8;
+                off[u] = (unsigned)(is_w ? min(r, p.n_out - 1 - n0) : min(r, N - 1)) * (unsigned)d * 2u +
+                         (unsigned)(((lane & 7) ^ ((r >> 1) & 7)) << 4);
+                dst[u] = (unsigned)(size_t)(lds_ptr)ring + (is_w ? kRows * 128 + (grp - e_groups) * 1024 : grp * 1024);
+                base[u] = is_w ? reinterpret_cast<const char*>(p.w) + (int64_t)n0 * d * 2 : reinterpret_cast<const char*>(p.e);
+            }
+            auto issue = [&](int t, int slot) {
+                if (t >= n_tiles) return;
 #pragma unroll
-        for (int a = 0; a < kAccs; ++a) acc[a] += *reinterpret_cast<const f32x4*>(xch + a * 256);
-        // lane (i16, kq) of accumulator (i, ni): rows (mg + 4 i)*16 + 4 kq + 0..3, feature n0 + 16 ni + i16.
-        // Token rows go out; their column sums make the carrier's row.
-        float csum[2] = {0.f, 0.f};
+                for (int u = 0; u < kLoads; ++u)
+                    asm volatile("s_mov_b32 m0, %[dst]\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %[o], %[b]"
+                                 :
+                                 : [dst] "s"(dst[u] + (unsigned)slot * kTileBytes), [o] "v"(off[u]), [b] "s"(base[u] + (int64_t)t * 128)
+                                 : "memory");
+            };
 #pragma unroll
-        for (int i = 0; i < 3; ++i)
+            for (int t = 0; t < kRing; ++t) issue(t, t);
+            int slot = kRing - 1;
+            for (int t = 0;; ++t) {
+                // this wavefront's part of tile t has landed when no more than the tiles behind it are under way
+                const int behind = min(t == 0 ? kRing - 1 : kRing - 2, n_tiles - 1 - t);
 #pragma unroll
-            for (int ni = 0; ni < 2; ++ni) {
-                const int n = n0 + 16 * ni + i16, m0 = (mg + 4 * i) * 16 + 4 * kq;
-#pragma unroll
-                for (int e = 0; e < 4; ++e) {
-                    if (m0 + e < N) {
-                        csum[ni] += acc[i * 2 + ni][e];
-                        if (n < p.n_out) *dest(p, m0 + e, n) = (__bf16)acc[i * 2 + ni][e];
-                    }
+                for (int k = 0; k < kRing; ++k)
+                    if (behind == k) asm volatile("s_waitcnt vmcnt(%0)" : : "n"(k * kLoads) : "memory");
+                __builtin_amdgcn_s_barrier();  // tile t is complete, and tile t-1 is in the registers of those who multiply
+                if (t == n_tiles) break;
+                if (t > 0) {
+                    slot = slot + 1 == kRing ? 0 : slot + 1;
+                    issue(t - 1 + kRing, slot);
                 }
             }
+        };
+        using std::integral_constant;
+        switch (mine) {
+            case 1: run(integral_constant<int, 1>{}); break;
+            case 2: run(integral_constant<int, 2>{}); break;
+            case 3: run(integral_constant<int, 3>{}); break;
+            case 4: run(integral_constant<int, 4>{}); break;
+            case 5: run(integral_constant<int, 5>{}); break;
+            case 6: run(integral_constant<int, 6>{}); break;
+            default: run(integral_constant<int, 7>{}); break;  // (24 + 4 groups at most)
+        }
+    }
+
+    f32x4 acc[RS][2];
+#pragma unroll
+    for (int i = 0; i < RS; ++i) acc[i][0] = acc[i][1] = f32x4{0.f, 0.f, 0.f, 0.f};
+    if (w < 4) {
+        // fragment reads: lane (i16, kq): piece h*4 + kq of row r for half h of the tile's 64 input features
+        const int rd = i16 * 128 + ((kq ^ ((i16 >> 1) & 7)) << 4);  // ((row >> 1) & 7 is the same in every 16-row sub-tile)
+        __builtin_amdgcn_s_barrier();  // tile 0 is complete
+        asm volatile("" : : : "memory");
+        bf16x8 af[2][2][RS], bfr[2][2][2];  // [register set][half][sub-tile]
+        int slot = 0;
+        auto read = [&](int set) {
+#pragma unroll
+            for (int h = 0; h < 2; ++h) {
+                const char* const at = ring + ((slot * kTileBytes + rd) ^ (h * 64));
+#pragma unroll
+                for (int i = 0; i < RS; ++i) af[set][h][i] = *reinterpret_cast<const bf16x8*>(at + (w + 4 * i) * 2048);
+#pragma unroll
+                for (int ni = 0; ni < 2; ++ni) bfr[set][h][ni] = *reinterpret_cast<const bf16x8*>(at + kRows * 128 + ni * 2048);
+            }
+            __builtin_amdgcn_sched_barrier(0);
+        };
+        auto step = [&](int set) {
+            asm volatile("s_waitcnt lgkmcnt(0)" : : : "memory");  // all of tile t is in registers
+            __builtin_amdgcn_s_barrier();                          // so for everybody; and tile t+1 is complete
+            asm volatile("" : : : "memory");
+            slot = slot + 1 == kRing ? 0 : slot + 1;
+            read(1 - set);  // tile t+1, while tile t is multiplied (behind the last one: whatever is there)
+#pragma unroll
+            for (int h = 0; h < 2; ++h)
+#pragma unroll
+                for (int i = 0; i < RS; ++i)
+#pragma unroll
+                    for (int ni = 0; ni < 2; ++ni)
+                        acc[i][ni] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(af[set][h][i], bfr[set][h][ni], acc[i][ni], 0, 0, 0);
+            __builtin_amdgcn_sched_barrier(0);
+        };
+        read(0);
+        for (int t = 0; t < n_tiles; t += 2) {
+            step(0);
+            if (t + 1 < n_tiles) step(1);
+        }
+    }
+    __syncthreads();  // (the ring is free)
+
+    // ---- the sums leave through LDS as a row-major tile, 8 neighbouring features of a row per thread.
+    // lane (i16, kq) of acc[i][ni]: rows (w + 4 i)*16 + 4 kq + 0..3, feature n0 + 16 ni + i16.  Their column
+    // sums make the carrier's row. ----
+    float* const tile = reinterpret_cast<float*>(ring);  // [kRows][kTileN + 4]
+    if (w < 4) {
+        float csum[2] = {0.f, 0.f};
+#pragma unroll
+        for (int i = 0; i < RS; ++i)
+#pragma unroll
+            for (int ni = 0; ni < 2; ++ni)
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    const int m = (w + 4 * i) * 16 + 4 * kq + e;
+                    if (m < N) csum[ni] += acc[i][ni][e];
+                    tile[m * (kTileN + 4) + 16 * ni + i16] = acc[i][ni][e];
+                }
 #pragma unroll
         for (int ni = 0; ni < 2; ++ni) {
             csum[ni] += __shfl_xor(csum[ni], 16);
             csum[ni] += __shfl_xor(csum[ni], 32);
-            if (kq == 0) colsum[mg][16 * ni + i16] = csum[ni];
+            if (kq == 0) colsum[w][16 * ni + i16] = csum[ni];
         }
     }
     __syncthreads();
     if (tid < kTileN && n0 + tid < p.n_out)
         *dest(p, N, n0 + tid) =
             (__bf16)((((colsum[0][tid] + colsum[1][tid]) + colsum[2][tid]) + colsum[3][tid]) / (float)N);
-
-    // ---- the carrier embedding, a share of the columns per workgroup ----
-    if (p.c_out) {
-        const int c_begin = (int)((int64_t)d * blockIdx.x / gridDim.x), c_end = (int)((int64_t)d * (blockIdx.x + 1) / gridDim.x);
-        for (int c0 = c_begin; c0 < c_end; c0 += 32) {  // 32 columns x 16 row groups at a time
-            const int col = c0 + (tid & 31), rg = tid >> 5;
-            float sum = 0.f;
-            if (col < c_end)
-                for (int r = rg; r < N; r += 16) sum += (float)p.e[(int64_t)r * d + col];
-            poolsum[rg][tid & 31] = sum;
-            __syncthreads();
-            if (tid < 32 && col < c_end) {
-                float tot = poolsum[0][tid];
-#pragma unroll
-                for (int g = 1; g < 16; ++g) tot += poolsum[g][tid];
-                p.c_out[col] = (__bf16)(tot / (float)N);
-            }
-            __syncthreads();
-        }
+    for (int idx = tid; idx < N * (kTileN / 8); idx += kThreads) {
+        const int m = idx / (kTileN / 8), c8 = (idx % (kTileN / 8)) * 8;
+        const f32x4 lo = *reinterpret_cast<const f32x4*>(tile + m * (kTileN + 4) + c8);
+        const f32x4 hi = *reinterpret_cast<const f32x4*>(tile + m * (kTileN + 4) + c8 + 4);
+        const bf16x8 y = {(__bf16)lo[0], (__bf16)lo[1], (__bf16)lo[2], (__bf16)lo[3],
+                          (__bf16)hi[0], (__bf16)hi[1], (__bf16)hi[2], (__bf16)hi[3]};
+        // (head_dim is 128: a block of 32 features lies in one of the three tensors, and n_out is a multiple of it)
+        *reinterpret_cast<bf16x8*>(dest(p, m, n0 + c8)) = y;
     }
+    if (p.c_out && (int)gridDim.x == p.n_blocks) pool_share(p, blockIdx.x, gridDim.x, poolsum, tid);  // (no helpers)
 }
 
 }  // namespace
 
-template <int ROWS, int RING>
+template <int RS>
 hipError_t launch_qkv_variant(const QkvParams& p, int dev, hipStream_t st) {
     static bool attr_set_on[16] = {};  // dynamic LDS above 64 KB has to be allowed once per kernel and device
-    constexpr int kLds = RING * (ROWS + kTileN) * 128;
+    constexpr int kLds = QkvTile<RS>::kLds;
     if (!attr_set_on[dev]) {
-        hipError_t err = hipFuncSetAttribute(reinterpret_cast<const void*>(&frame_qkv_kernel<ROWS, RING>),
+        hipError_t err = hipFuncSetAttribute(reinterpret_cast<const void*>(&frame_qkv_kernel<RS>),
                                              hipFuncAttributeMaxDynamicSharedMemorySize, kLds);
         if (err != hipSuccess) return err;
         attr_set_on[dev] = true;
     }
-    frame_qkv_kernel<ROWS, RING><<<(p.n_out + kTileN - 1) / kTileN, kThreads, kLds, st>>>(p);
+    // helpers where at least two per XCD find a compute unit of their own
+    const int helpers = p.n_blocks + 2 * kXcds <= kCus ? kCus - p.n_blocks : 0;
+    frame_qkv_kernel<RS><<<p.n_blocks + helpers, kThreads, kLds, st>>>(p);
     return hipGetLastError();
 }
 
@@ -252,8 +316,9 @@ hipError_t launch_frame_qkv(const vs_shape& s, const void* e, int32_t n_visual, 
     p.nq = s.n_q_heads * s.head_dim;
     p.nk = s.n_kv_heads * s.head_dim;
     p.n_out = p.nq + 2 * p.nk;
-    // fewer rows per tile leave room for one more tile in flight
-    return n_visual <= 175 ? launch_qkv_variant<176, 6>(p, dev, st) : launch_qkv_variant<192, 5>(p, dev, st);
+    p.n_blocks = (p.n_out + kTileN - 1) / kTileN;
+    return n_visual <= 64 ? launch_qkv_variant<1>(p, dev, st)
+                          : n_visual <= 128 ? launch_qkv_variant<2>(p, dev, st) : launch_qkv_variant<3>(p, dev, st);
 }
 
 }  // namespace vs

@@ -687,6 +687,25 @@ def test_frame_projection_matches_oracle(N, d, heads):
     assert same_bits(q2, q.cpu()) and same_bits(k2, k.cpu()) and same_bits(v2, v.cpu())
 
 
+@pytest.mark.parametrize("N,d,heads", [
+    # rows at the edges of the 16-row groups and of the 64-row classes; d of one tile, of as many as the ring holds
+    # (5, 6) and one more, odd and even; counts of workgroups that are no multiple of 8, and with no compute unit
+    # left over for helpers
+    (1, 64, (8, 1)), (15, 128, (5, 5)), (16, 320, (6, 3)), (17, 384, (6, 3)), (63, 448, (5, 5)), (64, 320, (8, 1)), (65, 64, (5, 5)),
+    (112, 192, (6, 3)), (128, 384, (8, 8)), (129, 320, (5, 5)), (144, 128, (48, 8)), (161, 448, (40, 8)), (191, 384, (12, 6)),
+])
+def test_frame_projection_row_groups_ring_and_helpers(N, d, heads):
+    s = AttnShape(heads[0], heads[1], 128, "bf16")
+    (q, k, v, c), (rq, rk, rv), (e, _) = _projection_case(s, N, d, 1500 + N)
+    check_close(q, rq, "bf16", f"Q N={N} d={d}")
+    check_close(k, rk, "bf16", f"K N={N} d={d}")
+    check_close(v, rv, "bf16", f"V N={N} d={d}")
+    pooled = torch.empty(d, dtype=torch.bfloat16, device=DEV)
+    vs.carrier_mean_pool(e.to(DEV), pooled, "bf16")
+    torch.cuda.synchronize()
+    assert same_bits(c, pooled.cpu())
+
+
 def test_frame_projection_feeds_the_prefill():
     """E and W in, attention out: projection, then prefill with compaction, against the oracle's
     projection followed by its prefill (inputs of the second stage rounded to bf16 on both sides)."""
