@@ -494,8 +494,10 @@ void prefill_mfma_kernel(PrefillParams p) {
             const float m_old = (l_run[r] + xhalf(l_run[r]) > 0.f) ? m_ref[r] : -INFINITY;  // the row's history
             const float m_new = fmaxf(m_old, mx);
             alpha[r] = (m_new == -INFINITY) ? 1.f : __builtin_amdgcn_exp2f(m_old - m_new);
-            m_ref[r] = m_new;
+            // (a row that has seen no key yet keeps the made-up reference 0, which is what its next sub-blocks
+            // will be taken against)
             const float m_sub = (m_new == -INFINITY) ? 0.f : m_new;
+            m_ref[r] = m_sub;
             ms[r] = m_sub;
             float sum = 0.f;
 #pragma unroll

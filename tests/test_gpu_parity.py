@@ -1009,6 +1009,20 @@ def test_prefill_random_shapes_sweep():
             assert row == L and cache.len == L + 1 and same_bits(cache.k[L], kf[T - 1]) and same_bits(cache.v[L], vf[T - 1])
 
 
+@pytest.mark.parametrize("kv_groups,splits", [(2, 1), (2, 2), (1, 1), (1, 3)])
+def test_prefill_rows_whose_first_tile_is_masked_beside_rows_that_are_redone(kv_groups, splits):
+    """A lane that starts with a tile some of its rows do not see at all, while others need the exact redo of
+    that tile (peaked scores): the former must keep a usable reference for the tiles that follow."""
+    s, L, T = AttnShape(12, 4, 128, "bf16"), 200, 101
+    hk, hv = cache_rows(726, s, L, 0.5)
+    q, kf, vf = frame_inputs(726, s, T, 0.5, q_gain=6)
+    vs.set_tuning(vs.TUNE_PREFILL_KV_GROUPS, kv_groups)
+    vs.set_tuning(vs.TUNE_PREFILL_SPLITS, splits)
+    out, _, _ = run_prefill(s, hk, hv, L, q, kf, vf)
+    ref = oracle_prefill_rows(s, q, hk, hv, L, kf, vf)
+    check_close(out, ref, "bf16", f"first tile masked, kv_groups={kv_groups} splits={splits}")
+
+
 @pytest.mark.parametrize("hq,hkv,L,T", [
     # units (KV heads x row tiles) that do not divide evenly over the XCDs, with keys enough to be split up to
     # what an XCD holds; one key group and two; more than 8 splits and fewer
