@@ -1104,10 +1104,11 @@ constexpr int kPlanXcds = 8, kPlanCusPerXcd = 32;
 // per unit.  All splits of a unit run on one XCD, and units are dealt to XCDs evenly, so a launch goes
 // through the chip in one round iff units_per_xcd * nsplit workgroups fit an XCD (counting the chip as one pool
 // of 256 instead put 12 units with 20 splits, 40 workgroups, on each of six XCDs: a question of 37
-// tokens over 4552 rows took 29.4 us, 17.1 with 13 splits).  Among those plans the cheapest by a model in
-// us, fitted to 3400 measured (shape, tokens, rows, plan) combinations: a step of the pipeline (one tile per
-// key group), the second key group, the merge, and what a wavefront loads for it.  Its choice is 1.5 % from
-// the best measured plan on average, 8 % at worst.
+// tokens over 4552 rows took 29.4 us, 17.1 with 13 splits).  Among those plans the cheapest by a model
+// fitted to 8000 measured (shape, tokens, rows, plan) combinations: the steps of the longest lane (one tile
+// per key group), the tiles of the average lane, the second key group, the merge, and what a wavefront loads for it.
+// Over the sizes that come here (see prefers_short_kernel) its choice is 0.8 % from the best measured plan on
+// average and 7 % at worst; against 256 compute units as one pool it gains 4 % on average and loses 2 % at worst.
 struct SplitPlan {
     int kvg, nsplit;
 };
@@ -1120,8 +1121,8 @@ SplitPlan make_split_plan(int units, int max_tiles) {
         for (int ns = 1; ns <= kMaxPrefillSplits; ++ns) {
             if (ns > 1 && (per_xcd * ns > kPlanCusPerXcd * (kvg == 1 ? 2 : 1) || ns * kvg > max_tiles + kvg - 1)) break;
             const int steps = (max_tiles + ns * kvg - 1) / (ns * kvg);
-            float cost = steps * (kvg == 1 ? 1.5f : 1.4f) + (kvg == 2 ? 0.7f : 0.f);
-            if (ns > 1) cost += 0.8f + 0.06f * (float)(ns * merge_pieces_per_wave(kvg, ns)) + (ns > 8 ? 0.3f : 0.f);
+            float cost = steps * (kvg == 1 ? 1.43f : 0.56f) + 1.0f * (float)max_tiles / (float)(ns * kvg) + (kvg == 2 ? 0.29f : 0.f);
+            if (ns > 1) cost += 2.34f + 0.116f * (float)(ns * merge_pieces_per_wave(kvg, ns)) + (ns > 8 ? 0.572f : 0.f);
             if (best_cost == 0.f || cost < best_cost) {
                 best_cost = cost;
                 best = SplitPlan{kvg, ns};
