@@ -28,6 +28,12 @@ template <typename T> __device__ __forceinline__ T from_f32(float x);
 template <> __device__ __forceinline__ float from_f32<float>(float x) { return x; }
 template <> __device__ __forceinline__ __bf16 from_f32<__bf16>(float x) { return (__bf16)x; }  // RNE
 
+// Sixteen bytes in registers.  keep_here() on a loaded value keeps its load where it is written: the
+// compiler otherwise moves a load down to a conditional use, and a batch becomes one load at a time.
+typedef unsigned int raw16 __attribute__((ext_vector_type(4)));
+__device__ __forceinline__ void keep_here(raw16& x) { asm volatile("" : "+v"(x)); }
+__device__ __forceinline__ void keep_here(float& x) { asm volatile("" : "+v"(x)); }
+
 // ---- launchers (each validates nothing: the C-ABI layer has done it) ---------
 // fp32-arithmetic reference-shaped path, any storage type (used for VS_F32).
 hipError_t launch_prefill_simple(const vs_shape& s, const void* kc, const void* vc, int32_t len,

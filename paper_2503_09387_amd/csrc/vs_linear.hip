@@ -463,6 +463,11 @@ __global__ __launch_bounds__(256) void linear_reduce_kernel(LinParams p, int n_b
 
 // RMS norm of T rows of d numbers: out = x * gamma / sqrt(mean(x^2) + eps), fp32 arithmetic, one
 // rounding.  One workgroup per row, 8 numbers per thread and pass.
+// A row stays in registers between the two passes over it, and gamma is on its way before the sum is
+// known: one trip to memory instead of three in a row (layers of 50 rows 110.0 -> 108.7 us, of 170 rows
+// 169.0 -> 167.9 us, two norms in each; what is left of a launch is its start and its end).
+// R: pieces of 8 features a thread holds, rows of up to 2048 R features; 0: longer rows, read twice.
+template <int R>
 __global__ __launch_bounds__(256) void rmsnorm_kernel(const __bf16* __restrict__ x, const __bf16* __restrict__ gamma,
                                                       __bf16* __restrict__ out, int d, float eps) {
     __shared__ float part[4];
@@ -472,10 +477,32 @@ __global__ __launch_bounds__(256) void rmsnorm_kernel(const __bf16* __restrict__
     bf16x8* orow = reinterpret_cast<bf16x8*>(out + row * d);
     const int n8 = d / 8;
     float ss = 0.f;
-    for (int i = threadIdx.x; i < n8; i += 256) {
-        const bf16x8 v = xr[i];
+    raw16 xv[R ? R : 1], gv[R ? R : 1];
+    if constexpr (R > 0) {
 #pragma unroll
-        for (int j = 0; j < 8; ++j) ss += (float)v[j] * (float)v[j];
+        for (int u = 0; u < R; ++u) {  // (past the end: the last piece, not used)
+            const int i = min((int)threadIdx.x + 256 * u, n8 - 1);
+            xv[u] = reinterpret_cast<const raw16*>(xr)[i];
+            gv[u] = reinterpret_cast<const raw16*>(gr)[i];
+        }
+#pragma unroll
+        for (int u = 0; u < R; ++u) {
+            keep_here(xv[u]);
+            keep_here(gv[u]);
+        }
+#pragma unroll
+        for (int u = 0; u < R; ++u) {
+            if ((int)threadIdx.x + 256 * u >= n8) break;
+            const bf16x8 v = __builtin_bit_cast(bf16x8, xv[u]);
+#pragma unroll
+            for (int j = 0; j < 8; ++j) ss += (float)v[j] * (float)v[j];
+        }
+    } else {
+        for (int i = threadIdx.x; i < n8; i += 256) {
+            const bf16x8 v = xr[i];
+#pragma unroll
+            for (int j = 0; j < 8; ++j) ss += (float)v[j] * (float)v[j];
+        }
     }
 #pragma unroll
     for (int off = 32; off >= 1; off >>= 1) ss += __shfl_xor(ss, off);
@@ -483,12 +510,21 @@ __global__ __launch_bounds__(256) void rmsnorm_kernel(const __bf16* __restrict__
     __syncthreads();
     const float tot = (part[0] + part[1]) + (part[2] + part[3]);
     const float r = 1.0f / sqrtf(tot / (float)d + eps);
-    for (int i = threadIdx.x; i < n8; i += 256) {
-        const bf16x8 v = xr[i], g = gr[i];
+    auto scaled = [&](bf16x8 v, bf16x8 g) {
         bf16x8 y;
 #pragma unroll
         for (int j = 0; j < 8; ++j) y[j] = (__bf16)((float)v[j] * r * (float)g[j]);
-        orow[i] = y;
+        return y;
+    };
+    if constexpr (R > 0) {
+#pragma unroll
+        for (int u = 0; u < R; ++u) {
+            const int i = threadIdx.x + 256 * u;
+            if (i >= n8) break;
+            orow[i] = scaled(__builtin_bit_cast(bf16x8, xv[u]), __builtin_bit_cast(bf16x8, gv[u]));
+        }
+    } else {
+        for (int i = threadIdx.x; i < n8; i += 256) orow[i] = scaled(xr[i], gr[i]);
     }
 }
 
@@ -617,7 +653,10 @@ hipError_t launch_linear(const void* x, int32_t ldx, const void* w, int32_t n_ro
 
 hipError_t launch_rmsnorm(const void* x, const void* gamma, int32_t n_rows, int32_t d, float eps, void* out,
                           hipStream_t st) {
-    rmsnorm_kernel<<<n_rows, 256, 0, st>>>((const __bf16*)x, (const __bf16*)gamma, (__bf16*)out, d, eps);
+    const __bf16 *xb = (const __bf16*)x, *gb = (const __bf16*)gamma;
+    if (d <= 2 * 2048) rmsnorm_kernel<2><<<n_rows, 256, 0, st>>>(xb, gb, (__bf16*)out, d, eps);
+    else if (d <= 4 * 2048) rmsnorm_kernel<4><<<n_rows, 256, 0, st>>>(xb, gb, (__bf16*)out, d, eps);
+    else rmsnorm_kernel<0><<<n_rows, 256, 0, st>>>(xb, gb, (__bf16*)out, d, eps);
     return hipGetLastError();
 }
 

@@ -87,6 +87,15 @@ def test_rmsnorm_against_the_oracle(T, d, eps):
     _check_stage(_f64(out), oracle.rmsnorm(to_f64(x), to_f64(g), eps32), 1e-7, f"rmsnorm {T}x{d} eps {eps}")
 
 
+@pytest.mark.parametrize("T,d", [(2, 2040), (2, 4096), (3, 4104), (2, 8192), (2, 8200)])
+def test_rmsnorm_around_the_rows_held_in_registers(T, d):
+    x = draw(910 + d, (T, d), 1.7, "bf16")
+    g = (1.0 + 0.2 * draw(911 + d, (d,), 1.0, "f32")).to(BF)
+    xd = _dev(x)
+    vs.rmsnorm(xd, _dev(g), xd, eps=1e-6)
+    _check_stage(_f64(xd), oracle.rmsnorm(to_f64(x), to_f64(g), float(np.float32(1e-6))), 1e-7, f"rmsnorm {T}x{d} in place")
+
+
 def test_rmsnorm_in_place_and_zero_rows():
     """A row of zeros stays zero when eps > 0; writing over the input is allowed."""
     x = draw(77, (4, 256), 1.0, "bf16")
