@@ -12,16 +12,21 @@
 //   2. bank_shift_kernel: every workgroup finds the victim from the M cosines (or reads the
 //      index an earlier call left in device memory), then a table of per-carrier rows (the
 //      embeddings, or one layer's K or V rows) drops that row, closes the gap and takes the
-//      new row last.  A workgroup owns a 1 KB wide column block of one table: it loads up to
-//      128 rows into registers, waits for all its wavefronts to have theirs, and stores them one
-//      row up, so the move is in place and takes one round trip per 128 rows.
+//      new row last.  A workgroup owns a 128-byte wide column block of one table: it loads up to
+//      256 rows into registers, waits for all its wavefronts to have theirs, and stores them one
+//      row up, so the move is in place and takes one round trip per 256 rows.  (The rate of a
+//      compute unit bounds it: 1 KB wide blocks left 7 workgroups for the embeddings and 56 for the
+//      rows of 28 layers, 9.3 us per launch on average at M = 128; these take 4.3 us.)
 #include "vs_internal.h"
 
 namespace vs {
 namespace {
 
-constexpr int kShiftThreads = 256;   // 4 rows of 64 16-byte pieces per step
-constexpr int kShiftSteps = 32;      // rows per thread and pass: 128 rows per pass
+constexpr int kShiftThreads = 256;
+constexpr int kShiftLanes = 8;                             // 16-byte pieces of a row side by side: a column block of 128 bytes
+constexpr int kShiftRows = kShiftThreads / kShiftLanes;    // rows per step
+constexpr int kShiftSteps = 8;                             // rows per thread and pass: 256 rows per pass
+constexpr int kShiftPass = kShiftRows * kShiftSteps;
 
 __device__ __forceinline__ double block_sum(double x, double* lds) {  // fixed order, every thread gets the sum
 #pragma unroll
@@ -33,19 +38,49 @@ __device__ __forceinline__ double block_sum(double x, double* lds) {  // fixed o
     return (lds[0] + lds[1]) + (lds[2] + lds[3]);
 }
 
+// Bound by the trips to memory: both rows are requested at once, 16 bytes per thread, and pass through
+// LDS, from where thread t takes the elements t, t + 256, .. in order (7.0 -> 4.3 us at 128 x 3584).
 template <typename T>
 __global__ __launch_bounds__(256) void bank_cosine_kernel(const T* __restrict__ e, const T* __restrict__ e_new,
                                                           int M, int d, int policy, double* __restrict__ cosines) {
+    constexpr int kVec = 16 / sizeof(T), kSeg = 512 * kVec;  // elements of a row in LDS at a time: 8 KB
+    __shared__ __attribute__((aligned(16))) T rows[2][kSeg];
     __shared__ double lds[4];
     const int i = blockIdx.x;
     const T* a = e + (int64_t)i * d;
     const T* b = (policy == 1 || i + 1 == M) ? e_new : e + (int64_t)(i + 1) * d;
     double ab = 0.0, aa = 0.0, bb = 0.0;
-    for (int j = threadIdx.x; j < d; j += 256) {
-        const double x = (double)to_f32(a[j]), y = (double)to_f32(b[j]);
-        ab += x * y;
-        aa += x * x;
-        bb += y * y;
+    for (int j0 = 0; j0 < d; j0 += kSeg) {
+        const int n = min(kSeg, d - j0), n16 = n / kVec;  // (rows are whole multiples of 16 bytes)
+        raw16 va[2], vb[2];
+#pragma unroll
+        for (int u = 0; u < 2; ++u) {
+            const int c = min((int)threadIdx.x + 256 * u, n16 - 1);
+            va[u] = reinterpret_cast<const raw16*>(a + j0)[c];
+            vb[u] = reinterpret_cast<const raw16*>(b + j0)[c];
+        }
+#pragma unroll
+        for (int u = 0; u < 2; ++u) {
+            keep_here(va[u]);
+            keep_here(vb[u]);
+        }
+        if (j0) __syncthreads();
+#pragma unroll
+        for (int u = 0; u < 2; ++u) {
+            const int c = threadIdx.x + 256 * u;
+            if (c < n16) {
+                reinterpret_cast<raw16*>(rows[0])[c] = va[u];
+                reinterpret_cast<raw16*>(rows[1])[c] = vb[u];
+            }
+        }
+        __syncthreads();
+#pragma unroll 4
+        for (int j = threadIdx.x; j < n; j += 256) {
+            const double x = (double)to_f32(rows[0][j]), y = (double)to_f32(rows[1][j]);
+            ab += x * y;
+            aa += x * x;
+            bb += y * y;
+        }
     }
     ab = block_sum(ab, lds);
     aa = block_sum(aa, lds);
@@ -73,8 +108,8 @@ __global__ __launch_bounds__(kShiftThreads) void bank_shift_kernel(ShiftParams p
     __shared__ double s_cos[kShiftThreads / 64];
     __shared__ int s_idx[kShiftThreads / 64];
     const int tid = threadIdx.x;
-    const int64_t col = (int64_t)blockIdx.x * 1024 + (tid & 63) * 16;  // this thread's 16 bytes of a row
-    const int lr = tid >> 6;
+    const int64_t col = (int64_t)blockIdx.x * (16 * kShiftLanes) + (tid % kShiftLanes) * 16;  // this thread's 16 bytes of a row
+    const int lr = tid / kShiftLanes;
     char* const base = p.t.base[blockIdx.y] + (int64_t)p.first * p.row_bytes;
     const char* const new_row = p.t.new_row[blockIdx.y];
     const bool in_row = col < p.row_bytes;
@@ -85,6 +120,17 @@ __global__ __launch_bounds__(kShiftThreads) void bank_shift_kernel(ShiftParams p
         if (p.victim_io && blockIdx.x == 0 && blockIdx.y == 0 && tid == 0) *p.victim_io = -1;
         return;
     }
+    // a bank that one pass holds is requested before the victim is known (a trip to memory less)
+    const bool one_pass = p.M - 1 <= kShiftPass;
+    raw16 v[kShiftSteps];
+    auto fetch = [&](int r0) {
+#pragma unroll
+        for (int u = 0; u < kShiftSteps; ++u) {  // destination rows (past the end: the last row, not stored)
+            const int r = min(r0 + kShiftRows * u + lr + 1, p.M - 1);
+            v[u] = *reinterpret_cast<const raw16*>(base + (int64_t)r * p.row_bytes + min(col, p.row_bytes - 16));
+        }
+    };
+    if (one_pass) fetch(0);
     int victim;
     if (p.cosines) {
         // largest cosine, of equal ones the smallest index: thread t looks at cosines t, t + 256, ..,
@@ -130,20 +176,18 @@ __global__ __launch_bounds__(kShiftThreads) void bank_shift_kernel(ShiftParams p
         victim = *p.victim_io;
     }
     victim = min(max(victim, 0), p.M - 1);  // (an index from device memory is not trusted to be in range)
-    // rows victim+1 .. M-1 move to victim .. M-2, 128 rows per pass: all loads of a pass, a barrier,
-    // all its stores (a later pass reads only rows that no earlier pass has written)
-    for (int r0 = victim; r0 + 1 < p.M; r0 += 4 * kShiftSteps) {
-        uint4 v[kShiftSteps];
+    // rows victim+1 .. M-1 move to victim .. M-2, kShiftPass rows per pass: all loads of a pass, a
+    // barrier, all its stores (a later pass reads only rows that no earlier pass has written)
+    for (int r0 = one_pass ? 0 : victim; r0 + 1 < p.M; r0 += kShiftPass) {
+        if (!one_pass) fetch(r0);
 #pragma unroll
-        for (int u = 0; u < kShiftSteps; ++u) {
-            const int r = r0 + 4 * u + lr;  // destination row
-            if (r + 1 < p.M && in_row) v[u] = *reinterpret_cast<const uint4*>(base + (int64_t)(r + 1) * p.row_bytes + col);
-        }
+        for (int u = 0; u < kShiftSteps; ++u) keep_here(v[u]);  // (this wavefront's rows are in registers)
         __syncthreads();
 #pragma unroll
         for (int u = 0; u < kShiftSteps; ++u) {
-            const int r = r0 + 4 * u + lr;
-            if (r + 1 < p.M && in_row) *reinterpret_cast<uint4*>(base + (int64_t)r * p.row_bytes + col) = v[u];
+            const int r = r0 + kShiftRows * u + lr;
+            if (r >= victim && r + 1 < p.M && in_row)
+                *reinterpret_cast<raw16*>(base + (int64_t)r * p.row_bytes + col) = v[u];
         }
         __syncthreads();
     }
@@ -178,7 +222,7 @@ hipError_t launch_bank_shift(int32_t n_tables, void* const* bases, const void* c
         p.append_at = append_at;
         p.cosines = cosines;
         p.victim_io = victim_io;
-        bank_shift_kernel<<<dim3((unsigned)((row_bytes + 1023) / 1024), (unsigned)n), kShiftThreads, 0, st>>>(p);
+        bank_shift_kernel<<<dim3((unsigned)((row_bytes + 16 * kShiftLanes - 1) / (16 * kShiftLanes)), (unsigned)n), kShiftThreads, 0, st>>>(p);
         hipError_t e = hipGetLastError();
         if (e != hipSuccess) return e;
     }

@@ -831,6 +831,33 @@ def test_memory_bank_stream(dtype, M, d, policy):
     assert near_ties <= extra // 4
 
 
+@pytest.mark.parametrize("dtype,M,d", [("bf16", 33, 4104), ("f32", 257, 2052), ("bf16", 258, 72), ("bf16", 600, 8), ("f32", 1, 4)])
+def test_memory_bank_at_the_edges_of_a_pass(dtype, M, d):
+    """Banks around what one pass of the row move holds (256 rows), embeddings around what the cosines take
+    through LDS at a time (8 KB): victims against the fp64 oracle, the moved rows bit for bit."""
+    dt = torch_dtype(dtype)
+    emb = carrier_embeddings(11, M + 6, d, dtype)
+    bank = vs.Bank(emb[:M].clone().to(DEV), dtype, M)
+    victim = torch.full((1,), -5, dtype=torch.int32, device=DEV)
+    ws = torch.empty(vs.memory_bank_workspace_bytes(M), dtype=torch.uint8, device=DEV)
+    dim = 64 if dtype == "f32" else 128
+    shape = vs.Shape.make(4, 2, dim, dtype)
+    rows = draw(12, (M + 6, 2, 2, dim), 1.0, dtype)
+    cache = vs.Cache(rows[:M, 0].contiguous().to(DEV), rows[:M, 1].contiguous().to(DEV), M)
+    want, want_k, want_v = emb[:M].clone(), rows[:M, 0].clone(), rows[:M, 1].clone()
+    for t in range(M, M + 6):
+        vs.memory_bank_push(bank, emb[t].to(DEV), victim, ws)
+        k_new, v_new = (rows[t:t + 1, i].contiguous().to(DEV) for i in (0, 1))
+        vs.carrier_evict_append(shape, [cache], 0, M, k_new, v_new, victim)
+        got = int(victim.cpu()[0])
+        expect, cos = oracle.bank_victim(to_f64(want), to_f64(emb[t]))
+        assert got == expect or abs(cos[got] - cos[expect]) <= 1e-6
+        move = lambda rows_, new: torch.cat([rows_[:got], rows_[got + 1:], new[None]])
+        want, want_k, want_v = move(want, emb[t]), move(want_k, rows[t, 0]), move(want_v, rows[t, 1])
+        assert same_bits(bank.e, want) and same_bits(cache.k, want_k) and same_bits(cache.v, want_v)
+        assert cache.len == M and bank.len == M
+
+
 def test_memory_bank_ties_and_zero_vectors():
     """Equal cosines: the smallest index goes; a zero vector has cosine 0 and never wins over a
     positive one."""
