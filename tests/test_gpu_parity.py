@@ -733,6 +733,25 @@ def test_mean_pool(n, d, dtype):
         assert np.all(np.abs(got - ref) <= np.abs(ref) * 2.0 ** -8 + 1e-30)
 
 
+@pytest.mark.parametrize("n,d,dtype", [(191, 72, "bf16"), (192, 64, "bf16"), (193, 200, "bf16"), (385, 36, "f32")])
+def test_mean_pool_around_one_trip(n, d, dtype):
+    """Row counts around what a thread requests at once (12 rows of 16 row groups), ragged column blocks: bit for
+    bit the sum in the documented order, 16 row groups in order and then their sums in order."""
+    e = draw(32, (n, d), 1.0, dtype)
+    out = torch.empty(d, dtype=torch_dtype(dtype), device=DEV)
+    vs.carrier_mean_pool(e.to(DEV), out, dtype)
+    parts = []
+    for g in range(16):
+        acc = torch.zeros(d)
+        for r in range(g, n, 16):
+            acc = acc + e[r].float()
+        parts.append(acc)
+    tot = parts[0]
+    for part in parts[1:]:
+        tot = tot + part
+    assert same_bits(out, (tot / float(n)).to(torch_dtype(dtype)))
+
+
 @pytest.mark.parametrize("n_caches,pinned", [(28, False), (4096, False), (4095, True), (4096, True), (4097, True), (50, True)])
 def test_batched_compaction(n_caches, pinned):
     s, T, cap = QW, 6, 5
