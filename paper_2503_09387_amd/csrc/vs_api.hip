@@ -99,9 +99,23 @@ vs_status prefill_common(const vs_shape* shape, vs_cache* cache, bool append, co
         e = launch_prefill_mfma(*shape, cache->k, cache->v, cache->len, q, k_f, v_f, n_tokens, out,
                                 kdst, vdst, wsb + prefill_counter_offset(*shape), wsb + ctrl, stream, 1, append_all);
     } else {
+        // the kept rows are copied by the attention launch itself, unless the caller's run lies where
+        // they go (a run projected straight into the cache, say): then after it, in a launch of their own
+        const int64_t kept_bytes = n_kept * rb;
+        auto apart = [&](const void* p, int64_t bytes) {
+            const uintptr_t a = reinterpret_cast<uintptr_t>(p);
+            auto clear_of = [&](const char* dst) {
+                const uintptr_t b = reinterpret_cast<uintptr_t>(dst);
+                return a + (uintptr_t)bytes <= b || b + (uintptr_t)kept_bytes <= a;
+            };
+            return clear_of(kdst) && clear_of(vdst);
+        };
+        const int64_t qo_bytes = (int64_t)n_tokens * shape->n_q_heads * shape->head_dim * (int64_t)elem_bytes(shape);
+        const bool fused = append && apart(k_f, n_tokens * rb) && apart(v_f, n_tokens * rb) && apart(q, qo_bytes) &&
+                           apart(out, qo_bytes);
         e = launch_prefill_simple(*shape, cache->k, cache->v, cache->len, q, k_f, v_f, n_tokens, out,
-                                  stream);
-        if (e == hipSuccess && append) {
+                                  fused ? kdst : nullptr, fused ? vdst : nullptr, n_kept, stream);
+        if (e == hipSuccess && append && !fused) {
             // (the kept rows are contiguous in the run and in the cache: one block of n_kept rows,
             // handed to the row copy as a single long row at the destination itself)
             LenTable t{};

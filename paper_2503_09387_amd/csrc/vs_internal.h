@@ -35,10 +35,11 @@ __device__ __forceinline__ void keep_here(raw16& x) { asm volatile("" : "+v"(x))
 __device__ __forceinline__ void keep_here(float& x) { asm volatile("" : "+v"(x)); }
 
 // ---- launchers (each validates nothing: the C-ABI layer has done it) ---------
-// fp32-arithmetic reference-shaped path, any storage type (used for VS_F32).
+// fp32-arithmetic reference-shaped path, any storage type (used for VS_F32).  k_kept (may be null):
+// where the run's last n_kept rows go in the same launch; it must not overlap what the launch reads.
 hipError_t launch_prefill_simple(const vs_shape& s, const void* kc, const void* vc, int32_t len,
                                  const void* q, const void* kf, const void* vf, int32_t n_tokens,
-                                 void* out, hipStream_t st);
+                                 void* out, void* k_kept, void* v_kept, int32_t n_kept, hipStream_t st);
 hipError_t launch_decode_simple(const vs_shape& s, int32_t n_streams, const void* k_slab,
                                 const void* v_slab, int32_t capacity, const LenTable& lens,
                                 const void* q, void* out, hipStream_t st);

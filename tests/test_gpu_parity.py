@@ -752,6 +752,33 @@ def test_mean_pool_around_one_trip(n, d, dtype):
     assert same_bits(out, (tot / float(n)).to(torch_dtype(dtype)))
 
 
+@pytest.mark.parametrize("dim,L,T,n_kept,overlap", [(64, 0, 1, 1, False), (64, 63, 50, 1, False), (128, 250, 9, 9, False),
+                                                    (64, 16, 20, 20, True), (64, 16, 20, 1, True)])
+def test_fp32_prefill_appends_in_its_launch(dim, L, T, n_kept, overlap):
+    """The kept rows are copied by the attention launch; a run that lies where they go is copied after it."""
+    s = AttnShape(4, 2, dim, "f32")
+    hk, hv = cache_rows(41, s, max(L, 1), 1.0)
+    q, kf, vf = frame_inputs(42, s, T, 1.0)
+    k = torch.full((L + T + 3, 2, dim), 7.0, device=DEV)
+    v = torch.full_like(k, -7.0)
+    k[:L].copy_(hk[:L])
+    v[:L].copy_(hv[:L])
+    cache = vs.Cache(k, v, L)
+    at = L + 1 if n_kept == 1 else L  # (the run's rows in the cache; all kept: they are where they go)
+    kd, vd = (k[at:at + T], v[at:at + T]) if overlap else (torch.empty_like(kf, device=DEV), torch.empty_like(vf, device=DEV))
+    kd.copy_(kf)
+    vd.copy_(vf)
+    out = torch.full(q.shape, float("nan"), device=DEV)
+    ws = vs.make_workspace(vs_shape(s), T, L + T, 1, DEV)
+    call = vs.question_prefill_append if n_kept == T and T > 1 else vs.frame_prefill_compact
+    call(vs_shape(s), cache, q.to(DEV), kd, vd, out, ws)
+    check_close(out, oracle_prefill_rows(s, q, hk, hv, L, kf, vf), "f32", f"fp32 append D={dim} L={L} T={T}")
+    assert cache.len == L + n_kept
+    assert same_bits(k[L:L + n_kept], kf[T - n_kept:]) and same_bits(v[L:L + n_kept], vf[T - n_kept:])
+    if not overlap:
+        assert bool((k[L + n_kept:] == 7).all()) and bool((v[L + n_kept:] == -7).all())
+
+
 @pytest.mark.parametrize("n_caches,pinned", [(28, False), (4096, False), (4095, True), (4096, True), (4097, True), (50, True)])
 def test_batched_compaction(n_caches, pinned):
     s, T, cap = QW, 6, 5
