@@ -11,11 +11,13 @@
 // blockIdx.y selects the group of 4 heads.)  The grid is one workgroup per compute unit, so
 // they all run at once and stream for the whole launch.  A wavefront works alone, with no
 // barrier anywhere in the kernel:
-//   * K rows go straight from global memory into the A operand of
-//     v_mfma_f32_16x16x32_bf16 (S^T = K Q^T; the G query heads of the KV head are the
-//     columns, padded to 16);
-//   * V rows are loaded coalesced, parked row-major in a wave-private LDS buffer and come
-//     back transposed through ds_read_b64_tr_b16 for O^T += V^T P^T;
+//   * K and V rows are loaded coalesced and parked row-major in wave-private LDS buffers; K comes
+//     back as the A operand of v_mfma_f32_16x16x32_bf16 (S^T = K Q^T; the G query heads of the KV
+//     head are the columns, padded to 16), V transposed through ds_read_b64_tr_b16 for
+//     O^T += V^T P^T.  (Loaded straight in the operand's layout, 16 rows of 64 bytes per
+//     instruction, a K tile kept the compute unit's load path four times as long: 8 tiles in one
+//     workgroup 8.1 -> 6.8 us, one stream of 512 rows over 16 workgroups 9.4 -> 9.25 us with its
+//     merge; no difference at 16 long streams.)
 //   * the next tile's 16 KB are already in flight while the current tile is computed;
 //   * the softmax reference maximum is refreshed only when a score exceeds it by more than
 //     2^8, which needs one ballot per tile instead of two cross-lane reductions and one
@@ -24,11 +26,7 @@
 // wavefront that owns the stream's last tile updates on the side).  Every wavefront leaves a
 // normalised partial result (fp16 with a power-of-two scale per row) with its reference and sum; a second small kernel merges
 // them (a launch that follows another on the same stream starts within about a microsecond of
-// it; what the merge costs is its one round trip to memory).  Merging inside the attention
-// kernel, by the last wavefront of a stream to arrive, would need the partials of workgroups on
-// all 8 XCDs, whose L2 caches are not coherent with each other inside a kernel: they would
-// have to be written through and re-read at device scope, which on the prefill kernel cost
-// more than the second launch does here.
+// it; what the merge costs is its one round trip to memory).
 #include "vs_internal.h"
 
 namespace vs {
@@ -45,6 +43,8 @@ constexpr int kThreads = 256;
 constexpr int kWaves = 4;
 constexpr int TR = 32;      // rows per wave tile
 constexpr int VSTR = 144;   // LDS row stride of the V tile in elements (288 B)
+constexpr int KSTR = 136;   // and of the K tile (272 B)
+constexpr int kWaveLds = TR * (VSTR + KSTR) * 2;  // bytes: V tile, then K tile
 constexpr float kLog2e = 1.4426950408889634f;
 constexpr float kLazyMax = 8.0f;  // scores may exceed the reference maximum by 2^8 before it is refreshed
 
@@ -84,19 +84,19 @@ __device__ __forceinline__ bf16x4 lds_read_tr(const __bf16* p) {
 }
 
 // One tile (32 rows) of one wave: scores, lazy-reference softmax, value accumulation.
-// K0..K7 are the staged K operands (rows r0+i16 and r0+16+i16, four 32-wide slices each),
-// the V tile has already been parked in the wave's LDS buffer.
-#define VS_TILE_COMPUTE(R0, K00, K01, K02, K03, K10, K11, K12, K13)                                   \
+// The K and V tiles have been parked in the wave's LDS buffers.
+#define VS_KFRAG(HALF, SLICE) (*reinterpret_cast<const bf16x8*>(krd + 16 * (HALF) * KSTR + 32 * (SLICE)))
+#define VS_TILE_COMPUTE(R0)                                                                           \
     do {                                                                                              \
         f32x4 sa = {0.f, 0.f, 0.f, 0.f}, sb = sa;                                                     \
-        sa = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, K00), qf0, sa, 0, 0, 0); \
-        sb = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, K10), qf0, sb, 0, 0, 0); \
-        sa = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, K01), qf1, sa, 0, 0, 0); \
-        sb = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, K11), qf1, sb, 0, 0, 0); \
-        sa = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, K02), qf2, sa, 0, 0, 0); \
-        sb = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, K12), qf2, sb, 0, 0, 0); \
-        sa = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, K03), qf3, sa, 0, 0, 0); \
-        sb = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, K13), qf3, sb, 0, 0, 0); \
+        sa = __builtin_amdgcn_mfma_f32_16x16x32_bf16(VS_KFRAG(0, 0), qf0, sa, 0, 0, 0);               \
+        sb = __builtin_amdgcn_mfma_f32_16x16x32_bf16(VS_KFRAG(1, 0), qf0, sb, 0, 0, 0);               \
+        sa = __builtin_amdgcn_mfma_f32_16x16x32_bf16(VS_KFRAG(0, 1), qf1, sa, 0, 0, 0);               \
+        sb = __builtin_amdgcn_mfma_f32_16x16x32_bf16(VS_KFRAG(1, 1), qf1, sb, 0, 0, 0);               \
+        sa = __builtin_amdgcn_mfma_f32_16x16x32_bf16(VS_KFRAG(0, 2), qf2, sa, 0, 0, 0);               \
+        sb = __builtin_amdgcn_mfma_f32_16x16x32_bf16(VS_KFRAG(1, 2), qf2, sb, 0, 0, 0);               \
+        sa = __builtin_amdgcn_mfma_f32_16x16x32_bf16(VS_KFRAG(0, 3), qf3, sa, 0, 0, 0);               \
+        sb = __builtin_amdgcn_mfma_f32_16x16x32_bf16(VS_KFRAG(1, 3), qf3, sb, 0, 0, 0);               \
         float z[8];                                                                                   \
         _Pragma("unroll") for (int e = 0; e < 4; ++e) {                                               \
             z[e] = ((R0) + 4 * kq + e < row_end) ? sa[e] * p.scale_log2e : -INFINITY;                 \
@@ -132,7 +132,7 @@ __device__ __forceinline__ bf16x4 lds_read_tr(const __bf16* p) {
             __builtin_shufflevector(lo, hi4, 0, 1, 2, 3, 4, 5, 6, 7), pf, ACC, 0, 0, 0);        \
     } while (0)
 
-#define VS_KPTR(row) (((row) == new_row ? knew : kslab + (int64_t)(row) * row_stride) + 8 * kq)
+#define VS_KPTR(row) (((row) == new_row ? knew : kslab + (int64_t)(row) * row_stride) + 8 * i16)
 #define VS_VPTR(row) (((row) == new_row ? vnew : vslab + (int64_t)(row) * row_stride) + 8 * i16)
 // every K/V byte is read once by one wavefront: the loads are marked non-temporal
 typedef unsigned int u32x4_t __attribute__((ext_vector_type(4)));
@@ -141,15 +141,19 @@ __device__ __forceinline__ uint4 ld_nt(const void* p) {
     return make_uint4(v[0], v[1], v[2], v[3]);
 }
 #define VS_LD(ptr) ld_nt(ptr)
-// loads one tile into the register set named by suffix X: 8 K operands (rows r+i16 and
-// r+16+i16) and 8 V row pieces (individually named registers, so that nothing lands in scratch)
+// loads one tile into the register set named by suffix X: 8 K and 8 V row pieces (individually named
+// registers, so that nothing lands in scratch)
 #define VS_FETCH(tile, X)                                                            \
     do {                                                                             \
         const int fr0 = row_begin + (tile) * TR;                                     \
-        const __bf16* kpa_ = VS_KPTR(min(fr0 + i16, last));                          \
-        const __bf16* kpb_ = VS_KPTR(min(fr0 + 16 + i16, last));                     \
-        k0##X = VS_LD(kpa_); k1##X = VS_LD(kpa_ + 32); k2##X = VS_LD(kpa_ + 64); k3##X = VS_LD(kpa_ + 96); \
-        k4##X = VS_LD(kpb_); k5##X = VS_LD(kpb_ + 32); k6##X = VS_LD(kpb_ + 64); k7##X = VS_LD(kpb_ + 96); \
+        k0##X = VS_LD(VS_KPTR(min(fr0 + kq, last)));                                 \
+        k1##X = VS_LD(VS_KPTR(min(fr0 + 4 + kq, last)));                            \
+        k2##X = VS_LD(VS_KPTR(min(fr0 + 8 + kq, last)));                            \
+        k3##X = VS_LD(VS_KPTR(min(fr0 + 12 + kq, last)));                           \
+        k4##X = VS_LD(VS_KPTR(min(fr0 + 16 + kq, last)));                           \
+        k5##X = VS_LD(VS_KPTR(min(fr0 + 20 + kq, last)));                           \
+        k6##X = VS_LD(VS_KPTR(min(fr0 + 24 + kq, last)));                           \
+        k7##X = VS_LD(VS_KPTR(min(fr0 + 28 + kq, last)));                           \
         v0##X = VS_LD(VS_VPTR(min(fr0 + kq, last)));                                 \
         v1##X = VS_LD(VS_VPTR(min(fr0 + 4 + kq, last)));                             \
         v2##X = VS_LD(VS_VPTR(min(fr0 + 8 + kq, last)));                             \
@@ -159,17 +163,22 @@ __device__ __forceinline__ uint4 ld_nt(const void* p) {
         v6##X = VS_LD(VS_VPTR(min(fr0 + 24 + kq, last)));                            \
         v7##X = VS_LD(VS_VPTR(min(fr0 + 28 + kq, last)));                            \
     } while (0)
-#define VS_PARK_ROW(n, reg) *reinterpret_cast<uint4*>(&vs_w[(4 * (n) + kq) * VSTR + 8 * i16]) = reg
+#define VS_PARK_ROW(n, kreg, vreg)                                                   \
+    do {                                                                             \
+        *reinterpret_cast<uint4*>(&vs_k[(4 * (n) + kq) * KSTR + 8 * i16]) = kreg;     \
+        *reinterpret_cast<uint4*>(&vs_w[(4 * (n) + kq) * VSTR + 8 * i16]) = vreg;     \
+    } while (0)
 #define VS_PARK(X)                                                                   \
     do {                                                                             \
-        VS_PARK_ROW(0, v0##X); VS_PARK_ROW(1, v1##X); VS_PARK_ROW(2, v2##X); VS_PARK_ROW(3, v3##X); \
-        VS_PARK_ROW(4, v4##X); VS_PARK_ROW(5, v5##X); VS_PARK_ROW(6, v6##X); VS_PARK_ROW(7, v7##X); \
+        VS_PARK_ROW(0, k0##X, v0##X); VS_PARK_ROW(1, k1##X, v1##X);                  \
+        VS_PARK_ROW(2, k2##X, v2##X); VS_PARK_ROW(3, k3##X, v3##X);                  \
+        VS_PARK_ROW(4, k4##X, v4##X); VS_PARK_ROW(5, k5##X, v5##X);                  \
+        VS_PARK_ROW(6, k6##X, v6##X); VS_PARK_ROW(7, k7##X, v7##X);                  \
     } while (0)
-#define VS_TILE(R0, X) VS_TILE_COMPUTE(R0, k0##X, k1##X, k2##X, k3##X, k4##X, k5##X, k6##X, k7##X)
 
 // Grid (n_wg, Hkv / nh).
 __global__ __launch_bounds__(kThreads, 2) void decode_mfma_kernel(DecodeParams p) {
-    __shared__ __attribute__((aligned(16))) char smem[kWaves * TR * VSTR * 2];  // per-wave V tiles
+    __shared__ __attribute__((aligned(16))) char smem[kWaves * kWaveLds];  // per-wave V and K tiles
 
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -187,7 +196,9 @@ __global__ __launch_bounds__(kThreads, 2) void decode_mfma_kernel(DecodeParams p
     const int len_of = p.lens.v[min(lane, kMaxStreamsPerLaunch - 1)];
     // stream of the first tile: the number of streams that end at or before it
     int s = __builtin_popcountll(__ballot(end_of <= flat));
-    __bf16* vs_w = reinterpret_cast<__bf16*>(smem) + wave * (TR * VSTR);
+    __bf16* vs_w = reinterpret_cast<__bf16*>(smem + wave * kWaveLds);
+    __bf16* vs_k = vs_w + TR * VSTR;
+    const __bf16* krd = &vs_k[i16 * KSTR + 8 * kq];
     const __bf16* vrd = &vs_w[(4 * kq + (i16 >> 2)) * VSTR + 4 * (i16 & 3)];
 
   for (; flat < flat_end; ++s) {
@@ -251,11 +262,11 @@ __global__ __launch_bounds__(kThreads, 2) void decode_mfma_kernel(DecodeParams p
     // the LDS buffer is private to the wave, whose LDS operations execute in program order
     for (int t = 0; t < n_tiles; t += 2) {
         VS_PARK(a);
-        VS_TILE(row_begin + t * TR, a);
+        VS_TILE_COMPUTE(row_begin + t * TR);
         if (t + 2 < n_tiles) VS_FETCH(t + 2, a);
         if (t + 1 < n_tiles) {
             VS_PARK(b);
-            VS_TILE(row_begin + (t + 1) * TR, b);
+            VS_TILE_COMPUTE(row_begin + (t + 1) * TR);
             if (t + 3 < n_tiles) VS_FETCH(t + 3, b);
         }
     }
@@ -314,20 +325,25 @@ __global__ __launch_bounds__(kThreads, 2) void decode_mfma_kernel(DecodeParams p
 #undef VS_FETCH
 #undef VS_PARK
 #undef VS_PARK_ROW
-#undef VS_TILE
+#undef VS_KFRAG
 
 // Merge of a stream's partials (a stream that one wavefront per head covered alone was written
 // directly).  Grid (streams, query heads), one wavefront each = 4 groups of 16 lanes: a lane owns
-// 8 output dims and the partials group, group + 4, ..; up to kCombineDepth of them per lane are
+// 8 output dims and the partials group, group + 4, ..; up to kDepth of them per lane are
 // requested at once (one round trip to memory for up to 64 partials), merged in the lane in index
-// order, and the four groups are then merged with two lane exchanges.  No LDS, no barrier.
-constexpr int kCombineGroups = 4, kCombineDepth = 16;
-__global__ __launch_bounds__(64) void decode_combine_kernel(DecodeParams p) {
+// order, and the four groups are then merged with two lane exchanges.  No LDS, no barrier.  A depth that
+// fits the number of partials leaves out loads that only repeat the last one: one stream of 700 rows
+// 9.45 -> 8.8 us per call; four wavefronts for more than 64: one stream of 8192 rows 17.2 -> 13.1 us.
+// kDepth: partials a group requests at once.  kCW > 1 (streams of more than 64 partials): that many
+// wavefronts, the groups of all of them dealing the partials out, which then meet in LDS.
+constexpr int kCombineGroups = 4;
+template <int kDepth, int kCW>
+__global__ __launch_bounds__(64 * kCW) void decode_combine_kernel(DecodeParams p) {
     const int s = blockIdx.x, hq = blockIdx.y;
     const int w_first = p.first_wg[s], n_wgs = p.n_wgs[s];
     if (n_wgs == 1 && p.nsub == 1) return;
     const int g = hq / p.G, h = hq - g * p.G;
-    const int lane = threadIdx.x, pg = lane >> 4, t = lane & 15, d8 = t * 8;
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, pg = lane >> 4, t = lane & 15, d8 = t * 8;
     const int n_parts = n_wgs * p.nsub;
     // partial c of the stream: workgroup w_first + c / nsub, sub-range c % nsub
     const int64_t slot_rows = (int64_t)p.Hkv * p.nsub * p.G;
@@ -338,22 +354,23 @@ __global__ __launch_bounds__(64) void decode_combine_kernel(DecodeParams p) {
     float acc[8], den = 0.f, mref = -INFINITY;
 #pragma unroll
     for (int j = 0; j < 8; ++j) acc[j] = 0.f;
-    for (int c0 = pg; c0 < n_parts; c0 += kCombineGroups * kCombineDepth) {
-        float4 ml[kCombineDepth];  // reference, sum, inverse scale of the stored row
-        f16x8 o[kCombineDepth];
+    constexpr int kStep = kCombineGroups * kCW;
+    for (int c0 = wave * kCombineGroups + pg; c0 < n_parts; c0 += kStep * kDepth) {
+        float4 ml[kDepth];  // reference, sum, inverse scale of the stored row
+        f16x8 o[kDepth];
 #pragma unroll
-        for (int u = 0; u < kCombineDepth; ++u) {
-            const int c = min(c0 + kCombineGroups * u, n_parts - 1);  // (past the end: a valid row, ignored below)
+        for (int u = 0; u < kDepth; ++u) {
+            const int c = min(c0 + kStep * u, n_parts - 1);  // (past the end: a valid row, ignored below)
             const int64_t pr = row_of(c);
             ml[u] = *reinterpret_cast<const float4*>(p.part_ml + pr * 4);
             o[u] = *reinterpret_cast<const f16x8*>(p.part_o + pr * D + d8);
         }
 #pragma unroll
-        for (int u = 0; u < kCombineDepth; ++u)
-            if (c0 + kCombineGroups * u >= n_parts) ml[u] = make_float4(-INFINITY, 0.f, 0.f, 0.f);
+        for (int u = 0; u < kDepth; ++u)
+            if (c0 + kStep * u >= n_parts) ml[u] = make_float4(-INFINITY, 0.f, 0.f, 0.f);
         float mx = mref;
 #pragma unroll
-        for (int u = 0; u < kCombineDepth; ++u) mx = fmaxf(mx, ml[u].x);
+        for (int u = 0; u < kDepth; ++u) mx = fmaxf(mx, ml[u].x);
         if (mx == -INFINITY) continue;
         const float sc = (mref == -INFINITY) ? 0.f : __builtin_amdgcn_exp2f(mref - mx);
         den *= sc;
@@ -361,7 +378,7 @@ __global__ __launch_bounds__(64) void decode_combine_kernel(DecodeParams p) {
         for (int j = 0; j < 8; ++j) acc[j] *= sc;
         mref = mx;
 #pragma unroll
-        for (int u = 0; u < kCombineDepth; ++u) {
+        for (int u = 0; u < kDepth; ++u) {
             const float wt = (ml[u].x == -INFINITY) ? 0.f : __builtin_amdgcn_exp2f(ml[u].x - mx) * ml[u].y;
             den += wt;
             const float wo = wt * ml[u].z;
@@ -385,6 +402,29 @@ __global__ __launch_bounds__(64) void decode_combine_kernel(DecodeParams p) {
         }
         den = low ? den * a0 + d2 * a1 : d2 * a1 + den * a0;
         mref = mx;
+    }
+    if constexpr (kCW > 1) {
+        __shared__ float s_acc[kCW][16][9], s_m[kCW], s_d[kCW];  // (9: rows of 8 apart from one another in the banks)
+        if (pg == 0) {
+#pragma unroll
+            for (int j = 0; j < 8; ++j) s_acc[wave][t][j] = acc[j];
+            if (t == 0) {
+                s_m[wave] = mref;
+                s_d[wave] = den;
+            }
+        }
+        __syncthreads();
+        if (wave != 0) return;
+#pragma unroll
+        for (int w = 1; w < kCW; ++w) {
+            const float m2 = s_m[w], mx = fmaxf(mref, m2);
+            const float a0 = (mref == -INFINITY) ? 0.f : __builtin_amdgcn_exp2f(mref - mx);
+            const float a1 = (m2 == -INFINITY) ? 0.f : __builtin_amdgcn_exp2f(m2 - mx);
+            den = den * a0 + s_d[w] * a1;
+#pragma unroll
+            for (int j = 0; j < 8; ++j) acc[j] = acc[j] * a0 + s_acc[w][t][j] * a1;
+            mref = mx;
+        }
     }
     if (pg != 0) return;
     const float inv = 1.0f / den;
@@ -475,7 +515,13 @@ hipError_t launch_decode_mfma(const vs_shape& s, int32_t n_streams, void* k_slab
     decode_mfma_kernel<<<grid, kThreads, 0, st>>>(p);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
-    decode_combine_kernel<<<dim3(n_streams, s.n_q_heads), 64, 0, st>>>(p);
+    int most = 1;  // partials of a stream
+    for (int i = 0; i < n_streams; ++i) most = p.n_wgs[i] * p.nsub > most ? p.n_wgs[i] * p.nsub : most;
+    const dim3 cgrid(n_streams, s.n_q_heads);
+    if (most <= 4 * kCombineGroups) decode_combine_kernel<4, 1><<<cgrid, 64, 0, st>>>(p);
+    else if (most <= 8 * kCombineGroups) decode_combine_kernel<8, 1><<<cgrid, 64, 0, st>>>(p);
+    else if (most <= 16 * kCombineGroups) decode_combine_kernel<16, 1><<<cgrid, 64, 0, st>>>(p);
+    else decode_combine_kernel<16, 4><<<cgrid, 256, 0, st>>>(p);
     return hipGetLastError();
 }
 
