@@ -26,7 +26,8 @@
 // wavefront that owns the stream's last tile updates on the side).  Every wavefront leaves a
 // normalised partial result (fp16 with a power-of-two scale per row) with its reference and sum; a second small kernel merges
 // them (a launch that follows another on the same stream starts within about a microsecond of
-// it; what the merge costs is its one round trip to memory).
+// it; what the merge costs is its one round trip to memory).  For few rows there is a kernel
+// that merges inside the launch, further down.
 #include "vs_internal.h"
 
 namespace vs {
@@ -317,6 +318,213 @@ __global__ __launch_bounds__(kThreads, 2) void decode_mfma_kernel(DecodeParams p
     flat = first_of + seg_b;  // next segment: the next stream
   }
 }
+// ---- few rows: one launch, merged inside ----
+// With few rows a step is a chain of latencies, and the second launch with its trip to memory is
+// 3 us of 8.  Here a workgroup is a share of ONE stream's rows for one KV head: its W wavefronts
+// take sub-ranges of the share (a tile or two each) and meet in LDS.  A stream of several shares
+// then passes fp32 partial results (G rows of 512 bytes per share) through memory at agent scope:
+// stores and loads that pass the L2s, which are not coherent with each other; every store
+// acknowledged before the workgroup counts itself in; the last one to arrive adds the shares in
+// index order, and nobody waits.  The counter goes back to zero with the last arrival.
+// Measured (28/4 heads, us per call, this kernel and the two launches): 1 stream of 128 rows 5.3 / 7.8,
+// of 256 6.8 / 7.7, of 700 8.6 / 8.8; 16 streams of 700 10.9 / 12.5, of 3000 22.7 / 25.5; 64 of 700 20.0 / 24.8.
+struct ShortParams {
+    __bf16* k_slab;
+    __bf16* v_slab;
+    const __bf16* q;
+    const __bf16* k_new;  // may be null
+    const __bf16* v_new;
+    __bf16* out;
+    float* part_o;        // [share][Hkv][G][D], not normalised
+    float* part_ml;       // [share][Hkv][G][2]: reference (log2 units), sum
+    unsigned* counters;   // [stream][Hkv], zero between launches
+    int64_t stream_stride;
+    int G, Hq, Hkv;
+    float scale_log2e;
+    LenTable lens;        // valid rows per stream, the appended row included
+    int share_end[kMaxStreamsPerLaunch];  // shares of the streams up to and with this one
+};
+
+__device__ __forceinline__ void store_agent(float* dst, float a, float b) {
+    const unsigned long long v = (unsigned long long)__float_as_uint(a) | ((unsigned long long)__float_as_uint(b) << 32);
+    __hip_atomic_store(reinterpret_cast<unsigned long long*>(dst), v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+__device__ __forceinline__ float2 load_agent(const float* src) {
+    const unsigned long long v = __hip_atomic_load(reinterpret_cast<const unsigned long long*>(src), __ATOMIC_RELAXED,
+                                                   __HIP_MEMORY_SCOPE_AGENT);
+    return make_float2(__uint_as_float((unsigned)v), __uint_as_float((unsigned)(v >> 32)));
+}
+
+// Grid (shares of all streams, Hkv).
+template <int W>
+__global__ __launch_bounds__(64 * W) void decode_short_kernel(ShortParams p) {
+    constexpr int kRowStride = D + 4;                                        // of a head's sums in LDS, in floats
+    constexpr int kWaveBytes = kWaveLds;
+    static_assert(kMaxGroup * kRowStride * 4 <= kWaveBytes, "a wavefront's sums take the place of its V tile");
+    __shared__ __attribute__((aligned(16))) char smem[W * kWaveBytes];
+    __shared__ float s_m[W][16], s_l[W][16];
+    __shared__ int s_last;
+
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int i16 = lane & 15, kq = lane >> 4;
+    const int g = blockIdx.y, share = blockIdx.x;
+    const int64_t row_stride = (int64_t)p.Hkv * D;
+    static_assert(kMaxStreamsPerLaunch == 64, "one lane per stream");
+    const int end_of = p.share_end[lane];
+    const int len_of = p.lens.v[lane];
+    const int s = __builtin_popcountll(__ballot(end_of <= share));
+    const int len = __builtin_amdgcn_readlane(len_of, s);
+    const int first_share = s ? __builtin_amdgcn_readlane(end_of, s - 1) : 0;
+    const int n_shares = __builtin_amdgcn_readlane(end_of, s) - first_share, j_share = share - first_share;
+    const int stream_tiles = (len + TR - 1) / TR;
+    const int seg_a = stream_tiles * j_share / n_shares, seg_b = stream_tiles * (j_share + 1) / n_shares;
+    const int tile_a = seg_a + (seg_b - seg_a) * wave / W;
+    const int tile_b = seg_a + (seg_b - seg_a) * (wave + 1) / W;
+    const int row_begin = tile_a * TR;
+    const int row_end = min(len, tile_b * TR);
+    const int n_tiles = tile_b - tile_a;
+    const int last = max(row_end - 1, 0);
+    const int new_row = p.k_new ? len - 1 : -1;
+    __bf16* kslab = p.k_slab + (int64_t)s * p.stream_stride + (int64_t)g * D;
+    __bf16* vslab = p.v_slab + (int64_t)s * p.stream_stride + (int64_t)g * D;
+    const __bf16* knew = p.k_new ? p.k_new + ((int64_t)s * p.Hkv + g) * D : nullptr;
+    const __bf16* vnew = p.v_new ? p.v_new + ((int64_t)s * p.Hkv + g) * D : nullptr;
+    __bf16* vs_w = reinterpret_cast<__bf16*>(smem + wave * kWaveBytes);
+    __bf16* vs_k = vs_w + TR * VSTR;
+    const __bf16* krd = &vs_k[i16 * KSTR + 8 * kq];
+    const __bf16* vrd = &vs_w[(4 * kq + (i16 >> 2)) * VSTR + 4 * (i16 & 3)];
+
+    f32x4 o0 = {0.f, 0.f, 0.f, 0.f}, o1 = o0, o2 = o0, o3 = o0, o4 = o0, o5 = o0, o6 = o0, o7 = o0;
+    float m_ref = -INFINITY, l_run = 0.f;
+    if (n_tiles > 0) {
+        const uint4 zz = make_uint4(0, 0, 0, 0);
+        uint4 k0a, k1a, k2a, k3a, k4a, k5a, k6a, k7a, v0a, v1a, v2a, v3a, v4a, v5a, v6a, v7a;
+        uint4 k0b = zz, k1b = zz, k2b = zz, k3b = zz, k4b = zz, k5b = zz, k6b = zz, k7b = zz;
+        uint4 v0b = zz, v1b = zz, v2b = zz, v3b = zz, v4b = zz, v5b = zz, v6b = zz, v7b = zz;
+        VS_FETCH(0, a);
+        if (1 < n_tiles) VS_FETCH(1, b);
+        if (new_row >= 0 && tile_b == stream_tiles && lane < 32) {  // (nobody reads the slab's copy in this launch)
+            const int c = lane & 15;
+            const uint4* src = reinterpret_cast<const uint4*>(lane < 16 ? knew : vnew) + c;
+            uint4* dst = reinterpret_cast<uint4*>((lane < 16 ? kslab : vslab) + (int64_t)new_row * row_stride) + c;
+            *dst = *src;
+        }
+        bf16x8 qf0, qf1, qf2, qf3;
+        {
+            const __bf16* qrow = p.q + ((int64_t)s * p.Hq + (int64_t)g * p.G + min(i16, p.G - 1)) * D + 8 * kq;
+            const uint4 a = VS_LD(qrow), b = VS_LD(qrow + 32), c = VS_LD(qrow + 64), d = VS_LD(qrow + 96);
+            qf0 = __builtin_bit_cast(bf16x8, a);  // (columns beyond the G heads repeat the last one and are not used)
+            qf1 = __builtin_bit_cast(bf16x8, b);
+            qf2 = __builtin_bit_cast(bf16x8, c);
+            qf3 = __builtin_bit_cast(bf16x8, d);
+        }
+        for (int t = 0; t < n_tiles; t += 2) {
+            VS_PARK(a);
+            VS_TILE_COMPUTE(row_begin + t * TR);
+            if (t + 2 < n_tiles) VS_FETCH(t + 2, a);
+            if (t + 1 < n_tiles) {
+                VS_PARK(b);
+                VS_TILE_COMPUTE(row_begin + (t + 1) * TR);
+                if (t + 3 < n_tiles) VS_FETCH(t + 3, b);
+            }
+        }
+        l_run += __shfl_xor(l_run, 16);
+        l_run += __shfl_xor(l_run, 32);
+    }
+
+    // ---- the wavefronts meet in LDS ----
+    if (kq == 0) {
+        s_m[wave][i16] = m_ref;
+        s_l[wave][i16] = l_run;
+    }
+    __syncthreads();
+    {
+        float mx = s_m[0][i16];
+#pragma unroll
+        for (int w = 1; w < W; ++w) mx = fmaxf(mx, s_m[w][i16]);
+        const float f = __builtin_amdgcn_exp2f(m_ref - mx);  // 0 for a wavefront without rows
+        float* row = reinterpret_cast<float*>(smem + wave * kWaveBytes) + i16 * kRowStride + 4 * kq;
+        if (i16 < p.G) {
+#define VS_OUT(ACC, DB) *reinterpret_cast<f32x4*>(row + 16 * (DB)) = ACC * f
+            VS_OUT(o0, 0); VS_OUT(o1, 1); VS_OUT(o2, 2); VS_OUT(o3, 3);
+            VS_OUT(o4, 4); VS_OUT(o5, 5); VS_OUT(o6, 6); VS_OUT(o7, 7);
+#undef VS_OUT
+        }
+    }
+    __syncthreads();
+    const int n_items = p.G * (D / 2);  // (head, pair of dims)
+    typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+    for (int it = tid; it < n_items; it += 64 * W) {
+        const int head = it / (D / 2), dp = 2 * (it % (D / 2));
+        float mx = s_m[0][head];
+#pragma unroll
+        for (int w = 1; w < W; ++w) mx = fmaxf(mx, s_m[w][head]);
+        float l = 0.f, a = 0.f, b = 0.f;
+#pragma unroll
+        for (int w = 0; w < W; ++w) {
+            l += s_l[w][head] * __builtin_amdgcn_exp2f(s_m[w][head] - mx);
+            const float2 v = *reinterpret_cast<const float2*>(reinterpret_cast<const float*>(smem + w * kWaveBytes) + head * kRowStride + dp);
+            a += v.x;
+            b += v.y;
+        }
+        if (n_shares == 1) {
+            const float inv = 1.0f / l;
+            *reinterpret_cast<bf16x2*>(p.out + ((int64_t)s * p.Hq + (int64_t)g * p.G + head) * D + dp) =
+                bf16x2{(__bf16)(a * inv), (__bf16)(b * inv)};
+        } else {
+            const int64_t pr = ((int64_t)share * p.Hkv + g) * p.G + head;
+            store_agent(p.part_o + pr * D + dp, a, b);
+            if (dp == 0) store_agent(p.part_ml + pr * 2, mx, l);
+        }
+    }
+    if (n_shares == 1) return;
+
+    // ---- the shares of the stream: the last to arrive adds them ----
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // this wavefront's partial results have arrived
+    __syncthreads();
+    if (tid == 0) {
+        unsigned* counter = p.counters + s * p.Hkv + g;
+        const unsigned before = __hip_atomic_fetch_add(counter, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        s_last = before == (unsigned)(n_shares - 1);
+        if (s_last) __hip_atomic_store(counter, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
+    __syncthreads();
+    if (!s_last) return;
+    constexpr int kDepth = 8;
+    for (int it = tid; it < n_items; it += 64 * W) {
+        const int head = it / (D / 2), dp = 2 * (it % (D / 2));
+        const int64_t pr0 = ((int64_t)first_share * p.Hkv + g) * p.G + head, step = (int64_t)p.Hkv * p.G;
+        float mref = -INFINITY, l = 0.f, a = 0.f, b = 0.f;
+        for (int j0 = 0; j0 < n_shares; j0 += kDepth) {
+            float2 ml[kDepth], o[kDepth];
+#pragma unroll
+            for (int u = 0; u < kDepth; ++u) {
+                const int64_t pr = pr0 + min(j0 + u, n_shares - 1) * step;
+                ml[u] = load_agent(p.part_ml + pr * 2);
+                o[u] = load_agent(p.part_o + pr * D + dp);
+            }
+            float mx = mref;
+#pragma unroll
+            for (int u = 0; u < kDepth; ++u) mx = fmaxf(mx, ml[u].x);
+            const float f = __builtin_amdgcn_exp2f(mref - mx);  // 0 before the first batch
+            l *= f;
+            a *= f;
+            b *= f;
+            mref = mx;
+#pragma unroll
+            for (int u = 0; u < kDepth; ++u) {
+                const float w = j0 + u < n_shares ? __builtin_amdgcn_exp2f(ml[u].x - mx) : 0.f;
+                l += w * ml[u].y;
+                a += w * o[u].x;
+                b += w * o[u].y;
+            }
+        }
+        const float inv = 1.0f / l;
+        *reinterpret_cast<bf16x2*>(p.out + ((int64_t)s * p.Hq + (int64_t)g * p.G + head) * D + dp) =
+            bf16x2{(__bf16)(a * inv), (__bf16)(b * inv)};
+    }
+}
 #undef VS_TILE_COMPUTE
 #undef VS_PV
 #undef VS_KPTR
@@ -440,6 +648,48 @@ constexpr int kDecodeMaxWorkgroups = 1024;
 // other wavefronts take sub-ranges of the share.  One rule for the sizing and the launch.
 int heads_per_workgroup(int n_kv_heads) { return n_kv_heads % 4 == 0 ? 4 : (n_kv_heads % 2 == 0 ? 2 : 1); }
 
+// Whether a step is one of few rows, and its shares: wavefronts per workgroup (0: the kernel that shares
+// all rows out equally) and tiles per share.
+struct ShortPlan {
+    int waves, tiles;
+};
+inline int shares_of(int rows, int tiles) { return ((rows + TR - 1) / TR + tiles - 1) / tiles; }
+
+// All workgroups must run at once, one per compute unit.  Measured at 28/4, 16/2, 24/8 and 12/6 heads, 1 to 64
+// streams of 64 to 8192 rows (us per call, this kernel / the two launches):
+//   * up to 8 tiles per stream: one share each and no merge, 4 wavefronts up to 4 tiles;
+//   * up to 32 tiles: shares of 4 tiles (8.6 / 8.8 at 1 x 700, 9.2 / 9.5 at 4 x 700; shares of 8: 9.0, 9.6);
+//   * beyond, the fewest tiles from 8 on with which the shares fit the chip, up to 24 (23.2 / 25.5 at 8 x 6000;
+//     32 tiles, 8 x 8192: 30.4 / 29.5) and up to 12 shares per stream, which one workgroup adds
+//     (24 and 32 shares, 1 x 6000 and 1 x 8192: 12.4 / 11.9 and 13.7 / 13.1);
+//   * shares are cut per stream: where ragged streams would leave the largest share more than 1.4 times
+//     its equal part of the rows, the other kernel's equal shares are better, except at 8 tiles, where
+//     latency decides and not the amount (10.4 / 11.0 at 4 x 1500).
+ShortPlan short_plan(const LenTable& lens, int n_streams, int n_kv_heads) {
+    int64_t total = 0;
+    int most = 0;
+    for (int i = 0; i < n_streams; ++i) {
+        const int t = (lens.v[i] + TR - 1) / TR;
+        total += t;
+        most = t > most ? t : most;
+    }
+    constexpr int kChip = 256, kMaxTiles = 24, kMaxShares = 12;
+    auto fits = [&](int tiles) {
+        int64_t n = 0;
+        for (int i = 0; i < n_streams; ++i) n += shares_of(lens.v[i], tiles);
+        return n * n_kv_heads <= kChip;
+    };
+    if (most > kMaxTiles * kMaxShares || total * n_kv_heads > (int64_t)kChip * kMaxTiles) return {0, 0};
+    if (most <= 4 && fits(4)) return {4, 4};
+    if (most > 8 && most <= 32 && fits(4)) return {4, 4};
+    for (int tiles = 8; tiles <= kMaxTiles; ++tiles) {
+        if ((most + tiles - 1) / tiles > kMaxShares || !fits(tiles)) continue;
+        if (tiles > 8 && 5.0 * tiles * kChip > 7.0 * (double)total * n_kv_heads) break;
+        return {8, tiles};
+    }
+    return {0, 0};
+}
+
 // Rows of partial results: a slot per (workgroup + stream of the segment), each with one row per
 // (KV head, sub-range, query head of the group).
 int64_t partial_rows(const vs_shape& s, int32_t n_streams) {
@@ -455,8 +705,37 @@ size_t decode_mfma_workspace_bytes(const vs_shape& s, int32_t n_streams, int32_t
 
 hipError_t launch_decode_mfma(const vs_shape& s, int32_t n_streams, void* k_slab, void* v_slab,
                               int32_t capacity, const LenTable& lens, const void* q,
-                              const void* k_new, const void* v_new, void* out, void* /*counters*/,
+                              const void* k_new, const void* v_new, void* out, void* counters,
                               void* workspace, hipStream_t st) {
+    const ShortPlan plan = g_tune_decode_chunk_rows ? ShortPlan{0, 0} : short_plan(lens, n_streams, s.n_kv_heads);
+    if (plan.waves) {
+        ShortParams h;
+        h.k_slab = (__bf16*)k_slab;
+        h.v_slab = (__bf16*)v_slab;
+        h.q = (const __bf16*)q;
+        h.k_new = (const __bf16*)k_new;
+        h.v_new = (const __bf16*)v_new;
+        h.out = (__bf16*)out;
+        h.stream_stride = (int64_t)capacity * s.n_kv_heads * D;
+        h.G = s.n_q_heads / s.n_kv_heads;
+        h.Hq = s.n_q_heads;
+        h.Hkv = s.n_kv_heads;
+        h.scale_log2e = s.softmax_scale * kLog2e;
+        h.lens = lens;
+        int n = 0;
+        for (int i = 0; i < kMaxStreamsPerLaunch; ++i) {
+            if (i < n_streams) n += shares_of(lens.v[i], plan.tiles);
+            h.share_end[i] = i < n_streams ? n : 0x7fffffff;  // (never "before" a share)
+        }
+        // (at most 256 shares of 520 bytes per query head; the workspace holds more than 1024 x 272)
+        h.counters = (unsigned*)counters;
+        h.part_ml = (float*)workspace;
+        h.part_o = h.part_ml + (int64_t)n * s.n_q_heads * 2;
+        const dim3 grid(n, s.n_kv_heads);
+        if (plan.waves == 4) decode_short_kernel<4><<<grid, 256, 0, st>>>(h);
+        else decode_short_kernel<8><<<grid, 512, 0, st>>>(h);
+        return hipGetLastError();
+    }
     DecodeParams p;
     p.k_slab = (__bf16*)k_slab;
     p.v_slab = (__bf16*)v_slab;

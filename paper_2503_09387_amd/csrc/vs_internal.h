@@ -62,16 +62,16 @@ int prefill_frames_splits(const vs_shape& s, int32_t n_frames, int32_t n_tokens,
 int prefill_frames_max_splits(const vs_shape& s, int32_t n_frames, int32_t n_tokens, int32_t max_len);
 
 // bf16 split-row decode over ragged streams; appends (k_new, v_new) on the side when given.
-// `counters` points at the front of an initialised workspace's control block: reserved for the decode
-// kernels, which at present keep no state between or within launches there.
+// `counters`: the front of an initialised workspace's control block, [kMaxStreamsPerLaunch][Hkv] arrival
+// counters that are zero between launches.
 size_t decode_mfma_workspace_bytes(const vs_shape& s, int32_t n_streams, int32_t max_rows);
 hipError_t launch_decode_mfma(const vs_shape& s, int32_t n_streams, void* k_slab, void* v_slab,
                               int32_t capacity, const LenTable& lens, const void* q,
                               const void* k_new, const void* v_new, void* out, void* counters,
                               void* workspace, hipStream_t st);
 
-// Control block at the start of every workspace: [kMaxStreamsPerLaunch][Hkv] words reserved for decode
-// (unused), then the prefill's arrival counters, one per unit = (KV head, frame, row tile), each alone
+// Control block at the start of every workspace: [kMaxStreamsPerLaunch][Hkv] arrival counters of the
+// decode steps of few rows, then the prefill's arrival counters, one per unit = (KV head, frame, row tile), each alone
 // in 128 bytes (the workgroups of a unit look at theirs while they wait for one another: counters of
 // other units in the same line would queue behind those looks).  A counter wraps to zero with the last
 // arrival, so all of them are zero between launches.

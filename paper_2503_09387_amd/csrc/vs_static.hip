@@ -50,8 +50,9 @@ vs_status vs_decode_attn_static(const vs_shape* shape, int32_t n_streams, void* 
     (void)hipGetLastError();
     unsigned char* ptr = nullptr;
     if (scratch_of_current_device(&ptr) != hipSuccess) return VS_ERR_HIP;
-    // Nothing in the array has to be zero for a decode call: every partial result that the merge
-    // reads is written earlier in the same call.
+    // Every partial result that a merge reads is written earlier in the same call.  The arrival counters
+    // at the front are zero when the code object is loaded and again after every launch; the partial
+    // results of any shape that fits the array begin behind the counters of every other.
     return vs::decode_entry(shape, n_streams, k_slab, v_slab, capacity, lens, q, k_new, v_new, out, ptr,
                             kScratchBytes, hip_stream);
 }

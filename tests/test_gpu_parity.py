@@ -545,6 +545,53 @@ def test_decode_result_does_not_depend_on_the_chunking():
         assert (out.float() - ref_out).abs().max().item() <= 2 ** -7 * ref_out.abs().max().item()
 
 
+# (hq, hkv, lens): one share of 4 and of 8 tiles and one row more, a full chip of them; shares of 4 tiles up to
+# 32 tiles; then 8 tiles, more than 8, 12 shares of a stream; ragged streams; other head counts; one stream that is
+# over every limit
+@pytest.mark.parametrize("hq,hkv,lens0", [
+    (28, 4, [127]), (28, 4, [128]), (28, 4, [255]), (28, 4, [256]), (28, 4, [0, 31, 127, 5]), (28, 4, [100] * 64), (28, 4, [255] * 64),
+    (28, 4, [700]), (28, 4, [1023, 1, 300]), (28, 4, [1024]), (28, 4, [3071, 200]), (28, 4, [700] * 16), (28, 4, [1500, 1400, 1000] * 3),
+    (28, 4, [2900] * 7), (28, 4, [703] * 64), (8, 1, [3071, 17]), (16, 2, [1500, 60, 900]), (12, 6, [1500] * 4), (6, 6, [333, 2]),
+    (8, 8, [255] * 32), (28, 4, [9300])])
+@pytest.mark.parametrize("gain", [1, 8])
+def test_decode_few_rows(hq, hkv, lens0, gain):
+    """The decode step that merges inside its launch, at the edges of its plan."""
+    s = AttnShape(hq, hkv, 128, "bf16")
+    out, ref, _ = _decode_case(s, lens0, max(lens0) + 1, 27, gain, with_new=gain == 1 or 0 in lens0)
+    check_close(out, ref, "bf16", f"decode Hq={hq} Hkv={hkv} lens={lens0[:4]} x{len(lens0)} gain={gain}")
+
+
+def test_decode_few_rows_replayed():
+    """The arrival counters are back at zero after every launch: a captured chain of steps of different plans over
+    one workspace gives the same bits on every replay, with eager work of the program in between."""
+    sh, cap = vs_shape(QW), 3200
+    k, v = (draw(51 + i, (16, cap, QW.n_kv_heads, 128), 0.5, "bf16").to(DEV) for i in (0, 1))
+    q = draw(53, (16, QW.n_q_heads, 128), 1.0, "bf16").to(DEV)
+    ws = workspace(QW, 0, cap, 16)
+    plans = [[700], [3000] * 4, [100] * 16, [700] * 16, [900]]
+    outs = [torch.empty_like(q[:len(lens0)]) for lens0 in plans]
+
+    def steps():
+        st = vs.current_stream_handle()
+        for lens0, out in zip(plans, outs):
+            n = len(lens0)
+            vs.decode_attn(sh, k[:n], v[:n], lens_array(lens0), q[:n], None, None, out, ws, stream=st)
+
+    steps()
+    want = [o.clone() for o in outs]
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        steps()
+    for _ in range(8):
+        for o in outs:
+            o.fill_(float("nan"))
+        graph.replay()
+        torch.cuda.synchronize()
+        assert all(same_bits(o, w.cpu()) for o, w in zip(outs, want))
+        steps()
+
+
 @pytest.mark.parametrize("hq,hkv", [(6, 3), (12, 6), (5, 5), (16, 2), (8, 1), (24, 8)])
 @pytest.mark.parametrize("chunk", [0, 32])
 def test_decode_other_kv_head_counts(hq, hkv, chunk):
