@@ -401,8 +401,7 @@ void prefill_mfma_kernel(PrefillParams p) {
     }
     asm volatile(VS_ASM_INIT_O : : : VS_CLOB_ACC, VS_CLOB_TMP);  // while the loads above are under way
 
-    float m_ref[2] = {-INFINITY, -INFINITY};  // softmax reference (log2 units)
-    float ms[2] = {0.f, 0.f};                 // what the blocks subtract: the reference, 0 while there is none
+    float ms[2] = {0.f, 0.f};  // softmax reference (log2 units), a made-up 0 while a row has seen no key
     float l_run[2] = {0.f, 0.f};              // this lane's share of the row sum
 
     // LDS read addresses (bytes inside a tile)
@@ -491,13 +490,12 @@ void prefill_mfma_kernel(PrefillParams p) {
 #pragma unroll
             for (int e = 0; e < 16; ++e) mx = fmaxf(mx, x[e]);
             mx = fmaxf(mx, xhalf(mx)) * p.scale_log2e;
-            const float m_old = (l_run[r] + xhalf(l_run[r]) > 0.f) ? m_ref[r] : -INFINITY;  // the row's history
+            const float m_old = (l_run[r] + xhalf(l_run[r]) > 0.f) ? ms[r] : -INFINITY;  // the row's history
             const float m_new = fmaxf(m_old, mx);
             alpha[r] = (m_new == -INFINITY) ? 1.f : __builtin_amdgcn_exp2f(m_old - m_new);
             // (a row that has seen no key yet keeps the made-up reference 0, which is what its next sub-blocks
             // will be taken against)
             const float m_sub = (m_new == -INFINITY) ? 0.f : m_new;
-            m_ref[r] = m_sub;
             ms[r] = m_sub;
             float sum = 0.f;
 #pragma unroll
@@ -575,7 +573,6 @@ void prefill_mfma_kernel(PrefillParams p) {
         }
         // step 0 = QK(1) | SM(0) against the reference 0 (fine whenever the scaled scores are
         // moderate; otherwise commit() redoes it exactly)
-        m_ref[0] = m_ref[1] = 0.f;
         if (tile_of(0) * BN + BN <= Lc) {
             const unsigned long long vsrc = (unsigned long long)(vc + ((int64_t)(tile_of(0) * BN + rb * 32) * Hkv + g) * kRowBytes);
             float sum0_, sum1_;
@@ -689,11 +686,11 @@ void prefill_mfma_kernel(PrefillParams p) {
                    "={v[64:79]}"(o[1][0]), "={v[80:95]}"(o[1][1]), "={v[96:111]}"(o[1][2]), "={v[112:127]}"(o[1][3])
                  :
                  : VS_CLOB_ACC);
-    float l_tot[2];
+    float l_tot[2], m_ref[2];
 #pragma unroll
     for (int r = 0; r < 2; ++r) {
         l_tot[r] = l_run[r] + xhalf(l_run[r]);
-        if (!(l_tot[r] > 0.f)) m_ref[r] = -INFINITY;  // nothing accumulated: the made-up reference must not count
+        m_ref[r] = l_tot[r] > 0.f ? ms[r] : -INFINITY;  // nothing accumulated: the made-up reference must not count
     }
 
     // ---- output of one row group: lane (q = l32, hi) holds dims 32*db + 8*(e>>2) + 4*hi + (e&3) ----
