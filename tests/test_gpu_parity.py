@@ -563,33 +563,49 @@ def test_decode_few_rows(hq, hkv, lens0, gain):
 
 def test_decode_few_rows_replayed():
     """The arrival counters are back at zero after every launch: a captured chain of steps of different plans over
-    one workspace gives the same bits on every replay, with eager work of the program in between."""
-    sh, cap = vs_shape(QW), 3200
-    k, v = (draw(51 + i, (16, cap, QW.n_kv_heads, 128), 0.5, "bf16").to(DEV) for i in (0, 1))
-    q = draw(53, (16, QW.n_q_heads, 128), 1.0, "bf16").to(DEV)
-    ws = workspace(QW, 0, cap, 16)
-    plans = [[700], [3000] * 4, [100] * 16, [700] * 16, [900]]
-    outs = [torch.empty_like(q[:len(lens0)]) for lens0 in plans]
-
-    def steps():
-        st = vs.current_stream_handle()
-        for lens0, out in zip(plans, outs):
-            n = len(lens0)
-            vs.decode_attn(sh, k[:n], v[:n], lens_array(lens0), q[:n], None, None, out, ws, stream=st)
-
+    one workspace gives the same bits on every replay, with eager work of the program in between.  In a process of
+    its own: once a process has used a second stream (capture does), the device may deal workgroups of the first
+    one from another XCD on, which the prefill reports as a misplaced launch."""
+    import os
+    import subprocess
+    import sys
+    root = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+    code = """
+import ctypes, sys
+sys.path.insert(0, %r)
+import torch
+import paper_2503_09387_amd as vs
+dev, cap = "cuda:0", 3200
+rn = lambda *dims: torch.randn(dims, generator=g, device=dev, dtype=torch.bfloat16)
+g = torch.Generator(device=dev).manual_seed(5)
+sh = vs.Shape.make(28, 4, 128, "bf16")
+k, v, q = rn(16, cap, 4, 128), rn(16, cap, 4, 128), rn(16, 28, 128)
+ws = vs.make_workspace(sh, 0, cap, 16, dev)
+plans = [[700], [3000] * 4, [100] * 16, [700] * 16, [900]]
+outs = [torch.empty_like(q[:len(p)]) for p in plans]
+def steps():
+    st = vs.current_stream_handle()
+    for p, out in zip(plans, outs):
+        n = len(p)
+        vs.decode_attn(sh, k[:n], v[:n], (ctypes.c_int32 * n)(*p), q[:n], None, None, out, ws, stream=st)
+steps()
+want = [o.clone() for o in outs]
+torch.cuda.synchronize()
+graph = torch.cuda.CUDAGraph()
+with torch.cuda.graph(graph):
     steps()
-    want = [o.clone() for o in outs]
+for _ in range(8):
+    for o in outs:
+        o.fill_(float("nan"))
+    graph.replay()
     torch.cuda.synchronize()
-    graph = torch.cuda.CUDAGraph()
-    with torch.cuda.graph(graph):
-        steps()
-    for _ in range(8):
-        for o in outs:
-            o.fill_(float("nan"))
-        graph.replay()
-        torch.cuda.synchronize()
-        assert all(same_bits(o, w.cpu()) for o, w in zip(outs, want))
-        steps()
+    assert all(torch.equal(o.view(torch.int16), w.view(torch.int16)) for o, w in zip(outs, want))
+    steps()
+torch.cuda.synchronize()
+print("ok")
+""" % root
+    r = subprocess.run([sys.executable, "-c", code], capture_output=True, text=True, timeout=100)
+    assert r.returncode == 0 and r.stdout.strip().endswith("ok"), r.stdout + r.stderr
 
 
 @pytest.mark.parametrize("hq,hkv", [(6, 3), (12, 6), (5, 5), (16, 2), (8, 1), (24, 8)])
