@@ -382,6 +382,7 @@ typedef enum {
  * weights per output feature), k a multiple of 64, n a multiple of 2.  `residual` [n_rows][n] is read in
  * mode VS_LINEAR_RESIDUAL only (it may be the same memory as out).  workspace: device,
  * vs_linear_workspace_bytes(n_rows, k, n) bytes (0 for shapes that need none: NULL is accepted then).
+ * The size is the same for every n_rows: one buffer serves runs of any length over the same weights.
  * Errors: VS_ERR_NULL, VS_ERR_SHAPE, VS_ERR_ALIGN, VS_ERR_WORKSPACE, VS_ERR_HIP.
  */
 size_t vs_linear_workspace_bytes(int32_t n_rows, int32_t k, int32_t n);
@@ -408,7 +409,7 @@ typedef struct {
  *   h1 = h_in + a w_o^T;  x2 = rmsnorm(h1, norm2);  h_out = h1 + (silu(x2 w_gate^T) * (x2 w_up^T)) w_down^T.
  * h_in, h_out [n_tokens][d_model] (may be the same memory), 1 <= n_tokens <= 192, bf16 only.
  * workspace: vs_layer_workspace_bytes (prepared with vs_workspace_init like every workspace that the
- * attention uses).  Errors as vs_frame_prefill_compact and vs_linear; cache->len grows by one on VS_OK.
+ * attention uses); what a run of n_tokens needs is enough for any shorter one.  Errors as vs_frame_prefill_compact and vs_linear; cache->len grows by one on VS_OK.
  * Seven launches on hip_stream.  Where a product's input features are shared out over several
  * workgroups, these add their sums inside the multiplying launch, placed, counted and waited for
  * exactly as the key splits of the attention are (vs_workspace_init); what they report comes back

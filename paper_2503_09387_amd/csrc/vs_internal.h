@@ -133,8 +133,11 @@ hipError_t launch_frame_qkv(const vs_shape& s, const void* e, int32_t n_visual, 
 
 // dense layers around the attention (Sections 3.1, 4.1): out = X W^T with fp32 sums and a choice of what
 // happens to them (vs_linear_mode); store mode may cut the output features into three tensors
-// (out: features < seg0, out1: < seg1, out2: the rest).  workspace: linear_workspace_bytes.
-size_t linear_workspace_bytes(int32_t n_rows, int32_t K, int32_t N);
+// (out: features < seg0, out1: < seg1, out2: the rest).  workspace: linear_workspace_need for the rows of
+// the call; linear_workspace_bytes is the most that any number of rows needs (each class of 64 rows has a
+// plan of its own, and a longer run may need less than a shorter one).
+size_t linear_workspace_need(int32_t n_rows, int32_t K, int32_t N);
+size_t linear_workspace_bytes(int32_t K, int32_t N);
 // arrival_counters: the prefill's counters in an initialised control block (null: none).  With them, and
 // at most kMaxRowTiles * Hkv blocks, the split-K shares are added inside the multiplying launch.
 hipError_t launch_linear(const void* x, int32_t ldx, const void* w, int32_t n_rows, int32_t K, int32_t N, int32_t mode,

@@ -23,13 +23,13 @@ vs_status check_linear(const void* x, const void* w, int32_t n_rows, int32_t k, 
     if (n_rows < 1 || n_rows > kMaxRows || k < 64 || k % 64 != 0 || k > (1 << 20) || n < 2 || n % 2 != 0 || n > (1 << 24))
         return VS_ERR_SHAPE;
     if (!aligned16(x) || !aligned16(w) || !aligned16(out) || !aligned16(residual) || !aligned16(workspace)) return VS_ERR_ALIGN;
-    const size_t need = linear_workspace_bytes(n_rows, k, n);
+    const size_t need = linear_workspace_need(n_rows, k, n);
     if (need > 0 && (!workspace || workspace_bytes < need)) return VS_ERR_WORKSPACE;
     return VS_OK;
 }
 
 struct LayerLayout {
-    size_t attn, x, q, k, v, a, h1, act, lin, total;  // byte offsets of the parts of the layer's workspace
+    size_t attn, x, q, k, v, a, h1, act, lin, total;  // byte offsets of the parts of the layer's workspace; total never falls as T grows
 };
 
 LayerLayout layer_layout(const vs_shape* s, const vs_layer_weights* wt, int32_t T) {
@@ -45,10 +45,10 @@ LayerLayout layer_layout(const vs_shape* s, const vs_layer_weights* wt, int32_t 
     l.h1 = off;   off += round256((size_t)T * wt->d_model * e);
     l.act = off;  off += round256((size_t)T * wt->d_ff * e);
     l.lin = off;
-    size_t lin = linear_workspace_bytes(T, wt->d_model, (int32_t)(nq + 2 * nk));
-    lin = std::max(lin, linear_workspace_bytes(T, (int32_t)nq, wt->d_model));
-    lin = std::max(lin, linear_workspace_bytes(T, wt->d_model, 2 * wt->d_ff));
-    lin = std::max(lin, linear_workspace_bytes(T, wt->d_ff, wt->d_model));
+    size_t lin = linear_workspace_bytes(wt->d_model, (int32_t)(nq + 2 * nk));
+    lin = std::max(lin, linear_workspace_bytes((int32_t)nq, wt->d_model));
+    lin = std::max(lin, linear_workspace_bytes(wt->d_model, 2 * wt->d_ff));
+    lin = std::max(lin, linear_workspace_bytes(wt->d_ff, wt->d_model));
     off += round256(lin);
     l.total = off;
     return l;
@@ -86,7 +86,7 @@ vs_status vs_rmsnorm(const void* x, const void* gamma, int32_t n_rows, int32_t d
 
 size_t vs_linear_workspace_bytes(int32_t n_rows, int32_t k, int32_t n) {
     if (n_rows < 1 || n_rows > kMaxRows || k < 64 || k % 64 != 0 || k > (1 << 20) || n < 2 || n % 2 != 0 || n > (1 << 24)) return 0;
-    return linear_workspace_bytes(n_rows, k, n);
+    return linear_workspace_bytes(k, n);
 }
 
 vs_status vs_linear(const void* x, const void* w, int32_t n_rows, int32_t k, int32_t n, int32_t mode,

@@ -602,10 +602,19 @@ hipError_t launch_lin_rows(const LinParams& p, const LinPlan& pl, int dev, hipSt
 
 }  // namespace
 
-size_t linear_workspace_bytes(int32_t n_rows, int32_t K, int32_t N) {
+size_t linear_workspace_need(int32_t n_rows, int32_t K, int32_t N) {
     const LinPlan pl = make_lin_plan(n_rows, N, K);
     if (pl.ksplit == 1) return 0;
     return (size_t)pl.ksplit * pl.n_blocks * 4 * (row_subs(n_rows) * pl.nsub) * 64 * sizeof(f32x4);
+}
+
+size_t linear_workspace_bytes(int32_t K, int32_t N) {
+    size_t most = 0;
+    for (int32_t rows : {64, 128, 192}) {  // the row classes of the plan
+        const size_t need = linear_workspace_need(rows, K, N);
+        if (need > most) most = need;
+    }
+    return most;
 }
 
 hipError_t launch_linear(const void* x, int32_t ldx, const void* w, int32_t n_rows, int32_t K, int32_t N, int32_t mode,

@@ -216,6 +216,21 @@ def test_dense_layer_argument_errors():
     assert L.vs_linear_workspace_bytes(0, 3584, 3584) == 0 and L.vs_linear_workspace_bytes(170, 100, 3584) == 0
 
 
+def test_workspace_of_the_dense_layers_serves_runs_of_every_length():
+    """One buffer serves a program's frames whatever their length: the plan of a product depends on the row
+    class (64, 128, 192), its workspace size does not; a layer's size never falls as the run grows."""
+    L = vs.lib()
+    for k in list(range(64, 4097, 64)) + [11008, 18944]:
+        for n in (64, 130, 256, 512, 768, 1472, 1536, 2048, 3584, 4608, 11008):
+            sizes = [L.vs_linear_workspace_bytes(t, k, n) for t in (1, 50, 64, 65, 128, 129, 170, 192)]
+            assert len(set(sizes)) == 1, f"k {k} n {n}: {sizes}"
+    for hq, hkv, d, dff in [(1, 1, 2752, 3200), (8, 8, 1664, 11008), (28, 4, 3584, 18944), (4, 1, 512, 832), (16, 2, 2048, 5504)]:
+        s = _shape(hq=hq, hkv=hkv)
+        w = binding._CLayerWeights(FAKE, FAKE, FAKE, FAKE, FAKE, FAKE, d, dff, 1e-6)
+        sizes = [L.vs_layer_workspace_bytes(ctypes.byref(s), ctypes.byref(w), t) for t in range(1, 193)]
+        assert sizes == sorted(sizes) and sizes[0] > 0, f"heads {hq}/{hkv} d {d} d_ff {dff}"
+
+
 def test_decoder_layer_argument_errors():
     L = vs.lib()
     s = _shape()

@@ -151,6 +151,20 @@ def test_linear_row_groups_and_rings(T, K, N):
     _check_stage(_f64(out), ref, slack, f"linear T={T} K={K} N={N}")
 
 
+@pytest.mark.parametrize("K,N", [(832, 256), (1152, 1536), (1344, 2048), (2880, 512)])
+def test_linear_workspace_of_one_length_serves_every_other(K, N):
+    """Shapes whose row classes differ in what they need; the buffer is sized once, for the longest and for the shortest run."""
+    w = _dev(draw(930 + N, (N, K), 0.2, "bf16"))
+    for sized_for in (192, 1):
+        ws = _linear_ws(sized_for, K, N)
+        for T in (1, 64, 128, 170):
+            x = draw(931 + T, (T, K), 1.0, "bf16")
+            out = torch.full((T, N), float("nan"), dtype=BF, device=DEV)
+            vs.linear(_dev(x), w, out, workspace=ws)
+            ref, slack = _ref_linear(x, w.cpu(), vs.LINEAR_STORE, None, cols=[0, N // 2, N - 1])
+            _check_stage(_f64(out)[:, [0, N // 2, N - 1]], ref, slack, f"linear {T}x{K}x{N}, workspace sized for {sized_for}")
+
+
 def test_linear_is_deterministic_and_leaves_inputs_alone():
     T, K, N = 170, 3584, 3584
     x, w = _dev(draw(11, (T, K), 1.0, "bf16")), _dev(draw(12, (N, K), K ** -0.5, "bf16"))
