@@ -91,8 +91,8 @@ size_t vs_workspace_bytes(const vs_shape *shape, int32_t max_q_tokens, int32_t m
 
 /*
  * Prepares a freshly allocated (or overwritten) workspace: clears the control
- * block at its start, which holds arrival counters that the kernels leave at zero
- * after every launch.  The first call on a device also runs a one-off probe of how the
+ * block at its start, which holds arrival counters that the kernels leave as they
+ * found them after every launch.  The first call on a device also runs a one-off probe of how the
  * device distributes workgroups and waits for it (hip_stream is synchronised once).
  * Must have completed on the device (same stream, or
  * synchronised) before the first call that uses the workspace; needed once, not per
@@ -202,6 +202,12 @@ vs_status vs_question_prefill_append(const vs_shape *shape, vs_cache *cache, con
  * If k_new is given, row lens[s] of stream s receives it first and lens[s] += 1;
  * the query then attends over all valid rows, the new one included.  Every stream
  * must end with at least one valid row.  1 <= n_streams <= 1024.
+ * The workspace's control block (see vs_workspace_init) holds arrival counters for steps of few rows.
+ * Where it has been overwritten (a buffer that also serves vs_linear or vs_memory_bank_push, say) or never
+ * prepared, results are right all the same, but a stream whose rows would be shared out is worked off by one workgroup
+ * per KV head, which is slower; vs_workspace_init puts it right.  Calls that overlap in time on one workspace, or a
+ * launch that was cut off, may leave counts behind that later steps take for their own: call vs_workspace_init
+ * then.
  * Streams are launched in groups of 64.  Should a launch fail (VS_ERR_HIP) after earlier
  * groups have been enqueued, lens has advanced for exactly those earlier groups, whose rows
  * are written and whose outputs are valid; the failed group and the ones behind it are
@@ -222,8 +228,9 @@ vs_status vs_decode_attn(const vs_shape *shape, int32_t n_streams, void *k_slab,
  * call would need more than the array holds (vs_workspace_bytes(shape, 0, capacity, n_streams)
  * is the measure: 28 query / 4 KV heads of 128 fit with room to spare; 64 query heads per
  * launch group of 64 streams do not).  All calls on one GPU share that GPU's array, which keeps
- * what the last call left in it (nothing in it has to be cleared for this call): two calls
- * that overlap in time on one GPU, on different streams, race; order them.
+ * what the last call left in it (nothing in it has to be cleared, and nothing of it is read by a
+ * later call): two calls that overlap in time on one GPU, on different streams, race and may spoil each other's
+ * outputs, not those of later calls; order them.
  */
 size_t vs_decode_static_scratch_bytes(void);
 vs_status vs_decode_attn_static(const vs_shape *shape, int32_t n_streams, void *k_slab, void *v_slab,

@@ -137,7 +137,7 @@ vs_status prefill_common(const vs_shape* shape, vs_cache* cache, bool append, co
 vs_status vs::decode_entry(const vs_shape* shape, int32_t n_streams, void* k_slab, void* v_slab,
                            int32_t capacity, int32_t* lens, const void* q, const void* k_new,
                            const void* v_new, void* out, void* workspace, size_t workspace_bytes,
-                           void* hip_stream) {
+                           void* hip_stream, bool stateless) {
     forget_stale_hip_error();
     vs_status st = check_shape(shape);
     if (st != VS_OK) return st;
@@ -179,7 +179,7 @@ vs_status vs::decode_entry(const vs_shape* shape, int32_t n_streams, void* k_sla
         if (mfma) {
             // the kernel reads the new row from k_new/v_new and stores it into the slab itself
             for (int32_t i = 0; i < ns; ++i) t.v[i] = lens[s0 + i] + add;
-            e = launch_decode_mfma(*shape, ns, ks, vs_, capacity, t, qs, kn, vn, os, workspace,
+            e = launch_decode_mfma(*shape, ns, ks, vs_, capacity, t, qs, kn, vn, os, stateless ? nullptr : workspace,
                                    static_cast<char*>(workspace) + ctrl, stream);
         } else {
             if (add) {
@@ -250,7 +250,11 @@ vs_status vs_workspace_init(const vs_shape* shape, void* workspace, size_t works
         if (getenv("VS_DEBUG")) fprintf(stderr, "vs_workspace_init: probe: %s\n", hipGetErrorString(e));
         return VS_ERR_HIP;
     }
-    e = launch_zero_fill(workspace, control_block_bytes(*shape), static_cast<hipStream_t>(hip_stream));
+    const size_t decode = prefill_counter_offset(*shape);
+    e = launch_fill(workspace, decode, kDecodeCounterStart, static_cast<hipStream_t>(hip_stream));
+    if (e == hipSuccess)
+        e = launch_fill(static_cast<char*>(workspace) + decode, control_block_bytes(*shape) - decode, 0u,
+                        static_cast<hipStream_t>(hip_stream));
     if (e != hipSuccess && getenv("VS_DEBUG")) fprintf(stderr, "vs_workspace_init: fill: %s\n", hipGetErrorString(e));
     return e == hipSuccess ? VS_OK : VS_ERR_HIP;
 }

@@ -325,7 +325,12 @@ __global__ __launch_bounds__(kThreads, 2) void decode_mfma_kernel(DecodeParams p
 // then passes fp32 partial results (G rows of 512 bytes per share) through memory at agent scope:
 // stores and loads that pass the L2s, which are not coherent with each other; every store
 // acknowledged before the workgroup counts itself in; the last one to arrive adds the shares in
-// index order, and nobody waits.  The counter goes back to zero with the last arrival.
+// index order, and nobody waits.  The counter goes back to where it started with the last arrival.
+// The upper 24 bits of a counter are a mark that vs_workspace_init puts there.  In memory that has been used for
+// something else since (or was never prepared) they are something else; every arrival sees that,
+// whatever the order, and the stream's first share then does the whole stream by itself: slow, but right.
+// A caller without a workspace (counters null) keeps no state between launches: the shares are then
+// added by decode_shares_kernel, a launch of its own, in the same order and so to the same bits.
 // Measured (28/4 heads, us per call, this kernel and the two launches): 1 stream of 128 rows 5.3 / 7.8,
 // of 256 6.8 / 7.7, of 700 8.6 / 8.8; 16 streams of 700 10.9 / 12.5, of 3000 22.7 / 25.5; 64 of 700 20.0 / 24.8.
 struct ShortParams {
@@ -337,7 +342,7 @@ struct ShortParams {
     __bf16* out;
     float* part_o;        // [share][Hkv][G][D], not normalised
     float* part_ml;       // [share][Hkv][G][2]: reference (log2 units), sum
-    unsigned* counters;   // [stream][Hkv], zero between launches
+    unsigned* counters;   // [stream][Hkv], kDecodeCounterStart between launches; null: the shares are added by a second launch
     int64_t stream_stride;
     int G, Hq, Hkv;
     float scale_log2e;
@@ -355,17 +360,59 @@ __device__ __forceinline__ float2 load_agent(const float* src) {
     return make_float2(__uint_as_float((unsigned)v), __uint_as_float((unsigned)(v >> 32)));
 }
 
+// The shares of stream s, KV head g, added in index order: dims dp, dp + 1 of query head `head` of the group.  kAgent: the partial
+// results were stored in this launch, by other workgroups.
+template <bool kAgent>
+__device__ __forceinline__ void add_shares(const ShortParams& p, int s, int g, int first_share, int n_shares, int head, int dp) {
+    typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+    constexpr int kDepth = 8;
+    const int64_t pr0 = ((int64_t)first_share * p.Hkv + g) * p.G + head, step = (int64_t)p.Hkv * p.G;
+    float mref = -INFINITY, l = 0.f, a = 0.f, b = 0.f;
+    for (int j0 = 0; j0 < n_shares; j0 += kDepth) {
+        float2 ml[kDepth], o[kDepth];
+#pragma unroll
+        for (int u = 0; u < kDepth; ++u) {
+            const int64_t pr = pr0 + min(j0 + u, n_shares - 1) * step;
+            ml[u] = kAgent ? load_agent(p.part_ml + pr * 2) : *reinterpret_cast<const float2*>(p.part_ml + pr * 2);
+            o[u] = kAgent ? load_agent(p.part_o + pr * D + dp) : *reinterpret_cast<const float2*>(p.part_o + pr * D + dp);
+        }
+        float mx = mref;
+#pragma unroll
+        for (int u = 0; u < kDepth; ++u) mx = fmaxf(mx, ml[u].x);
+        const float f = __builtin_amdgcn_exp2f(mref - mx);  // 0 before the first batch
+        l *= f;
+        a *= f;
+        b *= f;
+        mref = mx;
+#pragma unroll
+        for (int u = 0; u < kDepth; ++u) {
+            const float w = j0 + u < n_shares ? __builtin_amdgcn_exp2f(ml[u].x - mx) : 0.f;
+            l += w * ml[u].y;
+            a += w * o[u].x;
+            b += w * o[u].y;
+        }
+    }
+    const float inv = 1.0f / l;
+    *reinterpret_cast<bf16x2*>(p.out + ((int64_t)s * p.Hq + (int64_t)g * p.G + head) * D + dp) =
+        bf16x2{(__bf16)(a * inv), (__bf16)(b * inv)};
+}
+
 // Grid (shares of all streams, Hkv).
 template <int W>
-__global__ __launch_bounds__(64 * W) void decode_short_kernel(ShortParams p) {
+__global__ __launch_bounds__(64 * W, 2) void decode_short_kernel(ShortParams p) {
     constexpr int kRowStride = D + 4;                                        // of a head's sums in LDS, in floats
     constexpr int kWaveBytes = kWaveLds;
     static_assert(kMaxGroup * kRowStride * 4 <= kWaveBytes, "a wavefront's sums take the place of its V tile");
     __shared__ __attribute__((aligned(16))) char smem[W * kWaveBytes];
     __shared__ float s_m[W][16], s_l[W][16];
-    __shared__ int s_last;
+    __shared__ unsigned s_before;
 
-    const int tid = threadIdx.x, lane = tid & 63;
+  // once; a second time only where the first share of a stream does the whole stream (tid is made opaque: nothing
+  // worked out from it is kept in registers for that second time)
+  for (bool alone = false;; alone = true) {
+    int tid = threadIdx.x;
+    asm volatile("" : "+v"(tid));
+    const int lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int i16 = lane & 15, kq = lane >> 4;
     const int g = blockIdx.y, share = blockIdx.x;
@@ -376,15 +423,8 @@ __global__ __launch_bounds__(64 * W) void decode_short_kernel(ShortParams p) {
     const int s = __builtin_popcountll(__ballot(end_of <= share));
     const int len = __builtin_amdgcn_readlane(len_of, s);
     const int first_share = s ? __builtin_amdgcn_readlane(end_of, s - 1) : 0;
-    const int n_shares = __builtin_amdgcn_readlane(end_of, s) - first_share, j_share = share - first_share;
+    const int n_shares = alone ? 1 : __builtin_amdgcn_readlane(end_of, s) - first_share, j_share = share - first_share;
     const int stream_tiles = (len + TR - 1) / TR;
-    const int seg_a = stream_tiles * j_share / n_shares, seg_b = stream_tiles * (j_share + 1) / n_shares;
-    const int tile_a = seg_a + (seg_b - seg_a) * wave / W;
-    const int tile_b = seg_a + (seg_b - seg_a) * (wave + 1) / W;
-    const int row_begin = tile_a * TR;
-    const int row_end = min(len, tile_b * TR);
-    const int n_tiles = tile_b - tile_a;
-    const int last = max(row_end - 1, 0);
     const int new_row = p.k_new ? len - 1 : -1;
     __bf16* kslab = p.k_slab + (int64_t)s * p.stream_stride + (int64_t)g * D;
     __bf16* vslab = p.v_slab + (int64_t)s * p.stream_stride + (int64_t)g * D;
@@ -394,7 +434,15 @@ __global__ __launch_bounds__(64 * W) void decode_short_kernel(ShortParams p) {
     __bf16* vs_k = vs_w + TR * VSTR;
     const __bf16* krd = &vs_k[i16 * KSTR + 8 * kq];
     const __bf16* vrd = &vs_w[(4 * kq + (i16 >> 2)) * VSTR + 4 * (i16 & 3)];
-
+    typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+    const int n_items = p.G * (D / 2);  // (head, pair of dims)
+    const int seg_a = stream_tiles * j_share / n_shares, seg_b = stream_tiles * (j_share + 1) / n_shares;
+    const int tile_a = seg_a + (seg_b - seg_a) * wave / W;
+    const int tile_b = seg_a + (seg_b - seg_a) * (wave + 1) / W;
+    const int row_begin = tile_a * TR;
+    const int row_end = min(len, tile_b * TR);
+    const int n_tiles = tile_b - tile_a;
+    const int last = max(row_end - 1, 0);
     f32x4 o0 = {0.f, 0.f, 0.f, 0.f}, o1 = o0, o2 = o0, o3 = o0, o4 = o0, o5 = o0, o6 = o0, o7 = o0;
     float m_ref = -INFINITY, l_run = 0.f;
     if (n_tiles > 0) {
@@ -453,8 +501,6 @@ __global__ __launch_bounds__(64 * W) void decode_short_kernel(ShortParams p) {
         }
     }
     __syncthreads();
-    const int n_items = p.G * (D / 2);  // (head, pair of dims)
-    typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
     for (int it = tid; it < n_items; it += 64 * W) {
         const int head = it / (D / 2), dp = 2 * (it % (D / 2));
         float mx = s_m[0][head];
@@ -478,52 +524,31 @@ __global__ __launch_bounds__(64 * W) void decode_short_kernel(ShortParams p) {
             if (dp == 0) store_agent(p.part_ml + pr * 2, mx, l);
         }
     }
-    if (n_shares == 1) return;
+    if (n_shares == 1 || !p.counters) return;
 
     // ---- the shares of the stream: the last to arrive adds them ----
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // this wavefront's partial results have arrived
     __syncthreads();
-    if (tid == 0) {
-        unsigned* counter = p.counters + s * p.Hkv + g;
-        const unsigned before = __hip_atomic_fetch_add(counter, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        s_last = before == (unsigned)(n_shares - 1);
-        if (s_last) __hip_atomic_store(counter, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    }
+    unsigned* const counter = p.counters + s * p.Hkv + g;
+    if (tid == 0) s_before = __hip_atomic_fetch_add(counter, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     __syncthreads();
-    if (!s_last) return;
-    constexpr int kDepth = 8;
-    for (int it = tid; it < n_items; it += 64 * W) {
-        const int head = it / (D / 2), dp = 2 * (it % (D / 2));
-        const int64_t pr0 = ((int64_t)first_share * p.Hkv + g) * p.G + head, step = (int64_t)p.Hkv * p.G;
-        float mref = -INFINITY, l = 0.f, a = 0.f, b = 0.f;
-        for (int j0 = 0; j0 < n_shares; j0 += kDepth) {
-            float2 ml[kDepth], o[kDepth];
-#pragma unroll
-            for (int u = 0; u < kDepth; ++u) {
-                const int64_t pr = pr0 + min(j0 + u, n_shares - 1) * step;
-                ml[u] = load_agent(p.part_ml + pr * 2);
-                o[u] = load_agent(p.part_o + pr * D + dp);
-            }
-            float mx = mref;
-#pragma unroll
-            for (int u = 0; u < kDepth; ++u) mx = fmaxf(mx, ml[u].x);
-            const float f = __builtin_amdgcn_exp2f(mref - mx);  // 0 before the first batch
-            l *= f;
-            a *= f;
-            b *= f;
-            mref = mx;
-#pragma unroll
-            for (int u = 0; u < kDepth; ++u) {
-                const float w = j0 + u < n_shares ? __builtin_amdgcn_exp2f(ml[u].x - mx) : 0.f;
-                l += w * ml[u].y;
-                a += w * o[u].x;
-                b += w * o[u].y;
-            }
-        }
-        const float inv = 1.0f / l;
-        *reinterpret_cast<bf16x2*>(p.out + ((int64_t)s * p.Hq + (int64_t)g * p.G + head) * D + dp) =
-            bf16x2{(__bf16)(a * inv), (__bf16)(b * inv)};
+    const unsigned before = __builtin_amdgcn_readfirstlane(s_before);
+    if ((before & kDecodeCounterMark) != kDecodeCounterStart) {  // not prepared, or overwritten
+        if (j_share == 0) continue;
+        return;
     }
+    if (before - kDecodeCounterStart != (unsigned)(n_shares - 1)) return;
+    if (tid == 0) __hip_atomic_store(counter, kDecodeCounterStart, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    for (int it = tid; it < n_items; it += 64 * W) add_shares<true>(p, s, g, first_share, n_shares, it / (D / 2), 2 * (it % (D / 2)));
+    return;
+  }
+}
+
+// The shares of a stream added by a launch of their own.  Grid (streams, Hq), a wavefront each.
+__global__ __launch_bounds__(64) void decode_shares_kernel(ShortParams p) {
+    const int s = blockIdx.x, first_share = s ? p.share_end[s - 1] : 0, n_shares = p.share_end[s] - first_share;
+    const int g = blockIdx.y / p.G;
+    if (n_shares > 1) add_shares<false>(p, s, g, first_share, n_shares, blockIdx.y - g * p.G, 2 * threadIdx.x);
 }
 #undef VS_TILE_COMPUTE
 #undef VS_PV
@@ -734,6 +759,9 @@ hipError_t launch_decode_mfma(const vs_shape& s, int32_t n_streams, void* k_slab
         const dim3 grid(n, s.n_kv_heads);
         if (plan.waves == 4) decode_short_kernel<4><<<grid, 256, 0, st>>>(h);
         else decode_short_kernel<8><<<grid, 512, 0, st>>>(h);
+        const hipError_t e = hipGetLastError();
+        if (e != hipSuccess || counters || n == n_streams) return e;  // (n == n_streams: one share each)
+        decode_shares_kernel<<<dim3(n_streams, s.n_q_heads), 64, 0, st>>>(h);
         return hipGetLastError();
     }
     DecodeParams p;

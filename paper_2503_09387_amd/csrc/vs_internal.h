@@ -62,8 +62,9 @@ int prefill_frames_splits(const vs_shape& s, int32_t n_frames, int32_t n_tokens,
 int prefill_frames_max_splits(const vs_shape& s, int32_t n_frames, int32_t n_tokens, int32_t max_len);
 
 // bf16 split-row decode over ragged streams; appends (k_new, v_new) on the side when given.
-// `counters`: the front of an initialised workspace's control block, [kMaxStreamsPerLaunch][Hkv] arrival
-// counters that are zero between launches.
+// `counters`: the front of a workspace's control block, [kMaxStreamsPerLaunch][Hkv] arrival counters that are
+// at kDecodeCounterStart between launches (anything else costs time, not results); null: no state is kept
+// between launches, results are the same bits.
 size_t decode_mfma_workspace_bytes(const vs_shape& s, int32_t n_streams, int32_t max_rows);
 hipError_t launch_decode_mfma(const vs_shape& s, int32_t n_streams, void* k_slab, void* v_slab,
                               int32_t capacity, const LenTable& lens, const void* q,
@@ -73,8 +74,10 @@ hipError_t launch_decode_mfma(const vs_shape& s, int32_t n_streams, void* k_slab
 // Control block at the start of every workspace: [kMaxStreamsPerLaunch][Hkv] arrival counters of the
 // decode steps of few rows, then the prefill's arrival counters, one per unit = (KV head, frame, row tile), each alone
 // in 128 bytes (the workgroups of a unit look at theirs while they wait for one another: counters of
-// other units in the same line would queue behind those looks).  A counter wraps to zero with the last
-// arrival, so all of them are zero between launches.
+// other units in the same line would queue behind those looks).  A prefill counter wraps to zero with the
+// last arrival, a decode counter goes back to kDecodeCounterStart: so it is between launches.
+constexpr unsigned kDecodeCounterStart = 0x7fa5c300u;  // a mark in the upper 24 bits (as fp32 a signalling NaN, which no arithmetic leaves behind)
+constexpr unsigned kDecodeCounterMark = 0xffffff00u;
 constexpr int kMaxRowTiles = 256;
 constexpr int kCounterStrideBytes = 128;
 size_t control_block_bytes(const vs_shape& s);
@@ -82,7 +85,7 @@ inline size_t prefill_counter_offset(const vs_shape& s) {  // from the start of 
     const size_t n = (size_t)kMaxStreamsPerLaunch * s.n_kv_heads * sizeof(unsigned int);
     return (n + 127) & ~size_t(127);
 }
-hipError_t launch_zero_fill(void* p, size_t bytes, hipStream_t st);
+hipError_t launch_fill(void* p, size_t bytes, uint32_t word, hipStream_t st);
 // log2 of the number of XCDs workgroup ids are dealt to in turn on this device, -1 if unknown
 int xcd_shift_of_device(int dev);
 // Finds out once per device how workgroup ids are dealt to the XCDs (scratch: 256 bytes of device
@@ -105,10 +108,11 @@ struct XcdPlacement {
 };
 bool xcd_placement_of_device(int dev, XcdPlacement* out);
 
-// the body of vs_decode_attn (checks, launches, length bookkeeping) over any workspace
+// the body of vs_decode_attn (checks, launches, length bookkeeping) over any workspace; stateless: nothing in
+// it has to hold anything when the call begins
 vs_status decode_entry(const vs_shape* shape, int32_t n_streams, void* k_slab, void* v_slab, int32_t capacity,
                        int32_t* lens, const void* q, const void* k_new, const void* v_new, void* out,
-                       void* workspace, size_t workspace_bytes, void* hip_stream);
+                       void* workspace, size_t workspace_bytes, void* hip_stream, bool stateless = false);
 
 // row copies
 hipError_t launch_append_rows(int32_t n_caches, void* k_slab, void* v_slab, int64_t cache_stride_bytes,

@@ -295,9 +295,9 @@ __global__ __launch_bounds__(kPoolCols * kPoolRowGroups) void mean_pool_kernel(
     }
 }
 
-__global__ __launch_bounds__(256) void zero_fill_kernel(uint32_t* p, size_t n) {
+__global__ __launch_bounds__(256) void fill_kernel(uint32_t* p, size_t n, uint32_t word) {
     const size_t i = blockIdx.x * (size_t)256 + threadIdx.x;
-    if (i < n) p[i] = 0u;
+    if (i < n) p[i] = word;
 }
 
 }  // namespace
@@ -307,9 +307,9 @@ size_t control_block_bytes(const vs_shape& s) {
     return (n + 255) & ~size_t(255);
 }
 
-hipError_t launch_zero_fill(void* p, size_t bytes, hipStream_t st) {
+hipError_t launch_fill(void* p, size_t bytes, uint32_t word, hipStream_t st) {
     const size_t n = bytes / 4;
-    zero_fill_kernel<<<(unsigned)((n + 255) / 256), 256, 0, st>>>((uint32_t*)p, n);
+    fill_kernel<<<(unsigned)((n + 255) / 256), 256, 0, st>>>((uint32_t*)p, n, word);
     return hipGetLastError();
 }
 

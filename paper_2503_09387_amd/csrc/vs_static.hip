@@ -45,16 +45,18 @@ vs_status vs_decode_attn_static(const vs_shape* shape, int32_t n_streams, void* 
     // what vs_decode_attn would ask of a workspace for this call must fit the array
     const size_t need = vs_workspace_bytes(shape, 0, capacity > 0 ? capacity : 0, n_streams > 0 ? n_streams : 0);
     if (need == 0) return vs::decode_entry(shape, n_streams, k_slab, v_slab, capacity, lens, q, k_new, v_new, out,
-                                           nullptr, 0, hip_stream);  // (reports what is wrong with the arguments)
+                                           nullptr, 0, hip_stream, true);  // (reports what is wrong with the arguments)
     if (need > kScratchBytes) return VS_ERR_WORKSPACE;
     (void)hipGetLastError();
     unsigned char* ptr = nullptr;
     if (scratch_of_current_device(&ptr) != hipSuccess) return VS_ERR_HIP;
-    // Every partial result that a merge reads is written earlier in the same call.  The arrival counters
-    // at the front are zero when the code object is loaded and again after every launch; the partial
-    // results of any shape that fits the array begin behind the counters of every other.
+    // Every partial result that a merge reads is written earlier in the same call, and no arrival is counted
+    // here: a count left over from two calls that overlapped could not be put right again, because nobody
+    // can clear this array.  Where a stream's rows are shared out, the shares are added by a second
+    // launch (us per call without and with a workspace: one stream of 700 rows 8.1 and 7.9, of 3000 10.3 and 9.2,
+    // 16 of 1500 14.2 and 13.3; not shared out, 16 of 127, 5.0 both).
     return vs::decode_entry(shape, n_streams, k_slab, v_slab, capacity, lens, q, k_new, v_new, out, ptr,
-                            kScratchBytes, hip_stream);
+                            kScratchBytes, hip_stream, true);
 }
 
 }  // extern "C"

@@ -608,6 +608,87 @@ print("ok")
     assert r.returncode == 0 and r.stdout.strip().endswith("ok"), r.stdout + r.stderr
 
 
+@pytest.mark.parametrize("left", ["zeros", "ones", "sums", "other calls"])
+def test_decode_over_a_control_block_that_holds_something_else(left):
+    """Shared-out steps over a workspace that was never prepared, or has served other calls since, are right; and
+    vs_workspace_init gives the bits of a fresh workspace again, also over counts that were left behind."""
+    s, lens0, cap = QW, [700, 3000, 64, 1500], 3200
+    sh, n = vs_shape(s), len(lens0)
+    kv = [cache_rows(61, s, cap, 0.5, stream=i) for i in range(n)]
+    k, v = (torch.stack([c[j] for c in kv]).to(DEV) for j in (0, 1))
+    hq, _, _ = decode_step_inputs(61, s, n, 0.5, q_gain=4)
+    q = hq.to(DEV)
+    ws = vs.make_workspace(sh, 0, cap, n, DEV)
+
+    def step():
+        out = torch.full(q.shape, float("nan"), dtype=torch.bfloat16, device=DEV)
+        vs.decode_attn(sh, k, v, lens_array(lens0), q, None, None, out, ws)
+        torch.cuda.synchronize()
+        return out
+
+    fresh = step()
+    ref = np.stack([oracle.decode(to_f64(hq[i]), to_f64(kv[i][0]), to_f64(kv[i][1]), m, None, None, scale32(s))[0]
+                    for i, m in enumerate(lens0)])
+    check_close(fresh, ref, "bf16", "decode, fresh workspace")
+    if left == "zeros":
+        ws.zero_()
+    elif left == "ones":
+        ws.fill_(0xFF)
+    elif left == "sums":
+        ws.view(torch.float32)[:] = torch.randn(ws.numel() // 4, device=DEV)
+    else:  # a product's shares and a bank's cosines lie at the start of their workspaces
+        w = draw(62, (512, 3584), 0.2, "bf16").to(DEV)
+        o = torch.empty((170, 512), dtype=torch.bfloat16, device=DEV)
+        assert 0 < vs.linear_workspace_bytes(170, 3584, 512) <= ws.numel()
+        vs.linear(draw(63, (170, 3584), 1.0, "bf16").to(DEV), w, o, workspace=ws)
+        e = draw(64, (128, 256), 1.0, "bf16").to(DEV)
+        victim = torch.zeros(1, dtype=torch.int32, device=DEV)
+        vs.memory_bank_push(vs.Bank(e, "bf16", 128), e[3].clone(), victim, ws)
+    for _ in range(3):
+        check_close(step(), ref, "bf16", f"decode, control block: {left}")
+    ws[:4096].view(torch.int32).add_(3)  # counts that nobody will finish
+    vs.workspace_init(sh, ws)
+    for _ in range(2):
+        assert torch.equal(step().view(torch.int16), fresh.view(torch.int16))
+
+
+def test_decode_static_counts_nothing_in_its_array():
+    """The library's own array cannot be cleared, so a call over it may not rely on what an earlier one left there:
+    where rows are shared out, a second launch adds the shares (two nodes of a captured step, one with a
+    workspace); where they are not, one launch does."""
+    import os
+    import subprocess
+    import sys
+    root = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+    code = """
+import ctypes, os, sys
+sys.path.insert(0, %r)
+import torch
+import paper_2503_09387_amd as vs
+hip = ctypes.CDLL(os.path.join(os.path.dirname(torch.__file__), "lib", "libamdhip64.so"))
+dev = "cuda:0"
+sh = vs.Shape.make(28, 4, 128, "bf16")
+k, v, q = (torch.randn(d, device=dev).to(torch.bfloat16) for d in ((4, 800, 4, 128), (4, 800, 4, 128), (4, 28, 128)))
+ws = vs.make_workspace(sh, 0, 800, 4, dev)
+def launches(n, rows, static):
+    out = torch.empty_like(q[:n])
+    lens = (ctypes.c_int32 * n)(*[rows] * n)
+    call = (lambda: vs.decode_attn_static(sh, k[:n], v[:n], lens, q[:n], None, None, out)) if static else \
+        (lambda: vs.decode_attn(sh, k[:n], v[:n], lens, q[:n], None, None, out, ws))
+    call()
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph(keep_graph=True)
+    with torch.cuda.graph(graph):
+        call()
+    count = ctypes.c_size_t(0)
+    assert hip.hipGraphGetNodes(ctypes.c_void_p(graph.raw_cuda_graph()), None, ctypes.byref(count)) == 0
+    return count.value
+print([launches(n, rows, static) for n, rows in ((1, 700), (4, 100), (4, 700)) for static in (False, True)])
+""" % root
+    r = subprocess.run([sys.executable, "-c", code], capture_output=True, text=True, timeout=100)
+    assert r.returncode == 0 and r.stdout.strip().endswith("[1, 2, 1, 1, 1, 2]"), r.stdout + r.stderr
+
+
 @pytest.mark.parametrize("hq,hkv", [(6, 3), (12, 6), (5, 5), (16, 2), (8, 1), (24, 8)])
 @pytest.mark.parametrize("chunk", [0, 32])
 def test_decode_other_kv_head_counts(hq, hkv, chunk):
