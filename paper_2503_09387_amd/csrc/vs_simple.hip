@@ -63,8 +63,12 @@ struct Piece {
 // The launch is a chain of trips to memory: a thread requests its whole key row at once, and its
 // first kBatch value coordinates before the softmax needs them (50 tokens over 16 rows, 4 heads of 64:
 // 8.3 us and a row copy of 2.7 us behind it -> 6.9 us with the copy).
-template <typename T, int D>
-__global__ __launch_bounds__(kThreads) void attn_simple_kernel(
+// kWide holds a whole key row and 16 value rows in registers (206 for D = 128: 2 wavefronts per SIMD), the other form
+// 64 bytes of a row and 8 values, with 8 wavefronts per SIMD; same sums in the same order.  (28/4 heads of 128, us per call, kWide and
+// the other form: 170 tokens over 4096 rows 3161 and 1852, 50 over none 21.1 and 15.2, 1 over 4096 293 and 323; 4/1 heads of 64,
+// 50 tokens over 1000 rows 39.0 and 40.5, 170 tokens 68.7 and 64.0.)
+template <typename T, int D, bool kWide>
+__global__ __launch_bounds__(kThreads, kWide ? 1 : 8) void attn_simple_kernel(
     const T* __restrict__ kc, const T* __restrict__ vc, int64_t cache_stride, int32_t len,
     LenTable lens, int lens_used, const T* __restrict__ q, const T* __restrict__ kf,
     const T* __restrict__ vf, T* __restrict__ out, int Hq, int Hkv, float scale, KeptRows kept) {
@@ -83,21 +87,23 @@ __global__ __launch_bounds__(kThreads) void attn_simple_kernel(
     __shared__ float s_acc[kThreads];
 
     constexpr int KG = kThreads / D;  // key groups in the value accumulation
-    constexpr int kPieces = D / Piece<T>::N, kBatch = 16;
+    constexpr int kPieces = D / Piece<T>::N;
+    constexpr int kHeld = kWide ? kPieces : 4, kBatch = kWide ? 16 : 8;  // pieces of a key row, and value rows, under way
     const int d = tid % D, kg = tid / D;
     float m = -INFINITY, l = 0.f, acc = 0.f;
 
     const float q_mine = tid < D ? to_f32(q[qrow * D + tid]) : 0.f;
     for (int base = 0; base < n; base += kThreads) {
         const int cnt = min(kThreads, n - base);
-        Piece<T> kr[kPieces];  // this thread's key row (past the end: the last row, ignored below)
-        {
-            const int j = base + min(tid, cnt - 1);
-            const T* krow = (j < L) ? kcz + ((int64_t)j * Hkv + g) * D
-                                    : kf + ((int64_t)(j - L) * Hkv + g) * D;
+        Piece<T> kr[kHeld];  // of this thread's key row (past the end: the last row, ignored below)
+        const int jk = base + min(tid, cnt - 1);
+        const T* const krow = (jk < L) ? kcz + ((int64_t)jk * Hkv + g) * D
+                                       : kf + ((int64_t)(jk - L) * Hkv + g) * D;
+        auto fetch_k = [&](int e0) {
 #pragma unroll
-            for (int e = 0; e < kPieces; ++e) kr[e].raw = reinterpret_cast<const raw16*>(krow)[e];
-        }
+            for (int e = 0; e < kHeld; ++e) kr[e].raw = reinterpret_cast<const raw16*>(krow)[e0 + e];
+        };
+        fetch_k(0);
         float vr[kBatch];
         auto fetch_v = [&](int j0) {
 #pragma unroll
@@ -110,20 +116,27 @@ __global__ __launch_bounds__(kThreads) void attn_simple_kernel(
         };
         fetch_v(kg);
 #pragma unroll
-        for (int e = 0; e < kPieces; ++e) keep_here(kr[e].raw);
+        for (int e = 0; e < kHeld; ++e) keep_here(kr[e].raw);
 #pragma unroll
         for (int u = 0; u < kBatch; ++u) keep_here(vr[u]);
         if (base == 0) {
             if (tid < D) s_q[tid] = q_mine;
             __syncthreads();
         }
-        float zj = -INFINITY;
-        if (tid < cnt) {
-            float dot = 0.f;
+        float dot = 0.f;
 #pragma unroll
-            for (int e = 0; e < D; ++e) dot = fmaf(s_q[e], kr[e / Piece<T>::N].get(e % Piece<T>::N), dot);
-            zj = dot * scale;
+        for (int e0 = 0; e0 < kPieces; e0 += kHeld) {
+            if (e0) {
+                fetch_k(e0);
+#pragma unroll
+                for (int e = 0; e < kHeld; ++e) keep_here(kr[e].raw);
+            }
+#pragma unroll
+            for (int e = 0; e < kHeld; ++e)
+#pragma unroll
+                for (int j = 0; j < Piece<T>::N; ++j) dot = fmaf(s_q[(e0 + e) * Piece<T>::N + j], kr[e].get(j), dot);
         }
+        const float zj = tid < cnt ? dot * scale : -INFINITY;
         const float cmax = block_reduce<true>(zj, s_red);  // finite: key `base` is visible
         const float m_new = fmaxf(m, cmax);
         const float alpha = expf(m - m_new);                // 0 on the first chunk
@@ -167,12 +180,19 @@ hipError_t launch_attn_simple(const vs_shape& s, const void* kc, const void* vc,
                               const void* q, const void* kf, const void* vf, int32_t n_tokens,
                               void* out, hipStream_t st, KeptRows kept) {
     dim3 grid(n_tokens, s.n_q_heads, n_streams), block(kThreads);
-#define VS_GO(DD)                                                                              \
-    attn_simple_kernel<T, DD><<<grid, block, 0, st>>>(                                           \
+    // As many workgroups as the chip holds of the wide form at once: up to there what counts is the chain of one.
+    const bool wide = (int64_t)n_tokens * s.n_q_heads * n_streams <= 512;
+#define VS_GO(DD, WIDE)                                                                          \
+    attn_simple_kernel<T, DD, WIDE><<<grid, block, 0, st>>>(                                     \
         (const T*)kc, (const T*)vc, cache_stride, len, lens, lens_used, (const T*)q,             \
         (const T*)kf, (const T*)vf, (T*)out, s.n_q_heads, s.n_kv_heads, s.softmax_scale, kept)
-    if (s.head_dim == 64) VS_GO(64);
-    else VS_GO(128);
+    if (s.head_dim == 64) {
+        if (wide) VS_GO(64, true);
+        else VS_GO(64, false);
+    } else {
+        if (wide) VS_GO(128, true);
+        else VS_GO(128, false);
+    }
 #undef VS_GO
     return hipGetLastError();
 }

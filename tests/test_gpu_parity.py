@@ -487,6 +487,17 @@ def test_prefill_fp32_path_larger_shapes():
         check_close(out, oracle_prefill_rows(s, q, hk, hv, L, kf, vf), "f32", f"fp32 {hq}/{hkv}/{d} L={L}")
 
 
+@pytest.mark.parametrize("dim,hq,hkv,L,T", [(64, 4, 1, 203, 128), (64, 4, 1, 203, 129), (128, 8, 2, 500, 64), (128, 8, 2, 500, 65),
+                                            (128, 8, 8, 0, 70)])
+def test_fp32_prefill_on_both_sides_of_the_chip(dim, hq, hkv, L, T):
+    """Up to 512 workgroups and beyond, over one and several chunks of 256 keys."""
+    s = AttnShape(hq, hkv, dim, "f32")
+    hk, hv = cache_rows(43, s, max(L, 1), 1.0)
+    q, kf, vf = frame_inputs(43, s, T, 1.0)
+    out, _, _ = run_prefill(s, hk, hv, L, q, kf, vf)
+    check_close(out, oracle_prefill_rows(s, q, hk, hv, L, kf, vf), "f32", f"fp32 {hq}/{hkv}/{dim} L={L} T={T}")
+
+
 # ---------------------------------------------------------------------------- decode edges
 def _decode_case(s, lens0, cap, seed, gain=1.0, with_new=True):
     S = len(lens0)
