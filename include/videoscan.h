@@ -149,7 +149,9 @@ vs_status vs_carrier_compact_append(const vs_shape *shape, vs_cache *cache, cons
  * Prefill and compaction of one frame in a single launch: same result as
  * vs_frame_prefill_attn followed by vs_carrier_compact_append with
  * carrier_index = n_tokens-1.  Nothing is launched and len is unchanged if the
- * cache is full.
+ * cache is full.  Here and in the other calls that keep rows of a run, k_f and v_f may lie in the
+ * cache itself, at or behind row len (a run projected straight into it): the rows are then copied behind
+ * the attention, by launches of their own (none where they already are where they go).
  */
 vs_status vs_frame_prefill_compact(const vs_shape *shape, vs_cache *cache, const void *q,
                                    const void *k_f, const void *v_f, int32_t n_tokens, void *out,

@@ -68,6 +68,39 @@ constexpr int32_t kMaxStreams = 1024;
 
 size_t round256(size_t x) { return (x + 255) & ~size_t(255); }
 
+inline bool overlap(const void* p, int64_t p_bytes, const void* q, int64_t q_bytes) {
+    const uintptr_t a = reinterpret_cast<uintptr_t>(p), b = reinterpret_cast<uintptr_t>(q);
+    return a < b + (uintptr_t)q_bytes && b < a + (uintptr_t)p_bytes;
+}
+
+// Does anything that an attention launch reads or writes lie where the kept rows of its run go (a run projected
+// straight into the cache, say)?  Then those rows must not be copied by the launch itself, where other workgroups may
+// still read what they replace, but after it, by launches of their own.
+inline bool kept_rows_in_use(const vs_shape* s, const char* kdst, const char* vdst, int64_t kept_bytes, const void* q,
+                             const void* k_f, const void* v_f, const void* out, int64_t n_rows) {
+    const int64_t kv = n_rows * row_bytes(s), qo = n_rows * s->n_q_heads * s->head_dim * (int64_t)elem_bytes(s);
+    for (const char* dst : {kdst, vdst})
+        if (overlap(k_f, kv, dst, kept_bytes) || overlap(v_f, kv, dst, kept_bytes) || overlap(q, qo, dst, kept_bytes) ||
+            overlap(out, qo, dst, kept_bytes))
+            return true;
+    return false;
+}
+
+// Copies `bytes` bytes from src to dst, which may overlap: in pieces no longer than they are apart, from
+// the side on which a piece overwrites nothing that is still to be read.
+hipError_t copy_within(char* dst, const char* src, int64_t bytes, hipStream_t stream) {
+    if (dst == src) return hipSuccess;
+    const int64_t apart = dst < src ? src - dst : dst - src, piece = std::min({apart, bytes, int64_t(1) << 30});
+    LenTable at0{};
+    hipError_t e = hipSuccess;
+    for (int64_t done = 0; done < bytes && e == hipSuccess; done += piece) {
+        const int64_t n = piece < bytes - done ? piece : bytes - done, from = dst < src ? done : bytes - done - n;
+        // (the row copy takes a K and a V row; both are this one)
+        e = launch_append_rows(1, dst + from, dst + from, 0, &at0, nullptr, src + from, src + from, 0, 0, (int32_t)n, stream);
+    }
+    return e;
+}
+
 // append: the run's last row goes to the cache (a frame and its carrier); append_all: every row
 // of the run does (a question, whose tokens all stay for the answer)
 vs_status prefill_common(const vs_shape* shape, vs_cache* cache, bool append, const void* q,
@@ -88,6 +121,7 @@ vs_status prefill_common(const vs_shape* shape, vs_cache* cache, bool append, co
     const int64_t rb = row_bytes(shape);
     char* kdst = append ? static_cast<char*>(cache->k) + (int64_t)cache->len * rb : nullptr;
     char* vdst = append ? static_cast<char*>(cache->v) + (int64_t)cache->len * rb : nullptr;
+    const bool fused = append && !kept_rows_in_use(shape, kdst, vdst, n_kept * rb, q, k_f, v_f, out, n_tokens);
     hipError_t e;
     if (shape->dtype == VS_BF16) {
         const size_t ctrl = control_block_bytes(*shape);
@@ -97,31 +131,16 @@ vs_status prefill_common(const vs_shape* shape, vs_cache* cache, bool append, co
         if (placement_fault_reported()) return VS_ERR_PLACEMENT;
         char* wsb = static_cast<char*>(workspace);
         e = launch_prefill_mfma(*shape, cache->k, cache->v, cache->len, q, k_f, v_f, n_tokens, out,
-                                kdst, vdst, wsb + prefill_counter_offset(*shape), wsb + ctrl, stream, 1, append_all);
+                                fused ? kdst : nullptr, fused ? vdst : nullptr, wsb + prefill_counter_offset(*shape),
+                                wsb + ctrl, stream, 1, append_all);
     } else {
-        // the kept rows are copied by the attention launch itself, unless the caller's run lies where
-        // they go (a run projected straight into the cache, say): then after it, in a launch of their own
-        const int64_t kept_bytes = n_kept * rb;
-        auto apart = [&](const void* p, int64_t bytes) {
-            const uintptr_t a = reinterpret_cast<uintptr_t>(p);
-            auto clear_of = [&](const char* dst) {
-                const uintptr_t b = reinterpret_cast<uintptr_t>(dst);
-                return a + (uintptr_t)bytes <= b || b + (uintptr_t)kept_bytes <= a;
-            };
-            return clear_of(kdst) && clear_of(vdst);
-        };
-        const int64_t qo_bytes = (int64_t)n_tokens * shape->n_q_heads * shape->head_dim * (int64_t)elem_bytes(shape);
-        const bool fused = append && apart(k_f, n_tokens * rb) && apart(v_f, n_tokens * rb) && apart(q, qo_bytes) &&
-                           apart(out, qo_bytes);
         e = launch_prefill_simple(*shape, cache->k, cache->v, cache->len, q, k_f, v_f, n_tokens, out,
                                   fused ? kdst : nullptr, fused ? vdst : nullptr, n_kept, stream);
-        if (e == hipSuccess && append && !fused) {
-            // (the kept rows are contiguous in the run and in the cache: one block of n_kept rows,
-            // handed to the row copy as a single long row at the destination itself)
-            LenTable t{};
-            e = launch_append_rows(1, kdst, vdst, 0, &t, nullptr, k_f, v_f, 0,
-                                   (int64_t)(n_tokens - n_kept) * rb, (int32_t)(n_kept * rb), stream);
-        }
+    }
+    if (e == hipSuccess && append && !fused) {
+        const int64_t from = (int64_t)(n_tokens - n_kept) * rb;
+        e = copy_within(kdst, static_cast<const char*>(k_f) + from, n_kept * rb, stream);
+        if (e == hipSuccess) e = copy_within(vdst, static_cast<const char*>(v_f) + from, n_kept * rb, stream);
     }
     if (e != hipSuccess) return VS_ERR_HIP;
     if (append) {
@@ -418,10 +437,18 @@ vs_status vs_frames_prefill_attn(const vs_shape* shape, vs_cache* cache, const v
     char* wsb = static_cast<char*>(workspace);
     char* kdst = static_cast<char*>(cache->k) + (int64_t)cache->len * rb;
     char* vdst = static_cast<char*>(cache->v) + (int64_t)cache->len * rb;
-    if (launch_prefill_mfma(*shape, cache->k, cache->v, cache->len, q, k_f, v_f, n_tokens, out, kdst, vdst,
-                            wsb + prefill_counter_offset(*shape), wsb + ctrl, static_cast<hipStream_t>(hip_stream),
-                            n_frames) != hipSuccess)
-        return VS_ERR_HIP;
+    hipStream_t stream = static_cast<hipStream_t>(hip_stream);
+    const bool fused = !kept_rows_in_use(shape, kdst, vdst, n_frames * rb, q, k_f, v_f, out, (int64_t)n_frames * n_tokens);
+    hipError_t e = launch_prefill_mfma(*shape, cache->k, cache->v, cache->len, q, k_f, v_f, n_tokens, out,
+                                       fused ? kdst : nullptr, fused ? vdst : nullptr, wsb + prefill_counter_offset(*shape),
+                                       wsb + ctrl, stream, n_frames);
+    // (one frame after the other: a run that lies at or behind row len then loses no carrier before it is copied)
+    for (int32_t f = 0; !fused && f < n_frames && e == hipSuccess; ++f) {
+        const int64_t from = ((int64_t)f * n_tokens + n_tokens - 1) * rb;
+        e = copy_within(kdst + f * rb, static_cast<const char*>(k_f) + from, rb, stream);
+        if (e == hipSuccess) e = copy_within(vdst + f * rb, static_cast<const char*>(v_f) + from, rb, stream);
+    }
+    if (e != hipSuccess) return VS_ERR_HIP;
     cache->len += n_frames;
     return VS_OK;
 }

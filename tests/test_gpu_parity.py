@@ -934,6 +934,43 @@ def test_fp32_prefill_appends_in_its_launch(dim, L, T, n_kept, overlap):
         assert bool((k[L + n_kept:] == 7).all()) and bool((v[L + n_kept:] == -7).all())
 
 
+@pytest.mark.parametrize("call,F,T,L,at", [
+    ("frame", 1, 170, 40, 0), ("frame", 1, 170, 1500, 0), ("frame", 1, 2000, 100, 0), ("frame", 1, 50, 300, 2), ("frame", 1, 1, 300, 0),
+    ("question", 1, 37, 200, 0), ("question", 1, 37, 2000, 0), ("question", 1, 37, 2000, 5), ("question", 1, 900, 64, 1),
+    ("frames", 3, 50, 700, 0), ("frames", 5, 2, 90, 0), ("frames", 12, 170, 64, 0), ("frames", 4, 33, 200, 3)])
+def test_run_that_lies_in_the_cache_where_its_kept_rows_go(call, F, T, L, at):
+    """A run projected straight into the cache, at row len + at: the same bits, in the outputs and the kept rows, as from
+    tensors of its own.  (Long runs take several rounds of workgroups, which all read the run's first rows.)"""
+    s = QW
+    sh, rows = vs_shape(s), F * T
+    hk, hv = cache_rows(44, s, L, 0.5)
+    q, kf, vf = (t.to(DEV) for t in frame_inputs(44, s, rows, 0.5, q_gain=3))
+    kept = {"frame": 1, "question": T, "frames": F}[call]
+    need = vs.frames_workspace_bytes(sh, F, T, L + F) if call == "frames" else vs.workspace_bytes(sh, T, L, 0)
+    ws = torch.empty(need, dtype=torch.uint8, device=DEV)
+    vs.workspace_init(sh, ws)
+    got = []
+    for in_cache in (False, True):
+        k, v = (torch.full((L + at + rows + 2, s.n_kv_heads, s.head_dim), 3.0, dtype=torch.bfloat16, device=DEV) for _ in range(2))
+        k[:L].copy_(hk)
+        v[:L].copy_(hv)
+        kd, vd = (k[L + at:L + at + rows], v[L + at:L + at + rows]) if in_cache else (kf, vf)
+        if in_cache:
+            kd.copy_(kf)
+            vd.copy_(vf)
+        cache = vs.Cache(k, v, L)
+        out = torch.full(q.shape, float("nan"), dtype=torch.bfloat16, device=DEV)
+        if call == "frames":
+            vs.frames_prefill_attn(sh, cache, *(t.view(F, T, *t.shape[1:]) for t in (q, kd, vd, out)), ws)
+        else:
+            (vs.frame_prefill_compact if call == "frame" else vs.question_prefill_append)(sh, cache, q, kd, vd, out, ws)
+        torch.cuda.synchronize()
+        assert cache.len == L + kept
+        got.append((out, k[:L + kept].clone(), v[:L + kept].clone()))
+    for apart, inside in zip(*got):
+        assert torch.equal(apart.view(torch.int16), inside.view(torch.int16))
+
+
 @pytest.mark.parametrize("n_caches,pinned", [(28, False), (4096, False), (4095, True), (4096, True), (4097, True), (50, True)])
 def test_batched_compaction(n_caches, pinned):
     s, T, cap = QW, 6, 5
