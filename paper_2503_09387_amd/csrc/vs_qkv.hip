@@ -16,9 +16,9 @@
 // cache until its data is back and data comes back in order, so behind weights on their way from HBM the
 // rows of E, which wait in L2, come in no faster than those: 28.9 us (51 GB/s per compute unit).  But 144
 // workgroups leave 112 compute units idle: they run ahead as helpers and ask for the weight and embedding
-// rows of the workgroups of their XCD, so that these find both in L2: 17.3 us (30.9 without helpers, 23.6 with
-// helpers for the weights alone, the same with 4 .. 16 loads of a helper's wavefront under way, 22.6 with 2).
-// When done the helpers sum up the carrier embedding.
+// rows of the workgroups of their XCD, so that these find both in L2: 17.3 us over weights that the memory-side cache
+// holds (30.9 without helpers, 23.6 with helpers for the weights alone, the same with 4 .. 16 loads of a helper's
+// wavefront under way, 22.6 with 2), 17.6 .. 19.1 over 28 layers' weights.  When done the helpers sum up the carrier embedding.
 //
 // The carrier's row is not multiplied at all: the projection is linear, so its Q/K/V are the means
 // over the token rows of the fp32 sums the workgroup holds anyway (the mean enters unrounded).
@@ -282,6 +282,27 @@ __global__ __launch_bounds__(kThreads) void frame_qkv_kernel(QkvParams p) {
     if (p.c_out && (int)gridDim.x == p.n_blocks) pool_share(p, blockIdx.x, gridDim.x, poolsum, tid);  // (no helpers)
 }
 
+// Helpers per XCD.  For a tile of 64 input features those of an XCD bring in `rows` rows (all of E, and W for the XCD's
+// workgroups) at ~42 KB/us each; whoever multiplies takes (N + 32) rows at ~51 KB/us without their help, and no less than
+// 0.22 us.  They pay while their time is below ~0.6 of that; slower ones only read everything a second time, and
+// the launch waits for them (us with all idle compute units as helpers / with none, d 3584: 144 workgroups, 169 tokens 17.6 /
+// 29.9, 1 token 11.9 / 12.3; 160: 24.6 / 30.5, 13.2 / 12.7; 180: 29.1 / 30.9, 13.8 / 12.8; 192: 32.6 / 30.8; 224: 52.9 /
+// 31.5, 38.4 / 13.3; 240: 107.9 / 31.3).  The launch's fixed cost hides some more (192, d 1024: 10.4 / 11.9).  With a
+// quarter of the multiplying workgroups' rows for each there are enough of them (24 workgroups, 169 tokens: 48 helpers
+// 15.8, 232 helpers 15.7 us).  The counts are those of the whole chip: no helpers on a part of one.
+int helpers_per_xcd(const QkvParams& p, int dev) {
+    static int cus_of[16] = {};  // (asked for once per device)
+    if (!cus_of[dev] && hipDeviceGetAttribute(&cus_of[dev], hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess) return 0;
+    const int shift = xcd_shift_of_device(dev);  // (-1: not asked for yet)
+    if (cus_of[dev] != kCus || (shift >= 0 && 1 << shift != kXcds)) return 0;
+    const int idle = (kCus - p.n_blocks) / kXcds;
+    if (idle < 2) return 0;
+    const int rows = (p.N + 7) / 8 * 8 + kTileN * ((p.n_blocks + kXcds - 1) / kXcds), own = (p.N + 15) / 16 * 16 + kTileN;
+    if (rows > idle * ((own > 84 ? own / 2 : 42) + 25600 / p.d)) return 0;
+    const int enough = (4 * rows + own - 1) / own + 1;
+    return enough < idle ? enough : idle;
+}
+
 }  // namespace
 
 template <int RS>
@@ -294,9 +315,7 @@ hipError_t launch_qkv_variant(const QkvParams& p, int dev, hipStream_t st) {
         if (err != hipSuccess) return err;
         attr_set_on[dev] = true;
     }
-    // helpers where at least two per XCD find a compute unit of their own
-    const int helpers = p.n_blocks + 2 * kXcds <= kCus ? kCus - p.n_blocks : 0;
-    frame_qkv_kernel<RS><<<p.n_blocks + helpers, kThreads, kLds, st>>>(p);
+    frame_qkv_kernel<RS><<<p.n_blocks + kXcds * helpers_per_xcd(p, dev), kThreads, kLds, st>>>(p);
     return hipGetLastError();
 }
 

@@ -848,6 +848,8 @@ def test_frame_projection_matches_oracle(N, d, heads):
     # left over for helpers
     (1, 64, (8, 1)), (15, 128, (5, 5)), (16, 320, (6, 3)), (17, 384, (6, 3)), (63, 448, (5, 5)), (64, 320, (8, 1)), (65, 64, (5, 5)),
     (112, 192, (6, 3)), (128, 384, (8, 8)), (129, 320, (5, 5)), (144, 128, (48, 8)), (161, 448, (40, 8)), (191, 384, (12, 6)),
+    # 192 workgroups: with helpers, and with too few of them to pay; 12 workgroups: fewer helpers than idle compute units
+    (191, 1280, (32, 8)), (100, 1280, (32, 8)), (169, 512, (1, 1)),
 ])
 def test_frame_projection_row_groups_ring_and_helpers(N, d, heads):
     s = AttnShape(heads[0], heads[1], 128, "bf16")
