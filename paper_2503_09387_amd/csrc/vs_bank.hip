@@ -120,17 +120,6 @@ __global__ __launch_bounds__(kShiftThreads) void bank_shift_kernel(ShiftParams p
         if (p.victim_io && blockIdx.x == 0 && blockIdx.y == 0 && tid == 0) *p.victim_io = -1;
         return;
     }
-    // a bank that one pass holds is requested before the victim is known (a trip to memory less)
-    const bool one_pass = p.M - 1 <= kShiftPass;
-    raw16 v[kShiftSteps];
-    auto fetch = [&](int r0) {
-#pragma unroll
-        for (int u = 0; u < kShiftSteps; ++u) {  // destination rows (past the end: the last row, not stored)
-            const int r = min(r0 + kShiftRows * u + lr + 1, p.M - 1);
-            v[u] = *reinterpret_cast<const raw16*>(base + (int64_t)r * p.row_bytes + min(col, p.row_bytes - 16));
-        }
-    };
-    if (one_pass) fetch(0);
     int victim;
     if (p.cosines) {
         // largest cosine, of equal ones the smallest index: thread t looks at cosines t, t + 256, ..,
@@ -177,16 +166,25 @@ __global__ __launch_bounds__(kShiftThreads) void bank_shift_kernel(ShiftParams p
     }
     victim = min(max(victim, 0), p.M - 1);  // (an index from device memory is not trusted to be in range)
     // rows victim+1 .. M-1 move to victim .. M-2, kShiftPass rows per pass: all loads of a pass, a
-    // barrier, all its stores (a later pass reads only rows that no earlier pass has written)
-    for (int r0 = one_pass ? 0 : victim; r0 + 1 < p.M; r0 += kShiftPass) {
-        if (!one_pass) fetch(r0);
+    // barrier, all its stores (a later pass reads only rows that no earlier pass has written).  (Requesting the rows
+    // before the victim is known saves no time, because the launch is as long as its longest workgroup either way, and
+    // reads the rows in front of the victim for nothing: 28 layers of 128 rows of 1 KB, victim first / last, 4.1 / 2.4
+    // us and 4.1 / 3.1 so, rows of 8 KB 20.1 / 3.6 and 19.8 / 11.5.)
+    for (int r0 = victim; r0 + 1 < p.M; r0 += kShiftPass) {
+        raw16 v[kShiftSteps];
+#pragma unroll
+        for (int u = 0; u < kShiftSteps; ++u) {  // destination rows (past the end: the last row, not stored)
+            if (r0 + kShiftRows * u + 1 >= p.M) break;
+            const int r = min(r0 + kShiftRows * u + lr + 1, p.M - 1);
+            v[u] = *reinterpret_cast<const raw16*>(base + (int64_t)r * p.row_bytes + min(col, p.row_bytes - 16));
+        }
 #pragma unroll
         for (int u = 0; u < kShiftSteps; ++u) keep_here(v[u]);  // (this wavefront's rows are in registers)
         __syncthreads();
 #pragma unroll
         for (int u = 0; u < kShiftSteps; ++u) {
             const int r = r0 + kShiftRows * u + lr;
-            if (r >= victim && r + 1 < p.M && in_row)
+            if (r + 1 < p.M && in_row)
                 *reinterpret_cast<raw16*>(base + (int64_t)r * p.row_bytes + col) = v[u];
         }
         __syncthreads();
