@@ -39,7 +39,10 @@ __device__ __forceinline__ double block_sum(double x, double* lds) {  // fixed o
 }
 
 // Bound by the trips to memory: both rows are requested at once, 16 bytes per thread, and pass through
-// LDS, from where thread t takes the elements t, t + 256, .. in order (7.0 -> 4.3 us at 128 x 3584).
+// LDS, from where thread t takes the elements t, t + 256, .. in order (7.0 -> 4.3 us at 128 x 3584).  A short row is
+// read in that order right away (a push at 128 rows, this way and through LDS: 256 wide 6.4 and 6.8 us, 512 6.6 and 6.8, 1024 6.75
+// and 6.73).
+constexpr int kShortRow = 512;
 template <typename T>
 __global__ __launch_bounds__(256) void bank_cosine_kernel(const T* __restrict__ e, const T* __restrict__ e_new,
                                                           int M, int d, int policy, double* __restrict__ cosines) {
@@ -50,7 +53,14 @@ __global__ __launch_bounds__(256) void bank_cosine_kernel(const T* __restrict__ 
     const T* a = e + (int64_t)i * d;
     const T* b = (policy == 1 || i + 1 == M) ? e_new : e + (int64_t)(i + 1) * d;
     double ab = 0.0, aa = 0.0, bb = 0.0;
-    for (int j0 = 0; j0 < d; j0 += kSeg) {
+    if (d <= kShortRow) {
+        for (int j = threadIdx.x; j < d; j += 256) {
+            const double x = (double)to_f32(a[j]), y = (double)to_f32(b[j]);
+            ab += x * y;
+            aa += x * x;
+            bb += y * y;
+        }
+    } else for (int j0 = 0; j0 < d; j0 += kSeg) {
         const int n = min(kSeg, d - j0), n16 = n / kVec;  // (rows are whole multiples of 16 bytes)
         raw16 va[2], vb[2];
 #pragma unroll

@@ -1071,10 +1071,11 @@ def test_memory_bank_stream(dtype, M, d, policy):
     assert near_ties <= extra // 4
 
 
-@pytest.mark.parametrize("dtype,M,d", [("bf16", 33, 4104), ("f32", 257, 2052), ("bf16", 258, 72), ("bf16", 600, 8), ("f32", 1, 4)])
+@pytest.mark.parametrize("dtype,M,d", [("bf16", 33, 4104), ("f32", 257, 2052), ("bf16", 258, 72), ("bf16", 600, 8), ("f32", 1, 4),
+                                       ("bf16", 40, 512), ("bf16", 40, 520), ("f32", 40, 516)])
 def test_memory_bank_at_the_edges_of_a_pass(dtype, M, d):
     """Banks around what one pass of the row move holds (256 rows), embeddings around what the cosines take
-    through LDS at a time (8 KB): victims against the fp64 oracle, the moved rows bit for bit."""
+    through LDS at a time (8 KB) and around those they do not take through it (512 numbers): victims against the fp64 oracle, the moved rows bit for bit."""
     dt = torch_dtype(dtype)
     emb = carrier_embeddings(11, M + 6, d, dtype)
     bank = vs.Bank(emb[:M].clone().to(DEV), dtype, M)
