@@ -269,9 +269,12 @@ __global__ __launch_bounds__(kCopyThreads) void append_rows_kernel(
 // with many loads in flight.  Row group r sums rows r, r+16, ... in order in fp32 (up to 12 rows are
 // requested before the first is added: a frame of 169 tokens is one trip to memory, 4.2 -> 3.5 us at
 // d = 3584, where twice as many workgroups as with 16 chunks help too); the 16 partial sums are added
-// in order 0..15; one rounding.
-constexpr int kPoolCols = 8, kPoolRowGroups = 16, kPoolDepth = 12;
-template <typename T, int VEC>
+// in order 0..15; one rounding.  kPoolDepth: rows requested at once, no more than a group has (16 rows of 256 fp32 numbers: 2.1 us
+// for one, 2.3 for 12); kPoolCols: 16 chunks where 8 would give more than 512
+// workgroups (16 rows of 65536 bf16 numbers: 3.1 us, 3.8 with 8).  Full batches ask for no row twice: 1000 x 3584 takes 6.7 us, 7.0
+// with every address clamped.
+constexpr int kPoolRowGroups = 16;
+template <typename T, int VEC, int kPoolCols, int kPoolDepth>
 __global__ __launch_bounds__(kPoolCols * kPoolRowGroups) void mean_pool_kernel(
     const T* __restrict__ e, int n, int d, T* __restrict__ c) {
     const int cl = threadIdx.x % kPoolCols, rg = threadIdx.x / kPoolCols;
@@ -281,7 +284,22 @@ __global__ __launch_bounds__(kPoolCols * kPoolRowGroups) void mean_pool_kernel(
 #pragma unroll
     for (int k = 0; k < VEC; ++k) s[k] = 0.f;
     if (col < d) {
-        for (int r0 = rg; r0 < n; r0 += kPoolDepth * kPoolRowGroups) {
+        int r0 = rg;
+        for (; r0 + (kPoolDepth - 1) * kPoolRowGroups < n; r0 += kPoolDepth * kPoolRowGroups) {
+            raw16 tmp[kPoolDepth];
+#pragma unroll
+            for (int u = 0; u < kPoolDepth; ++u)
+                tmp[u] = *reinterpret_cast<const raw16*>(e + (int64_t)(r0 + u * kPoolRowGroups) * d + col);
+#pragma unroll
+            for (int u = 0; u < kPoolDepth; ++u) keep_here(tmp[u]);
+#pragma unroll
+            for (int u = 0; u < kPoolDepth; ++u) {
+                const T* t = reinterpret_cast<const T*>(&tmp[u]);
+#pragma unroll
+                for (int k = 0; k < VEC; ++k) s[k] += to_f32(t[k]);
+            }
+        }
+        if (r0 < n) {  // the rest of the group
             raw16 tmp[kPoolDepth];
 #pragma unroll
             for (int u = 0; u < kPoolDepth; ++u) {  // (past the end: the last row, not added)
@@ -385,13 +403,25 @@ hipError_t launch_append_rows(int32_t n_caches, void* k_slab, void* v_slab, int6
 
 hipError_t launch_mean_pool(const void* e, int32_t n, int32_t d, int32_t dtype, void* c_out,
                             hipStream_t st) {
-    if (dtype == VS_F32) {
-        const int blocks = (d / 4 + kPoolCols - 1) / kPoolCols;
-        mean_pool_kernel<float, 4><<<blocks, kPoolCols * kPoolRowGroups, 0, st>>>((const float*)e, n, d, (float*)c_out);
-    } else {
-        const int blocks = (d / 8 + kPoolCols - 1) / kPoolCols;
-        mean_pool_kernel<__bf16, 8><<<blocks, kPoolCols * kPoolRowGroups, 0, st>>>((const __bf16*)e, n, d, (__bf16*)c_out);
-    }
+    const int chunks = d / (dtype == VS_F32 ? 4 : 8);
+    const bool wide = chunks > 8 * 512;
+#define VS_GO(COLS, DEPTH)                                                                                                    \
+    do {                                                                                                                      \
+        const dim3 grid((chunks + COLS - 1) / COLS), block(COLS * kPoolRowGroups);                                            \
+        if (dtype == VS_F32) mean_pool_kernel<float, 4, COLS, DEPTH><<<grid, block, 0, st>>>((const float*)e, n, d, (float*)c_out); \
+        else mean_pool_kernel<__bf16, 8, COLS, DEPTH><<<grid, block, 0, st>>>((const __bf16*)e, n, d, (__bf16*)c_out);         \
+    } while (0)
+#define VS_GO_DEPTH(DEPTH)      \
+    do {                        \
+        if (wide) VS_GO(16, DEPTH); \
+        else VS_GO(8, DEPTH);   \
+    } while (0)
+    if (n <= kPoolRowGroups) VS_GO_DEPTH(1);
+    else if (n <= 4 * kPoolRowGroups) VS_GO_DEPTH(4);
+    else if (n <= 8 * kPoolRowGroups) VS_GO_DEPTH(8);
+    else VS_GO_DEPTH(12);
+#undef VS_GO_DEPTH
+#undef VS_GO
     return hipGetLastError();
 }
 

@@ -890,9 +890,11 @@ def test_mean_pool(n, d, dtype):
         assert np.all(np.abs(got - ref) <= np.abs(ref) * 2.0 ** -8 + 1e-30)
 
 
-@pytest.mark.parametrize("n,d,dtype", [(191, 72, "bf16"), (192, 64, "bf16"), (193, 200, "bf16"), (385, 36, "f32")])
+@pytest.mark.parametrize("n,d,dtype", [(191, 72, "bf16"), (192, 64, "bf16"), (193, 200, "bf16"), (385, 36, "f32"),
+                                       (16, 72, "bf16"), (17, 36, "f32"), (64, 200, "bf16"), (65, 36, "f32"), (17, 32776, "bf16"),
+                                       (200, 16388, "f32")])
 def test_mean_pool_around_one_trip(n, d, dtype):
-    """Row counts around what a thread requests at once (12 rows of 16 row groups), ragged column blocks: bit for
+    """Row counts around what a thread requests at once (1, 4 or 12 rows of 16 row groups), ragged column blocks of both widths: bit for
     bit the sum in the documented order, 16 row groups in order and then their sums in order."""
     e = draw(32, (n, d), 1.0, dtype)
     out = torch.empty(d, dtype=torch_dtype(dtype), device=DEV)
