@@ -465,7 +465,8 @@ __global__ __launch_bounds__(256) void linear_reduce_kernel(LinParams p, int n_b
 // rounding.  One workgroup per row, 8 numbers per thread and pass.
 // A row stays in registers between the two passes over it, and gamma is on its way before the sum is
 // known: one trip to memory instead of three in a row (layers of 50 rows 110.0 -> 108.7 us, of 170 rows
-// 169.0 -> 167.9 us, two norms in each; what is left of a launch is its start and its end).
+// 169.0 -> 167.9 us, two norms in each; what is left of a launch is its start and its end).  4096 rows of 64 / 1024 / 3584
+// features: 3.6 / 4.8 / 10.1 us (with two pieces for every thread 4.2 / 5.3 / 10.1, read twice 3.8 / 5.2 / 10.8).
 // R: pieces of 8 features a thread holds, rows of up to 2048 R features; 0: longer rows, read twice.
 template <int R>
 __global__ __launch_bounds__(256) void rmsnorm_kernel(const __bf16* __restrict__ x, const __bf16* __restrict__ gamma,
@@ -480,7 +481,8 @@ __global__ __launch_bounds__(256) void rmsnorm_kernel(const __bf16* __restrict__
     raw16 xv[R ? R : 1], gv[R ? R : 1];
     if constexpr (R > 0) {
 #pragma unroll
-        for (int u = 0; u < R; ++u) {  // (past the end: the last piece, not used)
+        for (int u = 0; u < R; ++u) {  // (past the end: the last piece, not used; a row of one piece is not padded)
+            if (R == 1 && (int)threadIdx.x >= n8) break;
             const int i = min((int)threadIdx.x + 256 * u, n8 - 1);
             xv[u] = reinterpret_cast<const raw16*>(xr)[i];
             gv[u] = reinterpret_cast<const raw16*>(gr)[i];
@@ -663,7 +665,8 @@ hipError_t launch_linear(const void* x, int32_t ldx, const void* w, int32_t n_ro
 hipError_t launch_rmsnorm(const void* x, const void* gamma, int32_t n_rows, int32_t d, float eps, void* out,
                           hipStream_t st) {
     const __bf16 *xb = (const __bf16*)x, *gb = (const __bf16*)gamma;
-    if (d <= 2 * 2048) rmsnorm_kernel<2><<<n_rows, 256, 0, st>>>(xb, gb, (__bf16*)out, d, eps);
+    if (d <= 2048) rmsnorm_kernel<1><<<n_rows, 256, 0, st>>>(xb, gb, (__bf16*)out, d, eps);
+    else if (d <= 2 * 2048) rmsnorm_kernel<2><<<n_rows, 256, 0, st>>>(xb, gb, (__bf16*)out, d, eps);
     else if (d <= 4 * 2048) rmsnorm_kernel<4><<<n_rows, 256, 0, st>>>(xb, gb, (__bf16*)out, d, eps);
     else rmsnorm_kernel<0><<<n_rows, 256, 0, st>>>(xb, gb, (__bf16*)out, d, eps);
     return hipGetLastError();
