@@ -1104,14 +1104,25 @@ constexpr int kPlanXcds = 8, kPlanCusPerXcd = 32;
 // tokens over 4552 rows took 29.4 us, 17.1 with 13 splits).  Among those plans the cheapest by a model
 // fitted to 8000 measured (shape, tokens, rows, plan) combinations: the steps of the longest lane (one tile
 // per key group), the tiles of the average lane, the second key group, the merge, and what a wavefront loads for it.
-// Over the sizes that come here (see prefers_short_kernel) its choice is 0.8 % from the best measured plan on
-// average and 7 % at worst; against 256 compute units as one pool it gains 4 % on average and loses 2 % at worst.
+// Over single runs of at least 9 tiles its choice is 0.8 % from the best measured plan on average and 7 % at worst;
+// against 256 compute units as one pool it gains 4 % on average and loses 2 % at worst.  With few tiles (runs of
+// frames at the start of a video, runs too long for the kernel that splits nothing) a launch is all fixed cost, which
+// the model puts too high for the merge: there as many workgroups per unit as there are tiles are best, as far as
+// they fit (2 frames of 170 tokens over 264 rows: 17.4 us unsplit, as the model has it, 13.2 so; over 451 plans
+// of up to 7 tiles 1.8 % from the best on average, the model 12.4 %), and at 8 tiles two key groups (2.6 %, the model 7.8 %).
 struct SplitPlan {
     int kvg, nsplit;
 };
 SplitPlan make_split_plan(int units, int max_tiles) {
     const int per_xcd = (units + kPlanXcds - 1) / kPlanXcds;
     SplitPlan best{1, 1};
+    if (max_tiles <= 8 && !g_tune_prefill_kv_groups) {
+        best.kvg = max_tiles == 8 ? 2 : 1;
+        const int fit = kPlanCusPerXcd * (best.kvg == 1 ? 2 : 1) / per_xcd, lanes = max_tiles / best.kvg;
+        best.nsplit = fit < lanes ? fit : lanes;
+        if (best.nsplit < 1) best.nsplit = 1;
+        return best;
+    }
     float best_cost = 0.f;
     for (int kvg = 1; kvg <= 2; ++kvg) {
         if (g_tune_prefill_kv_groups && kvg != g_tune_prefill_kv_groups) continue;
