@@ -106,9 +106,9 @@ size_t vs_workspace_bytes(const vs_shape *shape, int32_t max_q_tokens, int32_t m
  * memory a bounded number of times, a few milliseconds at most),
  * through the L2 cache that the compute units of one XCD (accelerator die) share; the library
  * therefore gives all those workgroups ids that the device deals to one XCD, which it learns
- * from the probe (ids go to the XCDs in turn).  Every workgroup of every such launch checks that
- * it really runs on the XCD the probe saw for its id.  If one does not (another partition mode,
- * masked compute units), or if one waits for the last of its row tile in vain (the workgroups of
+ * from the probe (ids go to the XCDs in turn).  Every such launch checks, row tile by row tile, that
+ * its workgroups really ran on one XCD; which one does not matter (it changes when a process uses more streams
+ * or graphs).  If they did not (another partition mode, masked compute units), or if one waits for the last of its row tile in vain (the workgroups of
  * the launch are not all running at once: the device is shared with other work), it sets a word
  * of pinned host memory (64 bytes per device, allocated by
  * the first vs_workspace_init on the device and kept until the process ends).  The next bf16
@@ -330,8 +330,8 @@ vs_status vs_carrier_evict_append(const vs_shape *shape, int32_t n_layers, vs_ca
  *                             workgroup of a row tile to arrive alone (not shared by the tile's
  *                             workgroups); 2 = always by the second kernel, never inside the
  *                             attention kernel; 3 = for tests of the placement guard (see
- *                             vs_workspace_init): the kernels are told the probed XCD order
- *                             rotated by one, so every workgroup reports itself misplaced while
+ *                             vs_workspace_init): every other workgroup of a row tile gives a
+ *                             neighbouring XCD as its own, so that every row tile is reported as misplaced while
  *                             the results stay correct; 4 = for tests of the bounded wait of the
  *                             shared merge: the workgroups that would wait for the last of their
  *                             tile give up at once and report, as if the workgroups of a tile

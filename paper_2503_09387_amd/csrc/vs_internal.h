@@ -4,6 +4,7 @@
 #include <stdint.h>
 
 #include "videoscan.h"
+#include "vs_prefill_map.h"
 
 namespace vs {
 
@@ -74,8 +75,8 @@ hipError_t launch_decode_mfma(const vs_shape& s, int32_t n_streams, void* k_slab
 // Control block at the start of every workspace: [kMaxStreamsPerLaunch][Hkv] arrival counters of the
 // decode steps of few rows, then the prefill's arrival counters, one per unit = (KV head, frame, row tile), each alone
 // in 128 bytes (the workgroups of a unit look at theirs while they wait for one another: counters of
-// other units in the same line would queue behind those looks).  A prefill counter wraps to zero with the
-// last arrival, a decode counter goes back to kDecodeCounterStart: so it is between launches.
+// other units in the same line would queue behind those looks).  The last arrival puts a
+// prefill counter back to zero, a decode counter to kDecodeCounterStart: so they are between launches.
 constexpr unsigned kDecodeCounterStart = 0x7fa5c300u;  // a mark in the upper 24 bits (as fp32 a signalling NaN, which no arithmetic leaves behind)
 constexpr unsigned kDecodeCounterMark = 0xffffff00u;
 constexpr int kMaxRowTiles = 256;
@@ -91,22 +92,60 @@ int xcd_shift_of_device(int dev);
 // Finds out once per device how workgroup ids are dealt to the XCDs (scratch: 256 bytes of device
 // memory; synchronises the stream the first time).
 hipError_t probe_xcd_mapping(void* scratch, hipStream_t st);
-// True once after a workgroup of an in-kernel-merge launch on this device has reported that it ran
-// on another XCD than probed; in-kernel merging is then off for the device until it is probed again.
+// True once after a unit of an in-kernel-merge launch on this device has reported that its workgroups were not on one
+// XCD, or not all running at once; in-kernel merging is then off for the device until it is probed again.
 bool prefill_placement_fault(int dev);
 void prefill_guard_test_mode(int on);
 // What a kernel that merges inside the launch needs to know about the device: how many XCDs ids are
-// dealt to in turn (log2), which XCD ids of residue r were seen on (4 bits each), the host word (as
-// the kernels address it) through which a workgroup reports, and how often a waiting workgroup looks
-// before it gives up.  False: not probed, a fault has been reported since, or merging inside kernels is
+// dealt to in turn (log2), the host word (as the kernels address it) through which a workgroup reports, and how
+// often a waiting workgroup looks before it gives up.  False: not probed, a fault has been reported since, or merging inside kernels is
 // switched off (VS_TUNE_PREFILL_MERGE = 2): merge with a second kernel.
 struct XcdPlacement {
     int xcd_shift;
-    unsigned long long xcc_of_residue;
     unsigned* misplaced;
     int max_looks;
+    unsigned lie;  // tests: 1 = every other workgroup of a unit gives a neighbouring XCD as its own; otherwise 0
 };
 bool xcd_placement_of_device(int dev, XcdPlacement* out);
+
+// What this workgroup, number `index` of its unit, counts itself in with.  (Asked for before the workgroup waits for its
+// stores: reading the XCD's id takes a while.)
+__device__ __forceinline__ unsigned own_arrival(int index, unsigned lie) {
+    unsigned xcc;
+    asm volatile("s_getreg_b32 %0, hwreg(HW_REG_XCC_ID)" : "=s"(xcc));
+    return arrival_of((xcc & 15u) ^ ((unsigned)index & lie));
+}
+// Each of the n workgroups of a unit counts itself in, at the L2 of its XCD, and waits until all are in; its first thread looks
+// again at most max_looks times.  1, or 2 for the last to arrive: all are in, and their stores before their arrival
+// are complete in this L2; 0: it has waited in vain, which is reported, as are arrivals from another XCD.  (The last
+// arrival clears the word: those who wait see all in, or zero.)  To be called by the whole workgroup; box: two words of LDS.
+__device__ __forceinline__ unsigned count_in(unsigned* box, unsigned* word, int n, unsigned mine, int max_looks, unsigned* misplaced,
+                                             int tid) {
+    const unsigned all = (unsigned)n * mine;
+    if (tid == 0) box[0] = __hip_atomic_fetch_add(word, mine, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+    __syncthreads();
+    unsigned seen = __builtin_amdgcn_readfirstlane(box[0]) + mine;
+    const bool last = arrivals_in(seen) == (unsigned)n;
+    if (last) {  // (behind the barrier, which would wait for the store)
+        if (tid == 0) __hip_atomic_store(word, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+    } else {
+        if (tid == 0) {
+            unsigned zero = 0;  // (a read-modify-write that the compiler cannot turn into a load, which the compute unit's cache could serve)
+            asm volatile("" : "+s"(zero));
+            seen = 0;
+            for (int looks = 0; looks < max_looks && !seen; ++looks) {
+                const unsigned v = __hip_atomic_fetch_add(word, zero, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+                seen = v == 0u ? all : arrivals_in(v) == (unsigned)n ? v : 0u;  // (cleared: by the last arrival, which has compared it)
+                if (!seen) __builtin_amdgcn_s_sleep(2);
+            }
+            box[1] = seen;
+        }
+        __syncthreads();
+        seen = __builtin_amdgcn_readfirstlane(box[1]);
+    }
+    if (seen != all && tid == 0) __hip_atomic_store(misplaced, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+    return !seen ? 0u : last ? 2u : 1u;
+}
 
 // the body of vs_decode_attn (checks, launches, length bookkeeping) over any workspace; stateless: nothing in
 // it has to hold anything when the call begins

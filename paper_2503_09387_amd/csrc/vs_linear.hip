@@ -75,8 +75,8 @@ struct LinParams {
     // (vs_prefill_map.h: unit = block, split = share), counted in and waited for in the same way.
     unsigned* arrivals;          // one counter per block, kCounterStrideBytes apart, zero between launches
     unsigned* misplaced;         // pinned host word through which a workgroup reports
-    unsigned long long xcc_of_residue;
     int xcd_shift, units_per_xcd, n_blocks, max_looks;
+    unsigned lie;
     float inv_ksplit;
 };
 
@@ -193,10 +193,6 @@ __global__ __launch_bounds__(kThreads) void linear_kernel(LinParams p) {
         // take consecutive slots of one residue
         const PrefillSlot at = prefill_slot_of_id(blockIdx.x, p.n_blocks, p.units_per_xcd, p.ksplit, p.inv_ksplit, p.xcd_shift);
         if (at.unit < 0) return;  // spare ids
-        unsigned xcc;
-        asm volatile("s_getreg_b32 %0, hwreg(HW_REG_XCC_ID)" : "=s"(xcc));
-        if ((xcc & 15u) != (unsigned)((p.xcc_of_residue >> (4 * at.xcd)) & 15u) && threadIdx.x == 0)
-            __hip_atomic_store(p.misplaced, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);  // (see vs_workspace_init)
         blk = __builtin_amdgcn_readfirstlane(at.unit);  // (worked out in floats, and so in vector registers)
         share = __builtin_amdgcn_readfirstlane(at.split);
     }
@@ -349,36 +345,22 @@ __global__ __launch_bounds__(kThreads) void linear_kernel(LinParams p) {
         // ---- The shares are added inside this launch, by the workgroups of the block together.
         // Every workgroup's stores above are complete in its XCD's L2 before it counts itself in
         // (all wavefronts wait for their stores, then the barrier, then the atomic, executed at that
-        // L2: an increment that wraps, so the counter is zero again with the last arrival).  Those
+        // L2; the last arrival puts the counter back to zero).  Those
         // that are not last look at the counter again with read-modify-writes (adding a zero the
         // compiler cannot see), never served by the compute unit's cache, a bounded number of times,
-        // until it reads zero; then every share of the block is complete in this L2 (these lines are
-        // read nowhere else in the launch, so the loads miss in the compute unit's cache).
+        // until all are in or it reads zero; then every share of the block is complete in this L2 (these lines are
+        // read nowhere else in the launch, so the loads miss in the compute unit's cache).  Were they not all on
+        // this XCD (see arrival_of), that is reported.
         // Workgroup j of the block then finishes the 16-row sub-tiles j, j + ksplit, ..: its wavefronts
         // add the shares of their (sub-tile, feature sub-tile) pairs in index order, as
         // linear_reduce_kernel does, and the rows leave through LDS as below.  A workgroup that has looked max_looks
         // times in vain reports through the host word of the placement guard and returns. ----
+        const unsigned mine_in = own_arrival(share, p.lie);
         __builtin_amdgcn_s_waitcnt(0x0F70);  // vmcnt(0)
         __syncthreads();
         unsigned* const box = reinterpret_cast<unsigned*>(ring);
         unsigned* const counter = p.arrivals + (int64_t)blk * (kCounterStrideBytes / 4);
-        if (tid == 0) *box = __builtin_amdgcn_atomic_inc32(counter, (unsigned)(p.ksplit - 1), __ATOMIC_RELAXED, "workgroup");
-        __syncthreads();
-        if (*box + 1 != (unsigned)p.ksplit) {
-            unsigned zero = 0;
-            asm volatile("" : "+s"(zero));
-            if (tid == 0) {
-                unsigned ok = 0;
-                for (int n = 0; n < p.max_looks && !ok; ++n) {
-                    ok = __hip_atomic_fetch_add(counter, zero, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP) == 0u;
-                    if (!ok) __builtin_amdgcn_s_sleep(2);
-                }
-                box[1] = ok;
-                if (!ok) __hip_atomic_store(p.misplaced, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
-            }
-            __syncthreads();
-            if (!box[1]) return;
-        }
+        if (!count_in(box, counter, p.ksplit, mine_in, p.max_looks, p.misplaced, tid)) return;
         // this workgroup's sub-tiles: rs = share, share + ksplit, .. below 12 and below T rows
         const int n_rs = (p.T + 15) >> 4;
         const int n_mine = share < n_rs ? (n_rs - share + p.ksplit - 1) / p.ksplit : 0;
@@ -645,7 +627,7 @@ hipError_t launch_linear(const void* x, int32_t ldx, const void* w, int32_t n_ro
     p.n_blocks = pl.n_blocks;
     p.arrivals = nullptr;
     p.misplaced = nullptr;
-    p.xcc_of_residue = 0;
+    p.lie = 0;
     p.xcd_shift = p.units_per_xcd = p.max_looks = 0;
     p.inv_ksplit = 1.0f / (float)pl.ksplit;
     XcdPlacement where;
@@ -653,7 +635,7 @@ hipError_t launch_linear(const void* x, int32_t ldx, const void* w, int32_t n_ro
         (1 << where.xcd_shift) == kPlanXcds) {
         p.arrivals = (unsigned*)arrival_counters;
         p.misplaced = where.misplaced;
-        p.xcc_of_residue = where.xcc_of_residue;
+        p.lie = where.lie;
         p.xcd_shift = where.xcd_shift;
         p.units_per_xcd = prefill_units_per_xcd(pl.n_blocks, where.xcd_shift);
         p.max_looks = where.max_looks;

@@ -4,9 +4,10 @@
 // and a host-side test (plain C++, no HIP types).
 //
 // The merge goes through the L2 cache that the compute units of one XCD share, so all splits
-// of a unit = (KV head, frame, row tile) must run on one XCD.  The hardware deals workgroup ids
-// to the XCDs in turn (id mod number of XCDs; read off the device once, and checked again by
-// every workgroup of every launch).  Unit u therefore takes the ids of one residue x:
+// of a unit = (KV head, frame, row tile) must run on one XCD; which one does not matter, and it changes: a
+// stream's ids start at another XCD once the process has used more streams or a graph.  The hardware deals
+// workgroup ids to the XCDs in turn (id mod number of XCDs; read off the device once, and checked again by
+// every unit of every launch, see arrival_of).  Unit u therefore takes the ids of one residue x:
 //     x = u / units_per_xcd,  j = u % units_per_xcd,  id = x + ((j * nsplit + split) << xcd_shift)
 // with units_per_xcd = ceil(units / 2^xcd_shift); consecutive units (the same KV head, whose K/V
 // that L2 then holds once) share an XCD.  Ids whose unit does not exist are spare and return.
@@ -30,6 +31,12 @@ VS_HD int div_small(int x, int d, float inv_d) {
     if ((qd + 1) * d <= x) ++qd;
     return qd;
 }
+
+// What a workgroup on XCD `xcc` adds to its unit's arrival word: itself, its XCD and the square of that, each
+// with room for 32 workgroups and 16 XCDs.  With n workgroups in, the word is n * arrival_of(x) if and only if all of
+// them ran on XCD x (n numbers whose sum is n x and whose squares' sum is n x^2 are all x).
+VS_HD unsigned arrival_of(unsigned xcc) { return 1u | xcc << 6 | (xcc * xcc) << 16; }
+VS_HD unsigned arrivals_in(unsigned word) { return word & 63u; }
 
 struct PrefillSlot {
     int unit;   // -1: a spare id

@@ -93,11 +93,10 @@ struct PrefillParams {
     unsigned* arrivals;       // [Hkv][frames][row tiles], kCounterStrideBytes apart, zero between launches
     int xcd_shift;            // log2 of the number of XCDs workgroup ids are dealt to in turn
     int units_per_xcd;
-    // the guard of that placement: the XCC_ID the probe read for every residue of the id (4 bits
-    // each, residue 0 lowest), and the word in pinned host memory that a workgroup finding itself
-    // on another XCD sets (the host looks at it before every launch)
-    unsigned long long xcc_of_residue;
+    // the guard of that placement: the word in pinned host memory that is set when the workgroups of a unit were not
+    // all on one XCD (the host looks at it before every launch)
     unsigned* misplaced;
+    unsigned long long lie;   // tests (see XcdPlacement)
     // merge shared by a unit's workgroups (0: the last one to arrive merges alone), and how often a
     // waiting workgroup looks at the counter before it gives up
     int share_merge;
@@ -261,13 +260,6 @@ void prefill_mfma_kernel(PrefillParams p) {
         const PrefillSlot at = prefill_slot_of_id(blockIdx.x, p.n_row_tiles * p.F * Hkv, p.units_per_xcd, nsplit,
                                                   inv_nsplit, p.xcd_shift);
         if (at.unit < 0) return;  // spare ids
-        // Guard: is this workgroup on the XCD that ids of its residue were seen on when the
-        // device was probed?  If not, the splits of its unit may not share an L2, and the merge
-        // below cannot be trusted: say so where the host sees it before its next launch.
-        unsigned xcc;
-        asm volatile("s_getreg_b32 %0, hwreg(HW_REG_XCC_ID)" : "=s"(xcc));
-        if ((xcc & 15u) != (unsigned)((p.xcc_of_residue >> (4 * at.xcd)) & 15u) && threadIdx.x == 0)
-            __hip_atomic_store(p.misplaced, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
         const int unit = at.unit;
         split = at.split;
         g = div_small(unit, p.n_row_tiles * p.F, p.inv_frame_tiles);
@@ -795,25 +787,23 @@ void prefill_mfma_kernel(PrefillParams p) {
         // of the unit run on this XCD).  Once the stores of all its wavefronts have been
         // acknowledged the workgroup counts itself in.  Then either the workgroups of the unit
         // share the merge (below), or the one that finds all others counted reads their partials
-        // back from L2 and writes the unit's output rows alone, and nobody waits for anybody.
+        // back from L2 and writes the unit's output rows alone (the others wait all the same: that is how a
+        // unit whose workgroups never meet is noticed).
         // Either way the sums run over the splits in index order and take a workgroup's own part
         // rounded as stored, so the result does not depend on which workgroup comes last, and
         // equals what prefill_combine_kernel computes. ----
+        const unsigned mine = own_arrival(split, (unsigned)p.lie);
         __builtin_amdgcn_s_waitcnt(0x0F70);  // vmcnt(0)
         __syncthreads();                     // also: the exchange area is free again
         unsigned* const box = reinterpret_cast<unsigned*>(dyn_smem);
         unsigned* const counter = p.arrivals + (int64_t)(gf * p.n_row_tiles + rt) * (kCounterStrideBytes / 4);
-        // (an increment that wraps: 0, 1, .., nsplit - 1, 0: the counter is back at zero with the last
-        // arrival, for the next launch and as the sign that all have arrived)
-        if (tid == 0) *box = __builtin_amdgcn_atomic_inc32(counter, (unsigned)(nsplit - 1), __ATOMIC_RELAXED, "workgroup");
-        __syncthreads();
-        const unsigned before = *box;
+        const unsigned in = count_in(box, counter, nsplit, mine, p.max_looks, p.misplaced, tid);
+        if (!in) return;
         if (p.share_merge) {
             // ---- The merge shared by the workgroups of the unit.  Those that are not the last to
-            // arrive look at the counter again, with read-modify-writes (adding a zero the compiler
-            // cannot see), which are executed at the L2 like the count itself and never served by the
-            // compute unit's cache, a bounded number of times: a zero says that the last one has
-            // arrived.  Whoever knows that, knows that every partial result of the unit is complete
+            // arrive look at the counter again, with read-modify-writes, which are executed at the L2 like the count
+            // itself and never served by the compute unit's cache, a bounded number of times.
+            // Whoever knows that all have arrived, knows that every partial result of the unit is complete
             // in this L2, and merges its own pieces: of the unit's 4 row groups x 8 pieces of 16
             // features per lane, wavefront w of split j takes those from (w nsplit + j) * ppw on, ppw = 1,
             // 2 or 4, so that the work is spread over the unit's compute units and (up to 8 splits) one
@@ -823,22 +813,6 @@ void prefill_mfma_kernel(PrefillParams p) {
             // running at once: the device is shared, or part of it is masked) reports through the
             // same host word as a misplaced one and leaves its pieces unmerged: the next call
             // returns VS_ERR_PLACEMENT and the library merges with the second kernel from then on. ----
-            if (before + 1 != (unsigned)nsplit) {
-                unsigned zero = 0;
-                asm volatile("" : "+s"(zero));
-                unsigned* const seen_box = box + 1;
-                if (tid == 0) {
-                    unsigned ok = 0;
-                    for (int n = 0; n < p.max_looks && !ok; ++n) {
-                        ok = __hip_atomic_fetch_add(counter, zero, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP) == 0u;
-                        if (!ok) __builtin_amdgcn_s_sleep(2);
-                    }
-                    *seen_box = ok;
-                    if (!ok) __hip_atomic_store(p.misplaced, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
-                }
-                __syncthreads();
-                if (!*seen_box) return;
-            }
             const int ppw = merge_pieces_per_wave(NKG, nsplit);
             const int first = (w * nsplit + split) * ppw;            // of the unit's 4 x 8 pieces: dealt to the workgroups in turn
             if (first >= 32) return;
@@ -941,7 +915,7 @@ void prefill_mfma_kernel(PrefillParams p) {
             }
             return;
         }
-        if (before + 1 == (unsigned)nsplit) {
+        if (in == 2u) {
             // the rows this wavefront has closed: row group kg of its 64 rows, or both
 #pragma unroll
             for (int r = 0; r < 2; ++r) {
@@ -1077,13 +1051,12 @@ struct Plan {
 // probed, or after a workgroup has reported that it ran elsewhere): then the splits are merged
 // by the second kernel.
 int g_xcd_shift[16] = {-1, -1, -1, -1, -1, -1, -1, -1, -1, -1, -1, -1, -1, -1, -1, -1};
-unsigned long long g_xcc_of_residue[16] = {};  // XCC_ID read for ids of residue r: bits 4r .. 4r+3
 // One word of pinned host memory per device (allocated by the probe, kept until the process
-// ends), set by any workgroup of an in-kernel-merge launch that finds itself on an XCD other
-// than the probed one.
+// ends), set by a workgroup of an in-kernel-merge launch whose unit was not on one XCD, or not
+// running all at once.
 unsigned* g_misplaced[16] = {};      // as the host addresses it
 unsigned* g_misplaced_dev[16] = {};  // as the kernels address it
-// tests: 3 = the probe-derived table is handed to the kernels rotated by one XCD; 4 = workgroups that
+// tests: 3 = every other workgroup of a unit gives a neighbouring XCD as its own; 4 = workgroups that
 // wait for the last of their unit do not look at all and give up
 int g_tune_guard_test = 0;
 
@@ -1243,8 +1216,6 @@ hipError_t probe_xcd_mapping(void* scratch, hipStream_t st) {
         for (int i = 0; i < n && ok; ++i)
             for (int j = 0; j < i && ok; ++j) ok = ids[i] != ids[j];                // n different XCDs
         if (ok) {
-            unsigned long long table = 0;
-            for (int i = 0; i < n; ++i) table |= (unsigned long long)(ids[i] & 15u) << (4 * i);
             if (!g_misplaced[dev]) {
                 void* flag = nullptr;
                 void* flag_dev = nullptr;
@@ -1254,7 +1225,6 @@ hipError_t probe_xcd_mapping(void* scratch, hipStream_t st) {
                 g_misplaced[dev] = static_cast<unsigned*>(flag);
                 g_misplaced_dev[dev] = static_cast<unsigned*>(flag_dev);
             }
-            g_xcc_of_residue[dev] = table;
             g_xcd_shift[dev] = shift;
             break;
         }
@@ -1275,9 +1245,7 @@ void prefill_guard_test_mode(int on) { g_tune_guard_test = on; }
 bool xcd_placement_of_device(int dev, XcdPlacement* out) {
     if (dev < 0 || dev >= 16 || g_xcd_shift[dev] < 0 || !g_misplaced_dev[dev] || g_tune_prefill_merge == 2) return false;
     out->xcd_shift = g_xcd_shift[dev];
-    out->xcc_of_residue = g_xcc_of_residue[dev];
-    if (g_tune_guard_test == 3 && out->xcd_shift > 0)  // (as for the prefill: the table rotated by one XCD)
-        out->xcc_of_residue = (out->xcc_of_residue >> 4) | ((out->xcc_of_residue & 15ull) << (4 * ((1 << out->xcd_shift) - 1)));
+    out->lie = g_tune_guard_test == 3 ? 1u : 0u;
     out->misplaced = g_misplaced_dev[dev];
     out->max_looks = g_tune_guard_test == 4 ? 0 : 8192;
     return true;
@@ -1350,7 +1318,7 @@ hipError_t launch_prefill_mfma(const vs_shape& s, const void* kc, const void* vc
     p.inv_nsplit = 1.0f / (float)pl.nsplit;
     p.arrivals = nullptr;
     p.xcd_shift = p.units_per_xcd = 0;
-    p.xcc_of_residue = 0;
+    p.lie = 0;
     p.misplaced = nullptr;
     p.share_merge = 0;
     p.max_looks = 0;
@@ -1363,14 +1331,10 @@ hipError_t launch_prefill_mfma(const vs_shape& s, const void* kc, const void* vc
         p.arrivals = (unsigned*)counters;
         p.xcd_shift = g_xcd_shift[dev];
         p.units_per_xcd = prefill_units_per_xcd(pl.n_row_tiles * s.n_kv_heads * n_frames, p.xcd_shift);
-        p.xcc_of_residue = g_xcc_of_residue[dev];
-        if (g_tune_guard_test == 3 && p.xcd_shift > 0)  // entry r names the XCD of residue r + 1: every workgroup is "misplaced"
-            p.xcc_of_residue = (p.xcc_of_residue >> 4) | ((p.xcc_of_residue & 15ull) << (4 * ((1 << p.xcd_shift) - 1)));
+        p.lie = g_tune_guard_test == 3 ? 1u : 0u;
         p.misplaced = g_misplaced_dev[dev];
-        if (g_tune_prefill_merge != 1) {
-            p.share_merge = 1;
-            p.max_looks = g_tune_guard_test == 4 ? 0 : 8192;  // ~0.3 us a look: some milliseconds at most
-        }
+        p.share_merge = g_tune_prefill_merge != 1;
+        p.max_looks = g_tune_guard_test == 4 ? 0 : 8192;  // ~0.3 us a look: some milliseconds at most
     }
     const int64_t slots = (int64_t)pl.nsplit * s.n_kv_heads * n_frames * pl.m_pad;
     p.part_ml = (float*)workspace;

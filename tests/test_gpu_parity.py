@@ -387,8 +387,8 @@ def test_runs_of_frames_merge_inside_the_kernel_equals_the_second_kernel(F, T, L
 
 
 def test_prefill_placement_guard_reports_and_falls_back():
-    """Every workgroup of an in-kernel-merge launch checks that it runs on the XCD that the probe
-    saw for its id.  With the probed order handed over rotated by one (tuning value 3) all of them
+    """Every unit of an in-kernel-merge launch checks that its workgroups ran on one XCD.  With every other
+    workgroup giving a neighbouring XCD as its own (tuning value 3) the units
     report themselves misplaced: the launch itself is still right (the real placement is
     unchanged), the next call launches nothing and returns VS_ERR_PLACEMENT, the calls after it merge
     with the second kernel and give the same bits, and a new vs_workspace_init probes again and
@@ -412,6 +412,63 @@ def test_prefill_placement_guard_reports_and_falls_back():
     again, _, _ = run_prefill(s, hk, hv, L, q, kf, vf, ws=ws2)
     assert same_bits(again, good.cpu())
     run_prefill(s, hk, hv, L, q, kf, vf, ws=ws2)                      # and nothing is reported this time
+
+
+def _captured(call):
+    """The call captured into a graph, and how many nodes that has."""
+    import os
+    graph = torch.cuda.CUDAGraph(keep_graph=True)
+    with torch.cuda.graph(graph):
+        call()
+    hip = ctypes.CDLL(os.path.join(os.path.dirname(torch.__file__), "lib", "libamdhip64.so"))
+    count = ctypes.c_size_t(0)
+    assert hip.hipGraphGetNodes(ctypes.c_void_p(graph.raw_cuda_graph()), None, ctypes.byref(count)) == 0
+    graph.instantiate()
+    return graph, count.value
+
+
+def test_prefill_in_a_program_with_several_streams_and_graphs():
+    """Once a process has used several streams or captured a graph, the device deals the ids of a stream from another
+    XCD on.  Ids of one residue still share one, so the splits are merged inside the launch as before (one node
+    per call), nothing is reported, and the bits are the same: eagerly, on other streams, and on every replay."""
+    s, L, T = QW, 1500, 170
+    sh = vs_shape(s)
+    hk, hv = cache_rows(77, s, L, 0.5)
+    q, kf, vf = (t.to(DEV) for t in frame_inputs(77, s, T, 0.5, q_gain=4))
+    cache = vs.Cache(hk.to(DEV), hv.to(DEV), L)
+    wss = [workspace(s, T, L, 0) for _ in range(5)]
+    outs = [torch.empty_like(q) for _ in wss]
+
+    def step(i):
+        vs.frame_prefill_attn(sh, cache, q, kf, vf, outs[i], wss[i])
+
+    step(0)
+    torch.cuda.synchronize()
+    good = outs[0].clone()
+
+    def check(used):
+        torch.cuda.synchronize()
+        for i in used:
+            assert torch.equal(outs[i].view(torch.int16), good.view(torch.int16))
+            outs[i].fill_(float("nan"))
+
+    streams = [torch.cuda.Stream() for _ in range(3)]
+    for _ in range(4):
+        for i, st in enumerate(streams):
+            with torch.cuda.stream(st):
+                step(1 + i)
+            st.synchronize()
+        check((1, 2, 3))
+        step(0)
+        check((0,))
+    graph, nodes = _captured(lambda: step(4))
+    assert nodes == 1
+    for _ in range(4):
+        graph.replay()
+        check((4,))
+        step(0)
+        check((0,))
+    assert _captured(lambda: step(4))[1] == 1  # (a report would have sent later calls to the second kernel)
 
 
 def test_prefill_shared_merge_gives_up_waiting_and_reports():
@@ -573,50 +630,35 @@ def test_decode_few_rows(hq, hkv, lens0, gain):
 
 
 def test_decode_few_rows_replayed():
-    """The arrival counters are back at zero after every launch: a captured chain of steps of different plans over
-    one workspace gives the same bits on every replay, with eager work of the program in between.  In a process of
-    its own: once a process has used a second stream (capture does), the device may deal workgroups of the first
-    one from another XCD on, which the prefill reports as a misplaced launch."""
-    import os
-    import subprocess
-    import sys
-    root = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
-    code = """
-import ctypes, sys
-sys.path.insert(0, %r)
-import torch
-import paper_2503_09387_amd as vs
-dev, cap = "cuda:0", 3200
-rn = lambda *dims: torch.randn(dims, generator=g, device=dev, dtype=torch.bfloat16)
-g = torch.Generator(device=dev).manual_seed(5)
-sh = vs.Shape.make(28, 4, 128, "bf16")
-k, v, q = rn(16, cap, 4, 128), rn(16, cap, 4, 128), rn(16, 28, 128)
-ws = vs.make_workspace(sh, 0, cap, 16, dev)
-plans = [[700], [3000] * 4, [100] * 16, [700] * 16, [900]]
-outs = [torch.empty_like(q[:len(p)]) for p in plans]
-def steps():
-    st = vs.current_stream_handle()
-    for p, out in zip(plans, outs):
-        n = len(p)
-        vs.decode_attn(sh, k[:n], v[:n], (ctypes.c_int32 * n)(*p), q[:n], None, None, out, ws, stream=st)
-steps()
-want = [o.clone() for o in outs]
-torch.cuda.synchronize()
-graph = torch.cuda.CUDAGraph()
-with torch.cuda.graph(graph):
+    """The arrival counters are back where they started after every launch: a captured chain of steps of different
+    plans over one workspace gives the same bits on every replay, with eager work of the program in between."""
+    cap = 3200
+    g = torch.Generator(device=DEV).manual_seed(5)
+    k, v, q = (torch.randn(d, generator=g, device=DEV, dtype=torch.bfloat16) for d in ((16, cap, 4, 128), (16, cap, 4, 128), (16, 28, 128)))
+    sh = vs_shape(QW)
+    ws = vs.make_workspace(sh, 0, cap, 16, DEV)
+    plans = [[700], [3000] * 4, [100] * 16, [700] * 16, [900]]
+    outs = [torch.empty_like(q[:len(p)]) for p in plans]
+
+    def steps():
+        st = vs.current_stream_handle()
+        for p, out in zip(plans, outs):
+            n = len(p)
+            vs.decode_attn(sh, k[:n], v[:n], lens_array(p), q[:n], None, None, out, ws, stream=st)
+
     steps()
-for _ in range(8):
-    for o in outs:
-        o.fill_(float("nan"))
-    graph.replay()
     torch.cuda.synchronize()
-    assert all(torch.equal(o.view(torch.int16), w.view(torch.int16)) for o, w in zip(outs, want))
-    steps()
-torch.cuda.synchronize()
-print("ok")
-""" % root
-    r = subprocess.run([sys.executable, "-c", code], capture_output=True, text=True, timeout=100)
-    assert r.returncode == 0 and r.stdout.strip().endswith("ok"), r.stdout + r.stderr
+    want = [o.clone() for o in outs]
+    graph, nodes = _captured(steps)
+    assert nodes == len(plans)
+    for _ in range(8):
+        for o in outs:
+            o.fill_(float("nan"))
+        graph.replay()
+        torch.cuda.synchronize()
+        assert all(torch.equal(o.view(torch.int16), w.view(torch.int16)) for o, w in zip(outs, want))
+        steps()
+    torch.cuda.synchronize()
 
 
 @pytest.mark.parametrize("left", ["zeros", "ones", "sums", "other calls"])
@@ -663,41 +705,28 @@ def test_decode_over_a_control_block_that_holds_something_else(left):
         assert torch.equal(step().view(torch.int16), fresh.view(torch.int16))
 
 
-def test_decode_static_counts_nothing_in_its_array():
+@pytest.mark.parametrize("n,rows,shared_out", [(1, 700, True), (4, 100, False), (4, 700, True)])
+def test_decode_static_counts_nothing_in_its_array(n, rows, shared_out):
     """The library's own array cannot be cleared, so a call over it may not rely on what an earlier one left there:
     where rows are shared out, a second launch adds the shares (two nodes of a captured step, one with a
     workspace); where they are not, one launch does."""
-    import os
-    import subprocess
-    import sys
-    root = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
-    code = """
-import ctypes, os, sys
-sys.path.insert(0, %r)
-import torch
-import paper_2503_09387_amd as vs
-hip = ctypes.CDLL(os.path.join(os.path.dirname(torch.__file__), "lib", "libamdhip64.so"))
-dev = "cuda:0"
-sh = vs.Shape.make(28, 4, 128, "bf16")
-k, v, q = (torch.randn(d, device=dev).to(torch.bfloat16) for d in ((4, 800, 4, 128), (4, 800, 4, 128), (4, 28, 128)))
-ws = vs.make_workspace(sh, 0, 800, 4, dev)
-def launches(n, rows, static):
-    out = torch.empty_like(q[:n])
-    lens = (ctypes.c_int32 * n)(*[rows] * n)
-    call = (lambda: vs.decode_attn_static(sh, k[:n], v[:n], lens, q[:n], None, None, out)) if static else \
-        (lambda: vs.decode_attn(sh, k[:n], v[:n], lens, q[:n], None, None, out, ws))
-    call()
-    torch.cuda.synchronize()
-    graph = torch.cuda.CUDAGraph(keep_graph=True)
-    with torch.cuda.graph(graph):
+    sh = vs_shape(QW)
+    k, v, q = (torch.randn(d, device=DEV).to(torch.bfloat16) for d in ((n, 800, 4, 128), (n, 800, 4, 128), (n, 28, 128)))
+    ws = vs.make_workspace(sh, 0, 800, n, DEV)
+    out = torch.empty_like(q)
+    own = lambda: vs.decode_attn_static(sh, k, v, lens_array([rows] * n), q, None, None, out)
+    given = lambda: vs.decode_attn(sh, k, v, lens_array([rows] * n), q, None, None, out, ws)
+    for call, nodes in ((given, 1), (own, 2 if shared_out else 1)):
         call()
-    count = ctypes.c_size_t(0)
-    assert hip.hipGraphGetNodes(ctypes.c_void_p(graph.raw_cuda_graph()), None, ctypes.byref(count)) == 0
-    return count.value
-print([launches(n, rows, static) for n, rows in ((1, 700), (4, 100), (4, 700)) for static in (False, True)])
-""" % root
-    r = subprocess.run([sys.executable, "-c", code], capture_output=True, text=True, timeout=100)
-    assert r.returncode == 0 and r.stdout.strip().endswith("[1, 2, 1, 1, 1, 2]"), r.stdout + r.stderr
+        torch.cuda.synchronize()
+        want = out.clone()
+        graph, count = _captured(call)
+        assert count == nodes
+        for _ in range(3):
+            out.fill_(float("nan"))
+            graph.replay()
+            torch.cuda.synchronize()
+            assert torch.equal(out.view(torch.int16), want.view(torch.int16))
 
 
 @pytest.mark.parametrize("hq,hkv", [(6, 3), (12, 6), (5, 5), (16, 2), (8, 1), (24, 8)])
