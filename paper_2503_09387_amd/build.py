@@ -67,10 +67,9 @@ def check_prefill_listing(listing: str) -> None:
             continue
         if t.startswith(".LBB"):
             label_line = ln
-        if kern is None or not t or t[0] in ";.":
-            continue
-        if t.startswith("s_endpgm"):
+        if t.startswith(".Lfunc_end"):  # (a kernel that returns early has several s_endpgm)
             kern = None
+        if kern is None or not t or t[0] in ";.":
             continue
         for m in re.finditer(r"\ba(\d+)\b|\ba\[(\d+):(\d+)\]", t):
             if int(m.group(1) or m.group(2)) < 192:
@@ -94,10 +93,51 @@ def check_prefill_listing(listing: str) -> None:
                            "blocks:\n" + "\n".join(f"  line {ln}: {t}" for ln, t, _ in bad[:20]))
 
 
+LINEAR_KERNELS = 12  # 3 row classes x 4 block widths
+
+
+def check_linear_listing(listing: str) -> None:
+    """The dense layers' kernel issues its matrix instructions as assembly, so the compiler does not know that a sum
+    may not be touched until some cycles after the last of them.  `listing` is the device assembly of vs_linear.hip:
+    between the first and the last matrix instruction of a kernel, in the order of the listing, no
+    compiler-generated instruction may touch an accumulation register (a copied sum), and none may go to
+    scratch memory."""
+    import re
+    kernels, kern, in_asm, touched = {}, None, False, []
+    bad = []
+    for ln, raw in enumerate(listing.split("\n"), 1):
+        t = raw.strip()
+        m = re.match(r"^(_Z\w*linear_kernelI\w*):", t)
+        if m:
+            kern, touched = m.group(1), []
+            kernels[kern] = 0
+        if t.startswith(";;#ASMSTART"):
+            in_asm = True
+        elif t.startswith(";;#ASMEND"):
+            in_asm = False
+        elif t.startswith(".Lfunc_end"):  # (a kernel that returns early has several s_endpgm)
+            kern = None
+        elif kern is None or not t or t[0] in ";.":
+            continue
+        elif in_asm:
+            if t.startswith("v_mfma"):
+                bad += touched  # (what lies between this one and the one before)
+                touched = []
+                kernels[kern] += 1
+        elif kernels[kern] and (re.search(r"\ba\d+\b|\ba\[\d+:\d+\]", t) or t.startswith("scratch_")):
+            touched.append((ln, t))
+    if len(kernels) != LINEAR_KERNELS or not all(kernels.values()):
+        raise RuntimeError(f"dense layers: the listing shows {len(kernels)} kernels with {sorted(kernels.values())} matrix "
+                           f"instructions; {LINEAR_KERNELS} with some were expected")
+    if bad:
+        raise RuntimeError("dense layers: the compiler touches sums between the matrix instructions:\n" +
+                           "\n".join(f"  line {ln}: {t}" for ln, t in bad[:20]))
+
+
 def build(verbose: bool = False) -> str:
-    """Compiles the library and checks the prefill kernel's listing from that same compile (the
-    compiler keeps its intermediate files, in a scratch directory); the library is put in place only
-    if the check passes."""
+    """Compiles the library and checks the prefill kernel's and the dense layers' listings from that same compile
+    (the compiler keeps its intermediate files, in a scratch directory); the library is put in place
+    only if the checks pass."""
     import glob as _glob
     import shutil
     import tempfile
@@ -108,10 +148,11 @@ def build(verbose: bool = False) -> str:
         if verbose:
             print(" ".join(cmd))
         subprocess.run(cmd, check=True, cwd=tmp)
-        found = _glob.glob(os.path.join(tmp, "vs_prefill_mfma*gfx950*.s"))
-        if len(found) != 1:
-            raise RuntimeError(f"prefill kernel: expected one device listing of vs_prefill_mfma.hip, found {found}")
-        check_prefill_listing(open(found[0]).read())
+        for source, check in (("vs_prefill_mfma", check_prefill_listing), ("vs_linear", check_linear_listing)):
+            found = _glob.glob(os.path.join(tmp, source + "*gfx950*.s"))
+            if len(found) != 1:
+                raise RuntimeError(f"expected one device listing of {source}.hip, found {found}")
+            check(open(found[0]).read())
         shutil.copyfile(out, LIB)
         os.chmod(LIB, 0o755)
     return LIB

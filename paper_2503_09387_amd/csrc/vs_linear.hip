@@ -80,9 +80,6 @@ struct LinParams {
     float inv_ksplit;
 };
 
-// s_waitcnt vmcnt(n) only (gfx9 encoding: vmcnt in bits 3:0 and 15:14; expcnt, lgkmcnt left at "no wait")
-#define VS_WAIT_VM(n) __builtin_amdgcn_s_waitcnt(((n) & 15) | (((n) >> 4) << 14) | 0x0F70)
-
 __device__ __forceinline__ float silu_mul(float g, float u) { return g / (1.0f + __expf(-g)) * u; }
 
 // The finished sums of a block of rows leave through LDS: the accumulators (lane (i16, kq) holds

@@ -352,6 +352,28 @@ def test_prefill_workgroup_placement_map(tmp_path):
     assert r.returncode == 0 and r.stdout.startswith("ok"), r.stdout + r.stderr
 
 
+def test_build_notices_a_sum_touched_between_matrix_instructions():
+    """check_linear_listing on a listing of the expected shape, and with one instruction planted in it."""
+    import importlib.util
+    spec = importlib.util.spec_from_file_location("vs_build", os.path.join(ROOT, "paper_2503_09387_amd", "build.py"))
+    build = importlib.util.module_from_spec(spec)
+    spec.loader.exec_module(build)
+    mfma = "\t;;#ASMSTART\n\tv_mfma_f32_16x16x32_bf16 a[0:3], v[0:3], v[4:7], a[0:3]\n\t;;#ASMEND\n"
+
+    def listing(before="", between="", behind="", n=build.LINEAR_KERNELS):
+        return "".join(f"_ZN2vs13linear_kernelILi{i}EEvNS_9LinParamsE:\n{before}{mfma}\tds_read_b128 v[0:3], v9\n\ts_endpgm\n{between}{mfma}"
+                       f"\ts_endpgm\n{behind}.Lfunc_end{i}:\n" for i in range(n))
+
+    copy = "\tv_accvgpr_read_b32 v1, a2\n"
+    build.check_linear_listing(listing())
+    build.check_linear_listing(listing(before="\tv_accvgpr_write_b32 a0, 0\n", behind=copy))
+    for planted in (copy, "\tv_accvgpr_mov_b32 a7, a3\n", "\tscratch_store_dword off, v3, off\n"):
+        with pytest.raises(RuntimeError, match="touches sums"):
+            build.check_linear_listing(listing(between=planted))
+    with pytest.raises(RuntimeError, match="were expected"):
+        build.check_linear_listing(listing(n=11))
+
+
 def test_bench_refuses_more_than_one_gpu():
     """bench.py --gpus N with N above 1 exits with a message that says so (nothing here uses a second GPU)."""
     import subprocess
