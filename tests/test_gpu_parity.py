@@ -288,8 +288,10 @@ def test_cfg5_dense_and_compact_cache_same_frame():
 # ---------------------------------------------------------------------------- prefill edges
 @pytest.mark.parametrize("L,T,gain", [(0, 1, 1), (0, 5, 1), (1, 1, 1), (63, 2, 1), (64, 64, 1), (65, 170, 1),
                                       (200, 170, 8), (263, 170, 1), (1000, 19, 8), (4551, 170, 8), (130, 512, 1)])
-def test_prefill_bf16_shapes_and_peaked_softmax(L, T, gain):
+@pytest.mark.parametrize("kv_groups", [0, 1, 2])  # 0: as dispatched (few keys: the kernel that splits nothing); else the other kernel
+def test_prefill_bf16_shapes_and_peaked_softmax(L, T, gain, kv_groups):
     s = QW
+    vs.set_tuning(vs.TUNE_PREFILL_KV_GROUPS, kv_groups)
     hk, hv = cache_rows(11, s, max(L, 1), 0.5)
     q, kf, vf = frame_inputs(11, s, T, 0.5, frame=L, layer=T % 7, q_gain=gain)
     out, _, _ = run_prefill(s, hk, hv, L, q, kf, vf)
@@ -299,8 +301,10 @@ def test_prefill_bf16_shapes_and_peaked_softmax(L, T, gain):
 
 
 @pytest.mark.parametrize("hq,hkv", [(8, 8), (8, 1), (12, 4), (16, 2)])
-def test_prefill_other_head_groupings(hq, hkv):
+@pytest.mark.parametrize("kv_groups", [0, 1, 2])
+def test_prefill_other_head_groupings(hq, hkv, kv_groups):
     s = AttnShape(hq, hkv, 128, "bf16")
+    vs.set_tuning(vs.TUNE_PREFILL_KV_GROUPS, kv_groups)
     L, T = 150, 70
     hk, hv = cache_rows(12, s, L, 0.5)
     q, kf, vf = frame_inputs(12, s, T, 0.5, q_gain=4)
@@ -327,7 +331,8 @@ def test_prefill_result_does_not_depend_on_the_split(kv_groups):
 
 
 @pytest.mark.parametrize("L,T,splits", [(4424, 170, 0), (1500, 170, 0), (1500, 170, 3), (3000, 300, 8), (700, 40, 2),
-                                          (200, 170, 0), (264, 170, 3), (100, 20, 2),
+                                          # (300 tokens: more groups of 32 rows than compute units, so not the kernel that splits nothing)
+                                          (100, 300, 0), (264, 170, 3), (100, 20, 2),
                                           # more than 8 splits (questions of a few tokens; several rounds of workgroups)
                                           (4552, 16, 0), (4552, 64, 0), (1500, 170, 12), (3000, 170, 32), (2100, 30, 9)])
 def test_prefill_merge_inside_the_kernel_equals_the_second_kernel(L, T, splits):
@@ -335,7 +340,7 @@ def test_prefill_merge_inside_the_kernel_equals_the_second_kernel(L, T, splits):
     once the last of them has arrived (the library's choice) or by that last one alone, or by a
     second kernel: the same sums in the same order, so the same bits; also on repeated calls
     through one workspace (the arrival counters return to zero, launch numbers move on) and with
-    the three ways taking turns."""
+    the three ways taking turns.  Every case is split: with the second kernel a call is two launches."""
     s = QW
     hk, hv = cache_rows(31, s, L, 0.5)
     q, kf, vf = frame_inputs(31, s, T, 0.5, q_gain=4)
@@ -345,6 +350,9 @@ def test_prefill_merge_inside_the_kernel_equals_the_second_kernel(L, T, splits):
     vs.set_tuning(vs.TUNE_PREFILL_MERGE, 2)
     two_kernels, _, _ = run_prefill(s, hk, hv, L, q, kf, vf, ws=ws)
     check_close(two_kernels, ref, "bf16", f"second-kernel merge L={L} T={T} splits={splits}")
+    dq, dk, dv, dcache = q.to(DEV), kf.to(DEV), vf.to(DEV), vs.Cache(hk.to(DEV), hv.to(DEV), L)
+    spare = torch.empty_like(dq)
+    assert _captured(lambda: vs.frame_prefill_attn(vs_shape(s), dcache, dq, dk, dv, spare, ws))[1] == 2
     for mode in (0, 0, 0, 1, 0, 1, 2, 0):
         vs.set_tuning(vs.TUNE_PREFILL_MERGE, mode)
         inside, _, _ = run_prefill(s, hk, hv, L, q, kf, vf, ws=ws)
@@ -498,14 +506,15 @@ def test_prefill_shared_merge_gives_up_waiting_and_reports():
         assert same_bits(again, good.cpu())
 
 
-@pytest.mark.parametrize("L", [130, 1500])
+@pytest.mark.parametrize("L,kv_groups", [(130, 0), (130, 1), (130, 2), (1500, 0), (1500, 1)])
 @pytest.mark.parametrize("mode", ["all_low", "all_high", "rising", "falling", "jump"])
-def test_prefill_extreme_score_ranges(mode, L):
+def test_prefill_extreme_score_ranges(mode, L, kv_groups):
     """Scaled scores far from 0 (in log2 units: around -400, around +400, climbing or falling by
     400 along the keys, or jumping by 60 in the middle): the speculative softmax reference has to
     be dropped and rebuilt, at the first sub-block and later ones, with the accumulators rescaled."""
     s = QW
     T = 170
+    vs.set_tuning(vs.TUNE_PREFILL_KV_GROUPS, kv_groups)
     hk, hv = cache_rows(21, s, L, 0.5)
     q, kf, vf = frame_inputs(21, s, T, 0.5)
     n = L + T
@@ -553,6 +562,37 @@ def test_fp32_prefill_on_both_sides_of_the_chip(dim, hq, hkv, L, T):
     q, kf, vf = frame_inputs(43, s, T, 1.0)
     out, _, _ = run_prefill(s, hk, hv, L, q, kf, vf)
     check_close(out, oracle_prefill_rows(s, q, hk, hv, L, kf, vf), "f32", f"fp32 {hq}/{hkv}/{dim} L={L} T={T}")
+
+
+@pytest.mark.parametrize("path,L", [("prefill", 100), ("prefill, general kernel", 100), ("prefill", 1500), ("fp32 prefill", 40),
+                                    ("decode", 100), ("decode", 700), ("decode", 9300), ("fp32 decode", 300)])
+def test_a_score_that_is_not_a_number_stays_in_its_row(path, L):
+    """A query row that holds a NaN comes out as NaN; every other row is what it is without it, to a rounding (the
+    softmax references of the rows of a wavefront may be refreshed at other tiles)."""
+    s = AttnShape(28, 4, 128, "f32" if "fp32" in path else "bf16")
+    sh, dt, T = vs_shape(s), torch_dtype(s.dtype), 1 if "decode" in path else 40
+    hk, hv = cache_rows(45, s, L, 0.5)
+    k, v = (torch.cat([t, torch.zeros_like(t[:1])]).to(DEV) for t in (hk, hv))
+    q, kf, vf = (t.to(DEV) for t in frame_inputs(45, s, T, 0.5))
+    if "general" in path:
+        vs.set_tuning(vs.TUNE_PREFILL_KV_GROUPS, 1)
+    ws = workspace(s, T, L + 1, 1)
+    outs = []
+    for bad in (False, True):
+        qd = q.clone()
+        if bad:
+            qd[T // 2, 9, 17] = float("nan")
+        out = torch.zeros(q.shape, dtype=dt, device=DEV)
+        if "decode" in path:
+            vs.decode_attn(sh, k[None], v[None], lens_array([L]), qd, None, None, out, ws)
+        else:
+            vs.frame_prefill_attn(sh, vs.Cache(k, v, L), qd, kf, vf, out, ws)
+        torch.cuda.synchronize()
+        outs.append(out)
+    assert bool(torch.isfinite(outs[0]).all()) and bool(torch.isnan(outs[1][T // 2, 9]).all())
+    outs[1][T // 2, 9] = outs[0][T // 2, 9]
+    a, b = outs[0].float(), outs[1].float()
+    assert bool((a - b).abs().max() <= 2 ** -7 * a.abs().max())
 
 
 # ---------------------------------------------------------------------------- decode edges
