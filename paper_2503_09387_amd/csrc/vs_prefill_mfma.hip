@@ -1074,15 +1074,15 @@ constexpr int kPlanXcds = 8, kPlanCusPerXcd = 32;
 // per unit.  All splits of a unit run on one XCD, and units are dealt to XCDs evenly, so a launch goes
 // through the chip in one round iff units_per_xcd * nsplit workgroups fit an XCD (counting the chip as one pool
 // of 256 instead put 12 units with 20 splits, 40 workgroups, on each of six XCDs: a question of 37
-// tokens over 4552 rows took 29.4 us, 17.1 with 13 splits).  Among those plans the cheapest by a model
+// tokens over 4552 rows took 29.4 us, 17.4 .. 17.7 with 12 .. 16 splits, of which the model takes 16).  Among those plans the cheapest by a model
 // fitted to 8000 measured (shape, tokens, rows, plan) combinations: the steps of the longest lane (one tile
 // per key group), the tiles of the average lane, the second key group, the merge, and what a wavefront loads for it.
 // Over single runs of at least 9 tiles its choice is 0.8 % from the best measured plan on average and 7 % at worst;
 // against 256 compute units as one pool it gains 4 % on average and loses 2 % at worst.  With few tiles (runs of
 // frames at the start of a video, runs too long for the kernel that splits nothing) a launch is all fixed cost, which
-// the model puts too high for the merge: there as many workgroups per unit as there are tiles are best, as far as
-// they fit (2 frames of 170 tokens over 264 rows: 17.4 us unsplit, as the model has it, 13.2 so; over 451 plans
-// of up to 7 tiles 1.8 % from the best on average, the model 12.4 %), and at 8 tiles two key groups (2.6 %, the model 7.8 %).
+// the model puts too high for the merge.  Measured best there (503 shapes): two tiles in the two key groups of one
+// workgroup, up to 6 tiles a workgroup for each as far as they fit, 7 and 8 tiles two to a workgroup (2 frames of 170
+// tokens over 264 rows: 17.4 us unsplit, as the model has it, 13.2 so; 0.8 % from the best plan on average, the model 12 %).
 struct SplitPlan {
     int kvg, nsplit;
 };
@@ -1090,11 +1090,11 @@ SplitPlan make_split_plan(int units, int max_tiles) {
     const int per_xcd = (units + kPlanXcds - 1) / kPlanXcds;
     SplitPlan best{1, 1};
     if (max_tiles <= 8 && !g_tune_prefill_kv_groups) {
-        best.kvg = max_tiles == 8 ? 2 : 1;
-        const int fit = kPlanCusPerXcd * (best.kvg == 1 ? 2 : 1) / per_xcd, lanes = max_tiles / best.kvg;
-        best.nsplit = fit < lanes ? fit : lanes;
-        if (best.nsplit < 1) best.nsplit = 1;
-        return best;
+        const int one_round = kPlanCusPerXcd / per_xcd;  // splits with a compute unit each
+        if (max_tiles == 2) return SplitPlan{2, 1};
+        if (max_tiles == 8 || (max_tiles == 7 && one_round >= 4)) return SplitPlan{2, one_round < 4 ? one_round : 4};
+        const int fit = 2 * kPlanCusPerXcd / per_xcd;
+        return SplitPlan{1, fit < max_tiles ? fit : max_tiles};
     }
     float best_cost = 0.f;
     for (int kvg = 1; kvg <= 2; ++kvg) {
