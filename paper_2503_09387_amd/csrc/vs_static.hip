@@ -53,8 +53,8 @@ vs_status vs_decode_attn_static(const vs_shape* shape, int32_t n_streams, void* 
     // Every partial result that a merge reads is written earlier in the same call, and no arrival is counted
     // here: a count left over from two calls that overlapped could not be put right again, because nobody
     // can clear this array.  Where a stream's rows are shared out, the shares are added by a second
-    // launch (us per call without and with a workspace: one stream of 700 rows 8.1 and 7.9, of 3000 10.3 and 9.2,
-    // 16 of 1500 14.2 and 13.3; not shared out, 16 of 127, 5.0 both).
+    // launch (us per call without and with a workspace: one stream of 700 rows 7.9 and 7.7, of 3000 10.0 and 9.2,
+    // 16 of 1500 14.0 and 13.4; not shared out, 16 of 127, 5.0 both).
     return vs::decode_entry(shape, n_streams, k_slab, v_slab, capacity, lens, q, k_new, v_new, out, ptr,
                             kScratchBytes, hip_stream, true);
 }
