@@ -96,7 +96,7 @@ struct PrefillParams {
     // the guard of that placement: the word in pinned host memory that is set when the workgroups of a unit were not
     // all on one XCD (the host looks at it before every launch)
     unsigned* misplaced;
-    unsigned long long lie;   // tests (see XcdPlacement)
+    unsigned long long lie;   // tests (see XcdPlacement; 8 bytes: with 4 the arguments behind it move, and frames took 0.3 % longer)
     // merge shared by a unit's workgroups (0: the last one to arrive merges alone), and how often a
     // waiting workgroup looks at the counter before it gives up
     int share_merge;
