@@ -6,7 +6,7 @@ instruction from hand-scheduled blocks of inline assembly:
 
   a[0:127]    output accumulators O^T: accumulator i = 4*row_group + dim_block in a[16i:16i+15]
   a[128:191]  query fragments: fragment 8*row_group + step in a[128+4i : 128+4i+3]
-              (the compiler never sees these two as values; every block lists them as
+              (the compiler never sees these as values; every block lists them as
               clobbered, which keeps it from holding anything of its own there across a block)
   v[128:191]  raw scores S[parity][row_group], 16 registers each: sub-block n (32 keys) of a
               key group uses parity n & 1; hidden from the compiler like the accumulators (the
@@ -42,7 +42,18 @@ Scheduling rules the blocks obey (gfx950, one wavefront per SIMD):
     earlier than three instructions later; M0 is not used by the instruction after the one that
     writes it.
 
-Row sums are taken over the bf16-rounded probabilities (v_dot2c_f32_bf16 against (1, 1)), the
+The steps whose tiles hold cache rows only run in a loop that is one block (loop_block).  A wavefront alone on its
+SIMD issues an instruction every 5 cycles (an exponential takes 8), a matrix instruction keeps the matrix pipe for 32, and a
+dot product behind one waits for that pipe (16 cycles).  With sums by dot product, the instructions dealt out by
+number, and the loop left to the compiler (some 130 scalar instructions a step), a step of two sub-blocks took 4190 cycles,
+of which the 64 matrix instructions are 2070.  In the loop the sums are taken with two shifts or masks and two additions per pair,
+the ordinary instructions are dealt out by the cycles they take, and the first fragments of a sub-block are requested behind the
+last matrix instructions of the one before: 3010 cycles (six frames of 170 tokens over 4296 rows 74.0 -> 66.2 us a
+launch; not in proportion, because the clock falls from 2.3 to 1.9 .. 2.2 GHz as the matrix pipe fills).  Sums by
+four more matrix instructions (ones times P) came to the same time, and staging spread over both sub-blocks with a third slot for V
+gained nothing.
+
+Row sums are taken over the bf16-rounded probabilities (outside that loop with v_dot2c_f32_bf16 against (1, 1)), the
 values that enter P V, so that the output is an exact convex combination of V rows.
 """
 import os
@@ -97,11 +108,11 @@ def emit_stage_load(b, u, first, last):
     piece, plus u chunks of 4 rows), M0 the LDS destination: it is set for the first chunk of a
     tile and stepped by 1 KB right after each load, so that the write and the next use are never
     neighbours."""
-    which, base = ("k", 88) if u < 8 else ("v", 90)
+    which, base = ("k", "s[88:89]") if u < 8 else ("v", "s[90:91]")
     if first or u == 8:
         b.emit(f"s_mov_b32 m0, %[lds{which}]")
         b.emit("s_nop 0")
-    b.emit(f"global_load_lds_dwordx4 %[{which}o{u & 7}], s[{base}:{base + 1}]")
+    b.emit(f"global_load_lds_dwordx4 %[{which}o{u & 7}], {base}")
     if not last and u != 7:
         b.emit("s_add_u32 m0, m0, 0x400")
 
@@ -244,6 +255,154 @@ def step(p, qk, pv, sm, masked=False, loads=()):
     return b
 
 
+LO, HI = {"ksrc": "s88", "vsrc": "s90"}, {"ksrc": "s89", "vsrc": "s91"}
+
+
+def loop_block():
+    """The loop over plain steps: step s is the pair of sub-block steps 2s+1 and 2s+2 (odd, even).  The caller has seen to it
+    that every row has accumulated something and that tiles s, s+1 and s+2 are the group's and cache rows only.  An
+    iteration requests K of tile s+2 and V of tile s+1.  Operands: ka, va the read addresses, ksrc / vsrc the
+    addresses of this wave's share of the next K and V tile, ldsk / ldsv where it goes, tstep the bytes between tiles, left the
+    number of steps to go, l and sum the sums without and of the last sub-block.  why: 0 all steps done, 1 / 2: left behind the
+    odd / even sub-block of a step because its sums came out above 2^8 (or not a number); the caller redoes that
+    sub-block (S and P are as step() leaves them).  Leaving behind the even one or at the end, everything has moved
+    on to the next step."""
+    b = Block()
+    HIGH = ONES  # (the register holds 0xffff0000 here)
+    # (kind, index, half, parity of the sub-block step), a fragment for two matrix instructions each
+    seq = []
+    for p in (1, 0):
+        half = 1 - p
+        seq += [("k", kk, half, p) for kk in range(8)]
+        for t in range(2):
+            seq += [("v", 4 * t + db, half, p) for db in range(4)]
+    def frag_read(m):
+        kind, i, half, p = seq[m]
+        buf = FR_BASE + 4 * (m % NBUF)
+        if kind == "k":
+            return [f"ds_read_b128 {vr(buf, 4)}, %[ka{i}] offset:{half * 32 * ROW}"]
+        t, db = divmod(i, 4)
+        off = (db >> 1) * 128 + (32 * half + 16 * t) * ROW
+        return [f"ds_read_b64_tr_b16 {vr(buf, 2)}, %[va{db & 1}] offset:{off}",
+                f"ds_read_b64_tr_b16 {vr(buf + 2, 2)}, %[va{db & 1}] offset:{off + 8 * ROW}"]
+
+    def mfma(j, r):
+        kind, i, half, p = seq[j]
+        buf = vr(FR_BASE + 4 * (j % NBUF), 4)
+        if kind == "k":
+            d = vr(S(1 - p, r), 16)
+            return f"{MFMA} {d}, {buf}, {Q(r, i)}, {'0' if i == 0 else d}"
+        t, db = divmod(i, 4)
+        return f"{MFMA} {O(r, db)}, {buf}, {vr(P(1 - p, r, t), 4)}, {O(r, db)}"
+
+    def softmax(p):
+        """items as in step(), two at a time"""
+        out = []
+        for k0 in range(0, 16, 2):
+            its = []
+            for k in (k0, k0 + 1):
+                r, e = (k >> 2) & 1, 8 * (k >> 3) + 2 * (k & 3)
+                its.append((r, e, S(p, r) + e, TMP + 2 * (k - k0)))
+            for (r, e, src, tmp) in its:
+                out += [f"v_fma_f32 v{tmp}, v{src}, %[scale], -%[ms{r}]", f"v_fma_f32 v{tmp + 1}, v{src + 1}, %[scale], -%[ms{r}]"]
+            for (r, e, src, tmp) in its:
+                out += [f"v_exp_f32_e32 v{tmp}, v{tmp}", f"v_exp_f32_e32 v{tmp + 1}, v{tmp + 1}"]
+            for (r, e, src, tmp) in its:
+                t, j = divmod(e, 8)
+                out.append(f"v_cvt_pk_bf16_f32 v{P(p, r, t) + j // 2}, v{tmp}, v{tmp + 1}")
+            for (r, e, src, tmp) in its:
+                t, j = divmod(e, 8)
+                out += [f"v_lshlrev_b32_e32 v{tmp}, 16, v{P(p, r, t) + j // 2}", f"v_and_b32_e32 v{tmp + 1}, v{HIGH}, v{P(p, r, t) + j // 2}"]
+            for (r, e, src, tmp) in its:
+                out.append(f"v_add_f32_e32 %[sum{r}], v{tmp}, v{tmp + 1}" if e == 0 else f"v_add_f32_e32 %[sum{r}], %[sum{r}], v{tmp}")
+                if e:
+                    out.append(f"v_add_f32_e32 %[sum{r}], %[sum{r}], v{tmp + 1}")
+        return out
+
+    def cost(line):
+        return 8 if line.startswith("v_exp") else 5
+
+    first_cover = 8  # instructions of the softmax in front of a step's first matrix instruction: they cover the LDS's latency
+    b.emit(f"v_mov_b32_e32 v{HIGH}, 0xffff0000")
+    b.emit(".Lplain_step_%=:")
+    b.emit("s_waitcnt vmcnt(0)")
+    b.emit("s_barrier")
+    pending = []  # fragments requested and not waited for: (number, instructions)
+    issued = 0
+
+    def request():
+        nonlocal issued
+        lines = frag_read(issued)
+        pending.append((issued, len(lines)))
+        issued += 1
+        return lines
+
+    for _ in range(DIST):
+        for l in request():
+            b.emit(l)
+    n_half = len(seq) // 2
+    for p in (1, 0):
+        stream = softmax(p)
+        j0 = 0 if p == 1 else n_half
+        for r in range(2):  # (the sub-block before this one is in order)
+            b.emit(f"v_add_f32_e32 %[l{r}], %[l{r}], %[sum{r}]")
+        if p == 1:
+            b.lines += stream[:first_cover]
+            stream = stream[first_cover:]
+        # the fixed part of every slot (a slot: one matrix instruction and what follows it)
+        slots = []
+        n_load = 0
+        for j in range(j0, j0 + n_half):
+            for r in (0, 1):
+                before, after = [], []
+                if r == 0:
+                    while pending and pending[0][0] <= j:
+                        pending.pop(0)
+                    before.append(f"s_waitcnt lgkmcnt({sum(c for _, c in pending)})")
+                if r == 0 and issued < len(seq):
+                    after += request()
+                if p == 1 and r == 1 and n_load < 16:
+                    blk = Block()
+                    emit_stage_load(blk, n_load, n_load == 0, n_load == 15)
+                    after += blk.lines
+                    n_load += 1
+                slots.append((before, mfma(j, r), after))
+        assert p == 0 or n_load == 16
+        total = sum(cost(l) for l in stream) + sum(5 * (len(x) + len(y)) for x, _, y in slots)
+        done, pos = 0, 0
+        for q, (before, mm, after) in enumerate(slots):
+            b.lines += before
+            b.emit(mm)
+            b.lines += after
+            done += 5 * (len(before) + len(after))
+            while pos < len(stream) and (q == len(slots) - 1 or done + cost(stream[pos]) / 2 <= total * (q + 1) / len(slots)):
+                b.emit(stream[pos])
+                done += cost(stream[pos])
+                pos += 1
+        assert pos == len(stream)
+        if p == 0:  # on to the next step
+            for kk in range(8):
+                b.emit(f"v_xor_b32_e32 %[ka{kk}], 0x4000, %[ka{kk}]")
+            b.emit("v_xor_b32_e32 %[va0], 0x4000, %[va0]")
+            b.emit("v_xor_b32_e32 %[va1], 0x4000, %[va1]")
+            for src in ("ksrc", "vsrc"):
+                b.emit(f"s_add_u32 {LO[src]}, {LO[src]}, %[tstep]")
+                b.emit(f"s_addc_u32 {HI[src]}, {HI[src]}, 0")
+            b.emit("s_xor_b32 %[ldsk], %[ldsk], 0x4000")
+            b.emit("s_xor_b32 %[ldsv], %[ldsv], 0x4000")
+            b.emit("s_sub_u32 %[left], %[left], 1")
+        b.emit(f"v_add_f32_e32 v{TMP}, %[sum0], %[sum1]")
+        b.emit(f"s_mov_b32 %[why], {2 - p}")
+        b.emit(f"v_cmp_nge_f32_e32 vcc, %[k256], v{TMP}")
+        b.emit("s_cbranch_vccnz .Lplain_end_%=")
+    b.emit("s_cmp_lg_u32 %[left], 0")
+    b.emit("s_cbranch_scc1 .Lplain_step_%=")
+    b.emit("s_mov_b32 %[why], 0")
+    b.emit(".Lplain_end_%=:")
+    b.emit("s_waitcnt lgkmcnt(0)")  # (fragments of the even sub-block, when left behind the odd one)
+    return b
+
+
 def init_o():
     """O = 0: eight matrix instructions with zero operands write the 128 accumulator registers."""
     b = Block()
@@ -307,7 +466,7 @@ def main(out_path):
         "VS_ASM_FIRST_MASKED": step(0, True, False, True, masked=True),
         "VS_ASM_ODD": step(1, True, True, True),                   # step 2t+1 with a next tile
         "VS_ASM_ODD_MASKED": step(1, True, True, True, masked=True),
-        "VS_ASM_ODD_LOADS": step(1, True, True, True, loads=range(16)),
+        "VS_ASM_PLAIN_STEPS": loop_block(),
         "VS_ASM_ODD_LAST": step(1, False, True, True),             # step 2t+1 of the last tile
         "VS_ASM_ODD_LAST_MASKED": step(1, False, True, True, masked=True),
         "VS_ASM_EVEN": step(0, True, True, True),                  # step 2t+2

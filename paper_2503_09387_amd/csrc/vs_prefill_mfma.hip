@@ -32,7 +32,8 @@
 //     issued from generated blocks of inline assembly over fixed registers, as a software
 //     pipeline over sub-blocks of 32 keys: scores of sub-block n+1, value product of n-1 and
 //     softmax of n in one block, the ordinary instructions dealt out one by one behind the
-//     matrix instructions (gen_prefill_asm.py documents registers and hazards).
+//     matrix instructions (gen_prefill_asm.py documents registers and hazards).  The steps over
+//     plain cache tiles run in a loop that is one block (what bounds it: gen_prefill_asm.py).
 //   * Softmax uses a stale reference: probabilities are computed against the reference
 //     left by earlier sub-blocks (for the first: against 0); no maximum, no rescale.  Only if
 //     a row sum comes out above 2^8, or a row without history underflows, is the sub-block
@@ -356,16 +357,29 @@ void prefill_mfma_kernel(PrefillParams p) {
             for (int u = 0; u < 8; ++u)
                 load_to_lds16(src + (int64_t)u * 4 * kv_row_bytes + (is_v ? v_src_off : k_src_off[u & 3]), dst + u * 1024);
         } else {
-            // the tile holds frame rows or runs past the end: rows past the last key re-read the
-            // last row (finite values; every such key is masked)
+            // The tile holds frame rows or runs past the end: rows past the last key re-read the last row (finite values;
+            // every such key is masked).  Row j lies at base + j * step, which differ for cache rows, carriers of the
+            // run's earlier frames and the frame's own rows: selects and a multiplication (written as a choice of
+            // expressions the compiler branches around every load, and a wavefront that starts on such a tile began its
+            // loop 0.95 us behind the others, which all wait for it in the merge).
+            const unsigned step = (unsigned)kv_row_bytes;
+            unsigned frame_step = step * (unsigned)T;
+            asm volatile("" : "+s"(frame_step));  // (not to be multiplied row by row)
+            const unsigned long long cache = (unsigned long long)((is_v ? vc : kc) + g * kRowBytes);
+            const unsigned long long frame_rows = (unsigned long long)((is_v ? vf : kf) + g * kRowBytes) - (unsigned long long)L * step;
+            const unsigned long long carriers = (unsigned long long)((is_v ? vf0 : kf0) + g * kRowBytes) +
+                                                (unsigned long long)(T - 1) * step - (unsigned long long)Lc * T * step;
 #pragma unroll
             for (int u = 0; u < 8; ++u) {
-                const int j = min(j0 + 4 * u + lr, L + T - 1);
-                const char* row = (j < Lc) ? (is_v ? vc : kc) + ((int64_t)j * Hkv + g) * kRowBytes
-                                  : (j < L) ? (is_v ? vf0 : kf0) + (((int64_t)(j - Lc) * T + (T - 1)) * Hkv + g) * kRowBytes
-                                            : (is_v ? vf : kf) + ((int64_t)(j - L) * Hkv + g) * kRowBytes;
+                const unsigned j = min(j0 + 4 * u + lr, L + T - 1);
+                const bool own = (int)j >= L, kept = (int)j < Lc;
+                unsigned lo = own ? (unsigned)frame_rows : (unsigned)carriers, up = own ? (unsigned)(frame_rows >> 32) : (unsigned)(carriers >> 32);
+                lo = kept ? (unsigned)cache : lo;
+                up = kept ? (unsigned)(cache >> 32) : up;
+                const unsigned by = own || kept ? step : frame_step;
                 const int piece = is_v ? (ls ^ (lr << 1)) : (ls ^ lr ^ ((u & 3) << 2));
-                load_to_lds16(row + (piece << 4), dst + u * 1024);
+                load_to_lds16(reinterpret_cast<const char*>(((unsigned long long)up << 32 | lo) + (unsigned long long)j * by) + (piece << 4),
+                              dst + u * 1024);
             }
         }
     };
@@ -394,7 +408,8 @@ void prefill_mfma_kernel(PrefillParams p) {
     asm volatile(VS_ASM_INIT_O : : : VS_CLOB_ACC, VS_CLOB_TMP);  // while the loads above are under way
 
     float ms[2] = {0.f, 0.f};  // softmax reference (log2 units), a made-up 0 while a row has seen no key
-    float l_run[2] = {0.f, 0.f};              // this lane's share of the row sum
+    // this lane's share of the row sum, but for the last sub-block (pend): that is added before the next step
+    float l_run[2] = {0.f, 0.f}, pend[2] = {0.f, 0.f};
 
     // LDS read addresses (bytes inside a tile)
     unsigned k_rd[8];  // K fragment of step kk: row l32 (+32b), piece 2kk+hi
@@ -419,7 +434,7 @@ void prefill_mfma_kernel(PrefillParams p) {
     for (int kk = 0; kk < 8; ++kk) k_rd[kk] += k_ring_lds;
     v_rd[0] += v_ring_lds;
     v_rd[1] += v_ring_lds;
-    int k_hop = kTileBytes, v_hop = kTileBytes;  // to the other slot
+    // (slots of a ring lie 16 KB apart and the rings at multiples of 32 KB: the other slot is one bit away)
 #define VS_ADDR                                                                                  \
     [ka0] "v"(k_rd[0]), [ka1] "v"(k_rd[1]), [ka2] "v"(k_rd[2]), [ka3] "v"(k_rd[3]),              \
     [ka4] "v"(k_rd[4]), [ka5] "v"(k_rd[5]), [ka6] "v"(k_rd[6]), [ka7] "v"(k_rd[7]),              \
@@ -439,6 +454,8 @@ void prefill_mfma_kernel(PrefillParams p) {
     // tile number s of this group: LDS byte addresses of its K and V tiles, first key index
     auto k_tile = [&](int s) { return k_ring_lds + (s & 1) * kTileBytes; };
     auto v_tile = [&](int s) { return v_ring_lds + (s & 1) * kTileBytes; };
+    // a sub-block from key all_see or before is visible to every row of this wave (its first row sees the fewest keys)
+    const int all_see = __builtin_amdgcn_readfirstlane(jmax[0]) - 31;
     auto key0 = [&](int n) { return tile_of(n >> 1) * BN + 32 * (n & 1); };  // of sub-block n
 
     // Sub-block n has gone through the speculative softmax (reference possibly stale); its PV
@@ -448,21 +465,7 @@ void prefill_mfma_kernel(PrefillParams p) {
     // A row that has accumulated nothing yet runs against the made-up reference 0: there an
     // underflow (a lane that can see a key of the sub-block but whose sum vanished) also sends
     // the sub-block to the exact pass, which treats such a row as having no reference at all.
-    auto commit = [&](int n, float sum0, float sum1, unsigned long long flag) {
-        if (flag == 0) {  // the common case, decided inside the block
-            l_run[0] += sum0;
-            l_run[1] += sum1;
-            return;
-        }
-        const int jl = key0(n) + 4 * hi;  // this lane's smallest key in the sub-block
-        const bool redo = !(sum0 <= 256.f) || !(sum1 <= 256.f) ||
-                          (l_run[0] == 0.f && jl <= jmax[0] && sum0 < 0x1p-40f) ||
-                          (l_run[1] == 0.f && jl <= jmax[1] && sum1 < 0x1p-40f);
-        if (!__any(redo)) {
-            l_run[0] += sum0;
-            l_run[1] += sum1;
-            return;
-        }
+    auto redo = [&](int n) {
         const int par = n & 1, j0 = key0(n);
         float alpha[2];
 #pragma unroll
@@ -473,7 +476,7 @@ void prefill_mfma_kernel(PrefillParams p) {
             if (par == 1 && r == 0) asm volatile("" : "={v[160:175]}"(x));
             if (par == 1 && r == 1) asm volatile("" : "={v[176:191]}"(x));
             const f32x16 x_raw = x;
-            if (j0 + 32 > L) {
+            if (j0 > all_see) {
 #pragma unroll
                 for (int e = 0; e < 16; ++e)
                     if (j0 + 8 * (e >> 2) + 4 * hi + (e & 3) > jmax[r]) x[e] = -INFINITY;
@@ -485,7 +488,7 @@ void prefill_mfma_kernel(PrefillParams p) {
             const float m_old = (l_run[r] + xhalf(l_run[r]) > 0.f) ? ms[r] : -INFINITY;  // the row's history
             const float m_new = fmaxf(m_old, mx);
             alpha[r] = (m_new == -INFINITY) ? 1.f : __builtin_amdgcn_exp2f(m_old - m_new);
-            // (a row that has seen no key yet keeps the made-up reference 0, which is what its next sub-blocks
+            // (a row that has seen no key yet keeps the made-up reference, which is what its next sub-blocks
             // will be taken against)
             const float m_sub = (m_new == -INFINITY) ? 0.f : m_new;
             ms[r] = m_sub;
@@ -514,7 +517,8 @@ void prefill_mfma_kernel(PrefillParams p) {
                     default: asm volatile("" : : "{v[244:247]}"(pk8)); break;
                 }
             }
-            l_run[r] = l_run[r] * alpha[r] + sum;
+            l_run[r] *= alpha[r];
+            pend[r] = sum;
             // the raw scores stay where they are to the end: this keeps the compiler from working
             // in place inside the fixed registers
             if (par == 0 && r == 0) asm volatile("" : : "{v[128:143]}"(x_raw));
@@ -525,12 +529,25 @@ void prefill_mfma_kernel(PrefillParams p) {
         if (__any(alpha[0] != 1.f || alpha[1] != 1.f))
             asm volatile(VS_ASM_RESCALE : : [alpha0] "v"(alpha[0]), [alpha1] "v"(alpha[1]) : VS_CLOB_ACC, VS_CLOB_TMP);
     };
+    auto commit = [&](int n, float sum0, float sum1, unsigned long long flag) {
+        if (flag != 0) {  // (decided inside the block)
+            const int jl = key0(n) + 4 * hi;  // this lane's smallest key in the sub-block
+            const bool stale = !(sum0 <= 256.f) || !(sum1 <= 256.f) ||
+                               (l_run[0] == 0.f && jl <= jmax[0] && sum0 < 0x1p-40f) ||
+                               (l_run[1] == 0.f && jl <= jmax[1] && sum1 < 0x1p-40f);
+            if (__any(stale)) return redo(n);
+        }
+        pend[0] = sum0;
+        pend[1] = sum1;
+    };
 
     // One pipeline step with a softmax part: runs the block `ASM` and commits sub-block n.
 #define VS_STEP(ASM, n)                                                                              \
     do {                                                                                             \
         float sum0_, sum1_;                                                                          \
         unsigned long long flag_;                                                                    \
+        l_run[0] += pend[0];                                                                         \
+        l_run[1] += pend[1];                                                                         \
         asm volatile(ASM : VS_SM_OUT : VS_ADDR, VS_SM_IN : VS_CLOBBERS);                             \
         commit(n, sum0_, sum1_, flag_);                                                              \
     } while (0)
@@ -540,6 +557,8 @@ void prefill_mfma_kernel(PrefillParams p) {
         unsigned long long flag_;                                                                    \
         const int d0_ = jmax[0] - (key0(n) + 4 * hi), d1_ = jmax[1] - (key0(n) + 4 * hi);            \
         unsigned long long mk0_, mk1_;                                                               \
+        l_run[0] += pend[0];                                                                         \
+        l_run[1] += pend[1];                                                                         \
         asm volatile(ASM                                                                             \
                      : VS_SM_OUT, [mk0] "=&s"(mk0_), [mk1] "=&s"(mk1_)                               \
                      : VS_ADDR, VS_SM_IN, [d0] "v"(d0_), [d1] "v"(d1_)                               \
@@ -576,66 +595,73 @@ void prefill_mfma_kernel(PrefillParams p) {
             commit(0, sum0_, sum1_, flag_);
         } else {
             issue(0, true);
-            if (key0(0) + 32 > L) VS_STEP_MASKED(VS_ASM_FIRST_MASKED, 0);
+            if (key0(0) > all_see) VS_STEP_MASKED(VS_ASM_FIRST_MASKED, 0);
             else VS_STEP(VS_ASM_FIRST, 0);
         }
     }
 #pragma unroll
-    for (int kk = 0; kk < 8; ++kk) k_rd[kk] += k_hop;  // the loop starts on K of tile 1, V of tile 0
-    k_hop = -k_hop;
+    for (int kk = 0; kk < 8; ++kk) k_rd[kk] ^= kTileBytes;  // the loop starts on K of tile 1, V of tile 0
+    auto next_slots = [&]() {
+#pragma unroll
+        for (int kk = 0; kk < 8; ++kk) k_rd[kk] ^= kTileBytes;
+        v_rd[0] ^= kTileBytes;
+        v_rd[1] ^= kTileBytes;
+    };
 
-    for (int s = 0; s < n_steps; ++s) {
-        // steps 2s+1 and 2s+2 of this group: they read K of tile s+1 and V of tile s
+    // A step is plain if its tile and the two behind it are cache rows only, and this group's.  Plain steps follow one
+    // another; they run in one block, unless a row has accumulated nothing yet (its first sums need the closer look of commit()).
+    const int plain_from = n_rest, plain_to = min(n_my, n_plain - run_first + n_rest) - 2;
+    for (int s = 0; s < n_steps;) {
+        // steps 2s+1 and 2s+2 of this group: they read K of tile s+1 and V of tile s, and K of tile s+2 and V of tile
+        // s+1 are requested
+        if (s >= plain_from && s < plain_to && __all(l_run[0] + pend[0] > 0.f && l_run[1] + pend[1] > 0.f)) {
+            // this wave's share of what the first of them requests: rows 32*rb .. 32*rb+31 of the two tiles, head g
+            unsigned long long ksrc = (unsigned long long)(kc + ((int64_t)(tile_of(s + 2) * BN + rb * 32) * Hkv + g) * kRowBytes);
+            unsigned long long vsrc = (unsigned long long)(vc + ((int64_t)(tile_of(s + 1) * BN + rb * 32) * Hkv + g) * kRowBytes);
+            unsigned ldsk = k_tile(s) + rb * (8 * 1024), ldsv = v_tile(s + 1) + rb * (8 * 1024);
+            int left = plain_to - s, why;
+            asm volatile(VS_ASM_PLAIN_STEPS
+                         : [ka0] "+v"(k_rd[0]), [ka1] "+v"(k_rd[1]), [ka2] "+v"(k_rd[2]), [ka3] "+v"(k_rd[3]),
+                           [ka4] "+v"(k_rd[4]), [ka5] "+v"(k_rd[5]), [ka6] "+v"(k_rd[6]), [ka7] "+v"(k_rd[7]),
+                           [va0] "+v"(v_rd[0]), [va1] "+v"(v_rd[1]), "={s[88:89]}"(ksrc), "={s[90:91]}"(vsrc),
+                           [ldsk] "+s"(ldsk), [ldsv] "+s"(ldsv), [left] "+s"(left), [why] "=&s"(why),
+                           [l0] "+v"(l_run[0]), [l1] "+v"(l_run[1]), [sum0] "+v"(pend[0]), [sum1] "+v"(pend[1])
+                         : VS_KOFF, VS_VOFF, "{s[88:89]}"(ksrc), "{s[90:91]}"(vsrc), [ms0] "v"(ms[0]), [ms1] "v"(ms[1]),
+                           [scale] "s"(p.scale_log2e), [tstep] "s"(BN * kv_row_bytes), [k256] "s"(256.f)
+                         : VS_CLOBBERS, "scc", "memory");
+            s = plain_to - left;
+            if (why == 1) {
+                redo(2 * s + 1);
+                VS_STEP(VS_ASM_EVEN, 2 * s + 2);  // the rest of the step that was left
+                next_slots();
+                ++s;
+            } else if (why == 2) {
+                redo(2 * s);
+            }
+            continue;
+        }
         __builtin_amdgcn_s_waitcnt(0x0F70);  // vmcnt(0): this wave's share of K(s+1), V(s) has landed
         __syncthreads();                     // ... and everybody's; K slot s&1 and V slot (s+1)&1 are free
-        // tiles to stage now: K of tile s+2, V of tile s+1.  When both lie inside the cache rows
-        // the first block issues the loads itself, between its matrix instructions.
-        // (the block that can do that is the unmasked one: tile s must be a plain tile too)
-        const bool loads_inside = s + 2 < n_my && tile_of(s + 2) * BN + BN <= Lc && tile_of(s + 1) * BN + BN <= Lc &&
-                                  tile_of(s) * BN + BN <= Lc;
-        if (!loads_inside) {
-            issue(s + 2, false);
-            issue(s + 1, true);
-        }
-        if (NKG > 1 && s >= n_my) continue;  // this group idles in the last step
-        const int n = 2 * s + 1;
-        if (s + 1 < n_my) {
-            // step 2s+1: QK(2s+2) | PV(2s) | SM(2s+1)
-            if (key0(n) + 32 > L) {
-                VS_STEP_MASKED(VS_ASM_ODD_MASKED, n);
-            } else if (loads_inside) {
-                // this wave's share: rows 32*rb .. 32*rb+31 of the two tiles, head g
-                const unsigned long long ksrc = (unsigned long long)(kc +
-                    ((int64_t)(tile_of(s + 2) * BN + rb * 32) * Hkv + g) * kRowBytes);
-                const unsigned long long vsrc = (unsigned long long)(vc +
-                    ((int64_t)(tile_of(s + 1) * BN + rb * 32) * Hkv + g) * kRowBytes);
-                float sum0_, sum1_;
-                unsigned long long flag_;
-                asm volatile(VS_ASM_ODD_LOADS
-                             : VS_SM_OUT
-                             : VS_ADDR, VS_SM_IN, VS_KOFF, VS_VOFF, "{s[88:89]}"(ksrc), "{s[90:91]}"(vsrc),
-                               [ldsk] "s"(k_tile(s) + rb * (8 * 1024)), [ldsv] "s"(v_tile(s + 1) + rb * (8 * 1024))
-                             : VS_CLOBBERS, "scc");
-                commit(n, sum0_, sum1_, flag_);
+        issue(s + 2, false);
+        issue(s + 1, true);
+        if (NKG == 1 || s < n_my) {  // (a group may idle in the last step)
+            const int n = 2 * s + 1;
+            if (s + 1 < n_my) {
+                // step 2s+1: QK(2s+2) | PV(2s) | SM(2s+1)
+                if (key0(n) > all_see) VS_STEP_MASKED(VS_ASM_ODD_MASKED, n);
+                else VS_STEP(VS_ASM_ODD, n);
+                // step 2s+2: QK(2s+3) | PV(2s+1) | SM(2s+2)
+                if (key0(n + 1) > all_see) VS_STEP_MASKED(VS_ASM_EVEN_MASKED, n + 1);
+                else VS_STEP(VS_ASM_EVEN, n + 1);
             } else {
-                VS_STEP(VS_ASM_ODD, n);
+                // the group's last tile: step 2s+1 = PV(2s) | SM(2s+1), then PV(2s+1)
+                if (key0(n) > all_see) VS_STEP_MASKED(VS_ASM_ODD_LAST_MASKED, n);
+                else VS_STEP(VS_ASM_ODD_LAST, n);
+                asm volatile(VS_ASM_TAIL : : VS_ADDR : VS_CLOBBERS);
             }
-            // step 2s+2: QK(2s+3) | PV(2s+1) | SM(2s+2)
-            if (key0(n + 1) + 32 > L) VS_STEP_MASKED(VS_ASM_EVEN_MASKED, n + 1);
-            else VS_STEP(VS_ASM_EVEN, n + 1);
-        } else {
-            // the group's last tile: step 2s+1 = PV(2s) | SM(2s+1), then PV(2s+1)
-            if (key0(n) + 32 > L) VS_STEP_MASKED(VS_ASM_ODD_LAST_MASKED, n);
-            else VS_STEP(VS_ASM_ODD_LAST, n);
-            asm volatile(VS_ASM_TAIL : : VS_ADDR : VS_CLOBBERS);
+            next_slots();
         }
-        // the next step reads the other slots
-#pragma unroll
-        for (int kk = 0; kk < 8; ++kk) k_rd[kk] += k_hop;
-        v_rd[0] += v_hop;
-        v_rd[1] += v_hop;
-        k_hop = -k_hop;
-        v_hop = -v_hop;
+        ++s;
     }
 #undef VS_ADDR
 #undef VS_KOFF
@@ -681,6 +707,7 @@ void prefill_mfma_kernel(PrefillParams p) {
     float l_tot[2], m_ref[2];
 #pragma unroll
     for (int r = 0; r < 2; ++r) {
+        l_run[r] += pend[r];
         l_tot[r] = l_run[r] + xhalf(l_run[r]);
         m_ref[r] = l_tot[r] > 0.f ? ms[r] : -INFINITY;  // nothing accumulated: the made-up reference must not count
     }

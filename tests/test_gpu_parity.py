@@ -529,6 +529,28 @@ def test_prefill_extreme_score_ranges(mode, L, kv_groups):
     check_close(out, oracle_prefill_rows(s, q, hk, hv, L, kf, vf), "bf16", f"{mode} L={L}")
 
 
+@pytest.mark.parametrize("kv_groups", [1, 2])
+@pytest.mark.parametrize("tiles,first_block,step", [(3, 2, 60.0), (4, 3, 60.0), (7, 4, 20.0), (7, 5, 20.0), (8, 6, 400.0), (8, 7, 400.0)])
+def test_prefill_reference_left_behind_inside_the_loop_of_plain_steps(tiles, first_block, step, kv_groups):
+    """Scores that jump at a chosen sub-block of 32 keys (even and odd ones, by `step` log2 units, and again two and three
+    sub-blocks later), over so many whole tiles in one lane: the loop over plain steps is left behind either half of a step,
+    the sub-block redone and the loop entered again, with an odd or even number of steps to go."""
+    s, T = AttnShape(8, 4, 128, "bf16"), 70
+    L = 64 * tiles * kv_groups + 5
+    vs.set_tuning(vs.TUNE_PREFILL_KV_GROUPS, kv_groups)
+    vs.set_tuning(vs.TUNE_PREFILL_SPLITS, 1)
+    hk, hv = cache_rows(44, s, L, 0.5)
+    q, kf, vf = frame_inputs(44, s, T, 0.5)
+    block = torch.arange(L + T) // 32
+    a = sum((block >= b).float() for b in (first_block, first_block + 2, first_block + 5)) * (step / 40.8)
+    # (k_j += a_j u, q += 10 u with u = 0.5 ones: score_j moves by 0.1275 * 10 * a_j * 32 log2 units)
+    hk = (hk.float() + 0.5 * a[:L, None, None]).to(torch.bfloat16)
+    kf = (kf.float() + 0.5 * a[L:, None, None]).to(torch.bfloat16)
+    q = (q.float() + 5.0).to(torch.bfloat16)
+    out, _, _ = run_prefill(s, hk, hv, L, q, kf, vf)
+    check_close(out, oracle_prefill_rows(s, q, hk, hv, L, kf, vf), "bf16", f"{tiles} tiles, block {first_block}, {kv_groups} key groups")
+
+
 def test_prefill_uniform_scores_is_running_mean_at_full_size():
     """Q = 0: every row is the mean of its visible V rows (closed form, any size)."""
     s = QW
