@@ -46,20 +46,30 @@ struct PrefillSlot {
 
 VS_HD int prefill_units_per_xcd(int units, int xcd_shift) { return (units + (1 << xcd_shift) - 1) >> xcd_shift; }
 
-VS_HD unsigned prefill_grid_ids(int units, int nsplit, int xcd_shift) {
-    return (unsigned)(prefill_units_per_xcd(units, xcd_shift) * nsplit) << xcd_shift;
+VS_HD unsigned prefill_grid_ids(int units, int nsplit, int xcd_shift, int whole = 0) {
+    return (unsigned)(whole + (prefill_units_per_xcd(units, xcd_shift) - whole) * nsplit) << xcd_shift;
 }
 
+// The first `whole` units of every XCD may be left whole, a workgroup each, which come first; the others are split nsplit ways.
+// (whole must be 0 where ids are not dealt by residue: a unit's place below is worked out from the XCD its id says.)
 VS_HD PrefillSlot prefill_slot_of_id(unsigned id, int units, int units_per_xcd, int nsplit, float inv_nsplit,
-                                     int xcd_shift) {
+                                     int xcd_shift, int whole = 0) {
     PrefillSlot s;
     s.xcd = (int)(id & ((1u << xcd_shift) - 1u));
-    const int slot = (int)(id >> xcd_shift);
-    const int j = div_small(slot, nsplit, inv_nsplit);
-    s.split = slot - j * nsplit;
+    const int slot = (int)(id >> xcd_shift), behind = slot - whole;
+    int j = slot;
+    s.split = 0;
+    if (behind >= 0) {
+        const int jj = div_small(behind, nsplit, inv_nsplit);
+        s.split = behind - jj * nsplit;
+        j = whole + jj;
+    }
     s.unit = s.xcd * units_per_xcd + j;
     if (j >= units_per_xcd || s.unit >= units) s.unit = -1;
     return s;
 }
+
+// A split unit's place among those that are split: 0 .. (units_per_xcd - whole) * XCDs - 1.
+VS_HD int prefill_part_of_unit(int unit, int xcd, int whole) { return unit - whole * (xcd + 1); }
 
 }  // namespace vs

@@ -75,17 +75,18 @@ struct PrefillParams {
     const __bf16* vf;
     __bf16* out;
     // partial accumulators, normalised, in register order:
-    // [nsplit*Hkv][row tiles][4 row groups of 32][4 dim blocks][2][64 lanes] x 8 bf16
+    // [nsplit][part_units][4 row groups of 32][4 dim blocks][2][64 lanes] x 8 bf16
     // (stored as fp16 after multiplying the row by a power of two that brings its largest entry
     // into [2^14, 2^15): 11 significant bits whatever the size of the values, in the bytes bf16
     // would take; the power's inverse travels with the row's reference and sum)
     _Float16* part_o;
-    float* part_ml;  // [nsplit*Hkv][m_pad][4]: reference (log2 units), row sum, inverse of the row's scale, unused
+    float* part_ml;  // [nsplit][part_units][128 rows][4]: reference (log2 units), row sum, inverse of the row's scale, unused
     __bf16* k_append_dst;    // frame rows append_first .. T-1 are copied here (null: none)
     __bf16* v_append_dst;
     int append_first;        // T - 1: the carrier alone; 0: every row of the run (a question)
     int L, T, G, Hq, Hkv;
-    int M, m_pad, nsplit, n_row_tiles;
+    int M, nsplit, n_row_tiles;
+    int part_units;           // units that are split: all of them, or those behind the whole ones of every XCD
     float scale_log2e;
     float inv_G, inv_nsplit;  // reciprocals for the index arithmetic of the prologue
     // Merging inside this kernel (see the end of the kernel): the workgroups of one (row tile,
@@ -94,6 +95,7 @@ struct PrefillParams {
     unsigned* arrivals;       // [Hkv][frames][row tiles], kCounterStrideBytes apart, zero between launches
     int xcd_shift;            // log2 of the number of XCDs workgroup ids are dealt to in turn
     int units_per_xcd;
+    int whole;                // of which so many, the first, are a workgroup each and not split
     // the guard of that placement: the word in pinned host memory that is set when the workgroups of a unit were not
     // all on one XCD (the host looks at it before every launch)
     unsigned* misplaced;
@@ -241,8 +243,10 @@ void prefill_mfma_kernel(PrefillParams p) {
     const char* vf = reinterpret_cast<const char*>(p.vf);
     const char* qbase = reinterpret_cast<const char*>(p.q);
     int L = p.L;
-    const int T = p.T, G = p.G, M = p.M, Hkv = p.Hkv, nsplit = p.nsplit;
-    const float inv_G = p.inv_G, inv_nsplit = p.inv_nsplit;
+    const int T = p.T, G = p.G, M = p.M, Hkv = p.Hkv;
+    int nsplit = p.nsplit;
+    const float inv_G = p.inv_G;
+    float inv_nsplit = p.inv_nsplit;
     asm volatile("" : : "s"(kc), "s"(vc), "s"(kf), "s"(vf), "s"(qbase), "s"(L), "s"(T), "s"(G), "s"(M), "s"(Hkv),
                  "s"(nsplit), "s"(inv_G), "s"(inv_nsplit), "s"(p.Hq), "s"(p.scale_log2e));
     const int tid = threadIdx.x;
@@ -259,7 +263,7 @@ void prefill_mfma_kernel(PrefillParams p) {
         // (consecutive units: the same KV head, whose K/V that L2 then holds once), each with
         // nsplit consecutive slots.
         const PrefillSlot at = prefill_slot_of_id(blockIdx.x, p.n_row_tiles * p.F * Hkv, p.units_per_xcd, nsplit,
-                                                  inv_nsplit, p.xcd_shift);
+                                                  inv_nsplit, p.xcd_shift, p.whole);
         if (at.unit < 0) return;  // spare ids
         const int unit = at.unit;
         split = at.split;
@@ -267,6 +271,10 @@ void prefill_mfma_kernel(PrefillParams p) {
         const int ft = unit - g * p.n_row_tiles * p.F;
         frame = div_small(ft, p.n_row_tiles, p.inv_row_tiles);
         rt = ft - frame * p.n_row_tiles;
+        if ((int)(blockIdx.x >> p.xcd_shift) < p.whole) {  // a whole unit
+            nsplit = 1;
+            inv_nsplit = 1.f;
+        }
     } else {
         // grid (Hkv, nsplit, frames x row tiles): x runs fastest in dispatch order, so with
         // nsplit*Hkv a multiple of the number of XCDs all workgroups that read one K/V slice
@@ -285,9 +293,7 @@ void prefill_mfma_kernel(PrefillParams p) {
     kf += (int64_t)frame * T * Hkv * kRowBytes;
     vf += (int64_t)frame * T * Hkv * kRowBytes;
     __bf16* const out = p.out + (int64_t)frame * T * p.Hq * D;
-    const int gf = g * p.F + frame, HF = Hkv * p.F;  // (head, frame) pairs index partial results and counters
-    const int c = split * HF + gf;  // which partial result
-    const int wg_id = rt * (nsplit * HF) + c;
+    const int gf = g * p.F + frame, HF = Hkv * p.F;  // (head, frame) pairs index the counters
     const int kv_row_bytes = Hkv * kRowBytes;
     char* const k_ring = dyn_smem + kg * kGroupLds;
     char* const v_ring = k_ring + 2 * kTileBytes;
@@ -678,21 +684,23 @@ void prefill_mfma_kernel(PrefillParams p) {
     // copied into the cache, 16 bytes per thread, the workgroups of the launch taking turns (the
     // carrier's 1 KB is done by the first one alone; no workgroup of this launch reads the
     // cache rows written here)
-    if (p.k_append_dst && p.F > 1) {
+    // (beside units left whole, the first workgroup of every unit alone)
+    const int n_thr = kGroupThreads * NKG, n_heads_tiles = p.n_row_tiles * HF;
+    const int n_wgs = p.whole ? n_heads_tiles : n_heads_tiles * nsplit, wg_id = rt * HF + gf + split * n_heads_tiles;
+    const bool copies = p.k_append_dst && (!p.whole || split == 0);
+    if (copies && p.F > 1) {
         // a run: row T-1 of every frame goes behind the cache's rows, frame f to row Lc + f
         const int c16 = kv_row_bytes / 16, n16 = p.F * c16;
-        const int n_thr = kGroupThreads * NKG, n_wgs = p.n_row_tiles * nsplit * HF;
         for (int ch = wg_id * n_thr + tid; ch < n16; ch += n_wgs * n_thr) {
             const int f = ch / c16;
             const int64_t from = ((int64_t)f * T + (T - 1)) * c16 + (ch - f * c16);
             reinterpret_cast<uint4*>(p.k_append_dst)[ch] = reinterpret_cast<const uint4*>(kf0)[from];
             reinterpret_cast<uint4*>(p.v_append_dst)[ch] = reinterpret_cast<const uint4*>(vf0)[from];
         }
-    } else if (p.k_append_dst) {
+    } else if (copies) {
         const int n16 = (T - p.append_first) * (kv_row_bytes / 16);
         const uint4* ksrc = reinterpret_cast<const uint4*>(kf + (int64_t)p.append_first * kv_row_bytes);
         const uint4* vsrc = reinterpret_cast<const uint4*>(vf + (int64_t)p.append_first * kv_row_bytes);
-        const int n_thr = kGroupThreads * NKG, n_wgs = p.n_row_tiles * nsplit * HF;
         for (int ch = wg_id * n_thr + tid; ch < n16; ch += n_wgs * n_thr) {
             reinterpret_cast<uint4*>(p.k_append_dst)[ch] = ksrc[ch];
             reinterpret_cast<uint4*>(p.v_append_dst)[ch] = vsrc[ch];
@@ -712,11 +720,13 @@ void prefill_mfma_kernel(PrefillParams p) {
         m_ref[r] = l_tot[r] > 0.f ? ms[r] : -INFINITY;  // nothing accumulated: the made-up reference must not count
     }
 
+    // the unit's place among the split ones (of every XCD the first `whole` are not)
+    const int part = prefill_part_of_unit(gf * p.n_row_tiles + rt, (int)(blockIdx.x & ((1u << p.xcd_shift) - 1u)), p.whole);
     // ---- output of one row group: lane (q = l32, hi) holds dims 32*db + 8*(e>>2) + 4*hi + (e&3) ----
     auto emit = [&](int r, const f32x16 (&oo)[4], float m_row, float l_row) {
         const float inv = (l_row > 0.f) ? 1.0f / l_row : 0.f;
         const int rg = rb * 2 + r;  // 32-row group inside the row tile
-        if (p.nsplit == 1) {
+        if (nsplit == 1) {
             if (r_mine[r] < p.M) {
                 const int t = r_mine[r] / G, hl = r_mine[r] - t * G;
                 __bf16* orow = out + ((int64_t)t * p.Hq + (int64_t)g * G + hl) * D;
@@ -732,8 +742,8 @@ void prefill_mfma_kernel(PrefillParams p) {
             }
         } else {
             // normalised partials in register order: every store instruction writes 1 KB contiguous
-            const int64_t unit = (int64_t)c * p.n_row_tiles + rt;
-            f16x8* po = reinterpret_cast<f16x8*>(p.part_o) + (unit * 4 + rg) * (8 * 64) + lane;
+            const int64_t slot = (int64_t)split * p.part_units + part;
+            f16x8* po = reinterpret_cast<f16x8*>(p.part_o) + (slot * 4 + rg) * (8 * 64) + lane;
             // the row's largest entry (this lane holds 64 of its 128 dims, lane ^ 32 the rest)
             float big = 0.f;
 #pragma unroll
@@ -756,7 +766,7 @@ void prefill_mfma_kernel(PrefillParams p) {
                     __builtin_nontemporal_store(wv, &po[(db * 2 + h2) * 64]);
                 }
             if (hi == 0) {
-                const int64_t prow = (int64_t)c * p.m_pad + r_mine[r];
+                const int64_t prow = slot * BM + rg * 32 + l32;
                 *reinterpret_cast<float4*>(p.part_ml + prow * 4) = make_float4(m_row, l_row, sc.inv_scale, 0.f);
             }
         }
@@ -808,7 +818,7 @@ void prefill_mfma_kernel(PrefillParams p) {
         if (kg == 0) take_over(0); else take_over(1);
     }
 
-    if (p.arrivals) {
+    if (p.arrivals && nsplit > 1) {
         // ---- merge of the splits inside this launch.  Every workgroup has stored its
         // partial result above (ordinary stores: they stay in the XCD's L2, and all splits
         // of the unit run on this XCD).  Once the stores of all its wavefronts have been
@@ -848,11 +858,10 @@ void prefill_mfma_kernel(PrefillParams p) {
             const bool row_ok = m < M;
             const int t = row_ok ? div_small(m, G, inv_G) : 0, hl = m - t * G;
             __bf16* const orow = out + ((int64_t)t * p.Hq + (int64_t)g * G + hl) * D;
-            const float* const ml0 = p.part_ml + ((int64_t)gf * p.m_pad + m) * 4;
-            const int64_t ml_step = (int64_t)HF * p.m_pad * 4;  // floats between splits
-            const f16x8* const po0 = reinterpret_cast<const f16x8*>(p.part_o) +
-                                      (((int64_t)gf * p.n_row_tiles + rt) * 4 + rg) * (8 * 64) + piece0 * 64 + lane;
-            const int64_t po_step = (int64_t)HF * p.n_row_tiles * 4 * (8 * 64);  // f16x8 between splits
+            const float* const ml0 = p.part_ml + ((int64_t)part * BM + rg * 32 + l32) * 4;
+            const int64_t ml_step = (int64_t)p.part_units * BM * 4;  // floats between splits
+            const f16x8* const po0 = reinterpret_cast<const f16x8*>(p.part_o) + ((int64_t)part * 4 + rg) * (8 * 64) + piece0 * 64 + lane;
+            const int64_t po_step = (int64_t)p.part_units * 4 * (8 * 64);  // f16x8 between splits
             auto share = [&](auto ns_tag, auto pieces_tag) {
                 constexpr int NS = decltype(ns_tag)::value, PIECES = decltype(pieces_tag)::value;
                 float4 ml[NS];  // reference, sum, inverse scale of the stored row
@@ -951,11 +960,10 @@ void prefill_mfma_kernel(PrefillParams p) {
                 const bool row_ok = r_mine[r] < M;
                 const int t = row_ok ? div_small(r_mine[r], G, inv_G) : 0, hl = r_mine[r] - t * G;
                 __bf16* const orow = out + ((int64_t)t * p.Hq + (int64_t)g * G + hl) * D;
-                const float* const ml0 = p.part_ml + ((int64_t)gf * p.m_pad + r_mine[r]) * 4;
-                const int64_t ml_step = (int64_t)HF * p.m_pad * 4;       // floats between splits
-                const f16x8* const po0 = reinterpret_cast<const f16x8*>(p.part_o) +
-                                          (((int64_t)gf * p.n_row_tiles + rt) * 4 + rg) * (8 * 64) + lane;
-                const int64_t po_step = (int64_t)HF * p.n_row_tiles * 4 * (8 * 64);  // f16x8 between splits
+                const float* const ml0 = p.part_ml + ((int64_t)part * BM + rg * 32 + l32) * 4;
+                const int64_t ml_step = (int64_t)p.part_units * BM * 4;  // floats between splits
+                const f16x8* const po0 = reinterpret_cast<const f16x8*>(p.part_o) + ((int64_t)part * 4 + rg) * (8 * 64) + lane;
+                const int64_t po_step = (int64_t)p.part_units * 4 * (8 * 64);  // f16x8 between splits
                 // NS splits, the 8 pieces of a lane in PASSES rounds: everything of a round is
                 // requested before anything is used (a round trip to L2 is what this tail costs)
                 auto tail = [&](auto ns_tag, auto passes_tag) {
@@ -1040,17 +1048,16 @@ __global__ __launch_bounds__(64) void prefill_combine_kernel(PrefillParams p) {
     const int rg = b & 3; b >>= 2;
     const int rt = b;
     const int g = blockIdx.y, frame = blockIdx.z;
-    const int gf = g * p.F + frame, HF = p.Hkv * p.F;
+    const int unit = (g * p.F + frame) * p.n_row_tiles + rt;  // (all units are split)
     if (rt * BM + rg * 32 >= p.M) return;  // whole block beyond the rows
     const int r = rt * BM + rg * 32 + l32;
-    const int rr = min(r, p.M - 1);
+    const int rr = min(r, p.M - 1) - rt * BM;
     float acc[8], denom;
     merge_splits_chunked<0>(
         p.nsplit,
-        [&](int u) { return *reinterpret_cast<const float4*>(p.part_ml + ((int64_t)(u * HF + gf) * p.m_pad + rr) * 4); },
+        [&](int u) { return *reinterpret_cast<const float4*>(p.part_ml + (((int64_t)u * p.part_units + unit) * BM + rr) * 4); },
         [&](int u) {
-            const int64_t unit = (int64_t)(u * HF + gf) * p.n_row_tiles + rt;
-            return (reinterpret_cast<const f16x8*>(p.part_o) + (unit * 4 + rg) * (8 * 64) + lane)[(db * 2 + h2) * 64];
+            return (reinterpret_cast<const f16x8*>(p.part_o) + (((int64_t)u * p.part_units + unit) * 4 + rg) * (8 * 64) + lane)[(db * 2 + h2) * 64];
         },
         acc, denom);
     if (r >= p.M) return;
@@ -1069,8 +1076,11 @@ __global__ __launch_bounds__(64) void prefill_combine_kernel(PrefillParams p) {
 }
 
 struct Plan {
-    int kvg, n_row_tiles, m_pad, nsplit;
+    int kvg, n_row_tiles, nsplit;
     bool merge_inside;  // the attention kernel merges the splits itself
+    // of a launch that goes through the chip in several rounds and merges inside: so many units of every XCD, the
+    // first, are left whole (0: all are split alike, nsplit ways), the others split mixed_nsplit ways
+    int whole, mixed_nsplit;
 };
 
 // How this device deals workgroup ids to its XCDs, found once per device by xcd_probe_kernel:
@@ -1159,7 +1169,6 @@ Plan make_plan(const vs_shape& s, int n_tokens, int len, int n_frames) {
     const int M = n_tokens * G;
     Plan pl;
     pl.n_row_tiles = (M + BM - 1) / BM;
-    pl.m_pad = pl.n_row_tiles * BM;
     const int units = pl.n_row_tiles * s.n_kv_heads * n_frames;
     const int max_tiles = (len + n_frames - 1 + n_tokens + BN - 1) / BN;
     // 4-wave workgroups (two key groups) when there are enough key tiles to share out
@@ -1177,8 +1186,9 @@ Plan make_plan(const vs_shape& s, int n_tokens, int len, int n_frames) {
     // than few long ones with a thin last round.  Estimated time of a launch in units of one
     // pipeline step (one tile per key group, ~2 us): rounds x (steps of a workgroup + its fixed
     // cost of ~2.25 steps), plus the merge when there are splits.
+    pl.whole = pl.mixed_nsplit = 0;
+    float best = 0.f;
     if (units > 128 && pl.kvg == 2) {
-        float best = 0.f;
         for (int cand = 1; cand <= 8 && cand <= max_tiles / pl.kvg; ++cand) {
             const int rounds = (units * cand + 255) / 256;
             const int steps = ((max_tiles + cand - 1) / cand + pl.kvg - 1) / pl.kvg;
@@ -1189,11 +1199,31 @@ Plan make_plan(const vs_shape& s, int n_tokens, int len, int n_frames) {
             }
         }
     }
+    // Whole rounds of whole units, a workgroup each, and the units of the last round, which would leave compute units
+    // idle, split over all of them behind (the merge inside the launch: the split units of an XCD stay on it).  Same
+    // estimate, and no more workspace than the plan above needs.  28/4 heads, 170 tokens over 4296 rows, per layer: 7 frames
+    // 123 -> 82 us, 8 frames 117 -> 88, 9 110 -> 99, 10 135 -> 127 (6, 11 and 12: nothing left over); a question of 1500
+    // tokens 156 -> 117.
+    const int per_xcd = (units + kPlanXcds - 1) / kPlanXcds, whole = per_xcd / kPlanCusPerXcd * kPlanCusPerXcd;
+    if (units > 128 && pl.kvg == 2 && whole > 0 && whole < per_xcd) {
+        for (int cand = 2; cand <= 8 && cand <= max_tiles / pl.kvg; ++cand) {
+            if (kPlanXcds * (per_xcd - whole) * cand > units * ns) break;
+            const int rounds = ((per_xcd - whole) * cand + kPlanCusPerXcd - 1) / kPlanCusPerXcd;
+            const int steps = ((max_tiles + cand - 1) / cand + pl.kvg - 1) / pl.kvg;
+            const float cost = whole / kPlanCusPerXcd * ((max_tiles + 1) / 2 + 2.25f) + rounds * (steps + 2.25f) + 1.25f;
+            if (cost < best) {
+                best = cost;
+                pl.whole = whole;
+                pl.mixed_nsplit = cand;
+            }
+        }
+    }
+    if (g_tune_prefill_splits) pl.whole = 0;
     if (g_tune_prefill_splits) ns = g_tune_prefill_splits < max_tiles ? g_tune_prefill_splits : (max_tiles > 0 ? max_tiles : 1);
     pl.nsplit = ns;
     int dev = 0;
     // (more than 8 splits: only the shared merge knows how)
-    pl.merge_inside = g_tune_prefill_merge != 2 && ns > 1 && (ns <= 8 || g_tune_prefill_merge != 1) &&
+    pl.merge_inside = g_tune_prefill_merge != 2 && (ns > 1 || pl.whole) && (ns <= 8 || g_tune_prefill_merge != 1) &&
                       ns <= kMaxPrefillSplits && pl.n_row_tiles * n_frames <= kMaxRowTiles &&
                       hipGetDevice(&dev) == hipSuccess && dev >= 0 && dev < 16 && g_xcd_shift[dev] >= 0 && g_misplaced[dev];
     return pl;
@@ -1213,7 +1243,7 @@ hipError_t launch_kvg(const PrefillParams& p, const Plan& pl, int n_kv_heads, hi
         attr_set = true;
     }
     // x runs fastest in dispatch order: all workgroups that read one K/V slice are neighbours
-    const dim3 grid = p.arrivals ? dim3(prefill_grid_ids(pl.n_row_tiles * p.F * n_kv_heads, pl.nsplit, p.xcd_shift))
+    const dim3 grid = p.arrivals ? dim3(prefill_grid_ids(pl.n_row_tiles * p.F * n_kv_heads, p.nsplit, p.xcd_shift, p.whole))
                                  : dim3(n_kv_heads, pl.nsplit, pl.n_row_tiles * p.F);
     prefill_mfma_kernel<KVG><<<grid, kGroupThreads * KVG, kLds, st>>>(p);
     hipError_t e = hipGetLastError();
@@ -1337,14 +1367,14 @@ hipError_t launch_prefill_mfma(const vs_shape& s, const void* kc, const void* vc
     p.Hq = s.n_q_heads;
     p.Hkv = s.n_kv_heads;
     p.M = n_tokens * p.G;
-    p.m_pad = pl.m_pad;
     p.nsplit = pl.nsplit;
     p.n_row_tiles = pl.n_row_tiles;
     p.scale_log2e = s.softmax_scale * kLog2e;
     p.inv_G = 1.0f / (float)p.G;
     p.inv_nsplit = 1.0f / (float)pl.nsplit;
     p.arrivals = nullptr;
-    p.xcd_shift = p.units_per_xcd = 0;
+    p.xcd_shift = p.units_per_xcd = p.whole = 0;
+    p.part_units = pl.n_row_tiles * s.n_kv_heads * n_frames;
     p.lie = 0;
     p.misplaced = nullptr;
     p.share_merge = 0;
@@ -1357,13 +1387,19 @@ hipError_t launch_prefill_mfma(const vs_shape& s, const void* kc, const void* vc
         (void)hipGetDevice(&dev);
         p.arrivals = (unsigned*)counters;
         p.xcd_shift = g_xcd_shift[dev];
-        p.units_per_xcd = prefill_units_per_xcd(pl.n_row_tiles * s.n_kv_heads * n_frames, p.xcd_shift);
+        p.units_per_xcd = prefill_units_per_xcd(p.part_units, p.xcd_shift);
+        if (pl.whole && (1 << p.xcd_shift) == kPlanXcds) {
+            p.whole = pl.whole;
+            p.nsplit = pl.mixed_nsplit;
+            p.inv_nsplit = 1.0f / (float)p.nsplit;
+            p.part_units = (p.units_per_xcd - p.whole) << p.xcd_shift;
+        }
         p.lie = g_tune_guard_test == 3 ? 1u : 0u;
         p.misplaced = g_misplaced_dev[dev];
         p.share_merge = g_tune_prefill_merge != 1;
         p.max_looks = g_tune_guard_test == 4 ? 0 : 8192;  // ~0.3 us a look: some milliseconds at most
     }
-    const int64_t slots = (int64_t)pl.nsplit * s.n_kv_heads * n_frames * pl.m_pad;
+    const int64_t slots = (int64_t)p.nsplit * p.part_units * BM;
     p.part_ml = (float*)workspace;
     p.part_o = (_Float16*)(p.part_ml + slots * 4);
     return pl.kvg == 1 ? launch_kvg<1>(p, pl, s.n_kv_heads, st) : launch_kvg<2>(p, pl, s.n_kv_heads, st);

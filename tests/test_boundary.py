@@ -352,6 +352,16 @@ def test_prefill_workgroup_placement_map(tmp_path):
     assert r.returncode == 0 and r.stdout.startswith("ok"), r.stdout + r.stderr
 
 
+def test_prefill_workgroup_map_with_whole_units(tmp_path):
+    """The same where some units of every XCD are left whole (tests/prefill_mixed_map_check.cpp)."""
+    import subprocess
+    exe = str(tmp_path / "mixed_map_check")
+    subprocess.run(["g++", "-O2", "-std=c++17", "-I", os.path.join(ROOT, "paper_2503_09387_amd", "csrc"),
+                    os.path.join(ROOT, "tests", "prefill_mixed_map_check.cpp"), "-o", exe], check=True)
+    r = subprocess.run([exe], capture_output=True, text=True)
+    assert r.returncode == 0 and r.stdout.startswith("ok"), r.stdout + r.stderr
+
+
 def test_build_notices_a_sum_touched_between_matrix_instructions():
     """check_linear_listing on a listing of the expected shape, and with one instruction planted in it."""
     import importlib.util

@@ -1418,6 +1418,54 @@ def test_prefill_short_key_sequences(hq, hkv, L, T, gain):
     assert row == L and cache.len == L + 1 and same_bits(cache.k[L], kf[T - 1]) and same_bits(cache.v[L], vf[T - 1])
 
 
+@pytest.mark.parametrize("F,T,L,hq,hkv", [(33, 124, 600, 8, 8), (39, 60, 520, 16, 8), (35, 117, 577, 8, 8), (9, 170, 700, 28, 4)])
+def test_run_of_frames_with_whole_and_split_units(F, T, L, hq, hkv):
+    """More units than compute units, and a last round of few: those are split, the others whole.  Against the oracle
+    (some frames), the kept rows bit for bit, three times through one workspace with the same bits, and close to
+    the second kernel's merge, which splits all units alike."""
+    s = AttnShape(hq, hkv, 128, "bf16")
+    hk, hv = cache_rows(65, s, L, 0.5)
+    q = draw(66, (F, T, hq, 128), 0.5, "bf16")
+    kf, vf = (draw(k, (F, T, hkv, 128), 0.5, "bf16") for k in (67, 68))
+    ws = torch.empty(vs.frames_workspace_bytes(vs_shape(s), F, T, L + F), dtype=torch.uint8, device=DEV)
+    vs.workspace_init(vs_shape(s), ws)
+    qd, kd, vd = q.to(DEV), kf.to(DEV), vf.to(DEV)
+
+    def run():
+        k, v = (torch.zeros((L + F, hkv, 128), dtype=torch.bfloat16, device=DEV) for _ in "kv")
+        k[:L].copy_(hk)
+        v[:L].copy_(hv)
+        out = torch.full(q.shape, float("nan"), dtype=torch.bfloat16, device=DEV)
+        vs.frames_prefill_attn(vs_shape(s), vs.Cache(k, v, L), qd, kd, vd, out, ws)
+        torch.cuda.synchronize()
+        assert same_bits(k[L:], kf[:, T - 1]) and same_bits(v[L:], vf[:, T - 1])
+        return out
+
+    first = run()
+    for f in (0, F // 2, F - 1):
+        k_all, v_all = torch.cat([hk, kf[:f, T - 1]]), torch.cat([hv, vf[:f, T - 1]])
+        check_close(first[f], oracle_prefill_rows(s, q[f], k_all, v_all, L + f, kf[f], vf[f]), "bf16", f"frame {f} of {F}")
+    assert all(same_bits(run(), first.cpu()) for _ in range(2))
+    vs.set_tuning(vs.TUNE_PREFILL_MERGE, 2)
+    assert (run().float() - first.float()).abs().max() <= 2 ** -7 * first.float().abs().max()
+
+
+def test_long_question_with_whole_and_split_units():
+    """The same for one long run whose rows are all kept: 264 units of 2100 tokens."""
+    s, T, L = AttnShape(16, 8, 128, "bf16"), 2100, 512
+    hk, hv = cache_rows(69, s, L, 0.5)
+    q, kt, vt = frame_inputs(69, s, T, 0.5)
+    k, v = (torch.zeros((L + T, 8, 128), dtype=torch.bfloat16, device=DEV) for _ in "kv")
+    k[:L].copy_(hk)
+    v[:L].copy_(hv)
+    out = torch.full(q.shape, float("nan"), dtype=torch.bfloat16, device=DEV)
+    vs.question_prefill_append(vs_shape(s), vs.Cache(k, v, L), q.to(DEV), kt.to(DEV), vt.to(DEV), out, workspace(s, T, L + T, 0))
+    torch.cuda.synchronize()
+    assert same_bits(k[L:], kt) and same_bits(v[L:], vt) and same_bits(k[:L], hk) and same_bits(v[:L], hv)
+    tokens = [0, 1, 63, 64, 1023, 1024, 2047, 2048, 2099]  # 64 tokens are a row tile; the last tile's units are split
+    check_close(out[tokens], oracle_prefill_rows(s, q, hk, hv, L, kt, vt, tokens), "bf16", "long question")
+
+
 def test_runs_of_frames_random_shapes_sweep():
     rng = np.random.default_rng(77)
     for case in range(24):
