@@ -32,6 +32,14 @@ VS_HD int div_small(int x, int d, float inv_d) {
     return qd;
 }
 
+// The same in two scalar instructions: floor(x / d) = floor(2 x m / 2^32) with m = floor(2^31 / d) + 1 worked out by the host,
+// exact while 0 <= x and x d < 2^31 (m d exceeds 2^31 by at most d, the product 2 x m / 2^32 the quotient by at most x / 2^31 < 1 / d).
+struct QuickDiv {
+    unsigned m;
+};
+VS_HD QuickDiv quick_div(int d) { return QuickDiv{(1u << 31) / (unsigned)d + 1u}; }
+VS_HD int div_by(int x, QuickDiv by) { return (int)(((unsigned long long)(2u * (unsigned)x) * by.m) >> 32); }
+
 // What a workgroup on XCD `xcc` adds to its unit's arrival word: itself, its XCD and the square of that, each
 // with room for 32 workgroups and 16 XCDs.  With n workgroups in, the word is n * arrival_of(x) if and only if all of
 // them ran on XCD x (n numbers whose sum is n x and whose squares' sum is n x^2 are all x).
@@ -50,23 +58,28 @@ VS_HD unsigned prefill_grid_ids(int units, int nsplit, int xcd_shift, int whole 
     return (unsigned)(whole + (prefill_units_per_xcd(units, xcd_shift) - whole) * nsplit) << xcd_shift;
 }
 
-// The first `whole` units of every XCD may be left whole, a workgroup each, which come first; the others are split nsplit ways.
-// (whole must be 0 where ids are not dealt by residue: a unit's place below is worked out from the XCD its id says.)
-VS_HD PrefillSlot prefill_slot_of_id(unsigned id, int units, int units_per_xcd, int nsplit, float inv_nsplit,
-                                     int xcd_shift, int whole = 0) {
+VS_HD PrefillSlot prefill_slot(unsigned id, int units, int units_per_xcd, int j, int split, int xcd_shift) {
     PrefillSlot s;
     s.xcd = (int)(id & ((1u << xcd_shift) - 1u));
-    const int slot = (int)(id >> xcd_shift), behind = slot - whole;
-    int j = slot;
-    s.split = 0;
-    if (behind >= 0) {
-        const int jj = div_small(behind, nsplit, inv_nsplit);
-        s.split = behind - jj * nsplit;
-        j = whole + jj;
-    }
+    s.split = split;
     s.unit = s.xcd * units_per_xcd + j;
     if (j >= units_per_xcd || s.unit >= units) s.unit = -1;
     return s;
+}
+
+VS_HD PrefillSlot prefill_slot_of_id(unsigned id, int units, int units_per_xcd, int nsplit, float inv_nsplit,
+                                     int xcd_shift) {
+    const int slot = (int)(id >> xcd_shift), j = div_small(slot, nsplit, inv_nsplit);
+    return prefill_slot(id, units, units_per_xcd, j, slot - j * nsplit, xcd_shift);
+}
+
+// The first `whole` units of every XCD may be left whole, a workgroup each, which come first; the others are split nsplit ways.
+// (whole must be 0 where ids are not dealt by residue: a unit's place below is worked out from the XCD its id says.)
+VS_HD PrefillSlot prefill_slot_of_id(unsigned id, int units, int units_per_xcd, int nsplit, QuickDiv by_nsplit, int xcd_shift,
+                                     int whole) {
+    const int slot = (int)(id >> xcd_shift), behind = slot - whole;
+    const int jj = behind < 0 ? behind : div_by(behind, by_nsplit);
+    return prefill_slot(id, units, units_per_xcd, whole + jj, behind < 0 ? 0 : behind - jj * nsplit, xcd_shift);
 }
 
 // A split unit's place among those that are split: 0 .. (units_per_xcd - whole) * XCDs - 1.

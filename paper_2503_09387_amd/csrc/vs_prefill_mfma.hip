@@ -88,7 +88,7 @@ struct PrefillParams {
     int M, nsplit, n_row_tiles;
     int part_units;           // units that are split: all of them, or those behind the whole ones of every XCD
     float scale_log2e;
-    float inv_G, inv_nsplit;  // reciprocals for the index arithmetic of the prologue
+    QuickDiv by_G, by_nsplit, by_lanes;  // for the index arithmetic of the prologue (by_lanes: nsplit x key groups)
     // Merging inside this kernel (see the end of the kernel): the workgroups of one (row tile,
     // KV head) unit are placed on one XCD and count their arrivals in `arrivals`; null = the
     // partial results are merged by prefill_combine_kernel.
@@ -104,13 +104,13 @@ struct PrefillParams {
     // waiting workgroup looks at the counter before it gives up
     int share_merge;
     int max_looks;
-    float inv_row_tiles;
+    QuickDiv by_row_tiles;
     // A run of F frames (semantic-aware mask, Section 3.4): frame a has its own T rows of q, kf,
     // vf and out, and sees L + a retained rows: the L rows of the cache and the carriers (last rows)
     // of the frames before it, which it reads from kf / vf; the launch also copies all F carriers
     // behind the cache's rows.  F = 1: the single frame.
     int F;
-    float inv_frame_tiles;    // 1 / (F * row tiles)
+    QuickDiv by_frame_tiles;  // F * row tiles
 };
 
 typedef __attribute__((address_space(1))) const void* global_cptr;
@@ -245,10 +245,10 @@ void prefill_mfma_kernel(PrefillParams p) {
     int L = p.L;
     const int T = p.T, G = p.G, M = p.M, Hkv = p.Hkv;
     int nsplit = p.nsplit;
-    const float inv_G = p.inv_G;
-    float inv_nsplit = p.inv_nsplit;
+    const QuickDiv by_G = p.by_G;
+    QuickDiv by_lanes = p.by_lanes;
     asm volatile("" : : "s"(kc), "s"(vc), "s"(kf), "s"(vf), "s"(qbase), "s"(L), "s"(T), "s"(G), "s"(M), "s"(Hkv),
-                 "s"(nsplit), "s"(inv_G), "s"(inv_nsplit), "s"(p.Hq), "s"(p.scale_log2e));
+                 "s"(nsplit), "s"(by_G.m), "s"(by_lanes.m), "s"(p.Hq), "s"(p.scale_log2e));
     const int tid = threadIdx.x;
     const int lane = tid & 63;
     const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -263,24 +263,24 @@ void prefill_mfma_kernel(PrefillParams p) {
         // (consecutive units: the same KV head, whose K/V that L2 then holds once), each with
         // nsplit consecutive slots.
         const PrefillSlot at = prefill_slot_of_id(blockIdx.x, p.n_row_tiles * p.F * Hkv, p.units_per_xcd, nsplit,
-                                                  inv_nsplit, p.xcd_shift, p.whole);
+                                                  p.by_nsplit, p.xcd_shift, p.whole);
         if (at.unit < 0) return;  // spare ids
         const int unit = at.unit;
         split = at.split;
-        g = div_small(unit, p.n_row_tiles * p.F, p.inv_frame_tiles);
+        g = div_by(unit, p.by_frame_tiles);
         const int ft = unit - g * p.n_row_tiles * p.F;
-        frame = div_small(ft, p.n_row_tiles, p.inv_row_tiles);
+        frame = div_by(ft, p.by_row_tiles);
         rt = ft - frame * p.n_row_tiles;
         if ((int)(blockIdx.x >> p.xcd_shift) < p.whole) {  // a whole unit
             nsplit = 1;
-            inv_nsplit = 1.f;
+            by_lanes = quick_div(NKG);
         }
     } else {
         // grid (Hkv, nsplit, frames x row tiles): x runs fastest in dispatch order, so with
         // nsplit*Hkv a multiple of the number of XCDs all workgroups that read one K/V slice
         // share an L2
         g = blockIdx.x, split = blockIdx.y;
-        frame = div_small(blockIdx.z, p.n_row_tiles, p.inv_row_tiles);
+        frame = div_by(blockIdx.z, p.by_row_tiles);
         rt = blockIdx.z - frame * p.n_row_tiles;
     }
     // the frame's own tensors and retained rows: Lc rows in the cache, then the carriers of the
@@ -301,8 +301,8 @@ void prefill_mfma_kernel(PrefillParams p) {
     const int row0 = rt * BM;
     const int wrow0 = row0 + rb * 64;
     const int last_row = min(row0 + BM, M) - 1;
-    const int tmax = div_small(last_row, G, inv_G);       // < T
-    const int n_tiles = (L + tmax + BN) / BN;             // key tiles this row tile can see
+    const int tmax = div_by(last_row, by_G);       // < T
+    const int n_tiles = (int)((unsigned)(L + tmax + BN) / BN);  // key tiles this row tile can see
     // The tiles are dealt to lanes = (split, key group) pairs, lane = split*NKG + kg.  Every lane
     // takes q or q+1 tiles (the first lanes one more), a contiguous run of plain cache tiles.
     // Tiles with frame rows cost more (causal mask, staging through the slower path), so they
@@ -313,13 +313,12 @@ void prefill_mfma_kernel(PrefillParams p) {
     // (frame tiles first: their slower staging then falls into the prologue, and the steady
     // state of the pipeline sees plain tiles only.)
     const int n_lanes = nsplit * NKG;
-    const float inv_lanes = NKG == 1 ? inv_nsplit : 0.5f * inv_nsplit;
-    const int n_plain = Lc / BN;            // tiles of cache rows only (<= n_tiles)
+    const int n_plain = (int)((unsigned)Lc / BN);  // tiles of cache rows only (<= n_tiles)
     const int n_frame = n_tiles - n_plain;
-    const bool small = n_tiles < (1 << 22);
-    const int q_all = small ? div_small(n_tiles, n_lanes, inv_lanes) : n_tiles / n_lanes;
+    // (at most 64 lanes, and memory has no room for 2^25 tiles)
+    const int q_all = div_by(n_tiles, by_lanes);
     const int r_all = n_tiles - q_all * n_lanes;
-    const int q_fr = small ? div_small(n_frame, n_lanes, inv_lanes) : n_frame / n_lanes;
+    const int q_fr = div_by(n_frame, by_lanes);
     const int r_fr = n_frame - q_fr * n_lanes;
     const bool dealt = q_fr < q_all;        // every lane has room for its frame tiles
     auto tiles_before = [&](int i) { return i * q_all + min(i, r_all); };
@@ -405,7 +404,7 @@ void prefill_mfma_kernel(PrefillParams p) {
         for (int r = 0; r < 2; ++r) {
             r_mine[r] = wrow0 + 32 * r + l32;
             const int rr = min(r_mine[r], M - 1);
-            const int t = div_small(rr, G, inv_G), hl = rr - t * G;
+            const int t = div_by(rr, by_G), hl = rr - t * G;
             jmax[r] = L + t;
             qrow[r] = qbase + ((int64_t)(t * p.Hq + g * G + hl) * D + 8 * hi) * 2;
         }
@@ -728,7 +727,7 @@ void prefill_mfma_kernel(PrefillParams p) {
         const int rg = rb * 2 + r;  // 32-row group inside the row tile
         if (nsplit == 1) {
             if (r_mine[r] < p.M) {
-                const int t = r_mine[r] / G, hl = r_mine[r] - t * G;
+                const int t = div_by(r_mine[r], by_G), hl = r_mine[r] - t * G;
                 __bf16* orow = out + ((int64_t)t * p.Hq + (int64_t)g * G + hl) * D;
 #pragma unroll
                 for (int db = 0; db < 4; ++db)
@@ -856,7 +855,7 @@ void prefill_mfma_kernel(PrefillParams p) {
             const int rg = first >> 3, piece0 = first & 7;
             const int m = rt * BM + rg * 32 + l32;  // the lane's row of the packed rows
             const bool row_ok = m < M;
-            const int t = row_ok ? div_small(m, G, inv_G) : 0, hl = m - t * G;
+            const int t = row_ok ? div_by(m, by_G) : 0, hl = m - t * G;
             __bf16* const orow = out + ((int64_t)t * p.Hq + (int64_t)g * G + hl) * D;
             const float* const ml0 = p.part_ml + ((int64_t)part * BM + rg * 32 + l32) * 4;
             const int64_t ml_step = (int64_t)p.part_units * BM * 4;  // floats between splits
@@ -958,7 +957,7 @@ void prefill_mfma_kernel(PrefillParams p) {
                 if (NKG == 2 && r != kg) continue;
                 const int rg = rb * 2 + r;
                 const bool row_ok = r_mine[r] < M;
-                const int t = row_ok ? div_small(r_mine[r], G, inv_G) : 0, hl = r_mine[r] - t * G;
+                const int t = row_ok ? div_by(r_mine[r], by_G) : 0, hl = r_mine[r] - t * G;
                 __bf16* const orow = out + ((int64_t)t * p.Hq + (int64_t)g * G + hl) * D;
                 const float* const ml0 = p.part_ml + ((int64_t)part * BM + rg * 32 + l32) * 4;
                 const int64_t ml_step = (int64_t)p.part_units * BM * 4;  // floats between splits
@@ -1370,8 +1369,7 @@ hipError_t launch_prefill_mfma(const vs_shape& s, const void* kc, const void* vc
     p.nsplit = pl.nsplit;
     p.n_row_tiles = pl.n_row_tiles;
     p.scale_log2e = s.softmax_scale * kLog2e;
-    p.inv_G = 1.0f / (float)p.G;
-    p.inv_nsplit = 1.0f / (float)pl.nsplit;
+    p.by_G = quick_div(p.G);
     p.arrivals = nullptr;
     p.xcd_shift = p.units_per_xcd = p.whole = 0;
     p.part_units = pl.n_row_tiles * s.n_kv_heads * n_frames;
@@ -1379,9 +1377,9 @@ hipError_t launch_prefill_mfma(const vs_shape& s, const void* kc, const void* vc
     p.misplaced = nullptr;
     p.share_merge = 0;
     p.max_looks = 0;
-    p.inv_row_tiles = 1.0f / (float)pl.n_row_tiles;
+    p.by_row_tiles = quick_div(pl.n_row_tiles);
     p.F = n_frames;
-    p.inv_frame_tiles = 1.0f / (float)(pl.n_row_tiles * n_frames);
+    p.by_frame_tiles = quick_div(pl.n_row_tiles * n_frames);
     if (pl.merge_inside && counters) {
         int dev = 0;
         (void)hipGetDevice(&dev);
@@ -1391,7 +1389,6 @@ hipError_t launch_prefill_mfma(const vs_shape& s, const void* kc, const void* vc
         if (pl.whole && (1 << p.xcd_shift) == kPlanXcds) {
             p.whole = pl.whole;
             p.nsplit = pl.mixed_nsplit;
-            p.inv_nsplit = 1.0f / (float)p.nsplit;
             p.part_units = (p.units_per_xcd - p.whole) << p.xcd_shift;
         }
         p.lie = g_tune_guard_test == 3 ? 1u : 0u;
@@ -1399,6 +1396,8 @@ hipError_t launch_prefill_mfma(const vs_shape& s, const void* kc, const void* vc
         p.share_merge = g_tune_prefill_merge != 1;
         p.max_looks = g_tune_guard_test == 4 ? 0 : 8192;  // ~0.3 us a look: some milliseconds at most
     }
+    p.by_nsplit = quick_div(p.nsplit);
+    p.by_lanes = quick_div(p.nsplit * pl.kvg);
     const int64_t slots = (int64_t)p.nsplit * p.part_units * BM;
     p.part_ml = (float*)workspace;
     p.part_o = (_Float16*)(p.part_ml + slots * 4);

@@ -54,7 +54,8 @@ struct ShortParams {
     int append_first;
     int L, T, G, Hq, Hkv, M;
     int n_row_groups, units_per_xcd;
-    float scale_log2e, inv_G, inv_row_groups;
+    float scale_log2e;
+    QuickDiv by_G, by_row_groups;
 };
 
 __device__ __forceinline__ bf16x4 lds_read_tr(const char* p) {
@@ -63,9 +64,22 @@ __device__ __forceinline__ bf16x4 lds_read_tr(const char* p) {
 
 // 16 bytes per lane from global memory straight into LDS, lane i's at dst + 16 i (assembly: for the
 // builtin form the compiler waits for all such loads before any LDS read); from a lane's own address,
-// or from an offset of its own to an address that is the wavefront's
-__device__ __forceinline__ void load_lds16(const char* base, unsigned off, unsigned dst) {
-    asm volatile("s_mov_b32 m0, %[d]\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %[o], %[b]" : : [d] "s"(dst), [o] "v"(off), [b] "s"(base) : "memory");
+// or eight in a row, 1 KB apart in LDS, from offsets of its own to an address that is the wavefront's (M0 is stepped
+// between them: a wavefront alone on its SIMD takes 5 cycles for every instruction)
+__device__ __forceinline__ void load_lds16x8(const char* base, const unsigned (&off)[8], unsigned dst) {
+    asm volatile("s_mov_b32 m0, %[d]\n\ts_nop 4\n\t"
+                 "global_load_lds_dwordx4 %[o0], %[b]\n\ts_add_u32 m0, m0, 0x400\n\ts_nop 0\n\t"
+                 "global_load_lds_dwordx4 %[o1], %[b]\n\ts_add_u32 m0, m0, 0x400\n\ts_nop 0\n\t"
+                 "global_load_lds_dwordx4 %[o2], %[b]\n\ts_add_u32 m0, m0, 0x400\n\ts_nop 0\n\t"
+                 "global_load_lds_dwordx4 %[o3], %[b]\n\ts_add_u32 m0, m0, 0x400\n\ts_nop 0\n\t"
+                 "global_load_lds_dwordx4 %[o4], %[b]\n\ts_add_u32 m0, m0, 0x400\n\ts_nop 0\n\t"
+                 "global_load_lds_dwordx4 %[o5], %[b]\n\ts_add_u32 m0, m0, 0x400\n\ts_nop 0\n\t"
+                 "global_load_lds_dwordx4 %[o6], %[b]\n\ts_add_u32 m0, m0, 0x400\n\ts_nop 0\n\t"
+                 "global_load_lds_dwordx4 %[o7], %[b]"
+                 :
+                 : [d] "s"(dst), [b] "s"(base), [o0] "v"(off[0]), [o1] "v"(off[1]), [o2] "v"(off[2]), [o3] "v"(off[3]),
+                   [o4] "v"(off[4]), [o5] "v"(off[5]), [o6] "v"(off[6]), [o7] "v"(off[7])
+                 : "memory", "scc");
 }
 __device__ __forceinline__ void load_lds16(const char* src, unsigned dst) {
     asm volatile("s_mov_b32 m0, %[d]\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %[s], off" : : [d] "s"(dst), [s] "v"(src) : "memory");
@@ -81,7 +95,7 @@ __global__ __launch_bounds__(kThreads, 1) void prefill_short_kernel(ShortParams 
     // head's K and V are read into few L2s
     const int slot = (int)(blockIdx.x >> 3), unit = (int)(blockIdx.x & 7) * p.units_per_xcd + slot;
     if (unit >= p.n_row_groups * p.Hkv) return;  // spare ids (slot < units_per_xcd by the grid)
-    const int g = __builtin_amdgcn_readfirstlane(div_small(unit, p.n_row_groups, p.inv_row_groups));
+    const int g = __builtin_amdgcn_readfirstlane(div_by(unit, p.by_row_groups));
     const int row0 = (unit - g * p.n_row_groups) * 32;
     const int L = p.L, T = p.T, M = p.M, G = p.G;
     const int kv_row = p.Hkv * kRowBytes;
@@ -89,7 +103,7 @@ __global__ __launch_bounds__(kThreads, 1) void prefill_short_kernel(ShortParams 
     // where in the argument block to load from)
     const char *kc = p.kc, *vc = p.vc, *kf = p.kf, *vf = p.vf, *qp = p.q;
     asm volatile("" : "+s"(kc), "+s"(vc), "+s"(kf), "+s"(vf), "+s"(qp));
-    const int tmax = __builtin_amdgcn_readfirstlane(div_small(min(row0 + 31, M - 1), G, p.inv_G));
+    const int tmax = __builtin_amdgcn_readfirstlane(div_by(min(row0 + 31, M - 1), p.by_G));
     const int n_blocks = (L + tmax + 32) >> 5;                                // of 32 keys, visible to some row here
     const int n_my = w < n_blocks ? (n_blocks - w + kWaves - 1) / kWaves : 0;  // this wavefront's: w, w + 4, ..
 
@@ -100,39 +114,47 @@ __global__ __launch_bounds__(kThreads, 1) void prefill_short_kernel(ShortParams 
 
     // ---- staging: one load instruction fills 4 rows of 256 B (1 KB): lane i -> row i >> 4, slot i & 15 ----
     const int lr = lane >> 4, ls = lane & 15;
-    unsigned k_off[4];  // of this lane's piece from the first row of a group of 4, for u & 3 = x
+    unsigned k_off[8], v_off[8];  // of this lane's piece in load u from a block's first row
 #pragma unroll
-    for (int x = 0; x < 4; ++x) k_off[x] = (unsigned)(lr * kv_row + ((ls ^ lr ^ (x << 2)) << 4));
-    const unsigned v_off = (unsigned)(lr * kv_row + ((ls ^ (lr << 1)) << 4));
+    for (int u = 0; u < 8; ++u) {
+        k_off[u] = (unsigned)((4 * u + lr) * kv_row + ((ls ^ lr ^ ((u & 3) << 2)) << 4));
+        v_off[u] = (unsigned)((4 * u + lr) * kv_row + ((ls ^ (lr << 1)) << 4));
+    }
     auto stage = [&](int i) {  // block number i of this wavefront: K rows, then V rows (16 loads)
         const int j0 = (w + kWaves * i) * 32;
         const unsigned dst = mine_lds + (unsigned)(i & 1) * kStageBytes;
         const bool in_cache = j0 + 32 <= L;
         if (in_cache || (j0 >= L && j0 + 32 <= L + T)) {  // all rows from one tensor
             const int64_t from = (int64_t)(in_cache ? j0 : j0 - L) * kv_row + g * kRowBytes;
-            const char* const kb = (in_cache ? kc : kf) + from;
-            const char* const vb = (in_cache ? vc : vf) + from;
-#pragma unroll
-            for (int u = 0; u < 8; ++u) load_lds16(kb + (int64_t)(4 * u) * kv_row, k_off[u & 3], dst + u * 1024);
-#pragma unroll
-            for (int u = 0; u < 8; ++u) load_lds16(vb + (int64_t)(4 * u) * kv_row, v_off, dst + kBlockBytes + u * 1024);
+            // (both worked out and one taken: a choice between the pointers alone becomes one between their places in memory)
+            const char *kb = kc + from, *vb = vc + from, *kb_run = kf + from, *vb_run = vf + from;
+            asm volatile("" : "+s"(kb), "+s"(vb), "+s"(kb_run), "+s"(vb_run));
+            load_lds16x8(in_cache ? kb : kb_run, k_off, dst);
+            load_lds16x8(in_cache ? vb : vb_run, v_off, dst + kBlockBytes);
         } else {
+            // Row j (rows past the last key repeat it: masked below) lies at base + j * kv_row, with one base for the cache's
+            // rows and one for the run's: selects (written as a choice of expressions the compiler branches around every load).
 #pragma unroll
-            for (int is_v = 0; is_v < 2; ++is_v)
+            for (int is_v = 0; is_v < 2; ++is_v) {
+                const unsigned long long in_c = (unsigned long long)((is_v ? vc : kc) + g * kRowBytes);
+                const unsigned long long in_f = (unsigned long long)((is_v ? vf : kf) + g * kRowBytes) - (unsigned long long)L * (unsigned)kv_row;
 #pragma unroll
                 for (int u = 0; u < 8; ++u) {
-                    const int j = min(j0 + 4 * u + lr, L + T - 1);  // (rows past the last key repeat it: masked below)
-                    const char* const src = j < L ? (is_v ? vc : kc) + (int64_t)j * kv_row : (is_v ? vf : kf) + (int64_t)(j - L) * kv_row;
+                    const unsigned j = min(j0 + 4 * u + lr, L + T - 1);
+                    const unsigned lo = (int)j < L ? (unsigned)in_c : (unsigned)in_f;
+                    const unsigned up = (int)j < L ? (unsigned)(in_c >> 32) : (unsigned)(in_f >> 32);
                     const int piece = is_v ? ls ^ (lr << 1) : ls ^ lr ^ ((u & 3) << 2);
-                    load_lds16(src + g * kRowBytes + (piece << 4), dst + is_v * kBlockBytes + u * 1024);
+                    load_lds16(reinterpret_cast<const char*>(((unsigned long long)up << 32 | lo) + (unsigned long long)j * (unsigned)kv_row) + (piece << 4),
+                               dst + is_v * kBlockBytes + u * 1024);
                 }
+            }
         }
     };
     // query rows: wavefront w brings rows 8 w .. 8 w + 7
 #pragma unroll
     for (int u = 0; u < 2; ++u) {
         const int r = 8 * w + 4 * u + lr, m = min(row0 + r, M - 1);
-        const int t = div_small(m, G, p.inv_G), hl = m - t * G;
+        const int t = div_by(m, p.by_G), hl = m - t * G;
         load_lds16(qp + ((int64_t)t * p.Hq + g * G + hl) * kRowBytes + ((ls ^ (r & 15)) << 4),
                    lds0 + kWaves * kWaveLds + (8 * w + 4 * u) * kRowBytes);
     }
@@ -140,7 +162,7 @@ __global__ __launch_bounds__(kThreads, 1) void prefill_short_kernel(ShortParams 
     if (n_my > 1) stage(1);
 
     // this lane's query row and the last key it sees
-    const int m_row = row0 + l32, t_row = div_small(min(m_row, M - 1), G, p.inv_G);
+    const int m_row = row0 + l32, t_row = div_by(min(m_row, M - 1), p.by_G);
     const int jmax = L + t_row;
 
     // the query rows are there for everybody (their two loads are the oldest of each wavefront's)
@@ -311,8 +333,8 @@ hipError_t launch_prefill_short(const vs_shape& s, const void* kc, const void* v
     p.n_row_groups = (p.M + 31) / 32;
     p.units_per_xcd = (p.n_row_groups * p.Hkv + 7) / 8;
     p.scale_log2e = s.softmax_scale * kLog2e;
-    p.inv_G = 1.0f / (float)p.G;
-    p.inv_row_groups = 1.0f / (float)p.n_row_groups;
+    p.by_G = quick_div(p.G);
+    p.by_row_groups = quick_div(p.n_row_groups);
     static bool attr_set_on[16] = {};  // dynamic LDS above 64 KB has to be allowed once per kernel and device
     int dev = 0;
     if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= 16) return hipErrorInvalidDevice;

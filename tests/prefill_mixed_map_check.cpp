@@ -17,7 +17,7 @@ int main() {
                     const int parts = (upx - whole) << shift;
                     std::vector<int> seen((size_t)units * nsplit, 0), place(parts, -1);
                     for (unsigned id = 0; id < ids; ++id) {
-                        const vs::PrefillSlot s = vs::prefill_slot_of_id(id, units, upx, nsplit, 1.0f / (float)nsplit, shift, whole);
+                        const vs::PrefillSlot s = vs::prefill_slot_of_id(id, units, upx, nsplit, vs::quick_div(nsplit), shift, whole);
                         if (s.unit < 0) continue;
                         const bool is_whole = (int)(id >> shift) < whole;
                         if (s.unit >= units || s.unit / upx != s.xcd || (s.unit % upx < whole) != is_whole ||
@@ -37,6 +37,11 @@ int main() {
                     ++checked;
                 }
             }
+    // div_by against the integer division: every divisor in use, products up to 2^31
+    for (int d = 1; d <= 70000; d += (d < 600 ? 1 : 331))
+        for (long x = 0; x * d < (1L << 31); x += (x < 4000 ? 1 : 1 + ((1L << 31) / d) / 5000))
+            for (long y : {x, x * d, x * d + d - 1})
+                if (y * d < (1L << 31) && vs::div_by((int)y, vs::quick_div(d)) != (int)(y / d)) { std::printf("div_by(%ld, %d)\n", y, d); return 1; }
     std::printf("ok %ld\n", checked);
     return 0;
 }
