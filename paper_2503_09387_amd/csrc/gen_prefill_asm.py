@@ -442,13 +442,28 @@ def rescale():
     return b
 
 
-def read_o():
-    b = Block()
+def settle(b):
+    """Between the last matrix instruction and another kind of instruction that reads its result."""
     b.emit("s_nop 7")
     b.emit("s_nop 7")
     b.emit("s_nop 3")
-    for i in range(128):
-        b.emit(f"v_accvgpr_read_b32 v{i}, a{i}")
+
+
+def read_o(r):
+    """O of row group r as ordinary values, in v[0:63]."""
+    b = Block()
+    settle(b)
+    for i in range(64):
+        b.emit(f"v_accvgpr_read_b32 v{i}, a{64 * r + i}")
+    return b
+
+
+def hand_o(r):
+    """O of row group r straight to LDS, 1 KB per instruction."""
+    b = Block()
+    settle(b)
+    for i in range(16):
+        b.emit(f"ds_write_b128 %[to], a[{64 * r + 4 * i}:{64 * r + 4 * i + 3}] offset:{1024 * i}")
     return b
 
 
@@ -475,7 +490,10 @@ def main(out_path):
         "VS_ASM_INIT_O": init_o(),
         "VS_ASM_LOAD_Q": load_q(),
         "VS_ASM_RESCALE": rescale(),
-        "VS_ASM_READ_O": read_o(),
+        "VS_ASM_READ_O0": read_o(0),
+        "VS_ASM_READ_O1": read_o(1),
+        "VS_ASM_HAND_O0": hand_o(0),
+        "VS_ASM_HAND_O1": hand_o(1),
     }
     parts = ["// Generated by gen_prefill_asm.py: do not edit.\n"]
     for name, blk in blocks.items():

@@ -705,12 +705,6 @@ void prefill_mfma_kernel(PrefillParams p) {
             reinterpret_cast<uint4*>(p.v_append_dst)[ch] = vsrc[ch];
         }
     }
-    f32x16 o[2][4];
-    asm volatile(VS_ASM_READ_O
-                 : "={v[0:15]}"(o[0][0]), "={v[16:31]}"(o[0][1]), "={v[32:47]}"(o[0][2]), "={v[48:63]}"(o[0][3]),
-                   "={v[64:79]}"(o[1][0]), "={v[80:95]}"(o[1][1]), "={v[96:111]}"(o[1][2]), "={v[112:127]}"(o[1][3])
-                 :
-                 : VS_CLOB_ACC);
     float l_tot[2], m_ref[2];
 #pragma unroll
     for (int r = 0; r < 2; ++r) {
@@ -752,13 +746,14 @@ void prefill_mfma_kernel(PrefillParams p) {
             big *= inv;
             big = fmaxf(big, xhalf(big));
             const PartScale sc = part_scale(big);
+            const float by = inv * sc.scale;  // (a power of two: exact)
 #pragma unroll
             for (int db = 0; db < 4; ++db)
 #pragma unroll
                 for (int h2 = 0; h2 < 2; ++h2) {
                     f16x8 wv;
 #pragma unroll
-                    for (int j = 0; j < 8; ++j) wv[j] = (_Float16)((oo[db][8 * h2 + j] * inv) * sc.scale);  // (the second product is exact)
+                    for (int j = 0; j < 8; ++j) wv[j] = (_Float16)(oo[db][8 * h2 + j] * by);
                     // (non-temporal also when this launch reads the partials back: the lines are then
                     // written through while the kernel runs, instead of being left for the write-back at
                     // its end: 0.3 us per launch)
@@ -771,9 +766,18 @@ void prefill_mfma_kernel(PrefillParams p) {
         }
     };
 
+    f32x16 o[4];
+    auto fetch_o = [&](int r) {
+        if (r == 0)
+            asm volatile(VS_ASM_READ_O0 : "={v[0:15]}"(o[0]), "={v[16:31]}"(o[1]), "={v[32:47]}"(o[2]), "={v[48:63]}"(o[3]) : : VS_CLOB_ACC);
+        else
+            asm volatile(VS_ASM_READ_O1 : "={v[0:15]}"(o[0]), "={v[16:31]}"(o[1]), "={v[32:47]}"(o[2]), "={v[48:63]}"(o[3]) : : VS_CLOB_ACC);
+    };
     if (NKG == 1) {
-        emit(0, o[0], m_ref[0], l_tot[0]);
-        emit(1, o[1], m_ref[1], l_tot[1]);
+        fetch_o(0);
+        emit(0, o, m_ref[0], l_tot[0]);
+        fetch_o(1);
+        emit(1, o, m_ref[1], l_tot[1]);
     } else {
         // ---- merge the key groups through LDS.  The two wavefronts that hold the same 64 rows
         //      (same lanes) swap halves: the wavefront of key group kg keeps row group kg, hands
@@ -782,15 +786,9 @@ void prefill_mfma_kernel(PrefillParams p) {
         float* xo = reinterpret_cast<float*>(dyn_smem);  // [4 waves][16 x f32x4][64 lanes]
         float* xml = xo + 4 * 16 * 64 * 4;               // [4 waves][32 rows][2]
         auto hand_over = [&](int r) {
-#pragma unroll
-            for (int db = 0; db < 4; ++db)
-#pragma unroll
-                for (int e4 = 0; e4 < 4; ++e4) {
-                    f32x4 wv;
-#pragma unroll
-                    for (int j = 0; j < 4; ++j) wv[j] = o[r][db][4 * e4 + j];
-                    *reinterpret_cast<f32x4*>(&xo[((w * 16 + db * 4 + e4) * 64 + lane) * 4]) = wv;
-                }
+            const unsigned to = (unsigned)(size_t)(lds_ptr)xo + (w * 16 * 64 + lane) * 16;
+            if (r == 0) asm volatile(VS_ASM_HAND_O0 : : [to] "v"(to) : VS_CLOB_ACC, "memory");
+            else asm volatile(VS_ASM_HAND_O1 : : [to] "v"(to) : VS_CLOB_ACC, "memory");
             if (hi == 0) {
                 xml[(w * 32 + l32) * 2 + 0] = m_ref[r];
                 xml[(w * 32 + l32) * 2 + 1] = l_tot[r];
@@ -802,17 +800,30 @@ void prefill_mfma_kernel(PrefillParams p) {
             const float m_new = fmaxf(m_ref[r], m1);
             const float a0 = (m_ref[r] == -INFINITY) ? 0.f : __builtin_amdgcn_exp2f(m_ref[r] - m_new);
             const float a1 = (m1 == -INFINITY) ? 0.f : __builtin_amdgcn_exp2f(m1 - m_new);
+            auto add = [&](auto weighted) {
 #pragma unroll
-            for (int db = 0; db < 4; ++db)
+                for (int db = 0; db < 4; ++db)
 #pragma unroll
-                for (int e4 = 0; e4 < 4; ++e4) {
-                    const f32x4 wv = *reinterpret_cast<const f32x4*>(&xo[((pw * 16 + db * 4 + e4) * 64 + lane) * 4]);
+                    for (int e4 = 0; e4 < 4; ++e4) {
+                        const f32x4 wv = *reinterpret_cast<const f32x4*>(&xo[((pw * 16 + db * 4 + e4) * 64 + lane) * 4]);
 #pragma unroll
-                    for (int j = 0; j < 4; ++j) o[r][db][4 * e4 + j] = o[r][db][4 * e4 + j] * a0 + wv[j] * a1;
-                }
-            emit(r, o[r], m_new, l_tot[r] * a0 + l1 * a1);
+                        for (int j = 0; j < 4; ++j)
+                            o[db][4 * e4 + j] = decltype(weighted)::value ? o[db][4 * e4 + j] * a0 + wv[j] * a1 : o[db][4 * e4 + j] + wv[j];
+                    }
+            };
+            // (both groups against the same references, as they are while scores are moderate: the same sums)
+            if (__all(a0 == 1.f && a1 == 1.f)) add(std::false_type{});
+            else add(std::true_type{});
+            emit(r, o, m_new, l_tot[r] * a0 + l1 * a1);
         };
-        if (kg == 0) hand_over(1); else hand_over(0);
+        if (kg == 0) {
+            hand_over(1);
+            fetch_o(0);
+        } else {
+            hand_over(0);
+            fetch_o(1);
+        }
+        asm volatile("s_waitcnt lgkmcnt(0)" : : : "memory");  // (the compiler does not know of what hand_over() writes)
         __syncthreads();
         if (kg == 0) take_over(0); else take_over(1);
     }
