@@ -255,13 +255,11 @@ def step(p, qk, pv, sm, masked=False, loads=()):
     return b
 
 
-LO, HI = {"ksrc": "s88", "vsrc": "s90"}, {"ksrc": "s89", "vsrc": "s91"}
-
-
 def loop_block():
     """The loop over plain steps: step s is the pair of sub-block steps 2s+1 and 2s+2 (odd, even).  The caller has seen to it
-    that every row has accumulated something and that tiles s, s+1 and s+2 are the group's and cache rows only.  An
-    iteration requests K of tile s+2 and V of tile s+1.  Operands: ka, va the read addresses, ksrc / vsrc the
+    that every row has accumulated something and that tiles s, s+1 and s+2 are the group's and cache rows only, or s+1 its last.  An
+    iteration requests K of tile s+2 and V of tile s+1 (hold = 1: the last step has no tile s+2 and requests K of
+    the group's last tile once more, which nobody reads).  Operands: ka, va the read addresses, ksrc / vsrc the
     addresses of this wave's share of the next K and V tile, ldsk / ldsv where it goes, tstep the bytes between tiles, left the
     number of steps to go, l and sum the sums without and of the last sub-block.  why: 0 all steps done, 1 / 2: left behind the
     odd / even sub-block of a step because its sums came out above 2^8 (or not a number); the caller redoes that
@@ -385,12 +383,15 @@ def loop_block():
                 b.emit(f"v_xor_b32_e32 %[ka{kk}], 0x4000, %[ka{kk}]")
             b.emit("v_xor_b32_e32 %[va0], 0x4000, %[va0]")
             b.emit("v_xor_b32_e32 %[va1], 0x4000, %[va1]")
-            for src in ("ksrc", "vsrc"):
-                b.emit(f"s_add_u32 {LO[src]}, {LO[src]}, %[tstep]")
-                b.emit(f"s_addc_u32 {HI[src]}, {HI[src]}, 0")
+            b.emit("s_sub_u32 %[left], %[left], 1")
+            b.emit("s_cmp_gt_u32 %[left], %[hold]")
+            b.emit("s_cselect_b32 %[why], %[tstep], 0")
+            b.emit("s_add_u32 s88, s88, %[why]")
+            b.emit("s_addc_u32 s89, s89, 0")
+            b.emit("s_add_u32 s90, s90, %[tstep]")
+            b.emit("s_addc_u32 s91, s91, 0")
             b.emit("s_xor_b32 %[ldsk], %[ldsk], 0x4000")
             b.emit("s_xor_b32 %[ldsv], %[ldsv], 0x4000")
-            b.emit("s_sub_u32 %[left], %[left], 1")
         b.emit(f"v_add_f32_e32 v{TMP}, %[sum0], %[sum1]")
         b.emit(f"s_mov_b32 %[why], {2 - p}")
         b.emit(f"v_cmp_nge_f32_e32 vcc, %[k256], v{TMP}")

@@ -613,15 +613,17 @@ void prefill_mfma_kernel(PrefillParams p) {
         v_rd[1] ^= kTileBytes;
     };
 
-    // A step is plain if its tile and the two behind it are cache rows only, and this group's.  Plain steps follow one
-    // another; they run in one block, unless a row has accumulated nothing yet (its first sums need the closer look of commit()).
-    const int plain_from = n_rest, plain_to = min(n_my, n_plain - run_first + n_rest) - 2;
+    // A step is plain if its tile and the two behind it are cache rows only, and this group's, or the one behind it is the
+    // group's last.  Plain steps follow one another; they run in one block, unless a row has accumulated nothing yet (its
+    // first sums need the closer look of commit()).
+    const int plain_from = n_rest, hold = n_my - n_rest <= n_plain - run_first ? 1 : 0;
+    const int plain_to = hold ? n_my - 1 : n_plain - run_first + n_rest - 2;
     for (int s = 0; s < n_steps;) {
         // steps 2s+1 and 2s+2 of this group: they read K of tile s+1 and V of tile s, and K of tile s+2 and V of tile
         // s+1 are requested
         if (s >= plain_from && s < plain_to && __all(l_run[0] + pend[0] > 0.f && l_run[1] + pend[1] > 0.f)) {
             // this wave's share of what the first of them requests: rows 32*rb .. 32*rb+31 of the two tiles, head g
-            unsigned long long ksrc = (unsigned long long)(kc + ((int64_t)(tile_of(s + 2) * BN + rb * 32) * Hkv + g) * kRowBytes);
+            unsigned long long ksrc = (unsigned long long)(kc + ((int64_t)(tile_of(min(s + 2, n_my - 1)) * BN + rb * 32) * Hkv + g) * kRowBytes);
             unsigned long long vsrc = (unsigned long long)(vc + ((int64_t)(tile_of(s + 1) * BN + rb * 32) * Hkv + g) * kRowBytes);
             unsigned ldsk = k_tile(s) + rb * (8 * 1024), ldsv = v_tile(s + 1) + rb * (8 * 1024);
             int left = plain_to - s, why;
@@ -632,7 +634,7 @@ void prefill_mfma_kernel(PrefillParams p) {
                            [ldsk] "+s"(ldsk), [ldsv] "+s"(ldsv), [left] "+s"(left), [why] "=&s"(why),
                            [l0] "+v"(l_run[0]), [l1] "+v"(l_run[1]), [sum0] "+v"(pend[0]), [sum1] "+v"(pend[1])
                          : VS_KOFF, VS_VOFF, "{s[88:89]}"(ksrc), "{s[90:91]}"(vsrc), [ms0] "v"(ms[0]), [ms1] "v"(ms[1]),
-                           [scale] "s"(p.scale_log2e), [tstep] "s"(BN * kv_row_bytes), [k256] "s"(256.f)
+                           [scale] "s"(p.scale_log2e), [tstep] "s"(BN * kv_row_bytes), [hold] "s"(__builtin_amdgcn_readfirstlane(hold)), [k256] "s"(256.f)
                          : VS_CLOBBERS, "scc", "memory");
             s = plain_to - left;
             if (why == 1) {
