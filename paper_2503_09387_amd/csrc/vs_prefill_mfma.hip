@@ -1162,18 +1162,18 @@ SplitPlan make_split_plan(int units, int max_tiles) {
     return best;
 }
 
-// Short key sequences go to the kernel that splits nothing (vs_prefill_short.hip).  Its time is ~5.2 us + ~1.05 us per
-// round of 4 x 32 keys, this kernel's 8.2 us and up with little dependence on the keys: 170 tokens over 16 / 264 /
-// 430 rows 8.3 / 9.1 / 10.4 us there, 11.4 / 12.0 / 12.6 here with the best plan, over 800 rows 13.8 and
-// 13.3; with few units (10 tokens: 4) this kernel starts lower, and the line lies at 4 rounds (430 rows: 9.2 and 9.9
-// us; 800 rows: 12.6 and 10.5).  It needs one compute unit per 32 packed rows and KV head.
+// Short key sequences go to the kernel that splits nothing (vs_prefill_short.hip).  Its time is ~5.0 us + ~0.92 us per
+// round of 4 x 32 keys, this kernel's 8 us and up with little dependence on the keys, the more the more units there are.
+// Measured on both sides of the line (us a launch there / here): 10 tokens (4 units) 5 rounds 9.4 / 10.0, 6 rounds 10.3 /
+// 10.0; 37 tokens (12) 6 rounds 10.4 / 11.1, 7 rounds 11.4 / 11.4; 100 tokens (24) 7 rounds 11.3 / 11.8, 8 rounds 12.2 / 11.8; 170
+// tokens (40) 8 rounds 12.1 / 13.0, 9 rounds 13.0 / 13.0.  It needs one compute unit per 32 packed rows and KV head.
 bool prefers_short_kernel(const vs_shape& s, int n_tokens, int len) {
     if (g_tune_prefill_splits || g_tune_prefill_kv_groups) return false;  // (a plan of this kernel has been asked for)
     const int64_t M = (int64_t)n_tokens * (s.n_q_heads / s.n_kv_heads);
     const int64_t workgroups = (M + 31) / 32 * s.n_kv_heads, units = (M + BM - 1) / BM * s.n_kv_heads;
     if (workgroups > kPlanXcds * kPlanCusPerXcd) return false;
     const int rounds = ((len + n_tokens + 31) / 32 + 3) / 4;
-    return rounds <= 4 + (units < 39 ? (int)units / 13 : 3);
+    return rounds <= (units < 5 ? 5 : units < 13 ? 6 : units < 39 ? 7 : 8);
 }
 
 Plan make_plan(const vs_shape& s, int n_tokens, int len, int n_frames) {

@@ -18,7 +18,9 @@
 //   * the four wavefronts' results (fp32) meet in LDS, each closing 32 of the 128 output dims.
 // Every workgroup of a KV head reads all of the head's K and V through its compute unit, at ~60 KB/us (what a
 // compute unit has under way, 32 KB, divided by the trip to L2): that is what bounds it and ends its range.
-// 170 tokens over 264 rows: 9.1 us per launch, 12.1 with the keys split over workgroups; over 16 rows 8.3 and 11.4.
+// The register budget is that of two wavefronts per SIMD, although one runs: with 512 registers the compiler keeps the sums
+// in accumulation registers and copies all 64 out and back in every block (170 tokens over 430 rows 10.4 -> 9.4 us a
+// launch, over 16 rows 6.6 -> 6.1).
 #include "vs_internal.h"
 #include "vs_prefill_map.h"
 
@@ -86,7 +88,7 @@ __device__ __forceinline__ void load_lds16(const char* src, unsigned dst) {
 }
 #define VS_WAIT_LOADS(n) asm volatile("s_waitcnt vmcnt(%0)" : : "n"(n) : "memory")
 
-__global__ __launch_bounds__(kThreads, 1) void prefill_short_kernel(ShortParams p) {
+__global__ __launch_bounds__(kThreads, 2) void prefill_short_kernel(ShortParams p) {
     extern __shared__ __attribute__((aligned(1024))) char smem[];
     const int tid = threadIdx.x, lane = tid & 63;
     const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
