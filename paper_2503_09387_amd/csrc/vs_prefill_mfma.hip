@@ -1126,7 +1126,8 @@ constexpr int kPlanXcds = 8, kPlanCusPerXcd = 32;
 // tokens over 4552 rows took 29.4 us, 17.4 .. 17.7 with 12 .. 16 splits, of which the model takes 16).  Among those plans the cheapest by a model
 // fitted to 8000 measured (shape, tokens, rows, plan) combinations: the steps of the longest lane (one tile
 // per key group), the tiles of the average lane, the second key group, the merge, and what a wavefront loads for it.
-// Over single runs of at least 9 tiles its choice is 0.8 % from the best measured plan on average and 7 % at worst;
+// Over single runs of at least 9 tiles its choice was 0.8 % from the best measured plan on average and 7 % at worst (with the
+// loop over plain steps in one block 1.8 % and 8.6 % over 65 shapes: fewer splits would sometimes do; a question of 37 tokens 16.4);
 // against 256 compute units as one pool it gains 4 % on average and loses 2 % at worst.  With few tiles (runs of
 // frames at the start of a video, runs too long for the kernel that splits nothing) a launch is all fixed cost, which
 // the model puts too high for the merge.  Measured best there (503 shapes): two tiles in the two key groups of one
@@ -1196,7 +1197,7 @@ Plan make_plan(const vs_shape& s, int n_tokens, int len, int n_frames) {
     // More units than half the chip has compute units (runs of frames, long runs of tokens): the
     // workgroups go through the chip in several rounds, and more, shorter ones may end sooner
     // than few long ones with a thin last round.  Estimated time of a launch in units of one
-    // pipeline step (one tile per key group, ~2 us): rounds x (steps of a workgroup + its fixed
+    // pipeline step (one tile per key group, 1.5 .. 2 us): rounds x (steps of a workgroup + its fixed
     // cost of ~2.25 steps), plus the merge when there are splits.
     pl.whole = pl.mixed_nsplit = 0;
     float best = 0.f;
