@@ -1216,9 +1216,10 @@ Plan make_plan(const vs_shape& s, int n_tokens, int len, int n_frames) {
     // idle, split over all of them behind (the merge inside the launch: the split units of an XCD stay on it).  Same
     // estimate, and no more workspace than the plan above needs.  28/4 heads, 170 tokens over 4296 rows, per layer: 7 frames
     // 123 -> 82 us, 8 frames 117 -> 88, 9 110 -> 99, 10 135 -> 127 (6, 11 and 12: nothing left over); a question of 1500
-    // tokens 156 -> 117.
+    // tokens 156 -> 117.  A split workgroup may wait for one of its unit that starts only when a whole unit's has ended, and a
+    // wait is given up after some 2.5 ms: up to 512 tiles, where a whole unit takes 0.4 ms.
     const int per_xcd = (units + kPlanXcds - 1) / kPlanXcds, whole = per_xcd / kPlanCusPerXcd * kPlanCusPerXcd;
-    if (units > 128 && pl.kvg == 2 && whole > 0 && whole < per_xcd) {
+    if (units > 128 && pl.kvg == 2 && whole > 0 && whole < per_xcd && max_tiles <= 512) {
         for (int cand = 2; cand <= 8 && cand <= max_tiles / pl.kvg; ++cand) {
             if (kPlanXcds * (per_xcd - whole) * cand > units * ns) break;
             const int rounds = ((per_xcd - whole) * cand + kPlanCusPerXcd - 1) / kPlanCusPerXcd;
