@@ -530,6 +530,36 @@ def test_prefill_extreme_score_ranges(mode, L, kv_groups):
 
 
 @pytest.mark.parametrize("kv_groups", [1, 2])
+@pytest.mark.parametrize("low", [1.0, 10.0, 38.0])
+@pytest.mark.parametrize("value", [0.0, 2.0 ** -120, 2.0 ** -80])
+def test_split_prefill_with_values_of_zero_or_next_to_it(value, low, kv_groups):
+    """All scores `low` log2 units below 0 (a row's sum over a split's keys is then far below 1, its reciprocal large) and values
+    of 0, or of next to nothing, in the keys of the first split or in all: a partial result is scaled by the
+    reciprocal and by a power of two, which must not meet each other before they meet the values.  2 to 32 splits, all three merges."""
+    s, T, L = AttnShape(8, 4, 128, "bf16"), 37, 2100
+    hk, hv = cache_rows(71, s, L, 0.05)
+    q, kf, vf = frame_inputs(71, s, T, 0.05)
+    q = (q.float() + 1.0).to(torch.bfloat16)
+    # (k_j - c against q + 1 moves score_j by 0.1275 * 128 * c log2 units)
+    hk, kf = ((t.float() - low / 16.32).to(torch.bfloat16) for t in (hk, kf))
+    vs.set_tuning(vs.TUNE_PREFILL_KV_GROUPS, kv_groups)
+    for splits, merge in ((2, 0), (2, 1), (2, 2), (3, 0), (5, 1), (8, 0), (8, 2), (12, 0), (32, 0), (32, 2)):
+        vs.set_tuning(vs.TUNE_PREFILL_SPLITS, splits)
+        vs.set_tuning(vs.TUNE_PREFILL_MERGE, merge)
+        for rows in (L // splits + 64, L):  # (the first split's keys are among the first, or all)
+            v_c, v_f = hv.clone(), vf.clone()
+            v_c[:rows] = value
+            if rows == L:
+                v_f[:] = value
+            out, _, _ = run_prefill(s, hk, v_c, L, q, kf, v_f)
+            what = f"V {value} in {rows} rows, {splits} splits, merge {merge}, {kv_groups} key groups"
+            if rows == L and value < 2.0 ** -112:  # (below 2^-112 the power's inverse is 0 in fp32: such rows come out as 0)
+                assert out.float().abs().max() <= value, what
+            else:
+                check_close(out, oracle_prefill_rows(s, q, hk, v_c, L, kf, v_f), "bf16", what, absolute=False)
+
+
+@pytest.mark.parametrize("kv_groups", [1, 2])
 @pytest.mark.parametrize("tiles,first_block,step", [(3, 2, 60.0), (4, 3, 60.0), (7, 4, 20.0), (7, 5, 20.0), (8, 6, 400.0), (8, 7, 400.0)])
 def test_prefill_reference_left_behind_inside_the_loop_of_plain_steps(tiles, first_block, step, kv_groups):
     """Scores that jump at a chosen sub-block of 32 keys (even and odd ones, by `step` log2 units, and again two and three
