@@ -718,7 +718,7 @@ void prefill_mfma_kernel(PrefillParams p) {
     // the unit's place among the split ones (of every XCD the first `whole` are not)
     const int part = prefill_part_of_unit(gf * p.n_row_tiles + rt, (int)(blockIdx.x & ((1u << p.xcd_shift) - 1u)), p.whole);
     // ---- output of one row group: lane (q = l32, hi) holds dims 32*db + 8*(e>>2) + 4*hi + (e&3) ----
-    auto emit = [&](int r, f32x16 (&oo)[4], float m_row, float l_row) {
+    auto emit = [&](int r, const f32x16 (&oo)[4], float m_row, float l_row) {
         const float inv = (l_row > 0.f) ? 1.0f / l_row : 0.f;
         const int rg = rb * 2 + r;  // 32-row group inside the row tile
         if (nsplit == 1) {
@@ -748,22 +748,17 @@ void prefill_mfma_kernel(PrefillParams p) {
             big *= inv;
             big = fmaxf(big, xhalf(big));
             const PartScale sc = part_scale(big);
-            // (oo * inv) * scale, with the two factors multiplied first where that is a number, which makes the same bits (scaling
-            // by a power of two is exact).  It is none where a row's sum is far below 1 and its values are 0 or next to it:
-            // inv then is large and the scale 2^127 or little less.
-            float by = inv * sc.scale;
-            if (!__all(by < INFINITY)) {
-#pragma unroll
-                for (int db = 0; db < 4; ++db) oo[db] *= inv;
-                by = sc.scale;
-            }
 #pragma unroll
             for (int db = 0; db < 4; ++db)
 #pragma unroll
                 for (int h2 = 0; h2 < 2; ++h2) {
                     f16x8 wv;
 #pragma unroll
-                    for (int j = 0; j < 8; ++j) wv[j] = (_Float16)(oo[db][8 * h2 + j] * by);
+                    for (int j = 0; j < 8; ++j)
+                        // (the second product is exact.  The two factors may not meet first: where a row's sum is far below 1 and its
+                        // values are 0 or next to it, inv is large, the scale 2^127 or little less and their product infinite; a
+                        // check for that instead costs more than the multiplications, 0.3 % of a launch over seven shapes)
+                        wv[j] = (_Float16)((oo[db][8 * h2 + j] * inv) * sc.scale);
                     // (non-temporal also when this launch reads the partials back: the lines are then
                     // written through while the kernel runs, instead of being left for the write-back at
                     // its end: 0.3 us per launch)
