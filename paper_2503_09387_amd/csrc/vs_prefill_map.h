@@ -84,5 +84,6 @@ VS_HD PrefillSlot prefill_slot_of_id(unsigned id, int units, int units_per_xcd, 
 
 // A split unit's place among those that are split: 0 .. (units_per_xcd - whole) * XCDs - 1.
 VS_HD int prefill_part_of_unit(int unit, int xcd, int whole) { return unit - whole * (xcd + 1); }
+VS_HD int prefill_unit_of_part(int part, int units_per_xcd, int whole) { return part + whole * (part / (units_per_xcd - whole) + 1); }
 
 }  // namespace vs

@@ -22,8 +22,8 @@
 //     inside the launch (all splits of a row tile run on one XCD and count themselves in
 //     through its L2): by the tile's workgroups together, each its share of the rows, once
 //     the last of them has arrived (the others wait for it, a bounded number of looks at the
-//     counter), or by that last one alone, or, where neither is possible, by a second small
-//     kernel.  Same sums, same order, same bits.
+//     counter), or by that last one alone, or, where neither is possible, or units are split beside others that
+//     are left whole, by a second small kernel.  Same sums, same order, same bits.
 //   * Scores are computed transposed, S^T = K Q^T (v_mfma_f32_32x32x16_bf16), so that a
 //     lane owns one query column: softmax statistics stay in the lane, and the
 //     probabilities are already laid out as the B operand of O^T += V^T P^T.  V^T comes
@@ -94,8 +94,8 @@ struct PrefillParams {
     // partial results are merged by prefill_combine_kernel.
     unsigned* arrivals;       // [Hkv][frames][row tiles], kCounterStrideBytes apart, zero between launches
     int xcd_shift;            // log2 of the number of XCDs workgroup ids are dealt to in turn
-    int units_per_xcd;
-    int whole;                // of which so many, the first, are a workgroup each and not split
+    int units_per_xcd;        // 0: a three-dimensional grid, ids placed nowhere in particular
+    int whole;                // of which so many, the first, are a workgroup each and not split (arrivals is null then)
     // the guard of that placement: the word in pinned host memory that is set when the workgroups of a unit were not
     // all on one XCD (the host looks at it before every launch)
     unsigned* misplaced;
@@ -256,7 +256,7 @@ void prefill_mfma_kernel(PrefillParams p) {
     const int kg = w >> 1;  // key group of this wave
     const int l32 = lane & 31, hi = lane >> 5;
     int g, split, rt, frame;
-    if (p.arrivals) {
+    if (p.units_per_xcd) {
         // 1-D grid.  Workgroup ids are dealt to the XCDs in turn (id mod number of XCDs), and a
         // unit = (KV head, frame, row tile) is merged through the L2 its XCD's compute units share, so
         // all splits of a unit take ids of one residue: XCD x holds units x*units_per_xcd ..
@@ -833,7 +833,7 @@ void prefill_mfma_kernel(PrefillParams p) {
         if (kg == 0) take_over(0); else take_over(1);
     }
 
-    if (p.arrivals && nsplit > 1) {
+    if (p.arrivals) {
         // ---- merge of the splits inside this launch.  Every workgroup has stored its
         // partial result above (ordinary stores: they stay in the XCD's L2, and all splits
         // of the unit run on this XCD).  Once the stores of all its wavefronts have been
@@ -1061,18 +1061,26 @@ __global__ __launch_bounds__(64) void prefill_combine_kernel(PrefillParams p) {
     const int h2 = b & 1; b >>= 1;
     const int db = b & 3; b >>= 2;
     const int rg = b & 3; b >>= 2;
-    const int rt = b;
-    const int g = blockIdx.y, frame = blockIdx.z;
-    const int unit = (g * p.F + frame) * p.n_row_tiles + rt;  // (all units are split)
+    int rt = b, g = blockIdx.y, frame = blockIdx.z;
+    int part = (g * p.F + frame) * p.n_row_tiles + rt;  // the unit's place among the split ones: all are
+    if (p.whole) {  // grid (32, split units, 1)
+        part = blockIdx.y;
+        const int unit = prefill_unit_of_part(part, p.units_per_xcd, p.whole);
+        if (unit >= p.n_row_tiles * p.F * p.Hkv) return;  // (spare, as in the attention launch)
+        g = div_by(unit, p.by_frame_tiles);
+        const int ft = unit - g * p.n_row_tiles * p.F;
+        frame = div_by(ft, p.by_row_tiles);
+        rt = ft - frame * p.n_row_tiles;
+    }
     if (rt * BM + rg * 32 >= p.M) return;  // whole block beyond the rows
     const int r = rt * BM + rg * 32 + l32;
     const int rr = min(r, p.M - 1) - rt * BM;
     float acc[8], denom;
     merge_splits_chunked<0>(
         p.nsplit,
-        [&](int u) { return *reinterpret_cast<const float4*>(p.part_ml + (((int64_t)u * p.part_units + unit) * BM + rr) * 4); },
+        [&](int u) { return *reinterpret_cast<const float4*>(p.part_ml + (((int64_t)u * p.part_units + part) * BM + rr) * 4); },
         [&](int u) {
-            return (reinterpret_cast<const f16x8*>(p.part_o) + (((int64_t)u * p.part_units + unit) * 4 + rg) * (8 * 64) + lane)[(db * 2 + h2) * 64];
+            return (reinterpret_cast<const f16x8*>(p.part_o) + (((int64_t)u * p.part_units + part) * 4 + rg) * (8 * 64) + lane)[(db * 2 + h2) * 64];
         },
         acc, denom);
     if (r >= p.M) return;
@@ -1093,7 +1101,7 @@ __global__ __launch_bounds__(64) void prefill_combine_kernel(PrefillParams p) {
 struct Plan {
     int kvg, n_row_tiles, nsplit;
     bool merge_inside;  // the attention kernel merges the splits itself
-    // of a launch that goes through the chip in several rounds and merges inside: so many units of every XCD, the
+    // of a launch that goes through the chip in several rounds: so many units of every XCD, the
     // first, are left whole (0: all are split alike, nsplit ways), the others split mixed_nsplit ways
     int whole, mixed_nsplit;
 };
@@ -1216,18 +1224,30 @@ Plan make_plan(const vs_shape& s, int n_tokens, int len, int n_frames) {
         }
     }
     // Whole rounds of whole units, a workgroup each, and the units of the last round, which would leave compute units
-    // idle, split over all of them behind (the merge inside the launch: the split units of an XCD stay on it).  Same
-    // estimate, and no more workspace than the plan above needs.  28/4 heads, 170 tokens over 4296 rows, per layer: 7 frames
-    // 123 -> 82 us, 8 frames 117 -> 88, 9 110 -> 99, 10 135 -> 127 (6, 11 and 12: nothing left over); a question of 1500
-    // tokens 156 -> 117.  A split workgroup may wait for one of its unit that starts only when a whole unit's has ended, and a
-    // wait is given up after some 2.5 ms: up to 512 tiles, where a whole unit takes 0.4 ms.
+    // idle, split over all of them behind; the second kernel merges.  (Merged inside the launch, a split workgroup would wait for
+    // one of its unit that starts only when a whole unit's has ended, which may be any time where the launch has
+    // not the device to itself.)  No more workspace than the plan above needs.  Both are estimated anew, in steps that take a
+    // third longer with all compute units at work than with half of them (the clock falls); splits cost 2.5 steps and 0.085 of a
+    // whole unit's (workgroups do not end all at once).  28/4 heads, 170 tokens, us per layer, all split alike (the best of 1 to 4) / so:
+    // over 4296 rows 7 frames 105 / 85, 8 107 / 93, 9 111 / 105, 10 117 / (127), over 1459 rows 55 / 45, 54 / 48, 57 / 53, 55 / (56),
+    // over 11016 rows 212 / 182, 222 / 205, 238 / 238; a question of 1500 tokens over 4296 rows 135 / 121.  Over 886 shapes the choice is
+    // 0.4 % from the better of the two on average and 6.5 % at worst; the plan above alone 10 % and 64 %.
+    int dev = 0;
+    const bool known = hipGetDevice(&dev) == hipSuccess && dev >= 0 && dev < 16 && g_xcd_shift[dev] >= 0 && g_misplaced[dev];
     const int per_xcd = (units + kPlanXcds - 1) / kPlanXcds, whole = per_xcd / kPlanCusPerXcd * kPlanCusPerXcd;
-    if (units > 128 && pl.kvg == 2 && whole > 0 && whole < per_xcd && max_tiles <= 512) {
+    if (units > 128 && pl.kvg == 2 && whole > 0 && whole < per_xcd && known && (1 << g_xcd_shift[dev]) == kPlanXcds) {
+        constexpr int kCus = kPlanXcds * kPlanCusPerXcd;
+        auto rounds = [&](int workgroups, int splits) {
+            const int steps = ((max_tiles + splits - 1) / splits + pl.kvg - 1) / pl.kvg, rest = workgroups % kCus;
+            const float last = rest ? 1.f + 0.33f * (rest > kCus / 2 ? (float)(rest - kCus / 2) / (kCus / 2) : 0.f) : 0.f;
+            return (steps + 2.25f) * (1.33f * (workgroups / kCus) + last);
+        };
+        const float merge = 2.5f + 0.085f * ((max_tiles + 1) / 2);
+        best = rounds(units * ns, ns) + (ns > 1 ? merge : 0.f);
         for (int cand = 2; cand <= 8 && cand <= max_tiles / pl.kvg; ++cand) {
-            if (kPlanXcds * (per_xcd - whole) * cand > units * ns) break;
-            const int rounds = ((per_xcd - whole) * cand + kPlanCusPerXcd - 1) / kPlanCusPerXcd;
-            const int steps = ((max_tiles + cand - 1) / cand + pl.kvg - 1) / pl.kvg;
-            const float cost = whole / kPlanCusPerXcd * ((max_tiles + 1) / 2 + 2.25f) + rounds * (steps + 2.25f) + 1.25f;
+            const int split = kPlanXcds * (per_xcd - whole) * cand;
+            if (split > units * ns) break;
+            const float cost = rounds(kPlanXcds * whole, 1) + rounds(split, cand) + merge;
             if (cost < best) {
                 best = cost;
                 pl.whole = whole;
@@ -1238,11 +1258,9 @@ Plan make_plan(const vs_shape& s, int n_tokens, int len, int n_frames) {
     if (g_tune_prefill_splits) pl.whole = 0;
     if (g_tune_prefill_splits) ns = g_tune_prefill_splits < max_tiles ? g_tune_prefill_splits : (max_tiles > 0 ? max_tiles : 1);
     pl.nsplit = ns;
-    int dev = 0;
     // (more than 8 splits: only the shared merge knows how)
-    pl.merge_inside = g_tune_prefill_merge != 2 && (ns > 1 || pl.whole) && (ns <= 8 || g_tune_prefill_merge != 1) &&
-                      ns <= kMaxPrefillSplits && pl.n_row_tiles * n_frames <= kMaxRowTiles &&
-                      hipGetDevice(&dev) == hipSuccess && dev >= 0 && dev < 16 && g_xcd_shift[dev] >= 0 && g_misplaced[dev];
+    pl.merge_inside = g_tune_prefill_merge != 2 && ns > 1 && !pl.whole && (ns <= 8 || g_tune_prefill_merge != 1) &&
+                      ns <= kMaxPrefillSplits && pl.n_row_tiles * n_frames <= kMaxRowTiles && known;
     return pl;
 }
 
@@ -1260,12 +1278,12 @@ hipError_t launch_kvg(const PrefillParams& p, const Plan& pl, int n_kv_heads, hi
         attr_set = true;
     }
     // x runs fastest in dispatch order: all workgroups that read one K/V slice are neighbours
-    const dim3 grid = p.arrivals ? dim3(prefill_grid_ids(pl.n_row_tiles * p.F * n_kv_heads, p.nsplit, p.xcd_shift, p.whole))
-                                 : dim3(n_kv_heads, pl.nsplit, pl.n_row_tiles * p.F);
+    const dim3 grid = p.units_per_xcd ? dim3(prefill_grid_ids(pl.n_row_tiles * p.F * n_kv_heads, p.nsplit, p.xcd_shift, p.whole))
+                                      : dim3(n_kv_heads, pl.nsplit, pl.n_row_tiles * p.F);
     prefill_mfma_kernel<KVG><<<grid, kGroupThreads * KVG, kLds, st>>>(p);
     hipError_t e = hipGetLastError();
-    if (e != hipSuccess || pl.nsplit == 1 || p.arrivals) return e;
-    prefill_combine_kernel<<<dim3(pl.n_row_tiles * 4 * 4 * 2, n_kv_heads, p.F), 64, 0, st>>>(p);
+    if (e != hipSuccess || p.nsplit == 1 || p.arrivals) return e;
+    prefill_combine_kernel<<<p.whole ? dim3(4 * 4 * 2, p.part_units) : dim3(pl.n_row_tiles * 4 * 4 * 2, n_kv_heads, p.F), 64, 0, st>>>(p);
     return hipGetLastError();
 }
 
@@ -1404,15 +1422,18 @@ hipError_t launch_prefill_mfma(const vs_shape& s, const void* kc, const void* vc
         p.arrivals = (unsigned*)counters;
         p.xcd_shift = g_xcd_shift[dev];
         p.units_per_xcd = prefill_units_per_xcd(p.part_units, p.xcd_shift);
-        if (pl.whole && (1 << p.xcd_shift) == kPlanXcds) {
-            p.whole = pl.whole;
-            p.nsplit = pl.mixed_nsplit;
-            p.part_units = (p.units_per_xcd - p.whole) << p.xcd_shift;
-        }
         p.lie = g_tune_guard_test == 3 ? 1u : 0u;
         p.misplaced = g_misplaced_dev[dev];
         p.share_merge = g_tune_prefill_merge != 1;
         p.max_looks = g_tune_guard_test == 4 ? 0 : 8192;  // ~0.3 us a look: some milliseconds at most
+    }
+    if (pl.whole) {
+        static_assert(kPlanXcds == 8, "ids of whole and split units are dealt to 8 XCDs");
+        p.xcd_shift = 3;
+        p.units_per_xcd = prefill_units_per_xcd(p.part_units, p.xcd_shift);
+        p.whole = pl.whole;
+        p.nsplit = pl.mixed_nsplit;
+        p.part_units = (p.units_per_xcd - p.whole) << p.xcd_shift;
     }
     p.by_nsplit = quick_div(p.nsplit);
     p.by_lanes = quick_div(p.nsplit * pl.kvg);

@@ -30,6 +30,7 @@ int main() {
                         const int part = vs::prefill_part_of_unit(s.unit, s.xcd, whole);
                         if (part < 0 || part >= parts || (place[part] >= 0 && place[part] != s.unit)) { std::printf("place\n"); return 1; }
                         place[part] = s.unit;
+                        if (vs::prefill_unit_of_part(part, upx, whole) != s.unit) { std::printf("unit of place %d\n", part); return 1; }
                     }
                     for (int u = 0; u < units; ++u)
                         for (int k = 0; k < nsplit; ++k)

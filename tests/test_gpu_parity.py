@@ -1448,17 +1448,41 @@ def test_prefill_short_key_sequences(hq, hkv, L, T, gain):
     assert row == L and cache.len == L + 1 and same_bits(cache.k[L], kf[T - 1]) and same_bits(cache.v[L], vf[T - 1])
 
 
-@pytest.mark.parametrize("F,T,L,hq,hkv", [(33, 124, 600, 8, 8), (39, 60, 520, 16, 8), (35, 117, 577, 8, 8), (9, 170, 700, 28, 4)])
+def partial_row_tiles(ws, s):
+    """How many (row tile, split) partial results a call has left in a workspace whose scratch area held 0xff before: 128 rows of
+    128 fp16 numbers and of 4 fp32 ones each, none of which is ever stored as that (partial_area says where it starts)."""
+    return int((partial_area(ws, s) != -1).sum()) / (128 * (64 + 4))
+
+
+def partial_area(ws, s):
+    ctrl = ((64 * s.n_kv_heads * 4 + 127) // 128 + 256 * s.n_kv_heads) * 128
+    return ws[ctrl:ctrl + (ws.numel() - ctrl) // 4 * 4].view(torch.int32)
+
+
+def check_whole_and_split(ws, s, F, T):
+    """The units behind the whole rounds of every XCD, and no others, have left partial results, 2 to 8 each."""
+    units = -(-T * (s.n_q_heads // s.n_kv_heads) // 128) * s.n_kv_heads * F
+    per_xcd = -(-units // 8)
+    split = sum(max(0, min(per_xcd, units - x * per_xcd) - per_xcd // 32 * 32) for x in range(8))
+    assert split > 0 and partial_row_tiles(ws, s) in [split * n for n in range(2, 9)]
+
+
+@pytest.mark.parametrize("F,T,L,hq,hkv", [
+    (33, 124, 600, 8, 8), (39, 60, 900, 16, 8), (35, 117, 577, 8, 8), (9, 170, 1500, 28, 4),
+    (12, 192, 600, 28, 4),                            # 66 units per XCD: two whole rounds in front
+    (33, 124, 32700 - 124, 8, 8), (33, 124, 33000, 8, 8),  # 512 tiles of keys and more
+])
 def test_run_of_frames_with_whole_and_split_units(F, T, L, hq, hkv):
     """More units than compute units, and a last round of few: those are split, the others whole.  Against the oracle
-    (some frames), the kept rows bit for bit, three times through one workspace with the same bits, and close to
-    the second kernel's merge, which splits all units alike."""
+    (some frames), the kept rows bit for bit, three times through one workspace with the same bits, whatever is said about merges, and
+    close to the result where all units are split alike."""
     s = AttnShape(hq, hkv, 128, "bf16")
     hk, hv = cache_rows(65, s, L, 0.5)
     q = draw(66, (F, T, hq, 128), 0.5, "bf16")
     kf, vf = (draw(k, (F, T, hkv, 128), 0.5, "bf16") for k in (67, 68))
     ws = torch.empty(vs.frames_workspace_bytes(vs_shape(s), F, T, L + F), dtype=torch.uint8, device=DEV)
     vs.workspace_init(vs_shape(s), ws)
+    partial_area(ws, s).fill_(-1)
     qd, kd, vd = q.to(DEV), kf.to(DEV), vf.to(DEV)
 
     def run():
@@ -1472,12 +1496,36 @@ def test_run_of_frames_with_whole_and_split_units(F, T, L, hq, hkv):
         return out
 
     first = run()
+    check_whole_and_split(ws, s, F, T)
+    tokens = [0, T // 2, T - 1] if L > 2000 else list(range(T))
     for f in (0, F // 2, F - 1):
         k_all, v_all = torch.cat([hk, kf[:f, T - 1]]), torch.cat([hv, vf[:f, T - 1]])
-        check_close(first[f], oracle_prefill_rows(s, q[f], k_all, v_all, L + f, kf[f], vf[f]), "bf16", f"frame {f} of {F}")
+        check_close(first[f][tokens], oracle_prefill_rows(s, q[f], k_all, v_all, L + f, kf[f], vf[f], tokens), "bf16", f"frame {f} of {F}")
     assert all(same_bits(run(), first.cpu()) for _ in range(2))
-    vs.set_tuning(vs.TUNE_PREFILL_MERGE, 2)
+    for merge in (1, 2):
+        vs.set_tuning(vs.TUNE_PREFILL_MERGE, merge)
+        assert same_bits(run(), first.cpu())
+    vs.set_tuning(vs.TUNE_PREFILL_MERGE, 0)
+    vs.set_tuning(vs.TUNE_PREFILL_SPLITS, 2)
     assert (run().float() - first.float()).abs().max() <= 2 ** -7 * first.float().abs().max()
+
+
+def test_run_of_frames_with_whole_and_split_units_waits_for_nobody():
+    """The workgroups of a split unit start when those of whole units have ended, which may be any time where the launch has part of
+    the device: with waits given up at once the result is complete all the same, and nothing is reported."""
+    s, F, T, L = AttnShape(8, 8, 128, "bf16"), 33, 124, 600
+    hk, hv = (t.to(DEV) for t in cache_rows(65, s, L, 0.5))
+    q, kf, vf = (draw(k, (F, T, 8, 128), 0.5, "bf16").to(DEV) for k in (66, 67, 68))
+    ws = torch.empty(vs.frames_workspace_bytes(vs_shape(s), F, T, L + F), dtype=torch.uint8, device=DEV)
+    vs.workspace_init(vs_shape(s), ws)
+    outs = []
+    for merge in (0, 4, 3, 0):
+        vs.set_tuning(vs.TUNE_PREFILL_MERGE, merge)
+        k, v = (torch.cat([t, torch.zeros_like(t[:F])]) for t in (hk, hv))
+        outs.append(torch.full(q.shape, float("nan"), dtype=torch.bfloat16, device=DEV))
+        vs.frames_prefill_attn(vs_shape(s), vs.Cache(k, v, L), q, kf, vf, outs[-1], ws)
+        torch.cuda.synchronize()
+    assert torch.isfinite(outs[0]).all() and all(same_bits(o, outs[0].cpu()) for o in outs[1:])
 
 
 def test_long_question_with_whole_and_split_units():
@@ -1489,8 +1537,11 @@ def test_long_question_with_whole_and_split_units():
     k[:L].copy_(hk)
     v[:L].copy_(hv)
     out = torch.full(q.shape, float("nan"), dtype=torch.bfloat16, device=DEV)
-    vs.question_prefill_append(vs_shape(s), vs.Cache(k, v, L), q.to(DEV), kt.to(DEV), vt.to(DEV), out, workspace(s, T, L + T, 0))
+    ws = workspace(s, T, L + T, 0)
+    partial_area(ws, s).fill_(-1)
+    vs.question_prefill_append(vs_shape(s), vs.Cache(k, v, L), q.to(DEV), kt.to(DEV), vt.to(DEV), out, ws)
     torch.cuda.synchronize()
+    check_whole_and_split(ws, s, 1, T)
     assert same_bits(k[L:], kt) and same_bits(v[L:], vt) and same_bits(k[:L], hk) and same_bits(v[:L], hv)
     tokens = [0, 1, 63, 64, 1023, 1024, 2047, 2048, 2099]  # 64 tokens are a row tile; the last tile's units are split
     check_close(out[tokens], oracle_prefill_rows(s, q, hk, hv, L, kt, vt, tokens), "bf16", "long question")
