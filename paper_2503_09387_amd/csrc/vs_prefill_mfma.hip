@@ -615,13 +615,18 @@ void prefill_mfma_kernel(PrefillParams p) {
 
     // A step is plain if its tile and the two behind it are cache rows only, and this group's, or the one behind it is the
     // group's last.  Plain steps follow one another; they run in one block, unless a row has accumulated nothing yet (its
-    // first sums need the closer look of commit()).
+    // first sums need the closer look of commit()).  A row is two lanes, of which one may stay at 0 for good (its keys far below
+    // the other's); a row of NaN goes in too, and is left at every sub-block.
+    auto all_begun = [&]() {
+        const float t0 = l_run[0] + pend[0], t1 = l_run[1] + pend[1];
+        return __all(t0 != 0.f && t1 != 0.f) || __all(t0 + xhalf(t0) != 0.f && t1 + xhalf(t1) != 0.f);
+    };
     const int plain_from = n_rest, hold = n_my - n_rest <= n_plain - run_first ? 1 : 0;
     const int plain_to = hold ? n_my - 1 : n_plain - run_first + n_rest - 2;
     for (int s = 0; s < n_steps;) {
         // steps 2s+1 and 2s+2 of this group: they read K of tile s+1 and V of tile s, and K of tile s+2 and V of tile
         // s+1 are requested
-        if (s >= plain_from && s < plain_to && __all(l_run[0] + pend[0] > 0.f && l_run[1] + pend[1] > 0.f)) {
+        if (s >= plain_from && s < plain_to && all_begun()) {
             // this wave's share of what the first of them requests: rows 32*rb .. 32*rb+31 of the two tiles, head g
             unsigned long long ksrc = (unsigned long long)(kc + ((int64_t)(tile_of(min(s + 2, n_my - 1)) * BN + rb * 32) * Hkv + g) * kRowBytes);
             unsigned long long vsrc = (unsigned long long)(vc + ((int64_t)(tile_of(s + 1) * BN + rb * 32) * Hkv + g) * kRowBytes);

@@ -581,6 +581,29 @@ def test_prefill_reference_left_behind_inside_the_loop_of_plain_steps(tiles, fir
     check_close(out, oracle_prefill_rows(s, q, hk, hv, L, kf, vf), "bf16", f"{tiles} tiles, block {first_block}, {kv_groups} key groups")
 
 
+@pytest.mark.parametrize("kv_groups", [1, 2])
+@pytest.mark.parametrize("far", [4, 0, -1])
+def test_prefill_rows_of_which_one_lane_never_sums_anything(far, kv_groups):
+    """A row's keys are shared out to two lanes by bit 2 of their number.  The keys with (far = 4) or without (0) that bit lie 200
+    log2 units below the others, or first the ones and then, from the middle on, the others do (-1): a lane whose sum is 0
+    goes through the loop of plain steps with its row, and its keys count from where they matter."""
+    s, T = AttnShape(8, 4, 128, "bf16"), 70
+    L = 64 * 8 * kv_groups + 5
+    vs.set_tuning(vs.TUNE_PREFILL_KV_GROUPS, kv_groups)
+    vs.set_tuning(vs.TUNE_PREFILL_SPLITS, 1)
+    hk, hv = cache_rows(45, s, L, 0.5)
+    q, kf, vf = frame_inputs(45, s, T, 0.5)
+    j = torch.arange(L + T)
+    low = (j & 4) == far if far >= 0 else ((j & 4) == 0) ^ (j % (64 * 8) >= 256)
+    # (k_j += a_j u, q += 10 u with u = 0.5 ones: score_j moves by 0.1275 * 10 * a_j * 32 log2 units)
+    a = low.float() * (-200.0 / 40.8)
+    hk = (hk.float() + 0.5 * a[:L, None, None]).to(torch.bfloat16)
+    kf = (kf.float() + 0.5 * a[L:, None, None]).to(torch.bfloat16)
+    q = (q.float() + 5.0).to(torch.bfloat16)
+    out, _, _ = run_prefill(s, hk, hv, L, q, kf, vf)
+    check_close(out, oracle_prefill_rows(s, q, hk, hv, L, kf, vf), "bf16", f"bit 2 {far}, {kv_groups} key groups")
+
+
 def test_prefill_uniform_scores_is_running_mean_at_full_size():
     """Q = 0: every row is the mean of its visible V rows (closed form, any size)."""
     s = QW
