@@ -1183,14 +1183,15 @@ SplitPlan make_split_plan(int units, int max_tiles) {
 // round of 4 x 32 keys, this kernel's 8 us and up with little dependence on the keys, the more the more units there are.
 // Measured on both sides of the line (us a launch there / here): 10 tokens (4 units) 5 rounds 9.4 / 10.0, 6 rounds 10.3 /
 // 10.0; 37 tokens (12) 6 rounds 10.4 / 11.1, 7 rounds 11.4 / 11.4; 100 tokens (24) 7 rounds 11.3 / 11.8, 8 rounds 12.2 / 11.8; 170
-// tokens (40) 8 rounds 12.1 / 13.0, 9 rounds 13.0 / 13.0.  It needs one compute unit per 32 packed rows and KV head.
+// tokens (40) 8 rounds 12.1 / 13.0, 9 rounds 13.0 / 13.0.  With 5 to 38 units of at most 4
+// rows, which leave next to nothing to merge, a round less: 1 token, 8/8 heads, 5 rounds 9.0 / 10.0, 6 rounds 10.0 / 9.5.  It needs one compute unit per 32 packed rows and KV head.
 bool prefers_short_kernel(const vs_shape& s, int n_tokens, int len) {
     if (g_tune_prefill_splits || g_tune_prefill_kv_groups) return false;  // (a plan of this kernel has been asked for)
     const int64_t M = (int64_t)n_tokens * (s.n_q_heads / s.n_kv_heads);
     const int64_t workgroups = (M + 31) / 32 * s.n_kv_heads, units = (M + BM - 1) / BM * s.n_kv_heads;
     if (workgroups > kPlanXcds * kPlanCusPerXcd) return false;
     const int rounds = ((len + n_tokens + 31) / 32 + 3) / 4;
-    return rounds <= (units < 5 ? 5 : units < 13 ? 6 : units < 39 ? 7 : 8);
+    return rounds <= (units < 5 ? 5 : units < 13 ? 6 : units < 39 ? 7 : 8) - (M < 5 && units >= 5 && units < 39 ? 1 : 0);
 }
 
 Plan make_plan(const vs_shape& s, int n_tokens, int len, int n_frames) {

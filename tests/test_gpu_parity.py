@@ -1456,7 +1456,7 @@ def test_prefill_plans_over_units_and_keys(hq, hkv, L, T):
 @pytest.mark.parametrize("gain", [1, 12])
 @pytest.mark.parametrize("hq,hkv,L,T", [
     # key counts at the edges of blocks of 32 and of rounds of four blocks, blocks that straddle cache and frame,
-    # packed rows at the edges of groups of 32, no cache, one token, every row count up to the last round taken
+    # packed rows at the edges of groups of 32, no cache, one token, row counts up to 7 rounds (the last ones taken: below)
     (28, 4, 0, 1), (28, 4, 0, 32), (28, 4, 1, 31), (28, 4, 31, 1), (28, 4, 32, 33), (28, 4, 33, 95), (8, 1, 95, 4), (8, 8, 96, 32),
     (16, 2, 127, 33), (12, 6, 128, 128), (24, 8, 200, 170), (28, 4, 264, 170), (28, 4, 342, 170), (28, 4, 511, 2), (28, 4, 700, 192),
 ])
@@ -1480,6 +1480,24 @@ def partial_row_tiles(ws, s):
 def partial_area(ws, s):
     ctrl = ((64 * s.n_kv_heads * 4 + 127) // 128 + 256 * s.n_kv_heads) * 128
     return ws[ctrl:ctrl + (ws.numel() - ctrl) // 4 * 4].view(torch.int32)
+
+
+@pytest.mark.parametrize("hq,hkv,T,rounds", [(28, 4, 10, 5), (28, 4, 37, 6), (28, 4, 100, 7), (28, 4, 170, 8), (8, 8, 1, 5), (8, 8, 4, 5),
+                                             (8, 8, 5, 6), (32, 32, 1, 6), (32, 32, 5, 7)])
+@pytest.mark.parametrize("beyond", [0, 1])
+def test_prefill_on_both_sides_of_the_short_kernels_range(hq, hkv, T, rounds, beyond):
+    """The last key count that the kernel for few keys takes (so many rounds of 128) and the next one, which is split and leaves
+    partial results in the workspace."""
+    s, L = AttnShape(hq, hkv, 128, "bf16"), 128 * rounds + beyond - T
+    hk, hv = cache_rows(1500 + T, s, L, 0.5)
+    q, kf, vf = frame_inputs(1500 + T, s, T, 0.5, q_gain=3)
+    ws = workspace(s, T, L + 1, 1)
+    partial_area(ws, s).fill_(-1)
+    out, cache, row = run_prefill(s, hk, hv, L, q, kf, vf, ws=ws, fused=True)
+    assert (partial_row_tiles(ws, s) > 0) == bool(beyond)
+    bound = oracle_prefill_rows(s, q, hk, hv.abs(), L, kf, vf.abs())
+    check_close(out, oracle_prefill_rows(s, q, hk, hv, L, kf, vf), "bf16", f"{hq}/{hkv} T={T} L={L}", abs_v_out=bound)
+    assert row == L and cache.len == L + 1 and same_bits(cache.k[L], kf[T - 1]) and same_bits(cache.v[L], vf[T - 1])
 
 
 def check_whole_and_split(ws, s, F, T):
