@@ -639,7 +639,8 @@ def test_fp32_prefill_on_both_sides_of_the_chip(dim, hq, hkv, L, T):
     check_close(out, oracle_prefill_rows(s, q, hk, hv, L, kf, vf), "f32", f"fp32 {hq}/{hkv}/{dim} L={L} T={T}")
 
 
-@pytest.mark.parametrize("path,L", [("prefill", 100), ("prefill, general kernel", 100), ("prefill", 1500), ("fp32 prefill", 40),
+@pytest.mark.parametrize("path,L", [("prefill", 100), ("prefill, general kernel", 100), ("prefill", 1500), ("prefill, one split", 1500),
+                                    ("prefill, general kernel, one split", 1500), ("fp32 prefill", 40),
                                     ("decode", 100), ("decode", 700), ("decode", 9300), ("fp32 decode", 300)])
 def test_a_score_that_is_not_a_number_stays_in_its_row(path, L):
     """A query row that holds a NaN comes out as NaN; every other row is what it is without it, to a rounding (the
@@ -651,6 +652,8 @@ def test_a_score_that_is_not_a_number_stays_in_its_row(path, L):
     q, kf, vf = (t.to(DEV) for t in frame_inputs(45, s, T, 0.5))
     if "general" in path:
         vs.set_tuning(vs.TUNE_PREFILL_KV_GROUPS, 1)
+    if "one split" in path:
+        vs.set_tuning(vs.TUNE_PREFILL_SPLITS, 1)
     ws = workspace(s, T, L + 1, 1)
     outs = []
     for bad in (False, True):
