@@ -117,7 +117,8 @@ size_t vs_workspace_bytes(const vs_shape *shape, int32_t max_q_tokens, int32_t m
  * VS_ERR_PLACEMENT, once: the outputs of the bf16 prefill calls enqueued since the last one that
  * returned VS_OK after a synchronisation are in doubt and should be repeated.  From then on the
  * partial results are merged by a second kernel, which needs no such placement, until a later
- * vs_workspace_init probes the device again.
+ * vs_workspace_init probes the device again.  (Runs with more row tiles than compute units, of which some are left
+ * whole and the others split, are always merged by the second kernel: they wait for nobody.)
  */
 vs_status vs_workspace_init(const vs_shape *shape, void *workspace, size_t workspace_bytes,
                             void *hip_stream);
@@ -329,7 +330,7 @@ vs_status vs_carrier_evict_append(const vs_shape *shape, int32_t n_layers, vs_ca
  *   VS_TUNE_PREFILL_MERGE     1 = split results are merged inside the attention kernel by the last
  *                             workgroup of a row tile to arrive alone (not shared by the tile's
  *                             workgroups); 2 = always by the second kernel, never inside the
- *                             attention kernel; 3 = for tests of the placement guard (see
+ *                             attention kernel (as runs that leave some row tiles whole are in any case); 3 = for tests of the placement guard (see
  *                             vs_workspace_init): every other workgroup of a row tile gives a
  *                             neighbouring XCD as its own, so that every row tile is reported as misplaced while
  *                             the results stay correct; 4 = for tests of the bounded wait of the

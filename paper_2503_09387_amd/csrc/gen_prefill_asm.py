@@ -49,7 +49,7 @@ number, and the loop left to the compiler (some 130 scalar instructions a step),
 of which the 64 matrix instructions are 2070.  In the loop the sums are taken with two shifts or masks and two additions per pair,
 the ordinary instructions are dealt out by the cycles they take, and the first fragments of a sub-block are requested behind the
 last matrix instructions of the one before: 3010 cycles (six frames of 170 tokens over 4296 rows 74.0 -> 66.2 us a
-launch; not in proportion, because the clock falls from 2.3 to 1.9 .. 2.2 GHz as the matrix pipe fills).  Sums by
+launch; not in proportion, because the clock falls from 2.3 to 1.85 GHz as the matrix pipe fills).  Sums by
 four more matrix instructions (ones times P) came to the same time, and staging spread over both sub-blocks with a third slot for V
 gained nothing.
 

@@ -11,6 +11,7 @@
 //     x = u / units_per_xcd,  j = u % units_per_xcd,  id = x + ((j * nsplit + split) << xcd_shift)
 // with units_per_xcd = ceil(units / 2^xcd_shift); consecutive units (the same KV head, whose K/V
 // that L2 then holds once) share an XCD.  Ids whose unit does not exist are spare and return.
+// (Launches that leave units whole beside split ones use the same map, for that L2 alone: a second kernel merges them.)
 #pragma once
 
 #ifdef __HIPCC__
